@@ -36,19 +36,16 @@ sys.path.insert(0, ROOT)
 import datagen  # noqa: E402
 
 EPS_TABLE = os.path.join(ROOT, "tests", "golden", "eps.json")
-TRAFFIC = os.path.join(ROOT, "profiles", "pmc_k_join_fp32_uniform_2m_d16.md")
-JOIN_SRC = os.path.join(ROOT, "paper_1809_09930_amd", "csrc", "sj_join.hip")
+TRAFFIC = os.path.join(ROOT, "profiles", "pmc_k_join_fp32_mxw_uniform_2m_d16.md")
+JOIN_SRC = os.path.join(ROOT, "paper_1809_09930_amd", "csrc", "sj_mx32.hip")
 
-# MI355X: 256 CUs x 4 SIMD x 16 lanes x 2.4 GHz = 3.93e13 FP32 lane
-# instructions/s.  The published FP32 vector peak, 157.3 TFLOP/s, counts
-# packed FMAs (2 lanes x 2 flops); packed FP32 math is disabled in this
-# build, so one FMA per lane and cycle, 78.6 TFLOP/s, is its own ceiling.
-# Both fractions are reported.
-PEAK_FP32_TFLOPS = 157.3
-PEAK_FP32_NONPACKED_TFLOPS = 78.6
-VALU_LANE_OPS_PER_S = 3.93e13
-# Dense FP16/BF16 matrix-core peak of MI355X.
+# Dense FP16/BF16 matrix-core peak of MI355X, and a third of it: the FP32
+# filter of large joins takes three FP16 products per FP32 one.
 PEAK_MFMA_16BIT_TFLOPS = 2500.0
+PEAK_FP32_SPLIT_TFLOPS = PEAK_MFMA_16BIT_TFLOPS / 3.0
+# 256 CUs x 4 SIMD x 16 lanes x 2.4 GHz lane instructions/s (one threshold
+# compare per pair in the matrix-core floor)
+VALU_LANE_OPS_PER_S = 3.93e13
 
 
 def parse():
@@ -144,6 +141,11 @@ def candidate_prefix_mean(P, perm, k, eps, n_queries=96, per_query=16384, seed=9
         num += m * float(dims.mean())
         den += m
     return num / den
+
+
+def fp32_kernel(d):
+    """The FP32 join kernel of large joins (per padded dimension)."""
+    return "k_join_fp32_mxw" if d <= 24 else "k_join_fp32_mxg"
 
 
 def traffic_for_join():
@@ -255,7 +257,7 @@ def bench_query_sets(a, table, P, Pd, targets, eps_list):
         join = np.array([i["ms_join"] / max(i["join_launches"], 1) for _, i in rows])
         c_sets = float(sum(i["candidates"] for _, i in rows))
         if prec == "fp32":  # operations the short-circuit leaves, per candidate (one direction)
-            flops_total += 3.0 * candidate_prefix_mean(P, e_info["perm"], e_info["k"], eps) * c_sets
+            flops_total += 2.0 * d * c_sets
         else:               # one d-long dot product per candidate
             flops_total += 2.0 * d * c_sets
         time_total += float(join.sum()) / 1e3
@@ -290,10 +292,10 @@ def bench_query_sets(a, table, P, Pd, targets, eps_list):
         "per_epsilon": per_eps,
     }
     achieved = flops_total / time_total / 1e12 if time_total > 0 else 0.0
-    peak = PEAK_FP32_TFLOPS if prec == "fp32" else PEAK_MFMA_16BIT_TFLOPS
-    out["roofline"] = {"bound": "alu" if prec == "fp32" else "mfma", "achieved": achieved,
+    peak = PEAK_FP32_SPLIT_TFLOPS if prec == "fp32" else PEAK_MFMA_16BIT_TFLOPS
+    out["roofline"] = {"bound": "mfma", "achieved": achieved,
                        "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak, "traffic": None,
-                       "kernel": "k_join_fp32" if prec == "fp32" else "k_join_mfma",
+                       "kernel": fp32_kernel(d) if prec == "fp32" else "k_join_mfma",
                        "mean_launch_ms": float(np.mean(join_all)) if join_all else 0.0}
     print(json.dumps(out), flush=True)
 
@@ -396,11 +398,10 @@ def timed_steps(sj, Pd, d, eps_list, targets, precision, steps, warmup, sortidu=
 
 def per_eps_table(P, recs, ntargets, precision):
     """Per-epsilon rows of the first recorded step, and the algorithmic work
-    and join time summed over them.  FP32: 3 flops per dimension the ideal
-    per-pair short-circuit evaluates (mean over candidate pairs), per
-    unordered pair.  Matrix cores: one d-long dot product (2d flops) per
-    unordered pair, and the floor max(MFMA time, one vector compare per
-    pair)."""
+    and join time summed over them: one d-long dot product (2d flops) per
+    unordered pair, and for the 16-bit filters the floor max(MFMA time, one
+    vector compare per pair).  FP32 rows also give the dimensions an ideal
+    per-pair short-circuit evaluates (mean over candidate pairs)."""
     n, d = P.shape
     per_eps, flops_total, time_total = {}, 0.0, 0.0
     for t, eps, total, info, perm in recs[:ntargets]:
@@ -418,9 +419,8 @@ def per_eps_table(P, recs, ntargets, precision):
         if precision == "fp32":
             pbar = candidate_prefix_mean(P, perm, info["k"], eps)
             row["shortc_prefix_mean"] = round(pbar, 3)
-            flops_total += 3.0 * pbar * npair
-        else:
-            flops_total += 2.0 * d * npair
+        flops_total += 2.0 * d * npair
+        if precision != "fp32":
             floor_s = max(2.0 * d * npair / (PEAK_MFMA_16BIT_TFLOPS * 1e12),
                           npair / VALU_LANE_OPS_PER_S)
             row["ms_floor_mfma_or_compare"] = round(floor_s * 1e3, 3)
@@ -441,8 +441,7 @@ def summarise(P, recs, elapsed, steps, ntargets, precision):
                                                  for r in recs]))}
     if precision == "fp32":
         out["kernel_achieved_tflops"] = achieved
-        out["kernel_frac_of_published_fp32_peak"] = achieved / PEAK_FP32_TFLOPS
-        out["kernel_frac_of_nonpacked_fp32"] = achieved / PEAK_FP32_NONPACKED_TFLOPS
+        out["kernel_frac_of_split_mfma_peak"] = achieved / PEAK_FP32_SPLIT_TFLOPS
     else:
         floor_ms = sum(r["ms_floor_mfma_or_compare"] for r in per_eps.values())
         out["kernel_achieved_tflops"] = achieved
@@ -685,27 +684,26 @@ def main():
                    "target_mean_neighbours": ([int(t) for t in targets]
                                               if "eps_fixed" not in w else None),
                    "epsilons": eps_list,
-                   "path": ("plain FP32 grid join" if fp32 else
+                   "path": ("FP32 grid join (large joins: FP32 split into two FP16 "
+                            "parts on the matrix cores, FP32 sums, FP64 recheck)" if fp32 else
                             "%s matrix-core join with FP64 band recheck" % a.precision)
                    + ", k auto in 4..8, symmetric tiles" + (", SORTIDU" if a.sortidu else "")
                    + (", result batches of at most %d pairs in pinned host memory"
                       % int(a.batch_pairs) if a.batch_pairs else "")},
         "result_pairs_per_s": head["result_pairs_per_s"],
         "per_epsilon": head["per_epsilon"],
-        "roofline": {"bound": "alu" if fp32 else "mfma", "achieved": achieved,
-                     "peak": PEAK_FP32_TFLOPS if fp32 else PEAK_MFMA_16BIT_TFLOPS,
+        "roofline": {"bound": "mfma", "achieved": achieved,
+                     "peak": PEAK_FP32_SPLIT_TFLOPS if fp32 else PEAK_MFMA_16BIT_TFLOPS,
                      "unit": "TFLOP/s",
-                     "frac": achieved / (PEAK_FP32_TFLOPS if fp32 else PEAK_MFMA_16BIT_TFLOPS),
+                     "frac": achieved / (PEAK_FP32_SPLIT_TFLOPS if fp32
+                                         else PEAK_MFMA_16BIT_TFLOPS),
                      "traffic": traffic,
-                     "kernel": "k_join_fp32" if fp32 else "k_join_mfma",
+                     "kernel": fp32_kernel(d) if fp32 else "k_join_mfma",
                      "mean_launch_ms": head["mean_join_launch_ms"],
                      "algorithmic_bytes": alg_bytes,
                      "traffic_over_algorithmic": (traffic / alg_bytes) if traffic else None,
                      "traffic_epsilon": eps_list[len(targets) // 2]},
     }
-    if fp32:
-        out["roofline"]["peak_nonpacked"] = PEAK_FP32_NONPACKED_TFLOPS
-        out["roofline"]["frac_nonpacked"] = achieved / PEAK_FP32_NONPACKED_TFLOPS
     compare = {}
     for prec in [x.strip() for x in a.compare.split(",") if x.strip() and x.strip() != a.precision]:
         print("bench: %s %s" % (a.workload, prec), file=sys.stderr, flush=True)

@@ -66,7 +66,8 @@ extern "C" {
 
 /* Distance filter used by selfjoin_run. */
 enum sj_precision {
-    SJ_PREC_FP32 = 0, /* difference form (a-b)^2 summed in FP32 on the vector ALUs, with short-circuit */
+    SJ_PREC_FP32 = 0, /* FP32 operands and sums (enum sj_fp32_form), with short-circuit; joins of some
+                         size on the matrix cores, each FP32 coordinate split into two FP16 parts */
     SJ_PREC_FP16 = 1, /* |a|^2+|b|^2-2a.b on the matrix cores, FP16 operands, FP32 accumulation,
                          FP64 recheck of the error band; falls back to BF16 when the centred data
                          exceed the FP16 range */
@@ -99,7 +100,11 @@ typedef struct sj_options {
  *   NORM:       |a|^2 + |b|^2 - 2 a.b from per-point prefix norms, one fused
  *               multiply-add per dimension; its error grows with the norms, so
  *               AUTO takes it only up to 16 dimensions and when the band
- *               stays narrow against eps^2. */
+ *               stays narrow against eps^2.
+ * AUTO also takes the norm form, on the matrix cores, for joins of at least
+ * 2^24 ordered candidate pairs whose cells fill the kernel's query blocks
+ * (sj_info.fp32_form: NORM).  Every pair that bound does not reject is then
+ * decided in FP64 unless the vector norm form's conditions hold. */
 enum sj_fp32_form { SJ_FP32_AUTO = 0, SJ_FP32_DIFFERENCE = 1, SJ_FP32_NORM = 2 };
 
 /* Work units of the single-join distance kernel (sj_info.units), chosen at

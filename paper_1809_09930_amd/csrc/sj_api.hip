@@ -339,9 +339,41 @@ constexpr bool kWuByStretch = SJ_WU_BY_STRETCH != 0;  // join work units in stre
 #define SJ_FP32_CELL_GROUPS 1
 #endif
 
+uint64_t default_budget();
 constexpr bool kFp32CellGroups = SJ_FP32_CELL_GROUPS != 0;
 constexpr double kLookupsPerSec = 2.0e10;
 constexpr double kPairsPerSec = 1.5e12;
+
+// Whether a handle's FP32 join may run on the matrix cores (sj_mx32.hip): it
+// does for joins of at least kMx32MinCandidates ordered candidate pairs with
+// at least kMx32LiveSlotShareMin of the tile work on live query rows.
+// Absolute error (scaled squared units) of FP16 parts below the normal range:
+// 2^-25 per coordinate, 4 sqrt(128) 2^-25 (|q~| + |a~|) <= 2^-23 (|q~|^2 + |a~|^2)
+// + 2^-17 (the first part is in mx32_kappa's).
+constexpr double kMx32Tiny = 0x1p-16;
+constexpr double kMx32MinCandidates = 16777216.0;
+constexpr double kMx32LiveSlotShareMin = 0.4;
+bool mx32_in_range(const sj_index &ix) {
+  if (ix.opt.precision != SJ_PREC_FP32 || ix.opt.fp32_form != SJ_FP32_AUTO || !ix.opt.shortc ||
+      ix.batch_job)
+    return false;
+  // far from the ends of the FP32 range, and eps not so small against the
+  // coordinates' range that the absolute error term nears eps^2
+  if (!(ix.eps2 >= 0x1p-80 && ix.eps2 <= 0x1p80)) return false;
+  double range = 0.0;
+  for (uint32_t t = 0; t < ix.d; ++t) {
+    if (!(std::max(std::fabs(ix.dmin[t]), std::fabs(ix.dmax[t])) <= 0x1p60)) return false;
+    range = std::max(range, ix.dmax[t] - ix.dmin[t]);
+  }
+  return range <= ix.eps * 0x1p15;
+}
+
+// Pivots in the sort key: where the group test of k_join_fp32_mxg can use
+// cluster-wise query blocks.
+constexpr uint64_t kPivotMinPoints = 4096;
+bool use_pivots(const sj_index &ix) {
+  return padded_dim(ix.d) > 24 && !ix.opt.sortidu && ix.n >= kPivotMinPoints && mx32_in_range(ix);
+}
 
 bool make_geometry(const sj_index &ix, uint32_t k, Geometry &g) {
   g = Geometry{};
@@ -384,9 +416,11 @@ bool make_geometry(const sj_index &ix, uint32_t k, Geometry &g) {
     fm = 1;
     fb = std::min<uint32_t>(24, 63 - std::min<uint32_t>(cell_bits, 63));
   }
-  while (fb > 0 && cell_bits + fm * fb > 63) --fb;
+  const uint32_t pb = use_pivots(ix) && cell_bits + kPivotBits <= 63 ? kPivotBits : 0u;
+  while (fb > 0 && cell_bits + pb + fm * fb > 63) --fb;
   g.kp.fm = fb ? fm : 0;
   g.kp.fb = fb;
+  g.kp.pb = pb;
   for (uint32_t r = 0; r < g.kp.fm; ++r) {
     const uint32_t t = ix.perm[ix.opt.sortidu ? u_rank : r];
     g.kp.fdim[r] = t;
@@ -394,7 +428,7 @@ bool make_geometry(const sj_index &ix, uint32_t k, Geometry &g) {
     const double span = ix.dmax[t] - ix.dmin[t];
     g.kp.fscale[r] = span > 0.0 ? (double)(1u << fb) / span : 0.0;
   }
-  g.fine_bits = g.kp.fm * g.kp.fb;
+  g.fine_bits = g.kp.fm * g.kp.fb + g.kp.pb;
   g.key_bits = cell_bits + g.fine_bits;
   g.u_rank = u_rank;
   uint64_t noff = 1;
@@ -417,7 +451,14 @@ uint64_t build_neighbors(sj_index &ix, const sj_index &E, NbrParams np, BuildTmp
 uint64_t build_grid(sj_index &ix, const float *P, const Geometry &g, BuildTmp &t, hipStream_t s,
                     bool keep) {
   const uint64_t n = ix.n;
-  launch_cellkey(P, n, ix.d, g.kp, t.keys[0].as<uint64_t>(), t.ids[0].as<uint32_t>(), s);
+  TmpBuf pid;
+  if (keep && g.kp.pb) {
+    ix.pivots.alloc(kPivots * ix.d * 4);
+    pid.alloc(n);
+    launch_pivot_table(P, n / kPivots, ix.d, ix.pivots.as<float>(), s);
+    launch_nearest_pivot(P, n, ix.d, ix.pivots.as<float>(), pid.as<uint8_t>(), s);
+  }
+  launch_cellkey(P, n, ix.d, g.kp, pid.as<uint8_t>(), t.keys[0].as<uint64_t>(), t.ids[0].as<uint32_t>(), s);
   uint64_t *kb[2] = {t.keys[0].as<uint64_t>(), t.keys[1].as<uint64_t>()};
   uint32_t *vb[2] = {t.ids[0].as<uint32_t>(), t.ids[1].as<uint32_t>()};
   // a probe of k only counts candidates: the cell part of the keys, without
@@ -723,6 +764,13 @@ uint32_t choose_tc(uint64_t eval_pairs, uint32_t tq) {
   return t;
 }
 
+// The same for an FP32 handle: a matrix-core unit that is a whole workgroup has
+// stretches four times as long for the same number of waves.
+uint32_t mx32_tc(const sj_index &ix, uint64_t eval_pairs) {
+  const uint32_t tc = choose_tc(eval_pairs, ix.tq);
+  return ix.mx32 && !mx32_per_wave(ix.dp) ? std::max<uint32_t>(1024, 4 * tc) : tc;
+}
+
 void compute_thresholds(sj_index &ix) {
   const double u32 = std::ldexp(1.0, -24), u64 = std::ldexp(1.0, -53);
   const double g32 = gamma_n((double)ix.dp + 2.0, u32);
@@ -829,6 +877,48 @@ NormParams norm_params(const sj_index &ix) {
   return p;
 }
 
+bool norm_band_narrow(const sj_index &ix, const NormParams &np, double mean_norm2) {
+  return np.kappa * (6.0 * mean_norm2 + 2.0 * np.s_hi) <= kNormBandMax * ix.eps2;
+}
+
+// The candidates' split rows and reject values, around the sample mean of
+// each dimension (clamped into its range; any centre is valid, and the error
+// grows with the distances from it).
+uint64_t mx32_rows(const sj_index &ix) { return ix.n + 64; }
+bool mx32_fits(const sj_index &ix) {
+  // the split rows take up to twice the bytes of the FP32 rows: large sets
+  // keep the vector form when they would not fit easily
+  const uint64_t bytes = mx32_rows(ix) * (mx32_k(ix.dp) * 4ull + 8ull);
+  return bytes < (1ull << 30) || bytes < default_budget() / 3;
+}
+void mx32_prepare(sj_index &ix, hipStream_t s) {
+  const uint32_t K = mx32_k(ix.dp);
+  const uint64_t np = mx32_rows(ix);
+  std::vector<float> centre(K, 0.0f);
+  for (uint32_t r = 0; r < ix.d; ++r) {
+    const uint32_t t = ix.perm[r];
+    centre[r] = (float)std::min(std::max(ix.dmean[t], ix.dmin[t]), ix.dmax[t]);
+  }
+  // centred coordinates of the points, and of queries up to two cell sides
+  // outside their range, stay below 2^14 (twice that is far inside FP16)
+  double reach = 0.0;
+  for (uint32_t r = 0; r < ix.d; ++r) {
+    const uint32_t t = ix.perm[r];
+    reach = std::max(reach, std::max(ix.dmax[t] - (double)centre[r], (double)centre[r] - ix.dmin[t]));
+  }
+  int e = 0;
+  (void)std::frexp((reach + 2.1 * ix.geom.kp.w) * 1.0001, &e);  // below 2^e
+  ix.mx_scale = (float)std::ldexp(1.0, 14 - e);
+  ix.mx_ctr.alloc(K * 4);
+  ix.mx_xs.alloc(np * K * 4);
+  ix.mx_nn.alloc(np * 4);
+  ix.mx_pn.alloc(np * 4);
+  SJ_HIP(hipMemcpyAsync(ix.mx_ctr.p, centre.data(), K * 4, hipMemcpyHostToDevice, s));
+  launch_mx32_prep(ix.X.as<float>(), ix.n, np, ix.dp, ix.mx_ctr.as<float>(), ix.mx_scale,
+                   mx32_kappa(ix.d), ix.mx_xs.p, ix.mx_nn.as<float>(), ix.mx_pn.as<float>(), s);
+  SJ_HIP(hipStreamSynchronize(s));  // the centre's host copy ends here
+}
+
 void choose_fp32_form(sj_index &ix, hipStream_t s) {
   ix.norm_form = false;
   ix.info.fp32_form = SJ_FP32_DIFFERENCE;
@@ -849,8 +939,7 @@ void choose_fp32_form(sj_index &ix, hipStream_t s) {
   double h = 0.0;
   SJ_HIP(hipMemcpyAsync(&h, nsum.p, 8, hipMemcpyDeviceToHost, s));
   SJ_HIP(hipStreamSynchronize(s));
-  const double mean = h / (double)ix.n;
-  const bool narrow = kappa * (6.0 * mean + 2.0 * s_hi) <= kNormBandMax * ix.eps2;
+  const bool narrow = norm_band_narrow(ix, np, h / (double)ix.n);
   if (ix.opt.fp32_form == SJ_FP32_NORM || narrow) {
     ix.norm_form = true;
     ix.info.fp32_form = SJ_FP32_NORM;
@@ -923,6 +1012,7 @@ void build(sj_index &ix, const float *points, hipStream_t s) {
   SJ_HIP(hipStreamSynchronize(s));
   if (hbad) fail(SJ_ERR_INVALID_ARG, "points contain NaN or Inf coordinates");
   ix.dmean.assign(hvar.begin() + d, hvar.end());
+  for (uint32_t t = 0; t < d; ++t) ix.mean_norm2 += hvar[t] + hvar[d + t] * hvar[d + t];
   for (uint32_t t = 0; t < d; ++t) {
     ix.dmin[t] = (double)ordered_to_float(hmin[t]);
     ix.dmax[t] = (double)ordered_to_float(hmax[t]);
@@ -1012,16 +1102,26 @@ void build(sj_index &ix, const float *points, hipStream_t s) {
   // candidate runs and the work units of the symmetric full join
   ix.n_runs_sym = build_runs(ix, 1, ix.run_off_sym, ix.runs_sym, t, s);
   ix.n_runs_full = build_runs(ix, 0, ix.run_off_full, ix.runs_full, t, s);
-  if (ix.opt.precision == SJ_PREC_FP32) choose_fp32_form(ix, s);
+  // FP32 on the matrix cores for joins of some size with most tile rows live
+  ix.mx32 = mx32_in_range(ix) && (double)ix.candidates >= kMx32MinCandidates && mx32_fits(ix) &&
+            live_slot_share(ix, t.cand_sum.as<uint64_t>(), mx32_queries(ix.dp), s) >=
+                kMx32LiveSlotShareMin;
+  if (ix.mx32) {
+    ix.info.fp32_form = SJ_FP32_NORM;
+    mx32_prepare(ix, s);
+  } else if (ix.opt.precision == SJ_PREC_FP32) {
+    choose_fp32_form(ix, s);
+  }
   // one query per lane when units of the class's width would spend more
   // than a quarter of their lane work on idle query slots (many small cells)
   // (a job of the batched path runs on the matrix cores with its own units)
   ix.small_cells =
-      !ix.batch_job &&
+      !ix.batch_job && !ix.mx32 &&
       live_slot_share(ix, t.cand_sum.as<uint64_t>(),
                       64u * (uint32_t)fp32_rq_for(ix.dp, ix.norm_form, false), s) <
           kLiveSlotShareMin;
-  ix.tq = 64u * (uint32_t)fp32_rq_for(ix.dp, ix.norm_form, ix.small_cells);
+  ix.tq = ix.mx32 ? mx32_queries(ix.dp)
+                  : 64u * (uint32_t)fp32_rq_for(ix.dp, ix.norm_form, ix.small_cells);
   ix.info.units = ix.small_cells ? SJ_UNITS_SMALL_CELLS : SJ_UNITS_CELL;
   uint64_t ev = 0;
   DevBuf probe, probe_r;
@@ -1033,7 +1133,7 @@ void build(sj_index &ix, const float *points, hipStream_t s) {
   } else {
     build_workunits(ix, 1, nullptr, 0, ix.run_off_sym, ix.runs_sym, ix.tq, 16384, probe, &ev, s,
                     false, su ? &probe_r : nullptr);
-    ix.tc = choose_tc(ev, ix.tq);
+    ix.tc = mx32_tc(ix, ev);
     // FP32 units of small cells from groups of neighbouring cells
     ix.wu_grouped = kFp32CellGroups && ix.small_cells && !su &&
                     ix.opt.precision == SJ_PREC_FP32;
@@ -1098,7 +1198,7 @@ void build_query(sj_index &q, const sj_index &E, const float *queries, hipStream
   q.fmt = E.fmt;
   q.kp = E.kp;
   q.norm_form = E.norm_form;
-  q.info.fp32_form = E.info.fp32_form;
+  q.info.fp32_form = E.mx32 ? SJ_FP32_DIFFERENCE : E.info.fp32_form;
   q.tq = E.tq;
   q.counters.alloc(64);
   q.perm_d.alloc(d * 4);
@@ -1171,7 +1271,12 @@ void build_query(sj_index &q, const sj_index &E, const float *queries, hipStream
   unsigned long long *d_far = reinterpret_cast<unsigned long long *>(t.small.as<char>() + 64);
   SJ_HIP(hipMemsetAsync(d_far, 0, 8, s));
   const uint64_t far_key = 1ull << g.key_bits;  // above every key of key_bits bits
-  launch_query_keys(P, m, d, g.kp, bd.as<double>(), bd.as<double>() + d, far_key,
+  TmpBuf pid;
+  if (g.kp.pb) {
+    pid.alloc(m);
+    launch_nearest_pivot(P, m, d, E.pivots.as<float>(), pid.as<uint8_t>(), s);
+  }
+  launch_query_keys(P, m, d, g.kp, pid.as<uint8_t>(), bd.as<double>(), bd.as<double>() + d, far_key,
                     t.keys[0].as<uint64_t>(), t.ids[0].as<uint32_t>(), d_far, s);
   uint64_t *kb[2] = {t.keys[0].as<uint64_t>(), t.keys[1].as<uint64_t>()};
   uint32_t *vb[2] = {t.ids[0].as<uint32_t>(), t.ids[1].as<uint32_t>()};
@@ -1200,11 +1305,19 @@ void build_query(sj_index &q, const sj_index &E, const float *queries, hipStream
   }
   if (q.ncell == 0) return finish();
   q.candidates = build_neighbors(q, E, g.np, t, s, true);
-  q.small_cells =  // as for an index, over the query cells
+  // as for an index, over the query cells; an index joined on the matrix cores
+  // has no norm tables, so its small query sets take the difference form
+  q.mx32 = E.mx32 && (double)q.candidates >= kMx32MinCandidates &&
+           live_slot_share(q, t.cand_sum.as<uint64_t>(), mx32_queries(q.dp), s) >=
+               kMx32LiveSlotShareMin;
+  if (q.mx32) q.info.fp32_form = SJ_FP32_NORM;
+  q.small_cells =
+      !q.mx32 &&
       live_slot_share(q, t.cand_sum.as<uint64_t>(),
                       64u * (uint32_t)fp32_rq_for(q.dp, q.norm_form, false), s) <
       kLiveSlotShareMin;
-  q.tq = 64u * (uint32_t)fp32_rq_for(q.dp, q.norm_form, q.small_cells);
+  q.tq = q.mx32 ? mx32_queries(q.dp)
+                : 64u * (uint32_t)fp32_rq_for(q.dp, q.norm_form, q.small_cells);
   q.info.units = q.small_cells ? SJ_UNITS_SMALL_CELLS : SJ_UNITS_CELL;
   q.n_runs_full = build_runs(q, 0, q.run_off_full, q.runs_full, t, s);
   if (q.norm_form) {  // the queries' table of the norm form (E holds the candidates')
@@ -1223,7 +1336,7 @@ void build_query(sj_index &q, const sj_index &E, const float *queries, hipStream
   const bool su = q.opt.sortidu != 0;  // units from per-block SORTIDU ranges
   build_workunits(q, 0, nullptr, 0, q.run_off_full, q.runs_full, q.tq, 16384, probe, &ev, s,
                   false, su ? &probe_r : nullptr);
-  q.tc = choose_tc(ev, q.tq);
+  q.tc = mx32_tc(q, ev);
   if (q.prec == SJ_PREC_FP32) {
     q.n_wu = build_workunits(q, 0, nullptr, 0, q.run_off_full, q.runs_full, q.tq, q.tc, q.wu,
                              &q.evaluated_sym, s, kWuByStretch, su ? &q.uruns : nullptr);
@@ -1337,28 +1450,62 @@ void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &ru
   a.skipped = ix.counters.as<unsigned long long>() + 3;
   Event e0, e1;
   SJ_HIP(hipEventRecord(e0.e, s));
-  if (ix.prec != SJ_PREC_FP32) {
+  const bool mf = ix.prec != SJ_PREC_FP32;
+  if (mf || ix.mx32) {
+    uint64_t *const keys = count_only ? nullptr : out;
+    const uint64_t slots = count_only ? 0 : cap;
     MfmaLaunch m{};
-    m.fmt = ix.fmt;
-    m.kp = ix.kp;
-    m.view = mfma_view(ix, a.runs, a.qlist, sym);
-    m.wu = a.wu;
-    m.n_wu = a.n_wu;
-    m.out = count_only ? nullptr : out;
-    m.capacity = count_only ? 0 : cap;
-    m.cursor = a.cursor;
-    m.rechecks = a.rechecks;
-    m.per_wave = ix.mfma_per_wave ? 1 : 0;
-    // hits common enough: scan the elements of every tile directly
-    const double per_tile = ix.hit_density * 1024.0;
-    m.hits_frequent = per_tile > kFrequentHits ? 1 : 0;
-    if (const int forced = debug_hits_mode(); forced >= 0) m.hits_frequent = forced;
-    // the query-box prefilter pays where 8 dimensions are a good part of
-    // the distance (the bound uses the first 8 of the variance order) and
-    // most candidates are far (measured: 2M x 16 uniform FP16 joins 25 % and
-    // 13 % faster at 0.004 and 0.03 hits per tile, 15 % slower at 0.26)
-    m.box = !m.per_wave && ix.d <= kBoxMaxDims && per_tile < kBoxMaxHitsPerTile ? 1 : 0;
-    if (const int forced = debug_box_mode(); forced >= 0) m.box = m.per_wave ? 0 : forced;
+    Mx32Launch x{};
+    MfmaView &view = mf ? m.view : x.view.m;
+    view = mfma_view(ix, a.runs, a.qlist, sym);
+    if (mf) {
+      m.fmt = ix.fmt;
+      m.kp = ix.kp;
+      m.wu = a.wu;
+      m.n_wu = a.n_wu;
+      m.out = keys;
+      m.capacity = slots;
+      m.cursor = a.cursor;
+      m.rechecks = a.rechecks;
+      m.per_wave = ix.mfma_per_wave ? 1 : 0;
+      // hits common enough: scan the elements of every tile directly
+      const double per_tile = ix.hit_density * 1024.0;
+      m.hits_frequent = per_tile > kFrequentHits ? 1 : 0;
+      if (const int forced = debug_hits_mode(); forced >= 0) m.hits_frequent = forced;
+      // the query-box prefilter pays where 8 dimensions are a good part of
+      // the distance (the bound uses the first 8 of the variance order) and
+      // most candidates are far (measured: 2M x 16 uniform FP16 joins 25 % and
+      // 13 % faster at 0.004 and 0.03 hits per tile, 15 % slower at 0.26)
+      m.box = !m.per_wave && ix.d <= kBoxMaxDims && per_tile < kBoxMaxHitsPerTile ? 1 : 0;
+      if (const int forced = debug_box_mode(); forced >= 0) m.box = m.per_wave ? 0 : forced;
+    } else {
+      const NormParams np = norm_params(ix);
+      const double sc = (double)E.mx_scale;
+      x.view.sc = E.mx_scale;
+      x.view.s_hi = np.s_hi * sc * sc;
+      x.view.s_lo = np.s_lo * sc * sc;
+      x.view.kappa = mx32_kappa(ix.d);
+      x.view.tiny = kMx32Tiny;
+      // Pairs are accepted on the split sums only where the vector norm form
+      // would be chosen, whose error is larger than theirs on every kind of
+      // data; everywhere else FP64 decides every pair that is not rejected
+      // (a huge factor: nothing passes the accept test).
+      x.view.kacc = ix.dp <= kNormAutoMaxDp && norm_band_narrow(E, np, E.mean_norm2)
+                        ? std::nextafter((float)(1.0 + 4.0 * x.view.kappa), 2.0f)
+                        : FLT_MAX;
+      x.view.XS = E.mx_xs.p;
+      x.view.nn = E.mx_nn.as<float>();
+      x.view.pn = E.mx_pn.as<float>();
+      x.view.ctr = E.mx_ctr.as<float>();
+      x.view.skip_below = skip_below;
+      x.view.orig_id = a.orig_id;
+      x.view.skipped = a.skipped;
+      x.wu = a.wu;
+      x.n_wu = a.n_wu;
+      x.out = keys;
+      x.capacity = slots;
+      x.cursor = a.cursor;
+    }
     {
       // band pairs are collected during the join and rechecked afterwards,
       // one per lane; a band list that overflowed is grown and the join rerun
@@ -1370,25 +1517,28 @@ void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &ru
         ix.band_cap = want;
         ix.band.alloc(ix.band_cap * 8);
       }
-      // result and recheck counts before this launch (a rerun starts from them)
-      uint64_t base[2] = {0, 0};
-      SJ_HIP(hipMemcpyAsync(base, ix.counters.p, 16, hipMemcpyDeviceToHost, s));
+      // result, recheck and skip counts before this launch (a rerun starts
+      // from them)
+      uint64_t base[4] = {0, 0, 0, 0};
+      SJ_HIP(hipMemcpyAsync(base, ix.counters.p, 32, hipMemcpyDeviceToHost, s));
       SJ_HIP(hipStreamSynchronize(s));
+      base[2] = 0;  // the band cursor
       for (int attempt = 0;; ++attempt) {
         SJ_HIP(hipMemsetAsync(band_cursor, 0, 8, s));
-        m.view.band = ix.band.as<uint64_t>();
-        m.view.band_cap = ix.band_cap;
-        m.view.band_cursor = band_cursor;
-        launch_join_mfma(m, s);
+        view.band = ix.band.as<uint64_t>();
+        view.band_cap = ix.band_cap;
+        view.band_cursor = band_cursor;
+        if (mf) launch_join_mfma(m, s);
+        else launch_join_mx32(x, s);
         if (!count_only) ix.info.join_launches++;
-        launch_band_recheck(m.view, m.out, m.capacity, a.cursor, a.rechecks, s);
+        launch_band_recheck(view, keys, slots, a.cursor, a.rechecks, s);
         const uint64_t nb = read_counter(ix, 2, s);
         if (nb <= ix.band_cap) break;
         if (attempt == 2) fail(SJ_ERR_DEVICE, "band list size did not settle");
         ix.band_cap = nb + nb / 8;
         ix.band.alloc(ix.band_cap * 8);
         // the launch starts over
-        SJ_HIP(hipMemcpyAsync(ix.counters.p, base, 16, hipMemcpyHostToDevice, s));
+        SJ_HIP(hipMemcpyAsync(ix.counters.p, base, 32, hipMemcpyHostToDevice, s));
         SJ_HIP(hipStreamSynchronize(s));
       }
     }
@@ -1437,21 +1587,25 @@ uint64_t estimate_pairs(sj_index &ix, hipStream_t s, float *ms) {
   uint64_t ev = 0;
   // the matrix-core path counts with its own filter and its band list (no
   // keys are stored at capacity 0); the FP32 path has a count-only kernel
-  const bool mf = ix.prec != SJ_PREC_FP32;
+  const bool mf = ix.prec != SJ_PREC_FP32, mx = ix.mx32;
   // candidate chunks of at most 4096: the sample's few units are split
   // finely enough to spread over the chip
   const uint64_t nwu = build_workunits(ix, 0, ql.as<uint32_t>(), nq, ix.run_off_full,
                                        ix.runs_full, mf ? ix.tq_single : ix.tq,
-                                       mf ? std::min<uint32_t>(ix.tc_single, 4096) : 4096, wu,
-                                       &ev, s);
+                                       mf   ? std::min<uint32_t>(ix.tc_single, 4096)
+                                       : mx ? std::min<uint32_t>(ix.tc, 4096)
+                                            : 4096,
+                                       wu, &ev, s);
   SJ_HIP(hipMemsetAsync(ix.counters.p, 0, 16, s));
   // the sample's band list: at most one pair in 512 is expected in the band
-  // (a larger band reruns the count with the list at its exact size)
-  if (mf) ix.band_hint = ev / 512;
+  // of the 16-bit filters, and fewer in the FP32 filter's, whose list holds
+  // every pair it cannot reject where it accepts none (a larger band reruns
+  // the count with the list at its exact size)
+  if (mf || mx) ix.band_hint = ev / (mf ? 512 : 1024);
   join_launch(ix, wu, nwu, ix.runs_full, ql.as<uint32_t>(), 0, 1, nullptr, 0, s, ms);
   const uint64_t cnt = read_counter(ix, 0, s);
   const double scale = (double)n / (double)nq;
-  if (mf) {
+  if (mf || mx) {
     // band pairs of the sample size the deferred recheck list of the join
     const double nband = (double)read_counter(ix, 1, s);
     ix.band_hint = (uint64_t)std::ceil(nband * scale * 1.25) + (1u << 16);
@@ -1514,7 +1668,7 @@ void run_single(sj_index &ix, uint64_t est, hipStream_t s) {
   ix.info.ms_join += ms_join;
   Event e0, e1;
   SJ_HIP(hipEventRecord(e0.e, s));
-  if (ix.prec != SJ_PREC_FP32)
+  if (ix.prec != SJ_PREC_FP32 || ix.mx32)
     launch_pos_to_id(ix.pairs.as<uint64_t>(), ix.total, ix.orig_id.as<uint32_t>(),
                      entries_of(ix).orig_id.as<uint32_t>(), s);
   other.alloc(ix.total * 8);
@@ -1657,6 +1811,9 @@ void run_batched(sj_index &ix, uint64_t est, uint64_t per_batch, bool sym, hipSt
     SJ_HIP(hipEventRecord(e0->e, s));
     DevBuf *res = &sl.keys;
     uint64_t cnt = got;
+    if (mf || ix.mx32)
+      launch_pos_to_id(sl.keys.as<uint64_t>(), got, ix.orig_id.as<uint32_t>(),
+                       entries_of(ix).orig_id.as<uint32_t>(), s);
     if (sym) {
       // this batch's pairs: the kept and mirrored join output, and the
       // spilled mirrors of earlier batches that belong here
@@ -1679,9 +1836,6 @@ void run_batched(sj_index &ix, uint64_t est, uint64_t per_batch, bool sym, hipSt
       sort_pairs(ix, sl.other, sl.keys, cnt, s, &sl.sort_tmp);
       res = &sl.other;
     } else {
-      if (mf)
-        launch_pos_to_id(sl.keys.as<uint64_t>(), got, ix.orig_id.as<uint32_t>(),
-                         entries_of(ix).orig_id.as<uint32_t>(), s);
       sl.other.ensure(std::max<uint64_t>(got, 1) * 8);
       sort_pairs(ix, sl.keys, sl.other, got, s, &sl.sort_tmp);
     }

@@ -116,7 +116,8 @@ __global__ __launch_bounds__(kBlock) void k_variance(const float *__restrict__ P
 // ---------------------------------------------------------------------------
 // a3: linearised cell key over the first k reordered dimensions.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ uint64_t sort_key(const float *__restrict__ x, const KeyParams &kp) {
+__device__ __forceinline__ uint64_t sort_key(const float *__restrict__ x, const KeyParams &kp,
+                                             uint32_t pid) {
   uint64_t key = 0;
   for (uint32_t r = 0; r < kp.k; ++r) {
     const double xv = (double)x[kp.dim[r]];
@@ -126,7 +127,7 @@ __device__ __forceinline__ uint64_t sort_key(const float *__restrict__ x, const 
     ci = ci > kp.cmax[r] ? kp.cmax[r] : ci;
     key += ci * kp.mult[r];
   }
-  uint64_t fine = 0;
+  uint64_t fine = pid;
   if (kp.fm) {
     uint32_t f[kFineMaxDims];
     const uint32_t fmax = (1u << kp.fb) - 1u;
@@ -139,17 +140,59 @@ __device__ __forceinline__ uint64_t sort_key(const float *__restrict__ x, const 
     for (int b = (int)kp.fb - 1; b >= 0; --b)
       for (uint32_t r = 0; r < kp.fm; ++r) fine = (fine << 1) | ((f[r] >> b) & 1u);
   }
-  return (key << (kp.fm * kp.fb)) | fine;
+  return (key << (kp.fm * kp.fb + kp.pb)) | fine;
 }
 
 __global__ __launch_bounds__(kBlock) void k_cellkey(const float *__restrict__ P, uint64_t n,
                                                     uint32_t d, KeyParams kp,
+                                                    const uint8_t *__restrict__ pid,
                                                     uint64_t *__restrict__ keys,
                                                     uint32_t *__restrict__ ids) {
   const uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i >= n) return;
-  keys[i] = sort_key(P + i * d, kp);
+  keys[i] = sort_key(P + i * d, kp, pid ? pid[i] : 0u);
   ids[i] = (uint32_t)i;
+}
+
+// Nearest of the kPivots pivot points, in FP32 (any choice is a valid order).
+// Without it the in-cell order of clustered data above 24 dimensions mixes the
+// clusters: the Morton code sees only the dimensions of largest variance,
+// where the clusters overlap most.  The pivots' coordinates are wave-uniform
+// scalar loads; a lane holds one point's 64 sums.
+__global__ __launch_bounds__(kBlock) void k_pivot_table(const float *__restrict__ P,
+                                                        uint64_t stride, uint32_t d,
+                                                        float *__restrict__ table) {
+  const uint32_t e = blockIdx.x * kBlock + threadIdx.x;
+  if (e < kPivots * d) table[e] = P[(uint64_t)(e % kPivots) * stride * d + e / kPivots];
+}
+
+__global__ __launch_bounds__(kBlock) void k_nearest_pivot(const float *__restrict__ P, uint64_t n,
+                                                          uint32_t d,
+                                                          const float *__restrict__ table,
+                                                          uint8_t *__restrict__ pid) {
+  const uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= n) return;
+  float s[kPivots];
+#pragma unroll
+  for (uint32_t j = 0; j < kPivots; ++j) s[j] = 0.0f;
+  for (uint32_t t = 0; t < d; ++t) {
+    const float x = P[i * d + t];
+    const float *q = table + t * kPivots;
+#pragma unroll
+    for (uint32_t j = 0; j < kPivots; ++j) {
+      const float e = x - q[j];
+      s[j] = __builtin_fmaf(e, e, s[j]);
+    }
+  }
+  uint32_t best = 0;
+  float b = s[0];
+#pragma unroll
+  for (uint32_t j = 1; j < kPivots; ++j)
+    if (s[j] < b) {
+      b = s[j];
+      best = j;
+    }
+  pid[i] = (uint8_t)best;
 }
 
 // Keys of query points in the grid of an indexed set E (the general join
@@ -162,6 +205,7 @@ __global__ __launch_bounds__(kBlock) void k_cellkey(const float *__restrict__ P,
 // neighbour cells.
 __global__ __launch_bounds__(kBlock) void k_query_keys(const float *__restrict__ Q, uint64_t m,
                                                        uint32_t d, KeyParams kp,
+                                                       const uint8_t *__restrict__ pid,
                                                        const double *__restrict__ lo,
                                                        const double *__restrict__ hi,
                                                        uint64_t far_key,
@@ -176,7 +220,7 @@ __global__ __launch_bounds__(kBlock) void k_query_keys(const float *__restrict__
       const double v = (double)x[t];
       far = far || v < lo[t] || v > hi[t];
     }
-    keys[i] = far ? far_key : sort_key(x, kp);
+    keys[i] = far ? far_key : sort_key(x, kp, pid ? pid[i] : 0u);
     ids[i] = (uint32_t)i;
   }
   const uint64_t fm = ballot(far);
@@ -760,19 +804,33 @@ void launch_variance(const float *P, uint32_t d, uint64_t stride, uint64_t m, do
   SJ_HIP(hipGetLastError());
 }
 
-void launch_cellkey(const float *P, uint64_t n, uint32_t d, const KeyParams &kp, uint64_t *keys,
-                    uint32_t *ids, hipStream_t s) {
+void launch_cellkey(const float *P, uint64_t n, uint32_t d, const KeyParams &kp,
+                    const uint8_t *pid, uint64_t *keys, uint32_t *ids, hipStream_t s) {
   if (!n) return;
-  hipLaunchKernelGGL(k_cellkey, dim3(blocks_for(n)), dim3(kBlock), 0, s, P, n, d, kp, keys, ids);
+  hipLaunchKernelGGL(k_cellkey, dim3(blocks_for(n)), dim3(kBlock), 0, s, P, n, d, kp, pid, keys,
+                     ids);
+  SJ_HIP(hipGetLastError());
+}
+
+void launch_pivot_table(const float *P, uint64_t stride, uint32_t d, float *table, hipStream_t s) {
+  hipLaunchKernelGGL(k_pivot_table, dim3(blocks_for(kPivots * d)), dim3(kBlock), 0, s, P, stride, d,
+                     table);
+  SJ_HIP(hipGetLastError());
+}
+
+void launch_nearest_pivot(const float *P, uint64_t n, uint32_t d, const float *table, uint8_t *pid,
+                          hipStream_t s) {
+  if (!n) return;
+  hipLaunchKernelGGL(k_nearest_pivot, dim3(blocks_for(n)), dim3(kBlock), 0, s, P, n, d, table, pid);
   SJ_HIP(hipGetLastError());
 }
 
 void launch_query_keys(const float *Q, uint64_t m, uint32_t d, const KeyParams &kp,
-                       const double *lo, const double *hi, uint64_t far_key, uint64_t *keys,
-                       uint32_t *ids, unsigned long long *n_far, hipStream_t s) {
+                       const uint8_t *pid, const double *lo, const double *hi, uint64_t far_key,
+                       uint64_t *keys, uint32_t *ids, unsigned long long *n_far, hipStream_t s) {
   if (!m) return;
-  hipLaunchKernelGGL(k_query_keys, dim3(blocks_for(m)), dim3(kBlock), 0, s, Q, m, d, kp, lo, hi,
-                     far_key, keys, ids, n_far);
+  hipLaunchKernelGGL(k_query_keys, dim3(blocks_for(m)), dim3(kBlock), 0, s, Q, m, d, kp, pid, lo,
+                     hi, far_key, keys, ids, n_far);
   SJ_HIP(hipGetLastError());
 }
 

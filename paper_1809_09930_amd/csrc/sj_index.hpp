@@ -12,10 +12,11 @@ constexpr int kFineMaxDims = 16;
 // Sort key of a point: (cell key << fine_bits) | fine key.
 // Cell key: sum over r < k of c_r * mult[r], with
 // c_r = clamp(floor(((double)x[dim[r]] - org[r]) / w), 0, cmax[r]).
-// Fine key: Morton interleave of fb-bit coordinates of the first fm
-// reordered dimensions over their bounding box, so that points of a cell
-// are laid out along a space-filling curve (consecutive positions are near
-// each other).
+// Fine key: the nearest of 2^pb pivot points (pb = 0: none), then the Morton
+// interleave of fb-bit coordinates of the first fm reordered dimensions over
+// their bounding box, so that points of a cell are laid out cluster by
+// cluster along a space-filling curve (consecutive positions are near each
+// other).
 struct KeyParams {
   uint32_t k;
   uint32_t dim[kKeyMaxDims];
@@ -24,6 +25,7 @@ struct KeyParams {
   uint64_t cmax[kKeyMaxDims];
   double w;
   uint32_t fm, fb;                 // fine dimensions and bits per dimension
+  uint32_t pb;                     // bits of the pivot number above them
   uint32_t fdim[kFineMaxDims];
   double forg[kFineMaxDims], fscale[kFineMaxDims];
 };
@@ -44,14 +46,21 @@ void launch_minmax(const float *P, uint64_t n, uint32_t d, uint32_t *gmin, uint3
 // rows 0, stride, 2 stride, ... (m rows).
 void launch_variance(const float *P, uint32_t d, uint64_t stride, uint64_t m, double *var,
                      hipStream_t s);
-void launch_cellkey(const float *P, uint64_t n, uint32_t d, const KeyParams &kp, uint64_t *keys,
-                    uint32_t *ids, hipStream_t s);
+// pid: nearest pivots (launch_nearest_pivot), or null (number 0).
+void launch_cellkey(const float *P, uint64_t n, uint32_t d, const KeyParams &kp,
+                    const uint8_t *pid, uint64_t *keys, uint32_t *ids, hipStream_t s);
+// Table [d][kPivots] of the rows 0, stride, 2 stride, ... of P, and the number of
+// the row nearest to each of n points among them.
+constexpr uint32_t kPivotBits = 6, kPivots = 1u << kPivotBits;
+void launch_pivot_table(const float *P, uint64_t stride, uint32_t d, float *table, hipStream_t s);
+void launch_nearest_pivot(const float *P, uint64_t n, uint32_t d, const float *table, uint8_t *pid,
+                          hipStream_t s);
 // Sort keys of query points Q [m][d] in an indexed set's grid kp; queries
 // outside [lo_t, hi_t] in some dimension t get far_key (see k_query_keys),
 // and *n_far (device, zeroed by the caller) counts them.
 void launch_query_keys(const float *Q, uint64_t m, uint32_t d, const KeyParams &kp,
-                       const double *lo, const double *hi, uint64_t far_key, uint64_t *keys,
-                       uint32_t *ids, unsigned long long *n_far, hipStream_t s);
+                       const uint8_t *pid, const double *lo, const double *hi, uint64_t far_key,
+                       uint64_t *keys, uint32_t *ids, unsigned long long *n_far, hipStream_t s);
 void launch_gather(const float *P, uint64_t n, uint32_t d, uint32_t dp, const uint32_t *perm,
                    const uint32_t *sorted_ids, float *X, uint32_t *orig_id, uint32_t *pos_of,
                    hipStream_t s);

@@ -26,6 +26,7 @@
 // with a hit enter the per-element path.
 #include "sj_internal.hpp"
 #include "sj_mfma.hpp"
+#include "sj_tile.hpp"
 
 #include <algorithm>
 #include <cfloat>
@@ -34,11 +35,8 @@ namespace sj {
 
 namespace {
 
-constexpr int kStage = 512;
-
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float float16v __attribute__((ext_vector_type(16)));
 typedef float float4v __attribute__((ext_vector_type(4)));
 
 template <int FMT>
@@ -201,23 +199,6 @@ __global__ __launch_bounds__(kBlock) void k_mfma_maxima(uint64_t n, const double
 //   Tlo(b) = (max(0, sqrt(s_lo) - Delta_b))^2 - n_b - E'   (D <= Tlo => accept)
 // evaluated in FP64 with a relative margin and rounded outward to FP32.
 // ---------------------------------------------------------------------------
-// next float above a finite f (one ulp step on the bit pattern)
-__device__ __forceinline__ float next_up(float f) {
-  if (f == 0.0f) return __builtin_bit_cast(float, 1u);
-  const uint32_t b = __builtin_bit_cast(uint32_t, f);
-  return __builtin_bit_cast(float, f > 0.0f ? b + 1u : b - 1u);
-}
-__device__ __forceinline__ float round_up_f32(double v) {
-  if (v != v || v == __builtin_inf()) return __builtin_inff();
-  if (v == -__builtin_inf()) return -__builtin_inff();
-  float f = (float)v;
-  if ((double)f < v) f = next_up(f);
-  return f;
-}
-__device__ __forceinline__ float round_down_f32(double v) {
-  return -round_up_f32(-v);
-}
-
 __global__ __launch_bounds__(kBlock) void k_mfma_thresholds(
     uint64_t n, uint64_t n_pad, MfmaBand band, const double *__restrict__ norm2,
     const double *__restrict__ dist_c, const unsigned long long *__restrict__ maxima,
@@ -249,48 +230,6 @@ __global__ __launch_bounds__(kBlock) void k_mfma_thresholds(
   }
   thi[p] = round_up_f32(thi_v);
   tlo[p] = round_down_f32(tlo_v);
-}
-
-struct Stage {
-  uint64_t *buf;
-  uint32_t cnt;
-};
-
-__device__ __forceinline__ void flush(Stage &st, uint64_t *__restrict__ out, uint64_t capacity,
-                                      unsigned long long *__restrict__ cursor) {
-  if (st.cnt == 0) return;
-  __builtin_amdgcn_wave_barrier();
-  unsigned long long base = 0;
-  if (lane_id() == 0) base = atomicAdd(cursor, (unsigned long long)st.cnt);
-  base = uniform_u64(__shfl(base, 0));
-  for (uint32_t i = lane_id(); i < st.cnt; i += kWave) {
-    const uint64_t pos = base + i;
-    if (pos < capacity) out[pos] = st.buf[i];
-  }
-  __builtin_amdgcn_wave_barrier();
-  st.cnt = 0;
-}
-
-// Where the hit path sends band pairs: a per-wave LDS stage flushed to the
-// deferred-recheck list, or (buf == null) nowhere: the pair is rechecked in
-// place.
-constexpr int kBandStage = 128;
-struct BandSink {
-  uint64_t *buf;
-  uint64_t cap;
-  unsigned long long *cursor;
-  Stage st;
-};
-
-__device__ __forceinline__ float min16(const float16v &v) {
-  float a = __builtin_fminf(__builtin_fminf(v[0], v[1]), v[2]);
-  float b = __builtin_fminf(__builtin_fminf(v[3], v[4]), v[5]);
-  float c = __builtin_fminf(__builtin_fminf(v[6], v[7]), v[8]);
-  float e = __builtin_fminf(__builtin_fminf(v[9], v[10]), v[11]);
-  float f = __builtin_fminf(__builtin_fminf(v[12], v[13]), v[14]);
-  a = __builtin_fminf(__builtin_fminf(a, b), c);
-  e = __builtin_fminf(__builtin_fminf(e, f), v[15]);
-  return __builtin_fminf(a, e);
 }
 
 // Unroll factor of the element loop of the hit path.

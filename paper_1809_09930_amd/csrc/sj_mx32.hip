@@ -1,0 +1,861 @@
+// FP32 distance filter of the self-join on the matrix cores of gfx950.
+//
+// Form.  Points are taken relative to a centre c of the indexed set (the
+// sample mean) and scaled by a power of two, x~ = sc fl32(x - c) with all
+// |x~| <= 2^14, and every x~ is split into two FP16 numbers x1 + x2 (11 bits
+// each, the second one signed).  With queries as rows and candidates as
+// columns a 32x32 tile accumulates in FP32
+//     D = -Thi(q) - 2 q~ . a~
+// from the three products q1a1, q1a2, q2a1 (the fourth is below 2^-22 of
+// |q||a|): three v_mfma_f32_32x32x16_f16 per 16 dimensions, 96 matrix cycles
+// where 16 dimensions of v_mfma_f32_32x32x2_f32 take 512, three BF16 parts (six
+// products) 192.  D > -|a~|^2 (1 - kappa) rejects the pair.  Every other pair is
+// decided by the canonical FP64 predicate (deferred recheck), except where the
+// vector norm form would be the alternative (up to 16 dimensions, eps not small
+// against the norms): there D + (Thi - Tlo)(q) <= -|a~|^2 (1 + ...) accepts it
+// first.  The pair set is exact either way.
+//
+// Error.  With S~ the squared distance of the exact x~, |sqrt S~ - sqrt S| <=
+// u (|q~| + |a~|) (u = 2^-24: the rounded subtraction; S scaled by sc^2), and
+// S <= s_hi for every pair the canonical predicate accepts, hence
+//     S~ <= s_hi + u' (s_hi + 2 |q~|^2 + 2 |a~|^2).
+// The split leaves at most 2^-22 |x~| + 2^-25 per coordinate (FP16 subnormals
+// are kept by the conversions and by the MFMA) and drops q2a2, together at most
+// 1.5 2^-21 (|q~|^2 + |a~|^2) + 2^-22 (...) + tiny / 2, and the FP32 accumulation
+// of m exact products, in any order and even with truncating adds, at most
+// gamma_m(2^-23) (|Thi| + |q~|^2 + |a~|^2).  With kappa the sum of these
+// coefficients (mx32_kappa),
+//     Thi = s_hi - |q~|^2 + 2.1 kappa (|q~|^2 + s_hi) + tiny
+// and the factors on |a~|^2 cover them all, each rounded outward; Tlo is the
+// mirror image with s_lo.
+// Measured distance error against binary64 (rms over pairs at eps, in units
+// of the data; the vector norm form these joins took before in brackets):
+// uniform 8-D 4.7e-8 (1.3e-7), uniform 16-D 8.8e-8 (3.5e-7), mixture 14-D
+// 1.4e-7 (3.2e-7), exponential 16-D 1.52e-9 (1.62e-9).  Where the joins took the
+// vector difference form (uniform 64-D 6.2e-7, here 5.5e-7; mixture 90-D
+// 4.3e-7, here 7.4e-7) no pair is accepted on this estimate: what the FP32 sum
+// used to accept is now decided in FP64.
+// Measured joins, vector forms before and this: uniform 2M x 16 at S_D 64 505
+// and 131 ms, exponential 2M x 16 at eps 0.03 151 and 42 ms, mixture 515k x 90
+// 253 and 54 ms, mixture 301k x 37 in 5 result batches 177 and 50 ms.  The
+// matrix cores hold about 1.4 PFLOP/s on random FP16 operands here (power), so
+// the products of the 2M x 16 join (0.43 of 2e12 pairs after the box test, 83
+// TFLOP) cannot take less than 60 ms.
+//
+// Candidates reach a tile only after a test against all of the unit's queries
+// at once (a bound on the distance, so no pair is lost):
+//   up to 24 padded dimensions, the distance from the bounding box of the
+//   queries over the first 8 dimensions (k_join_fp32_mxw);
+//   above, the distance from the centres of groups of eight queries, itself a
+//   matrix product of the leading parts (k_join_fp32_mxg).
+#include "sj_mx32.hpp"
+
+#include <algorithm>
+#include <cmath>
+
+#include "sj_tile.hpp"
+
+namespace sj {
+
+namespace {
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ float16v mfma(half8 a, half8 b, float16v c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+}
+
+// x = a + b up to 2^-22 |x| + 2^-25
+__device__ __forceinline__ void split2(float x, _Float16 &a, _Float16 &b) {
+  a = (_Float16)x;
+  b = (_Float16)(x - (float)a);
+}
+
+// ---------------------------------------------------------------------------
+// Index build: the candidates' split rows [x1 | x2] of 2 K FP16 numbers, eight
+// consecutive ones of a part per thread, rows n .. n_pad - 1 zero.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kBlock) void k_mx32_split(const float *__restrict__ X, uint64_t n,
+                                                       uint64_t n_pad, uint32_t dp, uint32_t K,
+                                                       const float *__restrict__ ctr, float sc,
+                                                       half8 *__restrict__ XS) {
+  const uint32_t kv = K / 8;  // vectors of one part
+  const uint64_t total = n_pad * kv;
+  for (uint64_t e = (uint64_t)blockIdx.x * kBlock + threadIdx.x; e < total;
+       e += (uint64_t)gridDim.x * kBlock) {
+    const uint64_t p = e / kv;
+    const uint32_t v = (uint32_t)(e - p * kv), t0 = v * 8;
+    half8 a = {}, b = {};
+    if (p < n && t0 < dp) {  // dp is a multiple of 8
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        _Float16 s1, s2;
+        split2(sc * (X[p * dp + t0 + i] - ctr[t0 + i]), s1, s2);
+        a[i] = s1;
+        b[i] = s2;
+      }
+    }
+    half8 *dst = XS + p * (2 * kv) + v;
+    dst[0] = a;
+    dst[kv] = b;
+  }
+}
+
+// Per candidate, rounded up: nn = -|a~|^2 (1 - kappa), the tiles' reject value,
+// and pn = -(|a1|^2 (1 - 2^-13) - |a~|^2 (2^-11 + 2^-15)), that of the group
+// test (see k_join_fp32_mxg).  Rows n .. n_pad - 1 get -inf (never a hit).
+__global__ __launch_bounds__(kBlock) void k_mx32_norms(const float *__restrict__ X, uint64_t n,
+                                                       uint64_t n_pad, uint32_t dp,
+                                                       const float *__restrict__ ctr, float sc,
+                                                       double kappa,
+                                                       float *__restrict__ nn,
+                                                       float *__restrict__ pn) {
+  const uint64_t p = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (p >= n_pad) return;
+  if (p >= n) {
+    nn[p] = -__builtin_inff();
+    pn[p] = -__builtin_inff();
+    return;
+  }
+  const f32x4 *x4 = reinterpret_cast<const f32x4 *>(X + p * dp);
+  double s = 0.0, s1 = 0.0;
+  for (uint32_t t4 = 0; t4 < dp / 4; ++t4) {
+    const f32x4 x = x4[t4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float y = sc * (x[i] - ctr[4 * t4 + i]);
+      const float y1 = (float)(_Float16)y;
+      s += (double)y * (double)y;
+      s1 += (double)y1 * (double)y1;
+    }
+  }
+  nn[p] = round_up_f32(-s * (1.0 - kappa));
+  pn[p] = round_up_f32(-(s1 * (1.0 - 0x1p-13) - s * (0x1p-11 + 0x1p-15)));
+}
+
+// ---------------------------------------------------------------------------
+// Shared by the join kernels
+// ---------------------------------------------------------------------------
+// One query row's slice of 16 dimensions (8 per half-wave): centred, scaled by
+// -2 sc (exact) and split; *n += its part of |q~|^2.
+__device__ __forceinline__ void query_slice(const float *__restrict__ row, const Mx32View &v,
+                                            uint32_t t0, bool live, half8 &a1, half8 &a2,
+                                            double &n) {
+  f32x4 x[2] = {{0, 0, 0, 0}, {0, 0, 0, 0}};
+  if (live && t0 < v.m.dp) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      x[h] = (*reinterpret_cast<const f32x4 *>(row + t0 + 4 * h) -
+              *reinterpret_cast<const f32x4 *>(v.ctr + t0 + 4 * h)) *
+             v.sc;
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float y = x[i / 4][i % 4];
+    n += (double)y * (double)y;
+    _Float16 s1, s2;
+    split2(-2.0f * y, s1, s2);
+    a1[i] = s1;
+    a2[i] = s2;
+  }
+}
+
+// -Thi and Thi - Tlo of a query with |q~|^2 = n
+__device__ __forceinline__ void query_bounds(const Mx32View &v, double n, float &cinit,
+                                             float &delta) {
+  const double k2 = 2.1 * v.kappa;
+  const float thi = round_up_f32(v.s_hi - n + k2 * (n + v.s_hi) + v.tiny);
+  const double tlo = v.s_lo - n - k2 * (n + v.s_lo) - v.tiny;
+  cinit = -thi;
+  delta = round_up_f32((double)thi - tlo);
+}
+
+// Element e of a lane's accumulator is row 8 (e / 4) + 4 half + e % 4.
+__device__ __forceinline__ float16v rows_init(const float *rows32, uint32_t half) {
+  float16v c;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const f32x4 x = *reinterpret_cast<const f32x4 *>(rows32 + 8 * g + 4 * half);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c[4 * g + i] = x[i];
+  }
+  return c;
+}
+
+// One tile's hits as a 16-bit mask per lane (bit e: element e passes nn), and
+// with kAccept the mask of those proven within eps (delta32: Thi - Tlo of the
+// tile's rows).
+template <bool kAccept>
+__device__ __forceinline__ void tile_masks(const float16v &acc, float nn, float kacc,
+                                           const float *delta32, uint32_t half, uint32_t &hit,
+                                           uint32_t &within) {
+  hit = within = 0u;
+  const float nacc = nn * kacc;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    f32x4 d = {0, 0, 0, 0};
+    if constexpr (kAccept) d = *reinterpret_cast<const f32x4 *>(delta32 + 8 * g + 4 * half);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float x = acc[4 * g + i];
+      hit |= x <= nn ? 1u << (4 * g + i) : 0u;
+      if constexpr (kAccept) within |= x + d[i] <= nacc ? 1u << (4 * g + i) : 0u;
+    }
+  }
+}
+
+// Emits the hits of QB tiles of one 32-candidate block: every lane with hits
+// left takes its lowest one per round, so the rounds are few (a lane rarely
+// has two) and there is one copy of the emission code.  hits / within: bits
+// 16 j + e of tile j; cp: the lane's candidate; qpos: the tiles' query
+// positions.  Pairs proven within eps go to the result stage, the others to
+// the recheck list.
+template <bool kAccept, class M>
+__device__ __forceinline__ void emit_hits(M hits, M within, const uint32_t *qpos, uint32_t half,
+                                          uint32_t cp, bool sym, Stage &st, BandSink &bs,
+                                          uint64_t *__restrict__ out, uint64_t capacity,
+                                          unsigned long long *__restrict__ cursor) {
+  while (ballot(hits != 0)) {
+    const bool live = hits != 0;
+    const uint32_t e = live ? (uint32_t)__builtin_ctzll((uint64_t)hits) : 0u;
+    const uint32_t qp = qpos[(e & ~15u) * 2 + 8 * ((e & 15u) / 4) + 4 * half + (e & 3u)];
+    const bool ok = live && (!sym || qp <= cp);
+    const bool acc_ok = kAccept && ok && ((within >> e) & 1) != 0;
+    const bool band = ok && !acc_ok;
+    const uint64_t key = ((uint64_t)qp << 32) | cp;
+    const uint64_t bm = ballot(band);
+    if (bm) {
+      const uint32_t nb = (uint32_t)__builtin_popcountll(bm);
+      if (bs.st.cnt + nb > (uint32_t)kBandStage) flush(bs.st, bs.buf, bs.cap, bs.cursor);
+      if (band) bs.st.buf[bs.st.cnt + lanes_below(bm)] = key;
+      bs.st.cnt += nb;
+    }
+    if constexpr (kAccept) {
+      const uint64_t am = ballot(acc_ok);
+      if (am) {
+        const bool two = acc_ok && sym && qp != cp;
+        const uint64_t m2 = ballot(two);
+        const uint32_t total = (uint32_t)(__builtin_popcountll(am) + __builtin_popcountll(m2));
+        if (st.cnt + total > (uint32_t)kStage) flush(st, out, capacity, cursor);
+        const uint32_t off = st.cnt + lanes_below(am) + lanes_below(m2);
+        if (acc_ok) {
+          st.buf[off] = key;
+          if (two) st.buf[off + 1] = ((uint64_t)cp << 32) | qp;
+        }
+        st.cnt += total;
+      }
+    }
+    if (live) hits &= hits - 1;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Up to 24 padded dimensions: one wave per work unit of 32 QB queries, no
+// barriers.  The wave alternates two phases.  In the first it tests windows of
+// 64 candidates against the box of its queries (vector ALU; rows loaded two
+// windows ahead) until kBatch survivors' positions wait in a ring in LDS; in
+// the second it gathers 32 of them at a time straight into the B operands,
+// each block's loads in flight during the tiles of the block before it.  Long
+// phases let the two waves of a SIMD be in different ones: with a test between
+// any two blocks both units idled most of the time.  Four query blocks per
+// gathered block keep the gathers (96 bytes a row) well below the L2's rate;
+// more would not fit the registers of two waves per SIMD.
+// ---------------------------------------------------------------------------
+constexpr int kBoxDims = 8;
+constexpr uint32_t kBatch = 512;
+constexpr uint32_t kRingW = 1024;  // >= kBatch - 1 pending + two windows of 64
+
+template <int K, int QB>
+__global__ __launch_bounds__(kBlock) void k_join_fp32_mxw(Mx32View v,
+                                                          const WorkUnit *__restrict__ wus,
+                                                          uint64_t n_wu,
+                                                          uint64_t *__restrict__ out,
+                                                          uint64_t capacity,
+                                                          unsigned long long *__restrict__ cursor) {
+  constexpr int KS = K / 16;
+  constexpr int RV = 2 * (K / 8);  // 16-byte vectors per split row
+  constexpr bool kTwo = K > 16;    // a second accumulator for the small products
+  constexpr bool kAccept = K <= 16;
+  __shared__ uint64_t stage_mem[kWavesPerBlock][kAccept ? kStage : 1];
+  __shared__ uint64_t band_mem[kWavesPerBlock][kBandStage];
+  __shared__ uint32_t ring_mem[kWavesPerBlock][kRingW];
+  __shared__ __align__(16) float cinit_mem[kWavesPerBlock][QB * 32];
+  __shared__ __align__(16) float delta_mem[kWavesPerBlock][QB * 32];
+  __shared__ uint32_t qpos_mem[kWavesPerBlock][QB * 32];
+  const MfmaView &m = v.m;
+  const uint32_t w = uniform_u32(threadIdx.x / kWave);
+  const uint64_t u = (uint64_t)blockIdx.x * kWavesPerBlock + w;
+  if (u >= n_wu) return;  // whole wave leaves; no workgroup barrier follows
+  const WorkUnit wu = wus[u];
+  const uint32_t l = lane_id();
+  const uint32_t half = l >> 5, col = l & 31;
+  const uint32_t dp = m.dp;
+  const uint32_t nq = wu.q1 - wu.q0;  // 1 .. 32 QB
+  uint32_t *ring = ring_mem[w];
+
+  half8 A1[QB][KS], A2[QB][KS];
+  float blo[kBoxDims], bhi[kBoxDims];
+#pragma unroll
+  for (int t = 0; t < kBoxDims; ++t) {
+    blo[t] = __builtin_inff();
+    bhi[t] = -__builtin_inff();
+  }
+#pragma unroll
+  for (int j = 0; j < QB; ++j) {
+    const uint32_t idx = (uint32_t)j * 32 + col;
+    const bool live = idx < nq;
+    const uint32_t slot = wu.q0 + idx;
+    const uint32_t p = live ? (m.qlist ? m.qlist[slot] : slot) : 0u;
+    const float *row = m.Xq + (uint64_t)p * dp;
+    double n = 0.0;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      query_slice(row, v, (uint32_t)ks * 16 + half * 8, live, A1[j][ks], A2[j][ks], n);
+    n += __shfl_xor(n, 32);
+    if (half == 0) {
+      float ci, de;
+      query_bounds(v, n, ci, de);
+      cinit_mem[w][idx] = live ? ci : __builtin_inff();
+      delta_mem[w][idx] = live ? de : 0.0f;
+      qpos_mem[w][idx] = live ? p : 0xffffffffu;
+    }
+#pragma unroll
+    for (int t4 = 0; t4 < kBoxDims / 4; ++t4) {
+      const f32x4 x = *reinterpret_cast<const f32x4 *>(row + 4 * t4);
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (live) {
+          blo[4 * t4 + i] = __builtin_fminf(blo[4 * t4 + i], x[i]);
+          bhi[4 * t4 + i] = __builtin_fmaxf(bhi[4 * t4 + i], x[i]);
+        }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < kBoxDims; ++t) {
+    float a = blo[t], b = bhi[t];
+#pragma unroll
+    for (int off = 16; off > 0; off >>= 1) {
+      a = __builtin_fminf(a, __shfl_xor(a, off));
+      b = __builtin_fmaxf(b, __shfl_xor(b, off));
+    }
+    blo[t] = __builtin_bit_cast(float, uniform_u32(__builtin_bit_cast(uint32_t, a)));
+    bhi[t] = __builtin_bit_cast(float, uniform_u32(__builtin_bit_cast(uint32_t, b)));
+  }
+  __builtin_amdgcn_wave_barrier();
+  float16v c0[QB];
+#pragma unroll
+  for (int j = 0; j < QB; ++j) c0[j] = rows_init(&cinit_mem[w][j * 32], half);
+
+  Stage st{&stage_mem[w][0], 0u};
+  BandSink bs{m.band, m.band_cap, m.band_cursor, Stage{&band_mem[w][0], 0u}};
+  uint64_t n_skip = 0;
+  const bool sym = m.symmetric != 0;
+
+  // candidate windows of up to 64 positions of one run
+  uint32_t r = wu.run_first, c = wu.c_begin;
+  uint32_t ce = (r == wu.run_last) ? wu.c_end : scalar_run(m.runs, r).y;
+  auto normalise = [&]() {
+    while (c >= ce && r < wu.run_last) {
+      const uint2 run = scalar_run(m.runs, ++r);
+      c = run.x;
+      ce = (r == wu.run_last) ? wu.c_end : run.y;
+    }
+  };
+  normalise();
+  struct Window {
+    uint32_t c, n;  // first position, length (0: the stream is done)
+    f32x4 x0, x1;   // this lane's candidate: its first 8 dimensions
+  };
+  auto load_window = [&](Window &x) __attribute__((always_inline)) {
+    x.n = c < ce ? (ce - c < (uint32_t)kWave ? ce - c : (uint32_t)kWave) : 0u;
+    x.c = x.n ? c : 0u;
+    const f32x4 *xr =
+        reinterpret_cast<const f32x4 *>(m.X + (uint64_t)(x.c + (l < x.n ? l : 0u)) * dp);
+    x.x0 = xr[0];
+    x.x1 = xr[1];
+    c += x.n;
+    normalise();
+  };
+  uint32_t head = 0, cnt = 0;  // ring (wave-uniform)
+  auto test_window = [&](const Window &x) __attribute__((always_inline)) {
+    float lb = 0.0f;
+#pragma unroll
+    for (int t = 0; t < kBoxDims; ++t) {
+      const float y = t < 4 ? x.x0[t & 3] : x.x1[t & 3];
+      const float g = __builtin_fmaxf(__builtin_fmaxf(blo[t] - y, y - bhi[t]), 0.0f);
+      lb = __builtin_fmaf(g, g, lb);
+    }
+    bool keep = l < x.n && lb <= m.hi;
+    if (v.skip_below) {
+      // candidates of earlier result batches: their pairs were taken there
+      const bool early = l < x.n && v.orig_id[x.c + (l < x.n ? l : 0u)] < v.skip_below;
+      n_skip += (uint64_t)__builtin_popcountll(ballot(early)) * nq;
+      keep = keep && !early;
+    }
+    const uint64_t km = ballot(keep);
+    if (keep) ring[(head + cnt + lanes_below(km)) % kRingW] = x.c + l;
+    cnt += (uint32_t)__builtin_popcountll(km);
+  };
+  struct Block {
+    half8 b[2][KS];
+    float an;
+    uint32_t cp;
+  };
+  const half8 *__restrict__ XS = static_cast<const half8 *>(v.XS);
+  // The next nb <= 32 survivors, padding rows past them.  The loads are
+  // unconditional: under a branch the compiler copies their results at its
+  // end, and so waits for them there.
+  auto load_block = [&](Block &b, uint32_t nb) __attribute__((always_inline)) {
+    const uint32_t pos = col < nb ? ring[(head + col) % kRingW] : m.pad_row;
+    head += nb;
+    cnt -= nb;
+    const half8 *row = XS + (uint64_t)pos * RV + half;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) b.b[i][ks] = row[i * (K / 8) + 2 * ks];
+    b.an = v.nn[pos];
+    b.cp = pos;
+    __builtin_amdgcn_sched_barrier(0);  // issued here, ahead of the tiles
+  };
+  auto tiles = [&](const Block &cur) __attribute__((always_inline)) {
+    float16v acc[QB];
+    if constexpr (kTwo) {
+      float16v lo[QB];
+#pragma unroll
+      for (int j = 0; j < QB; ++j) {
+        acc[j] = c0[j];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) lo[j][e] = 0.0f;
+      }
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+#pragma unroll
+        for (int j = 0; j < QB; ++j) lo[j] = mfma(A1[j][ks], cur.b[1][ks], lo[j]);
+#pragma unroll
+        for (int j = 0; j < QB; ++j) acc[j] = mfma(A1[j][ks], cur.b[0][ks], acc[j]);
+#pragma unroll
+        for (int j = 0; j < QB; ++j) lo[j] = mfma(A2[j][ks], cur.b[0][ks], lo[j]);
+      }
+#pragma unroll
+      for (int j = 0; j < QB; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[j][e] += lo[j][e];
+    } else {
+#pragma unroll
+      for (int j = 0; j < QB; ++j) acc[j] = mfma(A1[j][0], cur.b[1][0], c0[j]);
+#pragma unroll
+      for (int j = 0; j < QB; ++j) acc[j] = mfma(A2[j][0], cur.b[0][0], acc[j]);
+#pragma unroll
+      for (int j = 0; j < QB; ++j) acc[j] = mfma(A1[j][0], cur.b[0][0], acc[j]);
+    }
+    bool any = false;
+#pragma unroll
+    for (int j = 0; j < QB; ++j) any |= min16(acc[j]) <= cur.an;
+    if (ballot(any)) {
+      uint64_t hits = 0, within = 0;
+#pragma unroll
+      for (int j = 0; j < QB; ++j) {
+        if (ballot(min16(acc[j]) <= cur.an) == 0) continue;
+        uint32_t h, a;
+        tile_masks<kAccept>(acc[j], cur.an, v.kacc, &delta_mem[w][j * 32], half, h, a);
+        hits |= (uint64_t)h << (16 * j);
+        within |= (uint64_t)a << (16 * j);
+      }
+      emit_hits<kAccept>(hits, within, qpos_mem[w], half, cur.cp, sym, st, bs, out, capacity,
+                         cursor);
+    }
+  };
+
+  Window w0, w1;
+  load_window(w0);
+  load_window(w1);
+  for (;;) {
+    while (cnt < kBatch && w0.n) {
+      test_window(w0);
+      load_window(w0);
+      test_window(w1);
+      load_window(w1);
+    }
+    if (cnt == 0) break;
+    __builtin_amdgcn_wave_barrier();
+    const uint32_t least = w0.n ? 32u : 1u;  // full blocks only while more may come
+    Block b0, b1;
+    load_block(b0, cnt < 32u ? cnt : 32u);
+    for (;;) {
+      uint32_t nb = cnt >= least ? (cnt < 32u ? cnt : 32u) : 0u;
+      load_block(b1, nb);
+      tiles(b0);
+      if (nb == 0) break;
+      nb = cnt >= least ? (cnt < 32u ? cnt : 32u) : 0u;
+      load_block(b0, nb);
+      tiles(b1);
+      if (nb == 0) break;
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+  flush(bs.st, bs.buf, bs.cap, bs.cursor);
+  if constexpr (kAccept) flush(st, out, capacity, cursor);
+  if (l == 0 && n_skip) atomicAdd(v.skipped, (unsigned long long)n_skip);
+}
+
+// ---------------------------------------------------------------------------
+// Above 24 padded dimensions: one workgroup per work unit of 256 queries.
+//
+// Group test.  The queries form 32 groups of eight consecutive ones; c_g is
+// the mean of a group's q~ rounded to FP16 and r_g the largest |q~ - c_g|.  A
+// pair within eps has |q~ - a~| <= R = sqrt(s_hi) (1 + 2^-18) + u (...), hence
+// |a1 - c_g| <= R + r_g + 2^-11 |a~|, and with 2xy <= x^2 + y^2
+//     |a1|^2 + |c_g|^2 - 2 c_g . a1 <= (R + r_g)^2 (1 + 2^-11)
+//                                      + |a~|^2 (2^-11 + 2^-22).
+// One 32x32 tile of leading products tests 32 candidates against all groups
+// (1/24 of the work it can save): the rows start from -T_g, and candidates
+// above pn in every row are dropped.  The margins of 2^-13 on both sides cover
+// the FP32 accumulation (gamma_129(2^-23) < 2^-15), the rounding of T_g and
+// that of the centring.
+//
+// Survivors' positions enter a ring in LDS; chunks of CH of them are staged,
+// split rows and all, into a double-buffered LDS tile that every wave reads.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kRing = 512;  // >= 63 pending + one window of 256
+
+// Tile shapes by K (dimensions padded to 16): waves per workgroup, query row
+// blocks per wave and candidate columns per staged chunk.
+template <int K>
+struct Shape {
+  static constexpr int NW = K <= 64 ? 4 : 8;
+  static constexpr int QB = K <= 64 ? 2 : 1;
+  static constexpr int CH = K <= 48 ? 64 : 32;
+};
+
+template <int K>
+__global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
+    Mx32View v, const WorkUnit *__restrict__ wus) {
+  constexpr int NW = Shape<K>::NW, QB = Shape<K>::QB, CH = Shape<K>::CH;
+  constexpr int NT = NW * kWave;    // threads
+  constexpr int TQ = NW * QB * 32;  // query rows
+  constexpr int KS = K / 16;
+  constexpr int RV = 2 * (K / 8);     // 16-byte vectors per split row
+  constexpr int RS = RV + 1;          // and per staged row (odd: no bank conflicts)
+  constexpr int PER_THREAD = (CH * RV + NT - 1) / NT;
+  constexpr uint32_t WIN = NW * 32;   // candidates tested at a time
+  static_assert(TQ == 256, "units hold 256 queries in 32 groups");
+  static_assert(RV % 2 == 0, "the padded stride is odd");
+  __shared__ uint64_t band_mem[NW][kBandStage];
+  __shared__ half8 tile[2][CH * RS];
+  __shared__ float tile_n[2][CH];
+  __shared__ uint32_t tile_pos[2][CH];
+  __shared__ uint32_t ring[kRing];
+  __shared__ __align__(16) float cinit[TQ];  // -Thi of each query row
+  __shared__ uint32_t qpos_s[TQ];
+  __shared__ __align__(16) float ginit[32];  // -T_g
+  __shared__ __align__(16) _Float16 gctr[32][K];
+  __shared__ uint32_t wcnt[NW];
+  const MfmaView &m = v.m;
+  const WorkUnit wu = wus[blockIdx.x];
+  const uint32_t tid = threadIdx.x;
+  const uint32_t w = uniform_u32(tid / kWave);
+  const uint32_t l = lane_id();
+  const uint32_t half = l >> 5, col = l & 31;
+  const uint32_t dp = m.dp;
+  const uint32_t nq = wu.q1 - wu.q0;  // 1 .. TQ
+
+  // query rows: split operands of -2 q~ and thresholds
+  half8 A1[QB][KS], A2[QB][KS];
+#pragma unroll
+  for (int j = 0; j < QB; ++j) {
+    const uint32_t idx = (w * QB + (uint32_t)j) * 32 + col;
+    const bool live = idx < nq;
+    const uint32_t slot = wu.q0 + idx;
+    const uint32_t p = live ? (m.qlist ? m.qlist[slot] : slot) : 0u;
+    const float *row = m.Xq + (uint64_t)p * dp;
+    double n = 0.0;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      query_slice(row, v, (uint32_t)ks * 16 + half * 8, live, A1[j][ks], A2[j][ks], n);
+    n += __shfl_xor(n, 32);
+    if (half == 0) {
+      float ci, de;
+      query_bounds(v, n, ci, de);
+      cinit[idx] = live ? ci : __builtin_inff();
+      qpos_s[idx] = live ? p : 0xffffffffu;
+    }
+  }
+  __syncthreads();
+  // group g = 8 rows; NT / 32 threads per group, each over every NT/32-th dimension
+  {
+    constexpr uint32_t TG = NT / 32;
+    const uint32_t g = tid / TG, i0 = tid % TG;
+    const uint32_t gn = g * 8 < nq ? (nq - g * 8 < 8u ? nq - g * 8 : 8u) : 0u;
+    double nc = 0.0, d2[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (uint32_t t = i0; t < (uint32_t)K; t += TG) {
+      float y[8], s = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const bool on = (uint32_t)i < gn && t < dp;
+        const uint32_t p = on ? qpos_s[g * 8 + i] : 0u;
+        y[i] = on ? v.sc * (m.Xq[(uint64_t)p * dp + t] - v.ctr[t]) : 0.0f;
+        s += y[i];
+      }
+      const float cf = (float)(_Float16)(gn ? s / (float)gn : 0.0f);
+      gctr[g][t] = (_Float16)(-2.0f * cf);  // exact
+      nc += (double)cf * (double)cf;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const double e = (double)y[i] - (double)cf;
+        if ((uint32_t)i < gn) d2[i] += e * e;
+      }
+    }
+#pragma unroll
+    for (uint32_t off = TG / 2; off > 0; off >>= 1) {
+      nc += __shfl_xor(nc, off);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) d2[i] += __shfl_xor(d2[i], off);
+    }
+    if (i0 == 0) {
+      double r2 = 0.0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) r2 = d2[i] > r2 ? d2[i] : r2;
+      // (1 + 2^-18): the rounded centring, at most u (|q~| + |a~|) against a
+      // margin of 2^-13 |a|^2
+      const double R = (__builtin_sqrt(v.s_hi) + __builtin_sqrt(r2)) * (1.0 + 0x1p-18);
+      const double T = R * R * (1.0 + 0x1p-11) + 0x1p-13 * (R * R + 2.0 * nc) + v.tiny - nc;
+      ginit[g] = gn ? -round_up_f32(T) : __builtin_inff();
+    }
+  }
+  __syncthreads();
+  half8 G[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks)
+    G[ks] = *reinterpret_cast<const half8 *>(&gctr[col][ks * 16 + half * 8]);
+  float16v c0[QB];
+#pragma unroll
+  for (int j = 0; j < QB; ++j) c0[j] = rows_init(&cinit[(w * QB + (uint32_t)j) * 32], half);
+
+  Stage none{nullptr, 0u};
+  BandSink bs{m.band, m.band_cap, m.band_cursor, Stage{&band_mem[w][0], 0u}};
+  uint64_t n_skip = 0;
+  const bool sym = m.symmetric != 0;
+  const half8 *__restrict__ XS = static_cast<const half8 *>(v.XS);
+
+  // candidate stream (uniform over the workgroup) and the ring of survivors
+  uint32_t r = wu.run_first, c = wu.c_begin;
+  uint32_t ce = (r == wu.run_last) ? wu.c_end : scalar_run(m.runs, r).y;
+  auto normalise = [&]() {
+    while (c >= ce && r < wu.run_last) {
+      const uint2 run = scalar_run(m.runs, ++r);
+      c = run.x;
+      ce = (r == wu.run_last) ? wu.c_end : run.y;
+    }
+  };
+  normalise();
+  uint32_t head = 0, tail = 0;  // ring positions (uniform)
+  // test windows until at least CH survivors wait or the stream ends
+  auto fill = [&]() __attribute__((always_inline)) {
+    while (tail - head < (uint32_t)CH && c < ce) {
+      const uint32_t wl = ce - c < WIN ? ce - c : WIN;
+      const uint32_t ci = w * 32 + col;  // this column's candidate (both halves)
+      const bool valid = ci < wl;
+      const uint32_t p = c + (valid ? ci : 0u);
+      const half8 *row = XS + (uint64_t)p * RV + half;
+      half8 b[KS];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) b[ks] = row[2 * ks];
+      const float pnv = v.pn[p];
+      const bool early = v.skip_below && valid && v.orig_id[p] < v.skip_below;
+      float16v a = rows_init(ginit, half);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) a = mfma(G[ks], b[ks], a);
+      // a column passes when some row of either half does
+      const uint64_t pm = ballot(min16(a) <= pnv && valid && !early);
+      const uint32_t keep = (uint32_t)pm | (uint32_t)(pm >> 32);
+      if (v.skip_below)  // earlier result batches took these pairs (halves agree)
+        n_skip += (uint64_t)__builtin_popcount((uint32_t)ballot(early)) * nq;
+      if (l == 0) wcnt[w] = (uint32_t)__builtin_popcount(keep);
+      __syncthreads();
+      uint32_t before = 0, total = 0;
+#pragma unroll
+      for (int i = 0; i < NW; ++i) {
+        const uint32_t k = wcnt[i];
+        before += (uint32_t)i < w ? k : 0u;
+        total += k;
+      }
+      if (half == 0 && ((keep >> col) & 1u))
+        ring[(tail + before + (uint32_t)__builtin_popcount(keep & ((1u << col) - 1u))) % kRing] =
+            p;
+      __syncthreads();  // the ring is read and wcnt rewritten after this
+      tail += total;
+      c += wl;
+      normalise();
+    }
+  };
+  half8 pre[PER_THREAD];
+  uint32_t pre_p = 0;
+  float pre_n = 0.0f;
+  // rows [head, head + nr) of the ring into registers (padding rows past nr)
+  auto gather = [&](uint32_t nr) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < PER_THREAD; ++i) {
+      const uint32_t e = tid + (uint32_t)i * NT;
+      if (e < (uint32_t)(CH * RV)) {
+        const uint32_t rr = e / RV;
+        const uint32_t pos = rr < nr ? ring[(head + rr) % kRing] : m.pad_row;
+        pre[i] = XS[(uint64_t)pos * RV + e % RV];
+      }
+    }
+    if (tid < (uint32_t)CH) {
+      pre_p = tid < nr ? ring[(head + tid) % kRing] : m.pad_row;
+      pre_n = v.nn[pre_p];
+    }
+  };
+  auto store = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < PER_THREAD; ++i) {
+      const uint32_t e = tid + (uint32_t)i * NT;
+      if (e < (uint32_t)(CH * RV)) tile[buf][(e / RV) * RS + e % RV] = pre[i];
+    }
+    if (tid < (uint32_t)CH) {
+      tile_pos[buf][tid] = pre_p;
+      tile_n[buf][tid] = pre_n;
+    }
+  };
+
+  fill();
+  uint32_t ncur = tail - head < (uint32_t)CH ? tail - head : (uint32_t)CH;
+  if (ncur) {
+    gather(ncur);
+    store(0);
+    head += ncur;
+    __syncthreads();
+  }
+  int cur = 0;
+  while (ncur) {
+    fill();
+    const uint32_t nn = tail - head < (uint32_t)CH ? tail - head : (uint32_t)CH;
+    if (nn) gather(nn);  // in flight during the tiles below
+#pragma nounroll
+    for (int blk = 0; blk < CH / 32; ++blk) {
+      if (ncur <= 32u * (uint32_t)blk) break;
+      const half8 *brow = &tile[cur][(blk * 32 + col) * RS + half];
+      float16v acc[QB], lo[QB];
+#pragma unroll
+      for (int j = 0; j < QB; ++j) {
+        acc[j] = c0[j];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) lo[j][e] = 0.0f;
+      }
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const half8 b1 = brow[ks * 2], b2 = brow[K / 8 + ks * 2];
+#pragma unroll
+        for (int j = 0; j < QB; ++j) lo[j] = mfma(A1[j][ks], b2, lo[j]);
+#pragma unroll
+        for (int j = 0; j < QB; ++j) acc[j] = mfma(A1[j][ks], b1, acc[j]);
+#pragma unroll
+        for (int j = 0; j < QB; ++j) lo[j] = mfma(A2[j][ks], b1, lo[j]);
+      }
+#pragma unroll
+      for (int j = 0; j < QB; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[j][e] += lo[j][e];
+      const float an = tile_n[cur][blk * 32 + col];
+      bool any = false;
+#pragma unroll
+      for (int j = 0; j < QB; ++j) any |= min16(acc[j]) <= an;
+      if (ballot(any)) {
+        const uint32_t cp = tile_pos[cur][blk * 32 + col];
+        uint32_t hits = 0, none_within = 0;
+#pragma unroll
+        for (int j = 0; j < QB; ++j) {
+          uint32_t h, a;
+          tile_masks<false>(acc[j], an, 0.0f, nullptr, half, h, a);
+          hits |= h << (16 * j);
+        }
+        emit_hits<false>(hits, none_within, &qpos_s[w * QB * 32], half, cp, sym, none, bs, nullptr,
+                         0, nullptr);
+      }
+    }
+    if (!nn) break;
+    store(cur ^ 1);
+    head += nn;
+    __syncthreads();
+    cur ^= 1;
+    ncur = nn;
+  }
+  flush(bs.st, bs.buf, bs.cap, bs.cursor);
+  if (l == 0 && n_skip) atomicAdd(v.skipped, (unsigned long long)n_skip);
+}
+
+constexpr int kQbBox16 = 4, kQbBox32 = 2;  // query blocks per wave of k_join_fp32_mxw
+
+template <int K, int QB>
+void launch_w(const Mx32Launch &a, hipStream_t s) {
+  const uint64_t grid = (a.n_wu + kWavesPerBlock - 1) / kWavesPerBlock;
+  hipLaunchKernelGGL((k_join_fp32_mxw<K, QB>), dim3((uint32_t)grid), dim3(kBlock), 0, s, a.view,
+                     a.wu, a.n_wu, a.out, a.capacity, a.cursor);
+  SJ_HIP(hipGetLastError());
+}
+
+template <int K>
+void launch_g(const Mx32Launch &a, hipStream_t s) {
+  hipLaunchKernelGGL((k_join_fp32_mxg<K>), dim3((uint32_t)a.n_wu), dim3(Shape<K>::NW * kWave), 0,
+                     s, a.view, a.wu);
+  SJ_HIP(hipGetLastError());
+}
+
+}  // namespace
+
+double mx32_kappa(uint32_t d) {
+  const double k = (double)((d + 15) / 16 * 16);
+  auto gamma = [](double n, double u) { return n * u / (1.0 - n * u); };
+  // sequential adds of the chain that holds the large products: one chain of
+  // all 3 K products at K = 16; above it the large products alone, and the
+  // small ones (below 2^-10 of them, 2 K adds) in a chain of their own
+  const double acc = k <= 16.0 ? gamma(3.0 * k + 2.0, std::ldexp(1.0, -23))
+                               : 1.02 * gamma(k + 4.0, std::ldexp(1.0, -23));
+  return 1.02 * (acc + 4.2 * std::ldexp(1.0, -24) + 2.0 * std::ldexp(1.0, -21));
+}
+
+uint32_t mx32_k(uint32_t dp) { return (dp + 15) / 16 * 16; }
+
+uint32_t mx32_queries(uint32_t dp) {
+  return dp <= 16 ? 32u * kQbBox16 : dp <= 24 ? 32u * kQbBox32 : 256u;
+}
+
+bool mx32_per_wave(uint32_t dp) { return dp <= 24; }
+
+void launch_mx32_prep(const float *X, uint64_t n, uint64_t n_pad, uint32_t dp, const float *ctr,
+                      float sc, double kappa, void *XS, float *nn, float *pn, hipStream_t s) {
+  if (!n_pad) return;
+  const uint32_t K = mx32_k(dp);
+  const uint64_t vecs = n_pad * (K / 8);
+  hipLaunchKernelGGL(k_mx32_split,
+                     dim3((uint32_t)std::min<uint64_t>((vecs + kBlock - 1) / kBlock, 1u << 20)),
+                     dim3(kBlock), 0, s, X, n, n_pad, dp, K, ctr, sc,
+                     static_cast<half8 *>(XS));
+  SJ_HIP(hipGetLastError());
+  hipLaunchKernelGGL(k_mx32_norms, dim3((uint32_t)((n_pad + kBlock - 1) / kBlock)), dim3(kBlock),
+                     0, s, X, n, n_pad, dp, ctr, sc, kappa, nn, pn);
+  SJ_HIP(hipGetLastError());
+}
+
+void launch_join_mx32(const Mx32Launch &a, hipStream_t s) {
+  if (!a.n_wu) return;
+  if (a.n_wu > 0x7fffffffull) fail(SJ_ERR_INVALID_ARG, "too many work units");
+  const uint32_t dp = a.view.m.dp;
+  if (dp <= 16) return launch_w<16, kQbBox16>(a, s);
+  if (dp <= 24) return launch_w<32, kQbBox32>(a, s);
+  switch (mx32_k(dp)) {
+    case 32: launch_g<32>(a, s); break;
+    case 48: launch_g<48>(a, s); break;
+    case 64: launch_g<64>(a, s); break;
+    case 80: launch_g<80>(a, s); break;
+    case 96: launch_g<96>(a, s); break;
+    case 112: launch_g<112>(a, s); break;
+    case 128: launch_g<128>(a, s); break;
+    default: fail(SJ_ERR_INVALID_ARG, "unsupported padded dimension");
+  }
+}
+
+}  // namespace sj

@@ -15,6 +15,7 @@
 #include "sj_index.hpp"
 #include "sj_internal.hpp"
 #include "sj_mfma.hpp"
+#include "sj_mx32.hpp"
 
 namespace sj {
 
@@ -295,11 +296,17 @@ struct sj_index {
   DevBuf XA, XB, cn, thi, tlo;  // 16-bit operands, FP32 candidate norms, thresholds
   bool mfma_per_wave = false;   // matrix-core single join with per-wave units
   uint32_t tq_single = 0, tc_single = 0;  // its unit shape (queries, candidates)
-  DevBuf band;                  // deferred recheck list of the matrix-core join
+  // FP32 on the matrix cores: split rows, reject values, centre (see Mx32View)
+  DevBuf mx_xs, mx_nn, mx_pn, mx_ctr;
+  float mx_scale = 1.0f;
+  double mean_norm2 = 0.0;      // mean squared norm of the points (variance sample)
+  DevBuf pivots;                // [d][kPivots] pivot points of the sort key (pb > 0)
+  DevBuf band;                  // deferred recheck list of the matrix-core joins
   uint64_t band_cap = 0;
   uint64_t band_hint = 0;       // its expected size from the sampled count
   double hit_density = 0.0;     // result + band pairs per evaluated pair of the sampled count
-  bool norm_form = false;       // FP32 filter in norm form
+  bool mx32 = false;            // FP32 filter on the matrix cores (sj_mx32.hip)
+  bool norm_form = false;       // FP32 filter in norm form on the vector ALUs
   DevBuf norm_qa, norm_cr;      // its per-point tables
   DevBuf wu_m;
   uint64_t n_wu_m = 0, evaluated_sym_m = 0;
