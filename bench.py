@@ -36,7 +36,7 @@ sys.path.insert(0, ROOT)
 import datagen  # noqa: E402
 
 EPS_TABLE = os.path.join(ROOT, "tests", "golden", "eps.json")
-TRAFFIC = os.path.join(ROOT, "profiles", "pmc_k_join_fp32_mxw_uniform_2m_d16.md")
+TRAFFIC = os.path.join(ROOT, "profiles", "pmc_k_join_box_uniform_2m_d16.md")
 JOIN_SRC = os.path.join(ROOT, "paper_1809_09930_amd", "csrc", "sj_mx32.hip")
 
 # Dense FP16/BF16 matrix-core peak of MI355X, and a third of it: the FP32
@@ -145,7 +145,7 @@ def candidate_prefix_mean(P, perm, k, eps, n_queries=96, per_query=16384, seed=9
 
 def fp32_kernel(d):
     """The FP32 join kernel of large joins (per padded dimension)."""
-    return "k_join_fp32_mxw" if d <= 24 else "k_join_fp32_mxg"
+    return "k_join_box" if d <= 24 else "k_join_fp32_mxg"
 
 
 def traffic_for_join():

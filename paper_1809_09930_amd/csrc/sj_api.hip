@@ -344,6 +344,8 @@ constexpr bool kFp32CellGroups = SJ_FP32_CELL_GROUPS != 0;
 constexpr double kLookupsPerSec = 2.0e10;
 constexpr double kPairsPerSec = 1.5e12;
 
+constexpr uint32_t kBoxMaxKp = 32;  // K padding up to which the 16-bit filters have the box form
+
 // Whether a handle's FP32 join may run on the matrix cores (sj_mx32.hip): it
 // does for joins of at least kMx32MinCandidates ordered candidate pairs with
 // at least kMx32LiveSlotShareMin of the tile work on live query rows.
@@ -843,7 +845,7 @@ void mfma_prepare(sj_index &ix, hipStream_t s) {
   band.u *= 1.0 + std::ldexp(1.0, -40);
   const double tiny = fmt == kFmtF16 ? std::ldexp(1.0, -14) : std::ldexp(1.0, -126);
   band.eta_term = 2.0 * tiny * 1.0001 * std::sqrt((double)d);
-  band.gamma_acc = gamma_n((double)ix.kp + 1.0, std::ldexp(1.0, -23));
+  band.gamma_acc = gamma_n((double)ix.kp + 4.0, std::ldexp(1.0, -23));
   const double g64 = gamma_n((double)d + 2.0, std::ldexp(1.0, -53));
   band.s_hi = ix.eps2 / (1.0 - g64);
   band.s_lo = ix.eps2 / (1.0 + g64);
@@ -891,6 +893,12 @@ bool mx32_fits(const sj_index &ix) {
   const uint64_t bytes = mx32_rows(ix) * (mx32_k(ix.dp) * 4ull + 8ull);
   return bytes < (1ull << 30) || bytes < default_budget() / 3;
 }
+// Rows of the query-box test of an indexed set.
+void box_prepare(sj_index &ix, hipStream_t s) {
+  ix.box_rows.alloc(ix.n * 32);
+  launch_box_rows(ix.X.as<float>(), ix.n, ix.dp, ix.box_rows.p, ix.box_rows.as<char>() + ix.n * 16,
+                  s);
+}
 void mx32_prepare(sj_index &ix, hipStream_t s) {
   const uint32_t K = mx32_k(ix.dp);
   const uint64_t np = mx32_rows(ix);
@@ -909,6 +917,7 @@ void mx32_prepare(sj_index &ix, hipStream_t s) {
   int e = 0;
   (void)std::frexp((reach + 2.1 * ix.geom.kp.w) * 1.0001, &e);  // below 2^e
   ix.mx_scale = (float)std::ldexp(1.0, 14 - e);
+  if (mx32_per_wave(ix.dp)) box_prepare(ix, s);
   ix.mx_ctr.alloc(K * 4);
   ix.mx_xs.alloc(np * K * 4);
   ix.mx_nn.alloc(np * 4);
@@ -1154,6 +1163,8 @@ void build(sj_index &ix, const float *points, hipStream_t s) {
     // (also for a job of the batched path: its sampled count runs these units)
     ix.mfma_per_wave =
         live_slot_share(ix, t.cand_sum.as<uint64_t>(), tq_wg, s) < kLiveSlotShareMin;
+    // (a query set may have workgroup units where the index has not)
+    if (ix.kp <= kBoxMaxKp && !ix.batch_job) box_prepare(ix, s);
     ix.info.units = ix.mfma_per_wave ? SJ_UNITS_SMALL_CELLS : SJ_UNITS_CELL;
     ix.tq_single = ix.mfma_per_wave ? mfma_wave_queries() : tq_wg;
     ix.tc_single = ix.mfma_per_wave ? choose_tc(ev, ix.tq_single)
@@ -1397,6 +1408,8 @@ MfmaView mfma_view(const sj_index &ix, const uint2 *runs, const uint32_t *qlist,
   v.pshift = 32;
   v.key_hi = 0;
   v.hi = ix.hi32;
+  v.box0 = E.box_rows.p;
+  v.box1 = E.box_rows.p ? E.box_rows.as<char>() + E.n * 16 : nullptr;
   v.pad_row = (uint32_t)E.n;  // rows n .. n_pad-1: zero operands, norm +inf
   return v;
 }
@@ -1466,7 +1479,6 @@ void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &ru
       m.out = keys;
       m.capacity = slots;
       m.cursor = a.cursor;
-      m.rechecks = a.rechecks;
       m.per_wave = ix.mfma_per_wave ? 1 : 0;
       // hits common enough: scan the elements of every tile directly
       const double per_tile = ix.hit_density * 1024.0;
@@ -1478,6 +1490,7 @@ void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &ru
       // 13 % faster at 0.004 and 0.03 hits per tile, 15 % slower at 0.26)
       m.box = !m.per_wave && ix.d <= kBoxMaxDims && per_tile < kBoxMaxHitsPerTile ? 1 : 0;
       if (const int forced = debug_box_mode(); forced >= 0) m.box = m.per_wave ? 0 : forced;
+      if (!E.box_rows.p) m.box = 0;  // (batched jobs' sampled counts, K padding above 32)
     } else {
       const NormParams np = norm_params(ix);
       const double sc = (double)E.mx_scale;

@@ -273,8 +273,8 @@ void record(sj_batch &b, hipStream_t s) {
   launch_fill_u64(b.last.as<unsigned long long>(), nj, 0ull, s);
   launch_join_batched(b.jobs_d.as<BatchJob>(), b.wus.as<WorkUnit>(), b.n_wu, b.grab,
                       reinterpret_cast<unsigned int *>(ctl_ptr(b, 3)), b.keys[0].as<uint64_t>(),
-                      ctl_ptr(b, 2), ctl_ptr(b, 0), ctl_ptr(b, 1), b.grid,
-                      b.band.as<uint64_t>(), b.band_cap, ctl_ptr(b, 4), s);
+                      ctl_ptr(b, 2), ctl_ptr(b, 0), b.grid, b.band.as<uint64_t>(), b.band_cap,
+                      ctl_ptr(b, 4), s);
   launch_band_recheck_batched(b.jobs_d.as<BatchJob>(), b.band.as<uint64_t>(), ctl_ptr(b, 4),
                               b.band_cap, b.keys[0].as<uint64_t>(), ctl_ptr(b, 2), ctl_ptr(b, 0),
                               ctl_ptr(b, 1), b.grid, s);
@@ -332,8 +332,8 @@ float time_join(sj_batch &b) {
   SJ_HIP(hipEventRecord(e0.e, b.cs));
   launch_join_batched(b.jobs_d.as<BatchJob>(), b.wus.as<WorkUnit>(), b.n_wu, b.grab,
                       reinterpret_cast<unsigned int *>(ctl_ptr(b, 3)), b.keys[0].as<uint64_t>(),
-                      ctl_ptr(b, 2), ctl_ptr(b, 0), ctl_ptr(b, 1), b.grid,
-                      b.band.as<uint64_t>(), b.band_cap, ctl_ptr(b, 4), b.cs);
+                      ctl_ptr(b, 2), ctl_ptr(b, 0), b.grid, b.band.as<uint64_t>(), b.band_cap,
+                      ctl_ptr(b, 4), b.cs);
   launch_band_recheck_batched(b.jobs_d.as<BatchJob>(), b.band.as<uint64_t>(), ctl_ptr(b, 4),
                               b.band_cap, b.keys[0].as<uint64_t>(), ctl_ptr(b, 2), ctl_ptr(b, 0),
                               ctl_ptr(b, 1), b.grid, b.cs);

@@ -3,29 +3,30 @@
 //
 // Form.  With a fixed centre c, every point is stored as x~ = Q(x - c) in
 // FP16 or BF16 (Q = round to nearest; magnitudes below the format's
-// smallest normal are flushed to 0).  For a candidate row a and a query
-// column b one 32x32 MFMA tile computes
-//     D = fl32(n_a) - 2 a~ . b~        (n_a = |a~|^2 in FP64)
-// with fl32(n_a) as the tile's initial accumulator, so that D + n_b is the
-// squared distance of the quantised points up to the FP32 accumulation
-// error and the rounding of n_a (the fold residual |n_a - fl32(n_a)|), both
-// inside the band.  The operands are laid out K-contiguous and zero-padded
-// to K: A rows [a~ | 0], B columns [-2 b~ | 0]; scaling by -2 is exact.
+// smallest normal are flushed to 0).  For a query row b and a candidate
+// column a one 32x32 MFMA tile computes
+//     D = -Thi(b) - 2 b~ . a~
+// with the query's threshold as the row's initial accumulator, and the pair
+// is rejected when D > -fl32(n_a), n_a = |a~|^2 in FP64.  The operands are laid
+// out K-contiguous and zero-padded to K: query rows [-2 b~ | 0], candidate
+// columns [a~ | 0]; scaling by -2 is exact.
 //
 // Band.  Per query b the FP64 preparation below gives thresholds
-// Thi(b) >= D for every candidate the canonical predicate accepts, and
-// Tlo(b) such that D <= Tlo(b) proves acceptance (derivation in
-// k_mfma_thresholds).  D > Thi rejects, D <= Tlo accepts, the rest is
-// rechecked with the canonical FP64 predicate, so the pair set is exact.
+// Thi(b) >= n_a - 2 b~ . a~, up to every rounding of the tile, for every
+// candidate the canonical predicate accepts, and Tlo(b) such that a value at or
+// below it proves acceptance (derivation in k_mfma_thresholds).  Above Thi
+// rejects, at or below Tlo accepts, the rest is rechecked with the canonical
+// FP64 predicate, so the pair set is exact.
 //
-// Tiles.  Rows = 32 consecutive candidate positions, columns = 32 queries;
-// a wave holds QB query blocks (B operands and thresholds in registers) and
-// streams candidate blocks (A operands) from memory.  Each lane's 16
-// accumulators share one query column, so "any pair of this lane below its
-// threshold" is one min over 16 values (v_min3) and one compare; only tiles
-// with a hit enter the per-element path.
+// Tiles.  32 queries by 32 consecutive (or gathered) candidates; a wave holds
+// QB query blocks (A operands and thresholds in registers) and streams
+// candidate blocks (B operands).  Each lane's 16 accumulators share one
+// candidate column, so "any pair of this lane below its threshold" is one min
+// over 16 values (v_min3) and one compare; only tiles with a hit enter the
+// per-element path (tile_masks, emit_hits in sj_tile.hpp).
 #include "sj_internal.hpp"
 #include "sj_mfma.hpp"
+#include "sj_mx32.hpp"
 #include "sj_tile.hpp"
 
 #include <algorithm>
@@ -37,7 +38,6 @@ namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float float4v __attribute__((ext_vector_type(4)));
 
 template <int FMT>
 struct Fmt;
@@ -111,10 +111,10 @@ __global__ __launch_bounds__(kBlock) void k_mfma_prep(
 }
 
 // Per point, in dimension order: the quantised norm |x~|^2 and the distance
-// from the centre, both in FP64.  The norm enters the MFMA as the
-// candidate's initial accumulator, rounded to FP32; that rounding is the
-// "fold" error of the bound.  Padding rows get the norm +inf (D = +inf for
-// every query).  Each lane reads its own row as 16-byte vectors.
+// from the centre, both in FP64.  cn is what a tile element must stay below to
+// be a hit: the float above -fl32(norm); that rounding is the "fold" error of
+// the bound.  Padding rows get -inf (never a hit).  Each lane reads its own row
+// as 16-byte vectors.
 template <int FMT>
 __global__ __launch_bounds__(kBlock) void k_mfma_norms(
     const float *__restrict__ X, uint64_t n, uint64_t n_pad, uint32_t d, uint32_t dp,
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kBlock) void k_mfma_norms(
   const uint64_t p = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
   if (p >= n_pad) return;
   if (p >= n) {
-    cn[p] = __builtin_inff();
+    cn[p] = -__builtin_inff();
     return;
   }
   const float4 *x4 = reinterpret_cast<const float4 *>(X + p * dp);  // dp: a multiple of 8
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(kBlock) void k_mfma_norms(
     }
   }
   const float h = (float)nn;
-  cn[p] = h;
+  cn[p] = strict(-h);
   norm2[p] = nn;
   dist_c[p] = __builtin_sqrt(dc);
   fold_err[p] = __builtin_fabs(nn - (double)h);
@@ -190,13 +190,16 @@ __global__ __launch_bounds__(kBlock) void k_mfma_maxima(uint64_t n, const double
 //   (u16 = 2^-11 FP16, 2^-8 BF16; eta = the flush threshold), hence by the
 //   triangle inequality |sqrt(S_q) - sqrt(S)| <= Delta_b =
 //   u (|b-c| + R) + 2 eta sqrt(d), R = max over points of |x-c|.
-//   D = n_a - 2 a~.b~ up to E' = gamma_K(2^-23)(N + F + 2 |b~| Rq) + F + 2^-120
-//   (the MFMA starts from fl32(n_a) and adds K exact products in FP32 in
-//   any order, even with truncating adds; N, Rq, F = maxima of n_a, |a~|
-//   and |n_a - fl32(n_a)|), and S_q = D_exact + n_b.
+//   D = -Thi - 2 b~.a~ up to gamma_{K+4}(2^-23) (|Thi| + 2 |b~| Rq): the MFMA
+//   starts from Thi and adds K exact products in FP32 in any order, even with
+//   truncating adds.  With the rounding of n_a (F) and of the accept test's
+//   addition, everything stays within
+//     E' = gamma_{K+4}(2^-23) (1.01 (hi_root^2 + n_b) + N + F + 2 |b~| Rq) + F + 2^-120
+//   (N, Rq, F = maxima of n_a, |a~| and |n_a - fl32(n_a)|; |Thi| <= hi_root^2 +
+//   n_b up to the last percent), and S_q = n_a - 2 a~.b~ + n_b.
 // Then
-//   Thi(b) = (sqrt(s_hi) + Delta_b)^2 - n_b + E'   (canonical accept => D <= Thi)
-//   Tlo(b) = (max(0, sqrt(s_lo) - Delta_b))^2 - n_b - E'   (D <= Tlo => accept)
+//   Thi(b) = (sqrt(s_hi) + Delta_b)^2 - n_b + E'   (canonical accept => a hit)
+//   Tlo(b) = (max(0, sqrt(s_lo) - Delta_b))^2 - n_b - E'   (at or below: accept)
 // evaluated in FP64 with a relative margin and rounded outward to FP32.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void k_mfma_thresholds(
@@ -217,9 +220,10 @@ __global__ __launch_bounds__(kBlock) void k_mfma_thresholds(
   const double nb = norm2[p];
   const double bq = __builtin_sqrt(nb);
   const double delta = band.u * (dist_c[p] + R) + band.eta_term;
-  const double E = band.gamma_acc * (N + F + 2.0 * bq * Rq) + F + 0x1p-120;
   const double m = 0x1p-45;
   const double hi_root = __builtin_sqrt(band.s_hi) * (1.0 + m) + delta;
+  const double E = band.gamma_acc * (1.01 * (hi_root * hi_root + nb) + N + F + 2.0 * bq * Rq) + F +
+                   0x1p-120;
   const double thi_v = (hi_root * hi_root - nb + E) + m * (hi_root * hi_root + nb + E);
   double lo_root = __builtin_sqrt(band.s_lo) * (1.0 - m) - delta;
   double tlo_v;
@@ -232,231 +236,168 @@ __global__ __launch_bounds__(kBlock) void k_mfma_thresholds(
   tlo[p] = round_down_f32(tlo_v);
 }
 
-// Unroll factor of the element loop of the hit path.
-#ifndef SJ_HIT_UNROLL
-#define SJ_HIT_UNROLL 4
-#endif
-#define SJ_PRAGMA_(x) _Pragma(#x)
-#define SJ_UNROLL_(n) SJ_PRAGMA_(unroll n)
-#define SJ_UNROLL(n) SJ_UNROLL_(n)
-
-// Initial accumulator of a 32-row block: element e of a lane belongs to row
-// 8*(e/4) + 4*half + e%4, so the lane reads four aligned groups of four
-// candidate norms.
-__device__ __forceinline__ float16v norm_init(const float *__restrict__ nrm32, uint32_t half) {
-  float16v c;
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    const float4v q = *reinterpret_cast<const float4v *>(nrm32 + 8 * g + 4 * half);
-    c[4 * g + 0] = q[0];
-    c[4 * g + 1] = q[1];
-    c[4 * g + 2] = q[2];
-    c[4 * g + 3] = q[3];
-  }
-  return c;
-}
-
-// Does any element of the QB tiles pass its query's upper threshold?
-template <int QB>
-__device__ __forceinline__ bool tiles_any(const float16v (&acc)[QB], const float (&th)[QB]) {
-  bool any = false;
-#pragma unroll
-  for (int j = 0; j < QB; ++j) any |= (min16(acc[j]) <= th[j]);
-  return any;
-}
-
-// Hit path for tiles where hits are common (clustered data: a few result or
-// band pairs in most tiles).  No minimum over the tile first: the 16 element
-// compares of a query block are the wave masks themselves, taken four
-// elements at a time, and only elements with a hit do the row checks and
-// the emission.  Rows are valid without a check when the whole 32-row block
-// lies before cend.
-template <int QB>
-__device__ __forceinline__ void tiles_hits_scan(const float16v (&acc)[QB], const float (&th)[QB],
-                                                const float (&tl)[QB],
-                                                const uint32_t (&qpos)[QB], uint32_t c0,
-                                                uint32_t cend, uint32_t half, const MfmaView &v,
-                                                Stage &st, BandSink &bs,
-                                                uint64_t *__restrict__ out, uint64_t capacity,
-                                                unsigned long long *__restrict__ cursor,
-                                                uint64_t &n_recheck) {
-  const bool sym = v.symmetric != 0;
-  const bool full = c0 + 32u <= cend;  // wave-uniform
-  const uint32_t cbase = c0 + 4u * half;
-#pragma unroll
-  for (int j = 0; j < QB; ++j) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      uint64_t hm[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) hm[i] = ballot(acc[j][4 * g + i] <= th[j]);
-      if ((hm[0] | hm[1] | hm[2] | hm[3]) == 0) continue;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (hm[i] == 0) continue;
-        const int e = 4 * g + i;
-        const bool h = acc[j][e] <= th[j];
-        const uint32_t cp = cbase + (uint32_t)(8 * g + i);
-        const bool ok = h && (full || cp < cend) && (!sym || qpos[j] <= cp);
-        bool acc_ok = ok && acc[j][e] <= tl[j];
-        const bool band = ok && !acc_ok;
-        const uint64_t bm = ballot(band);
-        if (bm) {
-          if (bs.buf) {  // deferred: the pair waits in the band list
-            const uint32_t nb = (uint32_t)__builtin_popcountll(bm);
-            if (bs.st.cnt + nb > (uint32_t)kBandStage) flush(bs.st, bs.buf, bs.cap, bs.cursor);
-            if (band)
-              bs.st.buf[bs.st.cnt + lanes_below(bm)] =
-                  v.key_hi | ((uint64_t)qpos[j] << v.pshift) | cp;
-            bs.st.cnt += nb;
-          } else {
-            if (band)
-              acc_ok = canonical_within(v.Xq, qpos[j], v.X, cp, v.inv_perm, v.d, v.dp, v.eps2);
-            n_recheck += (uint64_t)__builtin_popcountll(bm);
-          }
-        }
-        const uint64_t am = ballot(acc_ok);
-        if (am == 0) continue;
-        const bool two = acc_ok && sym && qpos[j] != cp;
-        const uint64_t m2 = ballot(two);
-        const uint32_t total = (uint32_t)(__builtin_popcountll(am) + __builtin_popcountll(m2));
-        if (st.cnt + total > (uint32_t)kStage) flush(st, out, capacity, cursor);
-        const uint32_t off = st.cnt + lanes_below(am) + lanes_below(m2);
-        if (acc_ok) {
-          st.buf[off] = v.key_hi | ((uint64_t)qpos[j] << v.pshift) | cp;
-          if (two) st.buf[off + 1] = v.key_hi | ((uint64_t)cp << v.pshift) | qpos[j];
-        }
-        st.cnt += total;
-      }
-    }
-  }
-}
-
-// Hit modes of the single-join kernels: kHitsRare tests the minimum of each
-// tile first and scans the elements only of tiles with a hit; kHitsFrequent
-// goes straight to the element scan.
+// Hit modes of the join kernels: kHitsRare tests the minimum of each tile
+// first and builds the hit masks only of tiles with a hit; kHitsFrequent goes
+// straight to the masks.
 constexpr int kHitsRare = 0;
 constexpr int kHitsFrequent = 1;
 
-// Walks the 32-row candidate blocks of a work unit, run by run.
-struct BlockIter {
-  const uint2 *runs;
-  uint32_t r, r_last, c, ce, c_end_last;
-  __device__ __forceinline__ void init(const WorkUnit &wu, const uint2 *rs) {
-    runs = rs;
-    r = wu.run_first;
-    r_last = wu.run_last;
-    c_end_last = wu.c_end;
-    c = wu.c_begin;
-    ce = (r == r_last) ? c_end_last : runs[r].y;
-    normalise();
-  }
-  __device__ __forceinline__ bool valid() const { return c < ce; }
-  // move past exhausted runs; leaves c >= ce only when all runs are done
-  __device__ __forceinline__ void normalise() {
-    while (c >= ce && r < r_last) {
-      ++r;
-      c = runs[r].x;
-      ce = (r == r_last) ? c_end_last : runs[r].y;
-    }
-  }
-  __device__ __forceinline__ void advance() {
-    c += 32;
-    normalise();
-  }
+// The queries of a unit or a part of one: operands and initial accumulators in
+// registers, positions and accept margins in LDS tables of 32 QB entries.
+template <int KP, int FMT, int QB>
+struct Queries {
+  typedef typename Fmt<FMT>::V8 V8;
+  V8 A[QB][KP / 16];
+  float16v c0[QB];
+  const float *delta;    // Thi - Tlo, rounded up
+  const uint32_t *qpos;  // positions (0xffffffff: no query)
 };
 
-// One work unit of the matrix-core filter: QB query column blocks against
-// the candidate blocks of the unit's runs.  Accepted pairs are staged as
-// keys key_hi | pos_q << pshift | pos_c.
-template <int KP, int FMT, int QB, int HM = kHitsRare>
-__device__ __forceinline__ void mfma_unit(const MfmaView &v, const WorkUnit &wu, Stage &st,
-                                          BandSink &bs, float *__restrict__ nrm,
-                                          uint64_t *__restrict__ out, uint64_t capacity,
-                                          unsigned long long *__restrict__ cursor,
-                                          uint64_t &n_recheck) {
+// Loads the queries at slots [q0, q1) of v into q; cinit / delta / qpos: this
+// wave's LDS tables.
+template <int KP, int FMT, int QB>
+__device__ __forceinline__ void load_queries(const MfmaView &v, uint32_t q0, uint32_t q1,
+                                             float *cinit, float *delta, uint32_t *qpos,
+                                             Queries<KP, FMT, QB> &q) {
   typedef typename Fmt<FMT>::V8 V8;
-  constexpr int KS = KP / 16;   // MFMA K steps
-  constexpr int RV = KP / 8;    // 8-element vectors per row
-  const V8 *__restrict__ XA = static_cast<const V8 *>(v.XA);
+  constexpr int KS = KP / 16, RV = KP / 8;
   const V8 *__restrict__ XB = static_cast<const V8 *>(v.XB);
-  const uint32_t l = lane_id();
-  const uint32_t half = l >> 5, col = l & 31;
-
-  // query columns: B operands, both thresholds, positions
-  V8 B[QB][KS];
-  float th[QB], tl[QB];
-  uint32_t qpos[QB];
+  const uint32_t l = lane_id(), half = l >> 5, col = l & 31;
 #pragma unroll
   for (int j = 0; j < QB; ++j) {
-    const uint32_t slot = wu.q0 + (uint32_t)j * 32 + col;
-    const bool live = slot < wu.q1;
+    const uint32_t idx = (uint32_t)j * 32 + col;
+    const uint32_t slot = q0 + idx;
+    const bool live = slot < q1;
     const uint32_t p = live ? (v.qlist ? v.qlist[slot] : slot) : 0u;
-    qpos[j] = live ? p : 0xffffffffu;
-    th[j] = live ? v.thi[p] : -__builtin_inff();
-    tl[j] = live ? v.tlo[p] : -__builtin_inff();
+    const float hi = v.thi[p], lo = v.tlo[p];
+    if (half == 0) {
+      cinit[idx] = live ? -hi : __builtin_inff();
+      delta[idx] = live ? round_up_f32((double)hi - (double)lo) : 0.0f;
+      qpos[idx] = live ? p : 0xffffffffu;
+    }
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) B[j][ks] = XB[(uint64_t)p * RV + ks * 2 + half];
+    for (int ks = 0; ks < KS; ++ks) q.A[j][ks] = XB[(uint64_t)p * RV + ks * 2 + half];
   }
+  __builtin_amdgcn_wave_barrier();  // the tables belong to this wave
+#pragma unroll
+  for (int j = 0; j < QB; ++j) q.c0[j] = rows_init(cinit + j * 32, half);
+  q.delta = delta;
+  q.qpos = qpos;
+}
 
-  BlockIter it;
-  it.init(wu, v.runs);
-  if (!it.valid()) return;
-  // candidate operands of the current block; the next block's are fetched
-  // before the current block's MFMAs so their latency overlaps the math.
-  // Rows past the end of the run (at most 31, inside the padded arrays)
-  // are dropped in the hit path.
-  // The block's candidate norms (the MFMA's initial accumulator) go
-  // through the wave's 32-float LDS area, from one row per lane to the
-  // accumulator layout.
-  V8 A[KS];
-  uint32_t c = it.c, ce = it.ce;
+// The QB tiles of one 32-candidate block: operands b, reject value nn and
+// position cp of each lane's candidate.  A tile's products are issued before the
+// minima of the one ahead of it, so that a wave keeps the matrix unit busy by
+// itself.
+template <int KP, int FMT, int QB, int HM>
+__device__ __forceinline__ void tiles(const Queries<KP, FMT, QB> &q,
+                                      const typename Fmt<FMT>::V8 (&b)[KP / 16], float nn,
+                                      uint32_t cp, uint32_t half, const KeyForm &kf, Stage &st,
+                                      BandSink &bs, uint64_t *__restrict__ out, uint64_t capacity,
+                                      unsigned long long *__restrict__ cursor) {
+  static_assert(QB <= 4, "64 hit bits per lane");
+  auto product = [&](int j) __attribute__((always_inline)) {
+    float16v acc = q.c0[j];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) A[ks] = XA[(uint64_t)(c + col) * RV + ks * 2 + half];
-  float nc = v.cn[c + col];
-  it.advance();
-  for (;;) {
-    const bool more = it.valid();
-    V8 An[KS];
-    float ncn = 0.0f;
-    const uint32_t cnext = it.c, cen = it.ce;
-    if (more) {
+    for (int ks = 0; ks < KP / 16; ++ks) acc = Fmt<FMT>::mfma(q.A[j][ks], b[ks], acc);
+    return acc;
+  };
+  uint64_t hits = 0, within = 0;
+  float16v acc = product(0);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) An[ks] = XA[(uint64_t)(cnext + col) * RV + ks * 2 + half];
-      ncn = v.cn[cnext + col];
-      it.advance();
+  for (int j = 0; j < QB; ++j) {
+    float16v next = acc;
+    __builtin_amdgcn_sched_barrier(0);
+    if (j + 1 < QB) next = product(j + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    if (HM == kHitsFrequent || ballot(min16(acc, __builtin_inff()) < nn) != 0) {
+      uint32_t h, a;
+      tile_masks<true>(acc, nn, nn, q.delta + j * 32, half, h, a);
+      hits |= (uint64_t)h << (16 * j);
+      within |= (uint64_t)a << (16 * j);
     }
-    if (half == 0) nrm[col] = nc;
-    __builtin_amdgcn_wave_barrier();
-    const float16v c0 = norm_init(nrm, half);
-    __builtin_amdgcn_wave_barrier();
-    float16v acc[QB];
-#pragma unroll
-    for (int j = 0; j < QB; ++j) {
-      acc[j] = Fmt<FMT>::mfma(A[0], B[j][0], c0);
-#pragma unroll
-      for (int ks = 1; ks < KS; ++ks) acc[j] = Fmt<FMT>::mfma(A[ks], B[j][ks], acc[j]);
-    }
-    if constexpr (HM == kHitsFrequent) {
-      tiles_hits_scan<QB>(acc, th, tl, qpos, c, ce, half, v, st, bs, out, capacity, cursor,
-                          n_recheck);
-    } else if (ballot(tiles_any<QB>(acc, th))) {
-      tiles_hits_scan<QB>(acc, th, tl, qpos, c, ce, half, v, st, bs, out, capacity, cursor,
-                          n_recheck);
-    }
-    if (!more) break;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) A[ks] = An[ks];
-    nc = ncn;
-    c = cnext;
-    ce = cen;
+    acc = next;
   }
+  if (QB > 1 && HM != kHitsFrequent && ballot(hits != 0) == 0) return;
+  emit_hits<true>(hits, within, q.qpos, half, cp, kf, st, bs, out, capacity, cursor);
+}
+
+__device__ __forceinline__ KeyForm key_form(const MfmaView &v) {
+  return KeyForm{v.key_hi, v.pshift, v.symmetric != 0};
+}
+
+// One work unit of the matrix-core filter on one wave: 32 QB queries against
+// the candidate blocks of the unit's runs, read from memory.  The next block's
+// operands are in flight during the current block's tiles; their loads are
+// unconditional (past the last block they repeat it), as under a branch the
+// compiler copies their results at its end, and so waits for them there.
+template <int KP, int FMT, int QB, int HM = kHitsRare>
+__device__ __forceinline__ void mfma_unit(const MfmaView &v, const WorkUnit &wu, Stage &st,
+                                          BandSink &bs, float *cinit, float *delta, uint32_t *qpos,
+                                          uint64_t *__restrict__ out, uint64_t capacity,
+                                          unsigned long long *__restrict__ cursor) {
+  typedef typename Fmt<FMT>::V8 V8;
+  constexpr int KS = KP / 16, RV = KP / 8;
+  const V8 *__restrict__ XA = static_cast<const V8 *>(v.XA);
+  const uint32_t l = lane_id(), half = l >> 5, col = l & 31;
+  // candidate blocks, run by run; rows past the end of a run (at most 31,
+  // inside the padded arrays) get a reject value nothing passes
+  uint32_t r = wu.run_first, c = wu.c_begin;
+  uint32_t ce = (r == wu.run_last) ? wu.c_end : scalar_run(v.runs, r).y;
+  auto normalise = [&]() __attribute__((always_inline)) {
+    while (c >= ce && r < wu.run_last) {
+      const uint2 run = scalar_run(v.runs, ++r);
+      c = run.x;
+      ce = (r == wu.run_last) ? wu.c_end : run.y;
+    }
+  };
+  normalise();
+  if (c >= ce) return;
+  struct Block {
+    V8 b[KS];
+    float nn;
+    uint32_t cp, end;  // position, and where the run ends (0: no block)
+    // (selected at its use: earlier it would wait for the loads)
+    __device__ float reject() const { return cp < end ? nn : -__builtin_inff(); }
+  };
+  uint32_t last_c = c;
+  auto load = [&](Block &k) __attribute__((always_inline)) {
+    const bool more = c < ce;
+    const uint32_t at = more ? c : last_c;
+    k.cp = at + col;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) k.b[ks] = XA[(uint64_t)k.cp * RV + ks * 2 + half];
+    k.nn = v.cn[k.cp];
+    k.end = more ? ce : 0u;
+    __builtin_amdgcn_sched_barrier(0);  // issued here, ahead of the tiles
+    last_c = at;
+    if (more) {
+      c += 32;
+      normalise();
+    }
+    return more;
+  };
+  Queries<KP, FMT, QB> q;
+  load_queries<KP, FMT, QB>(v, wu.q0, wu.q1, cinit, delta, qpos, q);
+  wait_loads();
+  const KeyForm kf = key_form(v);
+  Block b0, b1;
+  bool more = load(b0);
+  for (;;) {
+    more = load(b1);
+    tiles<KP, FMT, QB, HM>(q, b0.b, b0.reject(), b0.cp, half, kf, st, bs, out, capacity, cursor);
+    if (!more) break;
+    more = load(b0);
+    tiles<KP, FMT, QB, HM>(q, b1.b, b1.reject(), b1.cp, half, kf, st, bs, out, capacity, cursor);
+    if (!more) break;
+  }
+  __builtin_amdgcn_wave_barrier();  // the tables are rewritten by the next unit
 }
 
 // Per-wave form for indexes with small cells: every wave takes a work unit
 // of its own (32 * SJ_WAVE_QB queries of one cell) and streams that unit's
 // candidates itself, so cells much smaller than a workgroup's 256 queries do
-// not leave most matrix columns empty.
+// not leave most matrix rows empty.
 #ifndef SJ_WAVE_QB
 #define SJ_WAVE_QB 1
 #endif
@@ -465,70 +406,64 @@ __global__ __launch_bounds__(kBlock) void k_join_mfma_wave(MfmaView v,
                                                            const WorkUnit *__restrict__ wus,
                                                            uint64_t n_wu, uint64_t *__restrict__ out,
                                                            uint64_t capacity,
-                                                           unsigned long long *__restrict__ cursor,
-                                                           unsigned long long *__restrict__ rechecks) {
+                                                           unsigned long long *__restrict__ cursor) {
   __shared__ uint64_t stage_mem[kWavesPerBlock][kStage];
   __shared__ uint64_t band_mem[kWavesPerBlock][kBandStage];
-  __shared__ __align__(16) float nrm_mem[kWavesPerBlock][32];
+  __shared__ __align__(16) float cinit[kWavesPerBlock][32 * SJ_WAVE_QB];
+  __shared__ __align__(16) float delta[kWavesPerBlock][32 * SJ_WAVE_QB];
+  __shared__ uint32_t qpos[kWavesPerBlock][32 * SJ_WAVE_QB];
   const uint32_t w = uniform_u32(threadIdx.x / kWave);
   const uint64_t u = (uint64_t)blockIdx.x * kWavesPerBlock + w;
   if (u >= n_wu) return;  // whole wave leaves; no workgroup barrier follows
   const WorkUnit wu = wus[u];
   Stage st{&stage_mem[w][0], 0u};
   BandSink bs{v.band, v.band_cap, v.band_cursor, Stage{&band_mem[w][0], 0u}};
-  uint64_t n_recheck = 0;
-  mfma_unit<KP, FMT, SJ_WAVE_QB, HM>(v, wu, st, bs, &nrm_mem[w][0], out, capacity, cursor,
-                                     n_recheck);
+  mfma_unit<KP, FMT, SJ_WAVE_QB, HM>(v, wu, st, bs, cinit[w], delta[w], qpos[w], out, capacity,
+                                     cursor);
   flush(st, out, capacity, cursor);
-  if (bs.buf) flush(bs.st, bs.buf, bs.cap, bs.cursor);
-  if (lane_id() == 0 && n_recheck) atomicAdd(rechecks, (unsigned long long)n_recheck);
+  flush(bs.st, bs.buf, bs.cap, bs.cursor);
 }
 
-// Workgroup-cooperative form of the same filter for a single join: the 4
-// waves of a workgroup own 4 x 32*QB query columns of one work unit and
+// Workgroup-cooperative form of the same filter for a single join: the waves
+// of a workgroup own the 256 query rows of one work unit, 32 QB each, and
 // share every candidate chunk of kChunk rows, which is fetched from memory
 // once into a double-buffered LDS stage (global -> registers during the
 // MFMAs of the previous chunk -> LDS) instead of once per wave.
-constexpr int kChunk = 64;  // candidate rows per LDS stage (2 MFMA row blocks)
+constexpr int kChunk = 64;  // candidate rows per LDS stage (2 MFMA column blocks)
 // LDS row stride of a staged chunk, in 16-byte vectors.  Lanes read the
 // same vector of 32 consecutive rows; with an odd stride (RV is even) the
-// reads of 8 consecutive rows fall in different bank groups.  Measured: at
-// K = 64 the FP16 join on 2M x 64 takes 246 / 284 ms with the padding and
-// 288 / 319 without; at K = 16 (a 2-way conflict only) the padded form was
-// slower where hits are frequent (207 against 169 ms), so K = 16 keeps the
-// dense rows.
+// reads of 8 consecutive rows fall in different bank groups.
 constexpr int lds_row_vectors(int rv) { return rv >= 4 ? rv + 1 : rv; }
-// query column blocks per wave for K padding up to 64, and above
-#ifndef SJ_WG_QB_SMALL
-#define SJ_WG_QB_SMALL 2
-#endif
-#ifndef SJ_WG_QB_LARGE
-#define SJ_WG_QB_LARGE 2
-#endif
-// 1: the MFMAs of a block are issued before the filter of the block before
-// it (two accumulator sets); 0: one block at a time
-#ifndef SJ_WG_PIPE
-#define SJ_WG_PIPE 0
-#endif
-static_assert(kChunk == 64, "the workgroup kernel pipelines exactly two 32-row blocks per chunk");
+// Query blocks per wave: four where two waves per SIMD still hold them (each
+// operand read from LDS then serves four products, and the chunk four tiles of
+// products without a wait).  Bound by the card's power on the matrix unit at K 64
+// (2M x 64 BF16 join, 1.17 PFLOP/s); measured there: 231 to 250 ms with two
+// blocks per wave, 223 to 233 with four (226 to 238 with candidates as rows).
+constexpr uint32_t kUnitQueries = 256;
+template <int KP>
+constexpr int wg_qb = KP <= 64 ? 4 : 2;
+
+template <int QB>
+constexpr int wg_threads = (int)kUnitQueries / (32 * QB) * kWave;
 
 template <int KP, int FMT, int QB, int HM>
-__global__ __launch_bounds__(kBlock) void k_join_mfma_wg(MfmaView v,
-                                                         const WorkUnit *__restrict__ wus,
-                                                         uint64_t n_wu, uint64_t *__restrict__ out,
-                                                         uint64_t capacity,
-                                                         unsigned long long *__restrict__ cursor,
-                                                         unsigned long long *__restrict__ rechecks) {
+__global__ __launch_bounds__(wg_threads<QB>) void k_join_mfma_wg(
+    MfmaView v, const WorkUnit *__restrict__ wus, uint64_t n_wu, uint64_t *__restrict__ out,
+    uint64_t capacity, unsigned long long *__restrict__ cursor) {
   typedef typename Fmt<FMT>::V8 V8;
+  constexpr int NT = wg_threads<QB>, NW = NT / kWave;
   constexpr int KS = KP / 16;                     // MFMA K steps
   constexpr int RV = KP / 8;                      // 8-element vectors per row
   constexpr int CHUNK_VECS = kChunk * RV;         // vectors per LDS stage
-  constexpr int PER_THREAD = (CHUNK_VECS + kBlock - 1) / kBlock;
-  __shared__ uint64_t stage_mem[kWavesPerBlock][kStage];
+  constexpr int PER_THREAD = (CHUNK_VECS + NT - 1) / NT;
+  __shared__ uint64_t stage_mem[NW][kStage];
   constexpr int RS = lds_row_vectors(RV);
   __shared__ V8 tile[2][kChunk * RS];
-  __shared__ __align__(16) float tile_n[2][kChunk];  // candidate norms of the chunk
-  __shared__ uint64_t band_mem[kWavesPerBlock][kBandStage];
+  __shared__ float tile_n[2][kChunk];  // reject values of the chunk
+  __shared__ uint64_t band_mem[NW][kBandStage];
+  __shared__ __align__(16) float cinit[NW][32 * QB];
+  __shared__ __align__(16) float delta[NW][32 * QB];
+  __shared__ uint32_t qpos[NW][32 * QB];
   const uint64_t u = blockIdx.x;
   if (u >= n_wu) return;  // whole workgroup leaves together
   const WorkUnit wu = wus[u];
@@ -536,434 +471,82 @@ __global__ __launch_bounds__(kBlock) void k_join_mfma_wg(MfmaView v,
   const uint32_t l = lane_id();
   const uint32_t half = l >> 5, col = l & 31;
   const V8 *__restrict__ XA = static_cast<const V8 *>(v.XA);
-  const V8 *__restrict__ XB = static_cast<const V8 *>(v.XB);
-
-  // this wave's query columns
-  V8 B[QB][KS];
-  float th[QB], tl[QB];
-  uint32_t qpos[QB];
-#pragma unroll
-  for (int j = 0; j < QB; ++j) {
-    const uint32_t slot = wu.q0 + (w * QB + (uint32_t)j) * 32 + col;
-    const bool live = slot < wu.q1;
-    const uint32_t p = live ? (v.qlist ? v.qlist[slot] : slot) : 0u;
-    qpos[j] = live ? p : 0xffffffffu;
-    th[j] = live ? v.thi[p] : -__builtin_inff();
-    tl[j] = live ? v.tlo[p] : -__builtin_inff();
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) B[j][ks] = XB[(uint64_t)p * RV + ks * 2 + half];
-  }
-  Stage st{&stage_mem[w][0], 0u};
-  BandSink bs{v.band, v.band_cap, v.band_cursor, Stage{&band_mem[w][0], 0u}};
-  uint64_t n_recheck = 0;
 
   // chunk walk (uniform over the workgroup)
   uint32_t r = wu.run_first, c = wu.c_begin;
-  uint32_t ce = (r == wu.run_last) ? wu.c_end : v.runs[r].y;
-  auto normalise = [&]() {
+  uint32_t ce = (r == wu.run_last) ? wu.c_end : scalar_run(v.runs, r).y;
+  auto normalise = [&]() __attribute__((always_inline)) {
     while (c >= ce && r < wu.run_last) {
-      ++r;
-      c = v.runs[r].x;
-      ce = (r == wu.run_last) ? wu.c_end : v.runs[r].y;
+      const uint2 run = scalar_run(v.runs, ++r);
+      c = run.x;
+      ce = (r == wu.run_last) ? wu.c_end : run.y;
     }
   };
   normalise();
+  if (c >= ce) return;  // empty unit (uniform)
   V8 pre[PER_THREAD];
-  float pre_n = 0.0f;
-  auto fetch = [&](uint32_t base) {
+  float pre_n;
+  uint32_t pre_rows;
+  // (loads without a branch: its end would wait for them)
+  auto fetch = [&](uint32_t base, uint32_t end) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < PER_THREAD; ++i) {
-      const uint32_t e = threadIdx.x + (uint32_t)i * kBlock;
-      if (e < (uint32_t)CHUNK_VECS) pre[i] = XA[(uint64_t)base * RV + e];
+      const uint32_t e = threadIdx.x + (uint32_t)i * NT;
+      pre[i] = XA[(uint64_t)base * RV + (e < (uint32_t)CHUNK_VECS ? e : 0u)];
     }
-    if (threadIdx.x < (uint32_t)kChunk) pre_n = v.cn[base + threadIdx.x];
+    pre_n = v.cn[base + threadIdx.x % kChunk];
+    pre_rows = end - base;
+    __builtin_amdgcn_sched_barrier(0);  // issued here, ahead of the tiles
   };
-  auto store = [&](int buf) {
+  auto store = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < PER_THREAD; ++i) {
-      const uint32_t e = threadIdx.x + (uint32_t)i * kBlock;
+      const uint32_t e = threadIdx.x + (uint32_t)i * NT;
       if (e < (uint32_t)CHUNK_VECS) tile[buf][(e / RV) * RS + e % RV] = pre[i];
     }
-    if (threadIdx.x < (uint32_t)kChunk) tile_n[buf][threadIdx.x] = pre_n;
+    if (threadIdx.x < (uint32_t)kChunk)  // rows past the run's end never hit
+      tile_n[buf][threadIdx.x] = threadIdx.x < pre_rows ? pre_n : -__builtin_inff();
   };
-  // filter of one 32-row block whose MFMA results are in acc; rows from
-  // c0, valid below cend
-  auto epilogue = [&](const float16v(&acc)[QB], uint32_t c0,
-                      uint32_t cend) __attribute__((always_inline)) {
-    if constexpr (HM == kHitsFrequent) {
-      tiles_hits_scan<QB>(acc, th, tl, qpos, c0, cend, half, v, st, bs, out, capacity, cursor,
-                          n_recheck);
-    } else if (ballot(tiles_any<QB>(acc, th))) {
-      tiles_hits_scan<QB>(acc, th, tl, qpos, c0, cend, half, v, st, bs, out, capacity, cursor,
-                          n_recheck);
-    }
-  };
-  auto block_mfma = [&](int buf, int blk, float16v(&acc)[QB]) __attribute__((always_inline)) {
-    V8 A[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) A[ks] = tile[buf][(blk * 32 + col) * RS + ks * 2 + half];
-    const float16v c0 = norm_init(&tile_n[buf][blk * 32], half);
-#pragma unroll
-    for (int j = 0; j < QB; ++j) {
-      acc[j] = Fmt<FMT>::mfma(A[0], B[j][0], c0);
-#pragma unroll
-      for (int ks = 1; ks < KS; ++ks) acc[j] = Fmt<FMT>::mfma(A[ks], B[j][ks], acc[j]);
-    }
-  };
-
-  if (c >= ce) return;  // empty unit (uniform)
-  fetch(c);
+  fetch(c, ce);
+  // this wave's query rows
+  Queries<KP, FMT, QB> q;
+  load_queries<KP, FMT, QB>(v, wu.q0 + w * QB * 32, wu.q1, cinit[w], delta[w], qpos[w], q);
+  const KeyForm kf = key_form(v);
+  Stage st{&stage_mem[w][0], 0u};
+  BandSink bs{v.band, v.band_cap, v.band_cursor, Stage{&band_mem[w][0], 0u}};
+  wait_loads();
   store(0);
   __syncthreads();
   int cur = 0;
-  // Software pipeline over the two 32-row blocks of each chunk: the MFMAs
-  // of a block are issued before the filter of the block before it, so the
-  // matrix unit works while the vector ALU runs the filter.  accA holds the
-  // first block of a chunk, accB the second (fixed registers, no copies).
-  float16v accA[QB], accB[QB];
-  uint32_t prev_c0 = 0, prev_end = 0;  // block held in accB
-  bool have_prev = false;
   for (;;) {
-    const uint32_t cc = c, cce = ce;
+    const uint32_t cc = c;
     c += kChunk;
     normalise();
     const bool more = c < ce;
-    if (more) fetch(c);
-#if SJ_WG_PIPE
-    block_mfma(cur, 0, accA);
-    if (have_prev) epilogue(accB, prev_c0, prev_end);
-    block_mfma(cur, 1, accB);
-    epilogue(accA, cc, cce);
-    prev_c0 = cc + 32;
-    prev_end = cce;
-    have_prev = true;
-#else
+    fetch(more ? c : cc, more ? ce : cc);
+    V8 b[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) b[ks] = tile[cur][col * RS + ks * 2 + half];
+    float nn = tile_n[cur][col];
 #pragma nounroll
-    for (int blk = 0; blk < 2; ++blk) {
-      block_mfma(cur, blk, accA);
-      epilogue(accA, cc + 32u * (uint32_t)blk, cce);
+    for (uint32_t blk = 0; blk < 2; ++blk) {
+      V8 b2[KS];  // the second block's operands, on their way during the first one's tiles
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) b2[ks] = tile[cur][(32 + col) * RS + ks * 2 + half];
+      const float nn2 = tile_n[cur][32 + col];
+      tiles<KP, FMT, QB, HM>(q, b, nn, cc + blk * 32 + col, half, kf, st, bs, out, capacity,
+                             cursor);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) b[ks] = b2[ks];
+      nn = nn2;
     }
-#endif
     if (!more) break;
     store(cur ^ 1);
     __syncthreads();
     cur ^= 1;
   }
-#if SJ_WG_PIPE
-  epilogue(accB, prev_c0, prev_end);
-#else
-  (void)accB;
-  (void)prev_c0;
-  (void)prev_end;
-  (void)have_prev;
-#endif
-  if (bs.buf) flush(bs.st, bs.buf, bs.cap, bs.cursor);
+  flush(bs.st, bs.buf, bs.cap, bs.cursor);
   flush(st, out, capacity, cursor);
-  if (l == 0 && n_recheck) atomicAdd(rechecks, (unsigned long long)n_recheck);
-}
-
-// Hit path of QB tiles whose 32 rows are the positions rows[0 .. nrows)
-// (rows past nrows are padding with norm +inf): as tiles_hits_scan, with each
-// hit's candidate position read from the row table.
-template <int QB>
-__device__ __forceinline__ void tiles_hits_rows(const float16v (&acc)[QB], const float (&th)[QB],
-                                                const float (&tl)[QB],
-                                                const uint32_t (&qpos)[QB],
-                                                const uint32_t *__restrict__ rows, uint32_t nrows,
-                                                uint32_t half, const MfmaView &v, Stage &st,
-                                                BandSink &bs, uint64_t *__restrict__ out,
-                                                uint64_t capacity,
-                                                unsigned long long *__restrict__ cursor,
-                                                uint64_t &n_recheck) {
-  const bool sym = v.symmetric != 0;
-#pragma unroll
-  for (int j = 0; j < QB; ++j) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      uint64_t hm[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) hm[i] = ballot(acc[j][4 * g + i] <= th[j]);
-      if ((hm[0] | hm[1] | hm[2] | hm[3]) == 0) continue;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (hm[i] == 0) continue;
-        const uint32_t ri = (uint32_t)(8 * g + i) + 4u * half;
-        const bool live = ri < nrows;
-        const uint32_t cp = rows[live ? ri : 0u];
-        const bool ok = acc[j][4 * g + i] <= th[j] && live && (!sym || qpos[j] <= cp);
-        bool acc_ok = ok && acc[j][4 * g + i] <= tl[j];
-        const bool band = ok && !acc_ok;
-        const uint64_t bm = ballot(band);
-        if (bm) {
-          if (bs.buf) {
-            const uint32_t nb = (uint32_t)__builtin_popcountll(bm);
-            if (bs.st.cnt + nb > (uint32_t)kBandStage) flush(bs.st, bs.buf, bs.cap, bs.cursor);
-            if (band)
-              bs.st.buf[bs.st.cnt + lanes_below(bm)] =
-                  v.key_hi | ((uint64_t)qpos[j] << v.pshift) | cp;
-            bs.st.cnt += nb;
-          } else {
-            if (band)
-              acc_ok = canonical_within(v.Xq, qpos[j], v.X, cp, v.inv_perm, v.d, v.dp, v.eps2);
-            n_recheck += (uint64_t)__builtin_popcountll(bm);
-          }
-        }
-        const uint64_t am = ballot(acc_ok);
-        if (am == 0) continue;
-        const bool two = acc_ok && sym && qpos[j] != cp;
-        const uint64_t m2 = ballot(two);
-        const uint32_t total = (uint32_t)(__builtin_popcountll(am) + __builtin_popcountll(m2));
-        if (st.cnt + total > (uint32_t)kStage) flush(st, out, capacity, cursor);
-        const uint32_t off = st.cnt + lanes_below(am) + lanes_below(m2);
-        if (acc_ok) {
-          st.buf[off] = v.key_hi | ((uint64_t)qpos[j] << v.pshift) | cp;
-          if (two) st.buf[off + 1] = v.key_hi | ((uint64_t)cp << v.pshift) | qpos[j];
-        }
-        st.cnt += total;
-      }
-    }
-  }
-}
-
-// The workgroup kernel with the query-box prefilter.  The workgroup's
-// queries span a box over the first kBoxDims dimensions (FP32 rows, the
-// variance order).  The unit's candidate positions are tested 256 at a time
-// (one per thread): the squared distance from a candidate to the box bounds
-// its squared distance to every query of the workgroup from below, and in
-// FP32 the bound is a sum of at most dp rounded squares, within the error
-// the FP32 reject threshold `hi` allows for, so a candidate whose bound
-// exceeds `hi` is rejected for all of them.  Survivors enter a ring of
-// positions in LDS; each chunk of the matrix tiles takes the next 64 of
-// them (gathered rows, positions kept beside the rows), so the tiles hold
-// only candidates that can be within eps of some query.  The rows of the
-// next chunk are fetched during the tiles of the current one, as in
-// k_join_mfma_wg.
-constexpr int kBoxDims = 8;
-constexpr uint32_t kRing = 512;  // >= 127 pending + one window of 256
-
-template <int KP, int FMT, int QB, int HM>
-__global__ __launch_bounds__(kBlock) void k_join_mfma_wg_box(MfmaView v,
-                                                             const WorkUnit *__restrict__ wus,
-                                                             uint64_t n_wu,
-                                                             uint64_t *__restrict__ out,
-                                                             uint64_t capacity,
-                                                             unsigned long long *__restrict__ cursor,
-                                                             unsigned long long *__restrict__ rechecks) {
-  typedef typename Fmt<FMT>::V8 V8;
-  constexpr int KS = KP / 16;
-  constexpr int RV = KP / 8;
-  constexpr int CHUNK_VECS = kChunk * RV;
-  constexpr int PER_THREAD = (CHUNK_VECS + kBlock - 1) / kBlock;
-  __shared__ uint64_t stage_mem[kWavesPerBlock][kStage];
-  constexpr int RS = lds_row_vectors(RV);
-  __shared__ V8 tile[2][kChunk * RS];
-  __shared__ __align__(16) float tile_n[2][kChunk];
-  __shared__ uint32_t tile_pos[2][kChunk];
-  __shared__ uint64_t band_mem[kWavesPerBlock][kBandStage];
-  __shared__ uint32_t ring[kRing];
-  __shared__ float wbox[kWavesPerBlock][2 * kBoxDims];
-  __shared__ uint32_t wcnt[kWavesPerBlock];
-  const uint64_t u = blockIdx.x;
-  if (u >= n_wu) return;  // whole workgroup leaves together
-  const WorkUnit wu = wus[u];
-  const uint32_t w = uniform_u32(threadIdx.x / kWave);
-  const uint32_t l = lane_id();
-  const uint32_t half = l >> 5, col = l & 31;
-  const V8 *__restrict__ XA = static_cast<const V8 *>(v.XA);
-  const V8 *__restrict__ XB = static_cast<const V8 *>(v.XB);
-
-  // this wave's query columns, and their part of the box
-  V8 B[QB][KS];
-  float th[QB], tl[QB];
-  uint32_t qpos[QB];
-  float blo[kBoxDims], bhi[kBoxDims];
-#pragma unroll
-  for (int t = 0; t < kBoxDims; ++t) {
-    blo[t] = __builtin_inff();
-    bhi[t] = -__builtin_inff();
-  }
-#pragma unroll
-  for (int j = 0; j < QB; ++j) {
-    const uint32_t slot = wu.q0 + (w * QB + (uint32_t)j) * 32 + col;
-    const bool live = slot < wu.q1;
-    const uint32_t p = live ? (v.qlist ? v.qlist[slot] : slot) : 0u;
-    qpos[j] = live ? p : 0xffffffffu;
-    th[j] = live ? v.thi[p] : -__builtin_inff();
-    tl[j] = live ? v.tlo[p] : -__builtin_inff();
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) B[j][ks] = XB[(uint64_t)p * RV + ks * 2 + half];
-    const float4 *qr = reinterpret_cast<const float4 *>(v.Xq + (uint64_t)p * v.dp);
-#pragma unroll
-    for (int t4 = 0; t4 < kBoxDims / 4; ++t4) {
-      const float4 x = qr[t4];
-      const float xv[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (live) {
-          blo[4 * t4 + i] = __builtin_fminf(blo[4 * t4 + i], xv[i]);
-          bhi[4 * t4 + i] = __builtin_fmaxf(bhi[4 * t4 + i], xv[i]);
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < kBoxDims; ++t) {
-    float a = blo[t], b = bhi[t];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      a = __builtin_fminf(a, __shfl_xor(a, off));
-      b = __builtin_fmaxf(b, __shfl_xor(b, off));
-    }
-    if (l == 0) {
-      wbox[w][t] = a;
-      wbox[w][kBoxDims + t] = b;
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int t = 0; t < kBoxDims; ++t) {
-    float a = wbox[0][t], b = wbox[0][kBoxDims + t];
-#pragma unroll
-    for (int i = 1; i < kWavesPerBlock; ++i) {
-      a = __builtin_fminf(a, wbox[i][t]);
-      b = __builtin_fmaxf(b, wbox[i][kBoxDims + t]);
-    }
-    blo[t] = __builtin_bit_cast(float, uniform_u32(__builtin_bit_cast(uint32_t, a)));
-    bhi[t] = __builtin_bit_cast(float, uniform_u32(__builtin_bit_cast(uint32_t, b)));
-  }
-  const float hi = v.hi;
-  Stage st{&stage_mem[w][0], 0u};
-  BandSink bs{v.band, v.band_cap, v.band_cursor, Stage{&band_mem[w][0], 0u}};
-  uint64_t n_recheck = 0;
-
-  // candidate stream (uniform over the workgroup) and the ring of survivors
-  uint32_t r = wu.run_first, c = wu.c_begin;
-  uint32_t ce = (r == wu.run_last) ? wu.c_end : v.runs[r].y;
-  auto normalise = [&]() {
-    while (c >= ce && r < wu.run_last) {
-      ++r;
-      c = v.runs[r].x;
-      ce = (r == wu.run_last) ? wu.c_end : v.runs[r].y;
-    }
-  };
-  normalise();
-  uint32_t head = 0, tail = 0;  // ring positions (uniform; differ by <= 383)
-  // test windows until at least `want` survivors wait or the stream ends
-  auto fill = [&](uint32_t want) __attribute__((always_inline)) {
-    while (tail - head < want && c < ce) {
-      const uint32_t wl = ce - c < (uint32_t)kBlock ? ce - c : (uint32_t)kBlock;
-      const uint32_t p = c + threadIdx.x;
-      const bool valid = threadIdx.x < wl;
-      const float4 *xr = reinterpret_cast<const float4 *>(v.X + (uint64_t)(valid ? p : c) * v.dp);
-      float lb = 0.0f;
-#pragma unroll
-      for (int t4 = 0; t4 < kBoxDims / 4; ++t4) {
-        const float4 x = xr[t4];
-        const float xv[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float g = __builtin_fmaxf(
-              __builtin_fmaxf(blo[4 * t4 + i] - xv[i], xv[i] - bhi[4 * t4 + i]), 0.0f);
-          lb = __builtin_fmaf(g, g, lb);
-        }
-      }
-      const bool keep = valid && lb <= hi;
-      const uint64_t km = ballot(keep);
-      if (l == 0) wcnt[w] = (uint32_t)__builtin_popcountll(km);
-      __syncthreads();
-      uint32_t before = 0, total = 0;
-#pragma unroll
-      for (int i = 0; i < kWavesPerBlock; ++i) {
-        const uint32_t ci = wcnt[i];
-        before += (uint32_t)i < w ? ci : 0u;
-        total += ci;
-      }
-      if (keep) ring[(tail + before + lanes_below(km)) % kRing] = p;
-      __syncthreads();  // the ring is read and wcnt rewritten after this
-      tail += total;
-      c += wl;
-      normalise();
-    }
-  };
-  V8 pre[PER_THREAD];
-  float pre_n = 0.0f;
-  uint32_t pre_p = 0;
-  // rows [head, head + nr) of the ring into registers (padding rows past nr)
-  auto gather = [&](uint32_t nr) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const uint32_t e = threadIdx.x + (uint32_t)i * kBlock;
-      if (e < (uint32_t)CHUNK_VECS) {
-        const uint32_t rr = e / RV;
-        const uint32_t pos = rr < nr ? ring[(head + rr) % kRing] : v.pad_row;
-        pre[i] = XA[(uint64_t)pos * RV + e % RV];
-      }
-    }
-    if (threadIdx.x < (uint32_t)kChunk) {
-      const uint32_t rr = threadIdx.x;
-      pre_p = rr < nr ? ring[(head + rr) % kRing] : v.pad_row;
-      pre_n = v.cn[pre_p];
-    }
-  };
-  auto store = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i) {
-      const uint32_t e = threadIdx.x + (uint32_t)i * kBlock;
-      if (e < (uint32_t)CHUNK_VECS) tile[buf][(e / RV) * RS + e % RV] = pre[i];
-    }
-    if (threadIdx.x < (uint32_t)kChunk) {
-      tile_n[buf][threadIdx.x] = pre_n;
-      tile_pos[buf][threadIdx.x] = pre_p;
-    }
-  };
-  auto block_mfma = [&](int buf, int blk, float16v(&acc)[QB]) __attribute__((always_inline)) {
-    V8 A[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) A[ks] = tile[buf][(blk * 32 + col) * RS + ks * 2 + half];
-    const float16v c0 = norm_init(&tile_n[buf][blk * 32], half);
-#pragma unroll
-    for (int j = 0; j < QB; ++j) {
-      acc[j] = Fmt<FMT>::mfma(A[0], B[j][0], c0);
-#pragma unroll
-      for (int ks = 1; ks < KS; ++ks) acc[j] = Fmt<FMT>::mfma(A[ks], B[j][ks], acc[j]);
-    }
-  };
-
-  fill(kChunk);
-  uint32_t ncur = tail - head < (uint32_t)kChunk ? tail - head : (uint32_t)kChunk;
-  if (ncur == 0) return;  // every candidate rejected by the box (uniform)
-  gather(ncur);
-  store(0);
-  head += ncur;
-  __syncthreads();
-  int cur = 0;
-  for (;;) {
-    fill(kChunk);
-    const uint32_t nn = tail - head < (uint32_t)kChunk ? tail - head : (uint32_t)kChunk;
-    if (nn) gather(nn);  // in flight during the tiles below
-#pragma nounroll
-    for (int blk = 0; blk < 2; ++blk) {
-      const uint32_t nb = ncur > 32u * (uint32_t)blk ? ncur - 32u * (uint32_t)blk : 0u;
-      if (nb == 0) break;
-      float16v acc[QB];
-      block_mfma(cur, blk, acc);
-      bool any = true;
-      if constexpr (HM != kHitsFrequent) any = ballot(tiles_any<QB>(acc, th)) != 0;
-      if (any)
-        tiles_hits_rows<QB>(acc, th, tl, qpos, &tile_pos[cur][blk * 32],
-                            nb < 32u ? nb : 32u, half, v, st, bs, out, capacity, cursor,
-                            n_recheck);
-    }
-    if (!nn) break;
-    store(cur ^ 1);
-    head += nn;
-    __syncthreads();
-    cur ^= 1;
-    ncur = nn;
-  }
-  if (bs.buf) flush(bs.st, bs.buf, bs.cap, bs.cursor);
-  flush(st, out, capacity, cursor);
-  if (l == 0 && n_recheck) atomicAdd(rechecks, (unsigned long long)n_recheck);
 }
 
 // Deferred FP64 recheck of the band pairs of a launch: one pair per lane,
@@ -1073,27 +656,26 @@ __global__ __launch_bounds__(kWave) void k_band_recheck_staged(
 // wave leaves once the queue is exhausted, so the grid drains by itself.
 template <int KP, int FMT>
 __device__ __forceinline__ void batched_dispatch(const MfmaView &v, const WorkUnit &wu, Stage &st,
-                                                 BandSink &bs, float *__restrict__ nrm,
+                                                 BandSink &bs, float *tab,
                                                  uint64_t *__restrict__ out, uint64_t capacity,
-                                                 unsigned long long *__restrict__ cursor,
-                                                 uint64_t &n_recheck) {
-  mfma_unit<KP, FMT, SJ_BATCH_QB>(v, wu, st, bs, nrm, out, capacity, cursor, n_recheck);
+                                                 unsigned long long *__restrict__ cursor) {
+  mfma_unit<KP, FMT, SJ_BATCH_QB>(v, wu, st, bs, tab, tab + 32 * SJ_BATCH_QB,
+                                  reinterpret_cast<uint32_t *>(tab + 64 * SJ_BATCH_QB), out,
+                                  capacity, cursor);
 }
 
 __global__ __launch_bounds__(kBlock) void k_join_batched(
     const BatchJob *__restrict__ jobs, const WorkUnit *__restrict__ wus, uint64_t n_wu,
     uint32_t grab, unsigned int *__restrict__ queue, uint64_t *__restrict__ out,
     const unsigned long long *__restrict__ capacity_p, unsigned long long *__restrict__ cursor,
-    unsigned long long *__restrict__ rechecks, uint64_t *__restrict__ band, uint64_t band_cap,
-    unsigned long long *__restrict__ band_cursor) {
+    uint64_t *__restrict__ band, uint64_t band_cap, unsigned long long *__restrict__ band_cursor) {
   __shared__ uint64_t stage_mem[kWavesPerBlock][kStage];
   __shared__ uint64_t band_mem[kWavesPerBlock][kBandStage];
   const uint32_t w = uniform_u32(threadIdx.x / kWave);
-  __shared__ __align__(16) float nrm_mem[kWavesPerBlock][32];
-  float *nrm = &nrm_mem[w][0];
+  __shared__ __align__(16) float tables[kWavesPerBlock][96 * SJ_BATCH_QB];
+  float *tab = &tables[w][0];
   Stage st{&stage_mem[w][0], 0u};
   BandSink bs{band, band_cap, band_cursor, Stage{&band_mem[w][0], 0u}};
-  uint64_t n_recheck = 0;
   const uint64_t capacity = *capacity_p;
   for (;;) {
     unsigned int u0 = 0;
@@ -1107,23 +689,22 @@ __global__ __launch_bounds__(kBlock) void k_join_batched(
       MfmaView v = jobs[job].view;
       v.key_hi = (uint64_t)job << 40;
       switch (jobs[job].variant) {
-        case 0: batched_dispatch<16, kFmtF16>(v, wu, st, bs, nrm, out, capacity, cursor, n_recheck); break;
-        case 1: batched_dispatch<32, kFmtF16>(v, wu, st, bs, nrm, out, capacity, cursor, n_recheck); break;
-        case 2: batched_dispatch<48, kFmtF16>(v, wu, st, bs, nrm, out, capacity, cursor, n_recheck); break;
-        case 3: batched_dispatch<64, kFmtF16>(v, wu, st, bs, nrm, out, capacity, cursor, n_recheck); break;
-        case 4: batched_dispatch<80, kFmtF16>(v, wu, st, bs, nrm, out, capacity, cursor, n_recheck); break;
-        case 5: batched_dispatch<16, kFmtBF16>(v, wu, st, bs, nrm, out, capacity, cursor, n_recheck); break;
-        case 6: batched_dispatch<32, kFmtBF16>(v, wu, st, bs, nrm, out, capacity, cursor, n_recheck); break;
-        case 7: batched_dispatch<48, kFmtBF16>(v, wu, st, bs, nrm, out, capacity, cursor, n_recheck); break;
-        case 8: batched_dispatch<64, kFmtBF16>(v, wu, st, bs, nrm, out, capacity, cursor, n_recheck); break;
-        case 9: batched_dispatch<80, kFmtBF16>(v, wu, st, bs, nrm, out, capacity, cursor, n_recheck); break;
+        case 0: batched_dispatch<16, kFmtF16>(v, wu, st, bs, tab, out, capacity, cursor); break;
+        case 1: batched_dispatch<32, kFmtF16>(v, wu, st, bs, tab, out, capacity, cursor); break;
+        case 2: batched_dispatch<48, kFmtF16>(v, wu, st, bs, tab, out, capacity, cursor); break;
+        case 3: batched_dispatch<64, kFmtF16>(v, wu, st, bs, tab, out, capacity, cursor); break;
+        case 4: batched_dispatch<80, kFmtF16>(v, wu, st, bs, tab, out, capacity, cursor); break;
+        case 5: batched_dispatch<16, kFmtBF16>(v, wu, st, bs, tab, out, capacity, cursor); break;
+        case 6: batched_dispatch<32, kFmtBF16>(v, wu, st, bs, tab, out, capacity, cursor); break;
+        case 7: batched_dispatch<48, kFmtBF16>(v, wu, st, bs, tab, out, capacity, cursor); break;
+        case 8: batched_dispatch<64, kFmtBF16>(v, wu, st, bs, tab, out, capacity, cursor); break;
+        case 9: batched_dispatch<80, kFmtBF16>(v, wu, st, bs, tab, out, capacity, cursor); break;
         default: break;
       }
     }
   }
   flush(st, out, capacity, cursor);
-  if (bs.buf) flush(bs.st, bs.buf, bs.cap, bs.cursor);
-  if (lane_id() == 0 && n_recheck) atomicAdd(rechecks, (unsigned long long)n_recheck);
+  flush(bs.st, bs.buf, bs.cap, bs.cursor);
 }
 
 // Deferred recheck of a batched launch's band pairs (job << 40 | pos_q << 20
@@ -1216,42 +797,26 @@ __global__ __launch_bounds__(kBlock) void k_pos_to_id(uint64_t *__restrict__ key
   }
 }
 
-// K padding up to which the workgroup kernel has the query-box form
-constexpr int kBoxMaxKp = 32;
-
 template <int KP, int FMT>
 void launch_kp(const MfmaLaunch &a, hipStream_t s) {
   const uint32_t grid = (uint32_t)((a.n_wu + kWavesPerBlock - 1) / kWavesPerBlock);
   if (!grid) return;
-  constexpr int QB = KP <= 64 ? SJ_WG_QB_SMALL : SJ_WG_QB_LARGE;
-  MfmaView v = a.view;
+  const MfmaView v = a.view;
   if (a.per_wave) {  // one wave per work unit
     if (a.hits_frequent)
       hipLaunchKernelGGL((k_join_mfma_wave<KP, FMT, kHitsFrequent>), dim3(grid), dim3(kBlock), 0,
-                         s, v, a.wu, a.n_wu, a.out, a.capacity, a.cursor, a.rechecks);
+                         s, v, a.wu, a.n_wu, a.out, a.capacity, a.cursor);
     else
       hipLaunchKernelGGL((k_join_mfma_wave<KP, FMT, kHitsRare>), dim3(grid), dim3(kBlock), 0, s,
-                         v, a.wu, a.n_wu, a.out, a.capacity, a.cursor, a.rechecks);
-  } else if (KP <= kBoxMaxKp && a.box) {  // one workgroup per unit, query-box prefilter
-    if constexpr (KP <= kBoxMaxKp) {
-      if (a.hits_frequent)
-        hipLaunchKernelGGL((k_join_mfma_wg_box<KP, FMT, QB, kHitsFrequent>),
-                           dim3((uint32_t)a.n_wu), dim3(kBlock), 0, s, v, a.wu, a.n_wu, a.out,
-                           a.capacity, a.cursor, a.rechecks);
-      else
-        hipLaunchKernelGGL((k_join_mfma_wg_box<KP, FMT, QB, kHitsRare>), dim3((uint32_t)a.n_wu),
-                           dim3(kBlock), 0, s, v, a.wu, a.n_wu, a.out, a.capacity, a.cursor,
-                           a.rechecks);
-    }
-  } else {  // one workgroup per work unit (4 waves x 32*QB queries)
+                         v, a.wu, a.n_wu, a.out, a.capacity, a.cursor);
+  } else {  // one workgroup per work unit
+    constexpr int QB = wg_qb<KP>;
     if (a.hits_frequent)
       hipLaunchKernelGGL((k_join_mfma_wg<KP, FMT, QB, kHitsFrequent>), dim3((uint32_t)a.n_wu),
-                         dim3(kBlock), 0, s, v, a.wu, a.n_wu, a.out, a.capacity, a.cursor,
-                         a.rechecks);
+                         dim3(wg_threads<QB>), 0, s, v, a.wu, a.n_wu, a.out, a.capacity, a.cursor);
     else
       hipLaunchKernelGGL((k_join_mfma_wg<KP, FMT, QB, kHitsRare>), dim3((uint32_t)a.n_wu),
-                         dim3(kBlock), 0, s, v, a.wu, a.n_wu, a.out, a.capacity, a.cursor,
-                         a.rechecks);
+                         dim3(wg_threads<QB>), 0, s, v, a.wu, a.n_wu, a.out, a.capacity, a.cursor);
   }
   SJ_HIP(hipGetLastError());
 }
@@ -1267,7 +832,6 @@ void launch_fmt(const MfmaLaunch &a, hipStream_t s) {
     case 96: launch_kp<96, FMT>(a, s); break;
     case 112: launch_kp<112, FMT>(a, s); break;
     case 128: launch_kp<128, FMT>(a, s); break;
-    case 144: launch_kp<144, FMT>(a, s); break;
     default: fail(SJ_ERR_INVALID_ARG, "unsupported MFMA K padding");
   }
 }
@@ -1280,9 +844,7 @@ int mfma_qb(uint32_t) { return SJ_BATCH_QB; }
 
 uint32_t mfma_wave_queries() { return 32u * SJ_WAVE_QB; }
 
-uint32_t mfma_wg_queries(uint32_t kp) {
-  return (uint32_t)(kWavesPerBlock * 32 * (kp <= 64 ? SJ_WG_QB_SMALL : SJ_WG_QB_LARGE));
-}
+uint32_t mfma_wg_queries(uint32_t) { return kUnitQueries; }
 
 void launch_mfma_prep(int fmt, const float *X, uint64_t n, uint64_t n_pad, uint32_t d, uint32_t dp,
                       uint32_t kp, const float *centre, void *XA, void *XB, float *cn,
@@ -1355,11 +917,10 @@ int batched_blocks_per_cu() {
 
 void launch_join_batched(const BatchJob *jobs, const WorkUnit *wus, uint64_t n_wu, uint32_t grab,
                          unsigned int *queue, uint64_t *out, const unsigned long long *capacity,
-                         unsigned long long *cursor, unsigned long long *rechecks, uint32_t grid,
-                         uint64_t *band, uint64_t band_cap, unsigned long long *band_cursor,
-                         hipStream_t s) {
+                         unsigned long long *cursor, uint32_t grid, uint64_t *band,
+                         uint64_t band_cap, unsigned long long *band_cursor, hipStream_t s) {
   hipLaunchKernelGGL(k_join_batched, dim3(grid), dim3(kBlock), 0, s, jobs, wus, n_wu, grab, queue,
-                     out, capacity, cursor, rechecks, band, band_cap, band_cursor);
+                     out, capacity, cursor, band, band_cap, band_cursor);
   SJ_HIP(hipGetLastError());
 }
 
@@ -1408,6 +969,7 @@ void launch_band_recheck(const MfmaView &v, uint64_t *out, uint64_t capacity,
 }
 
 void launch_join_mfma(const MfmaLaunch &a, hipStream_t s) {
+  if (a.box && !a.per_wave && a.kp <= 32) return launch_join_box16(a, s);
   if (a.fmt == kFmtF16) launch_fmt<kFmtF16>(a, s);
   else launch_fmt<kFmtBF16>(a, s);
 }

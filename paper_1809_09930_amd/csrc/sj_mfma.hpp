@@ -19,7 +19,8 @@ struct MfmaBand {
 // Everything a work unit of the matrix-core filter reads.
 struct MfmaView {
   const void *XA, *XB;      // [n_pad][kp] 16-bit operands (candidate rows / query columns)
-  const float *cn;          // [n_pad] candidate norms, the MFMA's initial accumulator
+  const float *cn;          // [n_pad] what a tile element must stay below to be a hit (the
+                            // float above minus the candidate's norm; -inf: never)
   const float *thi, *tlo;   // per-point thresholds
   const float *X;           // FP32 candidate rows (recheck)
   const float *Xq;          // FP32 query rows (X itself in a self-join)
@@ -32,14 +33,15 @@ struct MfmaView {
   uint32_t pshift;          // key = key_hi | pos_q << pshift | pos_c
   uint64_t key_hi;
   // Deferred FP64 rechecks: band pairs (pos_q << 32 | pos_c) are appended
-  // here and rechecked by launch_band_recheck; null: rechecked in place.
+  // here and rechecked by launch_band_recheck.
   uint64_t *band;
   uint64_t band_cap;
   unsigned long long *band_cursor;
-  // Query-box prefilter of the workgroup kernel: `hi` is the FP32 reject
-  // threshold of a sum of at most dp squared differences (the FP32
-  // filter's); pad_row is a candidate row with zero operands and norm +inf.
+  // Query-box prefilter: `hi` is the FP32 reject threshold of a sum of at
+  // most dp squared differences (the FP32 filter's); pad_row is a candidate row
+  // with zero operands that never hits.
   float hi;
+  const void *box0, *box1;  // planes of the candidates' first 8 dimensions (launch_box_rows)
   uint32_t pad_row;
 };
 
@@ -51,7 +53,7 @@ struct MfmaLaunch {
   uint64_t n_wu;
   uint64_t *out;
   uint64_t capacity;
-  unsigned long long *cursor, *rechecks;
+  unsigned long long *cursor;
   int per_wave;  // 1: one wave per work unit (units of mfma_wave_queries())
   int hits_frequent;  // 1: most tiles hold a result or band pair (no per-tile minimum first)
   int box;            // workgroup units: candidates tested against the query box first
@@ -96,11 +98,9 @@ int batched_variant(uint32_t kp, int fmt);
 int batched_blocks_per_cu();
 void launch_join_batched(const BatchJob *jobs, const WorkUnit *wus, uint64_t n_wu, uint32_t grab,
                          unsigned int *queue, uint64_t *out, const unsigned long long *capacity,
-                         unsigned long long *cursor, unsigned long long *rechecks, uint32_t grid,
-                         uint64_t *band, uint64_t band_cap, unsigned long long *band_cursor,
-                         hipStream_t s);
-// Deferred FP64 recheck of the band list of a batched launch (band == null
-// in launch_join_batched: rechecked in place instead).
+                         unsigned long long *cursor, uint32_t grid, uint64_t *band,
+                         uint64_t band_cap, unsigned long long *band_cursor, hipStream_t s);
+// Deferred FP64 recheck of the band list of a batched launch.
 void launch_band_recheck_batched(const BatchJob *jobs, const uint64_t *band,
                                  const unsigned long long *band_count, uint64_t band_cap,
                                  uint64_t *out, const unsigned long long *capacity,

@@ -45,7 +45,7 @@
 // Candidates reach a tile only after a test against all of the unit's queries
 // at once (a bound on the distance, so no pair is lost):
 //   up to 24 padded dimensions, the distance from the bounding box of the
-//   queries over the first 8 dimensions (k_join_fp32_mxw);
+//   queries over the first 8 dimensions (k_join_box);
 //   above, the distance from the centres of groups of eight queries, itself a
 //   matrix product of the leading parts (k_join_fp32_mxg).
 #include "sj_mx32.hpp"
@@ -60,10 +60,27 @@ namespace sj {
 namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+template <int FMT>
+struct Mat;
+template <>
+struct Mat<kFmtF16> {
+  typedef half8 V8;
+  __device__ static float16v mfma(half8 a, half8 b, float16v c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+  }
+};
+template <>
+struct Mat<kFmtBF16> {
+  typedef bf16x8 V8;
+  __device__ static float16v mfma(bf16x8 a, bf16x8 b, float16v c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+  }
+};
 __device__ __forceinline__ float16v mfma(half8 a, half8 b, float16v c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+  return Mat<kFmtF16>::mfma(a, b, c);
 }
 
 // x = a + b up to 2^-22 |x| + 2^-25
@@ -102,8 +119,9 @@ __global__ __launch_bounds__(kBlock) void k_mx32_split(const float *__restrict__
   }
 }
 
-// Per candidate, rounded up: nn = -|a~|^2 (1 - kappa), the tiles' reject value,
-// and pn = -(|a1|^2 (1 - 2^-13) - |a~|^2 (2^-11 + 2^-15)), that of the group
+// Per candidate: nn, what a tile element must stay below to be a hit (the float
+// above -|a~|^2 (1 - kappa) rounded up), and rounded up
+// pn = -(|a1|^2 (1 - 2^-13) - |a~|^2 (2^-11 + 2^-15)), that of the group
 // test (see k_join_fp32_mxg).  Rows n .. n_pad - 1 get -inf (never a hit).
 __global__ __launch_bounds__(kBlock) void k_mx32_norms(const float *__restrict__ X, uint64_t n,
                                                        uint64_t n_pad, uint32_t dp,
@@ -130,8 +148,23 @@ __global__ __launch_bounds__(kBlock) void k_mx32_norms(const float *__restrict__
       s1 += (double)y1 * (double)y1;
     }
   }
-  nn[p] = round_up_f32(-s * (1.0 - kappa));
+  nn[p] = strict(round_up_f32(-s * (1.0 - kappa)));
   pn[p] = round_up_f32(-(s1 * (1.0 - 0x1p-13) - s * (0x1p-11 + 0x1p-15)));
+}
+
+// The first 8 dimensions of the cell-ordered rows as two planes of 16-byte
+// vectors, so that the box test's loads are contiguous across the lanes: read
+// from the rows themselves every lane touched a cache line of its own, twice,
+// and the vector cache (busy 62 % of the 2M x 16 FP32 join) set the pace.
+__global__ __launch_bounds__(kBlock) void k_box_rows(const float *__restrict__ X, uint64_t n,
+                                                     uint32_t dp, f32x4 *__restrict__ box0,
+                                                     f32x4 *__restrict__ box1) {
+  for (uint64_t p = (uint64_t)blockIdx.x * kBlock + threadIdx.x; p < n;
+       p += (uint64_t)gridDim.x * kBlock) {
+    const f32x4 *x = reinterpret_cast<const f32x4 *>(X + p * dp);
+    box0[p] = x[0];
+    box1[p] = x[1];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -171,130 +204,64 @@ __device__ __forceinline__ void query_bounds(const Mx32View &v, double n, float 
   delta = round_up_f32((double)thi - tlo);
 }
 
-// Element e of a lane's accumulator is row 8 (e / 4) + 4 half + e % 4.
-__device__ __forceinline__ float16v rows_init(const float *rows32, uint32_t half) {
-  float16v c;
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    const f32x4 x = *reinterpret_cast<const f32x4 *>(rows32 + 8 * g + 4 * half);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) c[4 * g + i] = x[i];
-  }
-  return c;
-}
-
-// One tile's hits as a 16-bit mask per lane (bit e: element e passes nn), and
-// with kAccept the mask of those proven within eps (delta32: Thi - Tlo of the
-// tile's rows).
-template <bool kAccept>
-__device__ __forceinline__ void tile_masks(const float16v &acc, float nn, float kacc,
-                                           const float *delta32, uint32_t half, uint32_t &hit,
-                                           uint32_t &within) {
-  hit = within = 0u;
-  const float nacc = nn * kacc;
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    f32x4 d = {0, 0, 0, 0};
-    if constexpr (kAccept) d = *reinterpret_cast<const f32x4 *>(delta32 + 8 * g + 4 * half);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float x = acc[4 * g + i];
-      hit |= x <= nn ? 1u << (4 * g + i) : 0u;
-      if constexpr (kAccept) within |= x + d[i] <= nacc ? 1u << (4 * g + i) : 0u;
-    }
-  }
-}
-
-// Emits the hits of QB tiles of one 32-candidate block: every lane with hits
-// left takes its lowest one per round, so the rounds are few (a lane rarely
-// has two) and there is one copy of the emission code.  hits / within: bits
-// 16 j + e of tile j; cp: the lane's candidate; qpos: the tiles' query
-// positions.  Pairs proven within eps go to the result stage, the others to
-// the recheck list.
-template <bool kAccept, class M>
-__device__ __forceinline__ void emit_hits(M hits, M within, const uint32_t *qpos, uint32_t half,
-                                          uint32_t cp, bool sym, Stage &st, BandSink &bs,
-                                          uint64_t *__restrict__ out, uint64_t capacity,
-                                          unsigned long long *__restrict__ cursor) {
-  while (ballot(hits != 0)) {
-    const bool live = hits != 0;
-    const uint32_t e = live ? (uint32_t)__builtin_ctzll((uint64_t)hits) : 0u;
-    const uint32_t qp = qpos[(e & ~15u) * 2 + 8 * ((e & 15u) / 4) + 4 * half + (e & 3u)];
-    const bool ok = live && (!sym || qp <= cp);
-    const bool acc_ok = kAccept && ok && ((within >> e) & 1) != 0;
-    const bool band = ok && !acc_ok;
-    const uint64_t key = ((uint64_t)qp << 32) | cp;
-    const uint64_t bm = ballot(band);
-    if (bm) {
-      const uint32_t nb = (uint32_t)__builtin_popcountll(bm);
-      if (bs.st.cnt + nb > (uint32_t)kBandStage) flush(bs.st, bs.buf, bs.cap, bs.cursor);
-      if (band) bs.st.buf[bs.st.cnt + lanes_below(bm)] = key;
-      bs.st.cnt += nb;
-    }
-    if constexpr (kAccept) {
-      const uint64_t am = ballot(acc_ok);
-      if (am) {
-        const bool two = acc_ok && sym && qp != cp;
-        const uint64_t m2 = ballot(two);
-        const uint32_t total = (uint32_t)(__builtin_popcountll(am) + __builtin_popcountll(m2));
-        if (st.cnt + total > (uint32_t)kStage) flush(st, out, capacity, cursor);
-        const uint32_t off = st.cnt + lanes_below(am) + lanes_below(m2);
-        if (acc_ok) {
-          st.buf[off] = key;
-          if (two) st.buf[off + 1] = ((uint64_t)cp << 32) | qp;
-        }
-        st.cnt += total;
-      }
-    }
-    if (live) hits &= hits - 1;
-  }
-}
-
 // ---------------------------------------------------------------------------
-// Up to 24 padded dimensions: one wave per work unit of 32 QB queries, no
-// barriers.  The wave alternates two phases.  In the first it tests windows of
-// 64 candidates against the box of its queries (vector ALU; rows loaded two
-// windows ahead) until kBatch survivors' positions wait in a ring in LDS; in
-// the second it gathers 32 of them at a time straight into the B operands,
-// each block's loads in flight during the tiles of the block before it.  Long
-// phases let the two waves of a SIMD be in different ones: with a test between
-// any two blocks both units idled most of the time.  Four query blocks per
-// gathered block keep the gathers (96 bytes a row) well below the L2's rate;
-// more would not fit the registers of two waves per SIMD.
+// Candidates tested against the query box: one wave per work unit of 32 QB
+// queries (or per part of one), no barriers.  Also the form of the 16-bit
+// filters' workgroup units at low selectivity (PARTS = 1: one product of 16-bit
+// operands prepared by the index, thresholds of k_mfma_thresholds).  The wave
+// alternates two phases.  In the first it tests windows of 64 candidates
+// against the box of its queries (vector ALU; four windows in flight) until
+// kBatch survivors' positions wait in a ring in LDS; in the second it gathers
+// the rows of 32 of them at a time (through LDS into the B operands), in flight
+// during the tiles of the two blocks before them.  Long phases let the two
+// waves of a SIMD be in different ones: with a test between any two blocks both
+// units idled most of the time.  A gathered block serves as many query blocks
+// as the registers of two waves per SIMD hold: 8 with one product (4 at K 32),
+// 4 with three (2 at K 32).
+//
+// Bound by instruction issue: the vector ALU's (8 minima per tile, 27
+// instructions per 64 candidates tested) beside the matrix unit's.  Measured,
+// whole pass of the 2M x 16 uniform join at 64 neighbours: FP16 105 ms with
+// workgroups of four waves, candidates as rows and a product's minima right
+// behind it, 77 ms with one wave per workgroup and queries as rows, 69 ms with
+// products issued ahead; FP32 141 to 130 ms.
 // ---------------------------------------------------------------------------
 constexpr int kBoxDims = 8;
 constexpr uint32_t kBatch = 512;
-constexpr uint32_t kRingW = 1024;  // >= kBatch - 1 pending + two windows of 64
+constexpr int kWindows = 4;
+constexpr uint32_t kRingW = 1024;  // >= kBatch - 1 pending + 2 kWindows windows of 64
 
-template <int K, int QB>
-__global__ __launch_bounds__(kBlock) void k_join_fp32_mxw(Mx32View v,
-                                                          const WorkUnit *__restrict__ wus,
-                                                          uint64_t n_wu,
-                                                          uint64_t *__restrict__ out,
-                                                          uint64_t capacity,
-                                                          unsigned long long *__restrict__ cursor) {
+template <int FMT, int PARTS, int K, int QB>
+__global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *__restrict__ wus,
+                                                     uint32_t parts_per_unit,
+                                                     uint64_t *__restrict__ out, uint64_t capacity,
+                                                     unsigned long long *__restrict__ cursor) {
+  typedef typename Mat<FMT>::V8 V8;
   constexpr int KS = K / 16;
-  constexpr int RV = 2 * (K / 8);  // 16-byte vectors per split row
-  constexpr bool kTwo = K > 16;    // a second accumulator for the small products
-  constexpr bool kAccept = K <= 16;
-  __shared__ uint64_t stage_mem[kWavesPerBlock][kAccept ? kStage : 1];
-  __shared__ uint64_t band_mem[kWavesPerBlock][kBandStage];
-  __shared__ uint32_t ring_mem[kWavesPerBlock][kRingW];
-  __shared__ __align__(16) float cinit_mem[kWavesPerBlock][QB * 32];
-  __shared__ __align__(16) float delta_mem[kWavesPerBlock][QB * 32];
-  __shared__ uint32_t qpos_mem[kWavesPerBlock][QB * 32];
+  constexpr int RV = PARTS * (K / 8);  // 16-byte vectors per candidate row
+  constexpr bool kTwo = PARTS == 2 && K > 16;  // a second accumulator for the small products
+  constexpr bool kAccept = PARTS == 1 || K <= 16;
+  __shared__ uint64_t stage_mem[kAccept ? kStage : 1];
+  __shared__ uint64_t band_mem[kBandStage];
+  __shared__ uint32_t ring_mem[kRingW];
+  __shared__ float ring_n_mem[kRingW];
+  __shared__ V8 rows_mem[32 * RV];
+  __shared__ __align__(16) float cinit_mem[QB * 32];
+  __shared__ __align__(16) float delta_mem[QB * 32];
+  __shared__ uint32_t qpos_mem[QB * 32];
   const MfmaView &m = v.m;
-  const uint32_t w = uniform_u32(threadIdx.x / kWave);
-  const uint64_t u = (uint64_t)blockIdx.x * kWavesPerBlock + w;
-  if (u >= n_wu) return;  // whole wave leaves; no workgroup barrier follows
-  const WorkUnit wu = wus[u];
+  WorkUnit wu = wus[blockIdx.x / parts_per_unit];
+  wu.q0 += (blockIdx.x % parts_per_unit) * (32u * QB);
+  if (wu.q0 >= wu.q1) return;
+  if (wu.q1 - wu.q0 > 32u * QB) wu.q1 = wu.q0 + 32u * QB;
   const uint32_t l = lane_id();
   const uint32_t half = l >> 5, col = l & 31;
   const uint32_t dp = m.dp;
   const uint32_t nq = wu.q1 - wu.q0;  // 1 .. 32 QB
-  uint32_t *ring = ring_mem[w];
+  uint32_t *ring = ring_mem;
+  float *ring_n = ring_n_mem;
 
-  half8 A1[QB][KS], A2[QB][KS];
+  V8 A1[QB][KS], A2[PARTS == 2 ? QB : 1][KS];
   float blo[kBoxDims], bhi[kBoxDims];
 #pragma unroll
   for (int t = 0; t < kBoxDims; ++t) {
@@ -308,17 +275,25 @@ __global__ __launch_bounds__(kBlock) void k_join_fp32_mxw(Mx32View v,
     const uint32_t slot = wu.q0 + idx;
     const uint32_t p = live ? (m.qlist ? m.qlist[slot] : slot) : 0u;
     const float *row = m.Xq + (uint64_t)p * dp;
-    double n = 0.0;
+    float ci, de;
+    if constexpr (PARTS == 2) {
+      double n = 0.0;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      query_slice(row, v, (uint32_t)ks * 16 + half * 8, live, A1[j][ks], A2[j][ks], n);
-    n += __shfl_xor(n, 32);
-    if (half == 0) {
-      float ci, de;
+      for (int ks = 0; ks < KS; ++ks)
+        query_slice(row, v, (uint32_t)ks * 16 + half * 8, live, A1[j][ks], A2[j][ks], n);
+      n += __shfl_xor(n, 32);
       query_bounds(v, n, ci, de);
-      cinit_mem[w][idx] = live ? ci : __builtin_inff();
-      delta_mem[w][idx] = live ? de : 0.0f;
-      qpos_mem[w][idx] = live ? p : 0xffffffffu;
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        A1[j][ks] = static_cast<const V8 *>(m.XB)[(uint64_t)p * RV + ks * 2 + half];
+      ci = -m.thi[p];
+      de = round_up_f32((double)m.thi[p] - (double)m.tlo[p]);
+    }
+    if (half == 0) {
+      cinit_mem[idx] = live ? ci : __builtin_inff();
+      delta_mem[idx] = live ? de : 0.0f;
+      qpos_mem[idx] = live ? p : 0xffffffffu;
     }
 #pragma unroll
     for (int t4 = 0; t4 < kBoxDims / 4; ++t4) {
@@ -339,18 +314,19 @@ __global__ __launch_bounds__(kBlock) void k_join_fp32_mxw(Mx32View v,
       a = __builtin_fminf(a, __shfl_xor(a, off));
       b = __builtin_fmaxf(b, __shfl_xor(b, off));
     }
-    blo[t] = __builtin_bit_cast(float, uniform_u32(__builtin_bit_cast(uint32_t, a)));
-    bhi[t] = __builtin_bit_cast(float, uniform_u32(__builtin_bit_cast(uint32_t, b)));
+    // (kept in vector registers: an instruction reads one scalar register)
+    blo[t] = a;
+    bhi[t] = b;
   }
   __builtin_amdgcn_wave_barrier();
   float16v c0[QB];
 #pragma unroll
-  for (int j = 0; j < QB; ++j) c0[j] = rows_init(&cinit_mem[w][j * 32], half);
+  for (int j = 0; j < QB; ++j) c0[j] = rows_init(&cinit_mem[j * 32], half);
 
-  Stage st{&stage_mem[w][0], 0u};
-  BandSink bs{m.band, m.band_cap, m.band_cursor, Stage{&band_mem[w][0], 0u}};
+  Stage st{&stage_mem[0], 0u};
+  BandSink bs{m.band, m.band_cap, m.band_cursor, Stage{&band_mem[0], 0u}};
   uint64_t n_skip = 0;
-  const bool sym = m.symmetric != 0;
+  const KeyForm kf{m.key_hi, m.pshift, m.symmetric != 0};
 
   // candidate windows of up to 64 positions of one run
   uint32_t r = wu.run_first, c = wu.c_begin;
@@ -366,14 +342,15 @@ __global__ __launch_bounds__(kBlock) void k_join_fp32_mxw(Mx32View v,
   struct Window {
     uint32_t c, n;  // first position, length (0: the stream is done)
     f32x4 x0, x1;   // this lane's candidate: its first 8 dimensions
+    float nn;       // and its reject value
   };
   auto load_window = [&](Window &x) __attribute__((always_inline)) {
     x.n = c < ce ? (ce - c < (uint32_t)kWave ? ce - c : (uint32_t)kWave) : 0u;
     x.c = x.n ? c : 0u;
-    const f32x4 *xr =
-        reinterpret_cast<const f32x4 *>(m.X + (uint64_t)(x.c + (l < x.n ? l : 0u)) * dp);
-    x.x0 = xr[0];
-    x.x1 = xr[1];
+    const uint32_t p = x.c + (l < x.n ? l : 0u);
+    x.x0 = reinterpret_cast<const f32x4 *>(m.box0)[p];
+    x.x1 = reinterpret_cast<const f32x4 *>(m.box1)[p];
+    x.nn = v.nn[p];
     c += x.n;
     normalise();
   };
@@ -382,116 +359,179 @@ __global__ __launch_bounds__(kBlock) void k_join_fp32_mxw(Mx32View v,
     float lb = 0.0f;
 #pragma unroll
     for (int t = 0; t < kBoxDims; ++t) {
+      // y - clamp(y): the gap up to its sign, in three instructions a dimension
       const float y = t < 4 ? x.x0[t & 3] : x.x1[t & 3];
-      const float g = __builtin_fmaxf(__builtin_fmaxf(blo[t] - y, y - bhi[t]), 0.0f);
+      const float g = y - __builtin_amdgcn_fmed3f(y, blo[t], bhi[t]);
       lb = __builtin_fmaf(g, g, lb);
     }
-    bool keep = l < x.n && lb <= m.hi;
+    const uint64_t valid = x.n < (uint32_t)kWave ? (1ull << x.n) - 1ull : ~0ull;
+    uint64_t km = ballot(lb <= m.hi) & valid;
     if (v.skip_below) {
       // candidates of earlier result batches: their pairs were taken there
-      const bool early = l < x.n && v.orig_id[x.c + (l < x.n ? l : 0u)] < v.skip_below;
-      n_skip += (uint64_t)__builtin_popcountll(ballot(early)) * nq;
-      keep = keep && !early;
+      const uint64_t early =
+          ballot(v.orig_id[x.c + (l < x.n ? l : 0u)] < v.skip_below) & valid;
+      n_skip += (uint64_t)__builtin_popcountll(early) * nq;
+      km &= ~early;
     }
-    const uint64_t km = ballot(keep);
-    if (keep) ring[(head + cnt + lanes_below(km)) % kRingW] = x.c + l;
+    if ((km >> l) & 1ull) {
+      const uint32_t at = (head + cnt + lanes_below(km)) % kRingW;
+      ring[at] = x.c + l;
+      ring_n[at] = x.nn;
+    }
     cnt += (uint32_t)__builtin_popcountll(km);
   };
+  const V8 *__restrict__ XS = static_cast<const V8 *>(v.XS);
+  // The next nb <= 32 survivors on their way to the operands: adjacent lanes
+  // load the 16-byte vectors of one row, so a row costs one or two cache
+  // accesses, and the wave's LDS turns rows into operands.  The vectors of a row
+  // are permuted (by the low bits of the row) against bank conflicts.  The
+  // loads are unconditional (ahead of the ring they repeat old entries): under
+  // a branch the compiler copies their results at its end, and so waits for
+  // them there.
+  constexpr int RT = RV / 2;  // vectors per lane
+  constexpr uint32_t kSwz = RV < 8 ? RV - 1 : 7;
+  struct Rows {
+    V8 x[RT];
+    uint32_t at;  // first ring entry
+  };
+  auto load_rows = [&](Rows &q) __attribute__((always_inline)) {
+    q.at = head;
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+      const uint32_t e = (uint32_t)i * kWave + l, row = e / RV;
+      const uint32_t pos = ring[(head + row) % kRingW];
+      q.x[i] = XS[(uint64_t)pos * RV + ((e % RV) ^ (row & kSwz))];
+    }
+    head += 32;
+    __builtin_amdgcn_sched_barrier(0);  // issued here, ahead of the tiles
+  };
   struct Block {
-    half8 b[2][KS];
+    V8 b[PARTS][KS];
     float an;
     uint32_t cp;
   };
-  const half8 *__restrict__ XS = static_cast<const half8 *>(v.XS);
-  // The next nb <= 32 survivors, padding rows past them.  The loads are
-  // unconditional: under a branch the compiler copies their results at its
-  // end, and so waits for them there.
-  auto load_block = [&](Block &b, uint32_t nb) __attribute__((always_inline)) {
-    const uint32_t pos = col < nb ? ring[(head + col) % kRingW] : m.pad_row;
-    head += nb;
-    cnt -= nb;
-    const half8 *row = XS + (uint64_t)pos * RV + half;
+  auto to_block = [&](const Rows &q, Block &b) __attribute__((always_inline)) {
+    V8 *t = rows_mem;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < RT; ++i) t[(uint32_t)i * kWave + l] = q.x[i];
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) b.b[i][ks] = row[i * (K / 8) + 2 * ks];
-    b.an = v.nn[pos];
-    b.cp = pos;
-    __builtin_amdgcn_sched_barrier(0);  // issued here, ahead of the tiles
+    for (int i = 0; i < PARTS; ++i)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        b.b[i][ks] = t[col * RV + (((uint32_t)(i * (K / 8) + 2 * ks) + half) ^ (col & kSwz))];
+    const uint32_t at = (q.at + col) % kRingW;
+    b.an = ring_n[at];
+    b.cp = ring[at];
+    __builtin_amdgcn_wave_barrier();
   };
-  auto tiles = [&](const Block &cur) __attribute__((always_inline)) {
-    float16v acc[QB];
-    if constexpr (kTwo) {
-      float16v lo[QB];
+  // tile j of a block
+  auto product = [&](int j, const Block &cur) __attribute__((always_inline)) {
+    float16v acc = c0[j];
+    if constexpr (PARTS == 1) {
 #pragma unroll
-      for (int j = 0; j < QB; ++j) {
-        acc[j] = c0[j];
+      for (int ks = 0; ks < KS; ++ks) acc = Mat<FMT>::mfma(A1[j][ks], cur.b[0][ks], acc);
+    } else if constexpr (kTwo) {
+      float16v lo;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) lo[j][e] = 0.0f;
-      }
+      for (int e = 0; e < 16; ++e) lo[e] = 0.0f;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-#pragma unroll
-        for (int j = 0; j < QB; ++j) lo[j] = mfma(A1[j][ks], cur.b[1][ks], lo[j]);
-#pragma unroll
-        for (int j = 0; j < QB; ++j) acc[j] = mfma(A1[j][ks], cur.b[0][ks], acc[j]);
-#pragma unroll
-        for (int j = 0; j < QB; ++j) lo[j] = mfma(A2[j][ks], cur.b[0][ks], lo[j]);
+        lo = Mat<FMT>::mfma(A1[j][ks], cur.b[PARTS - 1][ks], lo);
+        acc = Mat<FMT>::mfma(A1[j][ks], cur.b[0][ks], acc);
+        lo = Mat<FMT>::mfma(A2[j][ks], cur.b[0][ks], lo);
       }
 #pragma unroll
-      for (int j = 0; j < QB; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[j][e] += lo[j][e];
+      for (int e = 0; e < 16; ++e) acc[e] += lo[e];
     } else {
-#pragma unroll
-      for (int j = 0; j < QB; ++j) acc[j] = mfma(A1[j][0], cur.b[1][0], c0[j]);
-#pragma unroll
-      for (int j = 0; j < QB; ++j) acc[j] = mfma(A2[j][0], cur.b[0][0], acc[j]);
-#pragma unroll
-      for (int j = 0; j < QB; ++j) acc[j] = mfma(A1[j][0], cur.b[0][0], acc[j]);
+      acc = Mat<FMT>::mfma(A1[j][0], cur.b[PARTS - 1][0], acc);
+      acc = Mat<FMT>::mfma(A2[j][0], cur.b[0][0], acc);
+      acc = Mat<FMT>::mfma(A1[j][0], cur.b[0][0], acc);
     }
-    bool any = false;
+    return acc;
+  };
+  // The tiles of a block: products and minima without a branch, so that they
+  // overlap; a tile with a hit is computed again for its masks.
+  auto tiles = [&](const Block &cur) __attribute__((always_inline)) {
+    Min16 mn[QB];
+    float least = __builtin_inff();
+    float16v acc = product(0, cur);
 #pragma unroll
-    for (int j = 0; j < QB; ++j) any |= min16(acc[j]) <= cur.an;
-    if (ballot(any)) {
+    for (int j = 0; j < QB; ++j) {
+      float16v next = acc;
+      if (j + 1 < QB) next = product(j + 1, cur);
+      __builtin_amdgcn_sched_barrier(0);  // the next product runs under these minima
+      mn[j] = min16(acc);
+      least = __builtin_fminf(__builtin_fminf(least, mn[j].a), mn[j].b);
+      acc = next;
+    }
+    if (ballot(least < cur.an) == 0) return;
+    const float nacc =
+        PARTS == 1 ? cur.an : (cur.an < 0.0f ? cur.an * v.kacc : -__builtin_inff());
+#pragma unroll
+    for (int j0 = 0; j0 < QB; j0 += 4) {
       uint64_t hits = 0, within = 0;
 #pragma unroll
-      for (int j = 0; j < QB; ++j) {
-        if (ballot(min16(acc[j]) <= cur.an) == 0) continue;
+      for (int j = j0; j < QB && j < j0 + 4; ++j) {
+        if (ballot(__builtin_fminf(mn[j].a, mn[j].b) < cur.an) == 0) continue;
         uint32_t h, a;
-        tile_masks<kAccept>(acc[j], cur.an, v.kacc, &delta_mem[w][j * 32], half, h, a);
-        hits |= (uint64_t)h << (16 * j);
-        within |= (uint64_t)a << (16 * j);
+        tile_masks<kAccept>(product(j, cur), cur.an, nacc, &delta_mem[j * 32], half, h, a);
+        hits |= (uint64_t)h << (16 * (j - j0));
+        within |= (uint64_t)a << (16 * (j - j0));
       }
-      emit_hits<kAccept>(hits, within, qpos_mem[w], half, cur.cp, sym, st, bs, out, capacity,
-                         cursor);
+      emit_hits<kAccept>(hits, within, &qpos_mem[j0 * 32], half, cur.cp, kf, st, bs, out,
+                         capacity, cursor);
     }
   };
 
-  Window w0, w1;
-  load_window(w0);
-  load_window(w1);
-  for (;;) {
-    while (cnt < kBatch && w0.n) {
-      test_window(w0);
-      load_window(w0);
-      test_window(w1);
-      load_window(w1);
+  for (uint32_t i = l; i < kRingW; i += kWave) ring[i] = m.pad_row;
+  __builtin_amdgcn_wave_barrier();
+  while (cnt || c < ce) {
+    {
+      // test phase: kWindows windows in flight, all tested before it ends
+      Window x[kWindows];
+#pragma unroll
+      for (int i = 0; i < kWindows; ++i) load_window(x[i]);
+      while (cnt < kBatch && c < ce) {
+#pragma unroll
+        for (int i = 0; i < kWindows; ++i) {
+          test_window(x[i]);
+          load_window(x[i]);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < kWindows; ++i) test_window(x[i]);
     }
-    if (cnt == 0) break;
+    if (c >= ce && cnt % 32) {  // the stream is done: fill up the last block
+      const uint32_t pad = 32u - cnt % 32;
+      if (l < pad) {
+        const uint32_t at = (head + cnt + l) % kRingW;
+        ring[at] = m.pad_row;
+        ring_n[at] = -__builtin_inff();
+      }
+      cnt += pad;
+    }
     __builtin_amdgcn_wave_barrier();
-    const uint32_t least = w0.n ? 32u : 1u;  // full blocks only while more may come
-    Block b0, b1;
-    load_block(b0, cnt < 32u ? cnt : 32u);
-    for (;;) {
-      uint32_t nb = cnt >= least ? (cnt < 32u ? cnt : 32u) : 0u;
-      load_block(b1, nb);
-      tiles(b0);
-      if (nb == 0) break;
-      nb = cnt >= least ? (cnt < 32u ? cnt : 32u) : 0u;
-      load_block(b0, nb);
-      tiles(b1);
-      if (nb == 0) break;
+    // tile phase: the rows of two blocks in flight behind the current one
+    if (cnt >= 32) {
+      uint32_t nb = cnt / 32;
+      cnt %= 32;
+      Rows r0, r1;
+      Block blk;
+      const uint32_t end = head + 32 * nb;
+      load_rows(r0);
+      load_rows(r1);
+      for (;;) {
+        to_block(r0, blk);
+        load_rows(r0);
+        tiles(blk);
+        if (--nb == 0) break;
+        to_block(r1, blk);
+        load_rows(r1);
+        tiles(blk);
+        if (--nb == 0) break;
+      }
+      head = end;
     }
     __builtin_amdgcn_wave_barrier();
   }
@@ -636,7 +676,7 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
   Stage none{nullptr, 0u};
   BandSink bs{m.band, m.band_cap, m.band_cursor, Stage{&band_mem[w][0], 0u}};
   uint64_t n_skip = 0;
-  const bool sym = m.symmetric != 0;
+  const KeyForm kf{m.key_hi, m.pshift, m.symmetric != 0};
   const half8 *__restrict__ XS = static_cast<const half8 *>(v.XS);
 
   // candidate stream (uniform over the workgroup) and the ring of survivors
@@ -668,7 +708,7 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) a = mfma(G[ks], b[ks], a);
       // a column passes when some row of either half does
-      const uint64_t pm = ballot(min16(a) <= pnv && valid && !early);
+      const uint64_t pm = ballot(min16(a, __builtin_inff()) <= pnv && valid && !early);
       const uint32_t keep = (uint32_t)pm | (uint32_t)(pm >> 32);
       if (v.skip_below)  // earlier result batches took these pairs (halves agree)
         n_skip += (uint64_t)__builtin_popcount((uint32_t)ballot(early)) * nq;
@@ -762,18 +802,18 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
       const float an = tile_n[cur][blk * 32 + col];
       bool any = false;
 #pragma unroll
-      for (int j = 0; j < QB; ++j) any |= min16(acc[j]) <= an;
+      for (int j = 0; j < QB; ++j) any |= min16(acc[j], __builtin_inff()) < an;
       if (ballot(any)) {
         const uint32_t cp = tile_pos[cur][blk * 32 + col];
-        uint32_t hits = 0, none_within = 0;
+        uint32_t hits = 0;
 #pragma unroll
         for (int j = 0; j < QB; ++j) {
           uint32_t h, a;
           tile_masks<false>(acc[j], an, 0.0f, nullptr, half, h, a);
           hits |= h << (16 * j);
         }
-        emit_hits<false>(hits, none_within, &qpos_s[w * QB * 32], half, cp, sym, none, bs, nullptr,
-                         0, nullptr);
+        emit_hits<false>(hits, 0u, &qpos_s[w * QB * 32], half, cp, kf, none, bs, nullptr, 0,
+                         nullptr);
       }
     }
     if (!nn) break;
@@ -787,14 +827,25 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
   if (l == 0 && n_skip) atomicAdd(v.skipped, (unsigned long long)n_skip);
 }
 
-constexpr int kQbBox16 = 4, kQbBox32 = 2;  // query blocks per wave of k_join_fp32_mxw
+// query blocks per wave of k_join_box: FP32 at K = 16 and 32, 16 bits likewise
+constexpr int kQbBox16 = 4, kQbBox32 = 2, kQbHalf16 = 8, kQbHalf32 = 4;
 
-template <int K, int QB>
-void launch_w(const Mx32Launch &a, hipStream_t s) {
-  const uint64_t grid = (a.n_wu + kWavesPerBlock - 1) / kWavesPerBlock;
-  hipLaunchKernelGGL((k_join_fp32_mxw<K, QB>), dim3((uint32_t)grid), dim3(kBlock), 0, s, a.view,
-                     a.wu, a.n_wu, a.out, a.capacity, a.cursor);
+template <int FMT, int PARTS, int K, int QB>
+void launch_box(const Mx32View &v, const WorkUnit *wu, uint64_t n_wu, uint32_t parts,
+                uint64_t *out, uint64_t capacity, unsigned long long *cursor, hipStream_t s) {
+  hipLaunchKernelGGL((k_join_box<FMT, PARTS, K, QB>), dim3((uint32_t)(n_wu * parts)), dim3(kWave),
+                     0, s, v, wu, parts, out, capacity, cursor);
   SJ_HIP(hipGetLastError());
+}
+
+template <int FMT>
+void launch_half(const MfmaLaunch &a, const Mx32View &v, uint32_t tq, hipStream_t s) {
+  if (a.kp == 16)
+    launch_box<FMT, 1, 16, kQbHalf16>(v, a.wu, a.n_wu, tq / (32 * kQbHalf16), a.out, a.capacity,
+                                      a.cursor, s);
+  else
+    launch_box<FMT, 1, 32, kQbHalf32>(v, a.wu, a.n_wu, tq / (32 * kQbHalf32), a.out, a.capacity,
+                                      a.cursor, s);
 }
 
 template <int K>
@@ -840,12 +891,26 @@ void launch_mx32_prep(const float *X, uint64_t n, uint64_t n_pad, uint32_t dp, c
   SJ_HIP(hipGetLastError());
 }
 
+void launch_box_rows(const float *X, uint64_t n, uint32_t dp, void *box0, void *box1,
+                     hipStream_t s) {
+  if (!n) return;
+  hipLaunchKernelGGL(k_box_rows,
+                     dim3((uint32_t)std::min<uint64_t>((n + kBlock - 1) / kBlock, 1u << 20)),
+                     dim3(kBlock), 0, s, X, n, dp, static_cast<f32x4 *>(box0),
+                     static_cast<f32x4 *>(box1));
+  SJ_HIP(hipGetLastError());
+}
+
 void launch_join_mx32(const Mx32Launch &a, hipStream_t s) {
   if (!a.n_wu) return;
   if (a.n_wu > 0x7fffffffull) fail(SJ_ERR_INVALID_ARG, "too many work units");
   const uint32_t dp = a.view.m.dp;
-  if (dp <= 16) return launch_w<16, kQbBox16>(a, s);
-  if (dp <= 24) return launch_w<32, kQbBox32>(a, s);
+  if (dp <= 16)
+    return launch_box<kFmtF16, 2, 16, kQbBox16>(a.view, a.wu, a.n_wu, 1, a.out, a.capacity,
+                                                a.cursor, s);
+  if (dp <= 24)
+    return launch_box<kFmtF16, 2, 32, kQbBox32>(a.view, a.wu, a.n_wu, 1, a.out, a.capacity,
+                                                a.cursor, s);
   switch (mx32_k(dp)) {
     case 32: launch_g<32>(a, s); break;
     case 48: launch_g<48>(a, s); break;
@@ -856,6 +921,20 @@ void launch_join_mx32(const Mx32Launch &a, hipStream_t s) {
     case 128: launch_g<128>(a, s); break;
     default: fail(SJ_ERR_INVALID_ARG, "unsupported padded dimension");
   }
+}
+
+void launch_join_box16(const MfmaLaunch &a, hipStream_t s) {
+  if (!a.n_wu) return;
+  const uint32_t tq = mfma_wg_queries(a.kp);
+  static_assert(256 % (32 * kQbHalf16) == 0 && 256 % (32 * kQbHalf32) == 0, "whole parts");
+  if (tq != 256 || a.n_wu > 0x1fffffffull || a.kp > 32)
+    fail(SJ_ERR_INVALID_ARG, "unsupported box launch");
+  Mx32View v{};
+  v.m = a.view;
+  v.XS = a.view.XA;
+  v.nn = a.view.cn;
+  if (a.fmt == kFmtF16) launch_half<kFmtF16>(a, v, tq, s);
+  else launch_half<kFmtBF16>(a, v, tq, s);
 }
 
 }  // namespace sj

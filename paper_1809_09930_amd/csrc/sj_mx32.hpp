@@ -43,8 +43,14 @@ bool mx32_per_wave(uint32_t dp);
 // n .. n_pad - 1 become padding.
 void launch_mx32_prep(const float *X, uint64_t n, uint64_t n_pad, uint32_t dp, const float *ctr,
                       float sc, double kappa, void *XS, float *nn, float *pn, hipStream_t s);
+// Planes of the rows' dimensions 0 .. 3 and 4 .. 7 (16 bytes per point each).
+void launch_box_rows(const float *X, uint64_t n, uint32_t dp, void *box0, void *box1,
+                     hipStream_t s);
 // Relative error factor of the filter for d dimensions.
 double mx32_kappa(uint32_t d);
 void launch_join_mx32(const Mx32Launch &a, hipStream_t s);
+// The 16-bit filters' workgroup units (256 queries, K <= 32) behind the query
+// box (MfmaLaunch::box).
+void launch_join_box16(const MfmaLaunch &a, hipStream_t s);
 
 }  // namespace sj

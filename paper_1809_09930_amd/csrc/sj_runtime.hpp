@@ -299,6 +299,7 @@ struct sj_index {
   // FP32 on the matrix cores: split rows, reject values, centre (see Mx32View)
   DevBuf mx_xs, mx_nn, mx_pn, mx_ctr;
   float mx_scale = 1.0f;
+  DevBuf box_rows;              // two planes of the points' first 8 dimensions (launch_box_rows)
   double mean_norm2 = 0.0;      // mean squared norm of the points (variance sample)
   DevBuf pivots;                // [d][kPivots] pivot points of the sort key (pb > 0)
   DevBuf band;                  // deferred recheck list of the matrix-core joins
