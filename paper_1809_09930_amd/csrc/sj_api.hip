@@ -570,7 +570,7 @@ uint64_t build_runs(sj_index &ix, int sym, DevBuf &off, DevBuf &runs, BuildTmp &
   cnt.alloc((nc + 1) * 4);
   SJ_HIP(hipMemsetAsync(cnt.p, 0, (nc + 1) * 4, s));
   const uint32_t *ecs = entries_of(ix).cell_start.as<uint32_t>();  // candidate cells
-  launch_runs(0, sym, nc, ecs, ix.nbr_off.as<uint32_t>(), ix.nbr_cell.as<uint32_t>(),
+  launch_runs(0, sym, nc, ix.n_nbr, ecs, ix.nbr_off.as<uint32_t>(), ix.nbr_cell.as<uint32_t>(),
               cnt.as<uint32_t>(), nullptr, nullptr, s);
   off.alloc((nc + 1) * 4);
   uint32_t *d_tot = t.small.as<uint32_t>() + 8;
@@ -579,8 +579,8 @@ uint64_t build_runs(sj_index &ix, int sym, DevBuf &off, DevBuf &runs, BuildTmp &
   SJ_HIP(hipMemcpyAsync(&h_tot, d_tot, 4, hipMemcpyDeviceToHost, s));
   SJ_HIP(hipStreamSynchronize(s));
   runs.alloc((uint64_t)h_tot * sizeof(uint2));
-  launch_runs(1, sym, nc, ecs, ix.nbr_off.as<uint32_t>(), ix.nbr_cell.as<uint32_t>(), nullptr,
-              off.as<uint32_t>(), runs.as<uint2>(), s);
+  launch_runs(1, sym, nc, ix.n_nbr, ecs, ix.nbr_off.as<uint32_t>(),
+              ix.nbr_cell.as<uint32_t>(), nullptr, off.as<uint32_t>(), runs.as<uint2>(), s);
   return h_tot;
 }
 
@@ -666,13 +666,15 @@ uint64_t build_workunits(sj_index &ix, int sym, const uint32_t *qlist, uint64_t 
   const uint64_t nc = groups ? groups->n : ix.ncell;
   const uint32_t *cstart = groups ? groups->start.as<uint32_t>() : ix.cell_start.as<uint32_t>();
   ScratchScope scope;  // every temporary below is dead at the final synchronisation
-  TmpBuf qb_off, run_total, scan, tot;
+  TmpBuf qb_off, run_total, before, scan, tot;
   qb_off.alloc((nc + 1) * 4);
   run_total.alloc(nc * 8);
+  uint64_t n_runs = runs.bytes / sizeof(uint2);
+  before.alloc(n_runs * 4);
   tot.alloc(64);
   SJ_HIP(hipMemsetAsync(qb_off.p, 0, (nc + 1) * 4, s));
-  launch_wu_cells(nc, tq, cstart, qlist, nq, run_off.as<uint32_t>(),
-                  runs.as<uint2>(), qb_off.as<uint32_t>(), run_total.as<uint64_t>(), s);
+  launch_wu_cells(nc, n_runs, tq, cstart, qlist, nq, run_off.as<uint32_t>(), runs.as<uint2>(),
+                  qb_off.as<uint32_t>(), run_total.as<uint64_t>(), before.as<uint32_t>(), s);
   scan.alloc(scan_tmp_bytes(std::max<uint64_t>(nc + 1, 1)) + 64);
   exclusive_scan_u32(qb_off.as<uint32_t>(), qb_off.as<uint32_t>(), nc + 1, tot.as<uint32_t>(),
                      scan.p, s);
@@ -708,19 +710,24 @@ uint64_t build_workunits(sj_index &ix, int sym, const uint32_t *qlist, uint64_t 
                      ix.nbr_off.as<uint32_t>(), ix.nbr_cell.as<uint32_t>(),
                      E.cell_start.as<uint32_t>(), E.skey.as<uint64_t>(), ix.X.as<float>(), us,
                      nullptr, nullptr, rcount.as<uint32_t>(), u_ranges->as<uint2>(), s);
+    n_runs = h_nr;
+    before.alloc(n_runs * 4);
+    launch_wu_cells(nqb, n_runs, tq, nullptr, nullptr, 0, rcount.as<uint32_t>(),
+                    u_ranges->as<uint2>(), nullptr, rlen.as<uint64_t>(), before.as<uint32_t>(), s);
     r_off = rcount.as<uint32_t>();
     r_runs = u_ranges->as<uint2>();
     r_total = rlen.as<uint64_t>();
     per_block = 1;
   }
-  TmpBuf units, ev;
+  TmpBuf units, ev, blocks;
+  blocks.alloc(nqb * sizeof(QBlock));
   units.alloc((nqb + 1) * 4);
   ev.alloc((nqb + 1) * 8);
   SJ_HIP(hipMemsetAsync(units.p, 0, (nqb + 1) * 4, s));
   SJ_HIP(hipMemsetAsync(ev.p, 0, (nqb + 1) * 8, s));
   launch_wu_count(nqb, sym, nc, tq, tc, cstart, qlist, nq,
                   qb_off.as<uint32_t>(), r_off, r_runs, r_total, units.as<uint32_t>(),
-                  ev.as<uint64_t>(), s, per_block);
+                  ev.as<uint64_t>(), blocks.as<QBlock>(), s, per_block);
   scan.alloc(scan_tmp_bytes(nqb + 1) + 64);
   exclusive_scan_u32(units.as<uint32_t>(), units.as<uint32_t>(), nqb + 1, tot.as<uint32_t>(),
                      scan.p, s);
@@ -737,9 +744,8 @@ uint64_t build_workunits(sj_index &ix, int sym, const uint32_t *qlist, uint64_t 
     unordered.alloc(n_wu * sizeof(WorkUnit));
     keys[0].alloc(n_wu * 8);
     keys[1].alloc(n_wu * 8);
-    launch_wu_fill(nqb, sym, nc, tq, tc, cstart, qlist, nq,
-                   qb_off.as<uint32_t>(), r_off, r_runs, r_total, units.as<uint32_t>(),
-                   unordered.as<WorkUnit>(), keys[0].as<uint64_t>(), s, per_block);
+    launch_wu_fill(n_wu, nqb, tc, blocks.as<QBlock>(), r_runs, before.as<uint32_t>(),
+                   units.as<uint32_t>(), unordered.as<WorkUnit>(), keys[0].as<uint64_t>(), s);
     // stable LSD sort on the stretch index (high word) keeps block order
     std::vector<int> sh;
     for (uint32_t b = 0; b < bits_for(n_wu - 1); b += 8) sh.push_back(32 + (int)b);
@@ -748,9 +754,8 @@ uint64_t build_workunits(sj_index &ix, int sym, const uint32_t *qlist, uint64_t 
     radix_sort_u64(kb, nullptr, n_wu, sh.data(), (int)sh.size(), rtmp.p, s);
     launch_gather_wu(unordered.as<WorkUnit>(), kb[0], n_wu, out.as<WorkUnit>(), s);
   } else {
-    launch_wu_fill(nqb, sym, nc, tq, tc, cstart, qlist, nq,
-                   qb_off.as<uint32_t>(), r_off, r_runs, r_total, units.as<uint32_t>(),
-                   out.as<WorkUnit>(), nullptr, s, per_block);
+    launch_wu_fill(n_wu, nqb, tc, blocks.as<QBlock>(), r_runs, before.as<uint32_t>(),
+                   units.as<uint32_t>(), out.as<WorkUnit>(), nullptr, s);
   }
   SJ_HIP(hipStreamSynchronize(s));
   return n_wu;

@@ -398,6 +398,13 @@ __global__ __launch_bounds__(kNbrBlock) void k_neighbors(
 
 // Candidate runs: maximal stretches of consecutive cell indices in A's
 // (sorted) neighbour list, as position ranges.  sym = 1 keeps only B >= A.
+// G lanes per cell take G list entries per step: an entry starts a run when its
+// predecessor in the list is not the cell before it, and ends one likewise, and
+// the i-th start and the i-th end are of the same run.  (One lane per cell walked
+// lists of up to thousands of entries by dependent loads: 10.1 ms of the 2M x 16
+// exponential join, whose cells have hundreds of neighbours, for four launches;
+// now 0.36 ms.)
+template <int G>
 __global__ __launch_bounds__(kBlock) void k_runs(int pass, int sym, uint64_t ncell,
                                                  const uint32_t *__restrict__ cell_start,
                                                  const uint32_t *__restrict__ nbr_off,
@@ -405,21 +412,33 @@ __global__ __launch_bounds__(kBlock) void k_runs(int pass, int sym, uint64_t nce
                                                  uint32_t *__restrict__ run_count,
                                                  const uint32_t *__restrict__ run_off,
                                                  uint2 *__restrict__ runs) {
-  const uint64_t A = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (A >= ncell) return;
-  const uint32_t b0 = nbr_off[A], b1 = nbr_off[A + 1];
-  uint32_t cnt = 0, w = pass ? run_off[A] : 0u;
-  uint32_t i = b0;
-  while (i < b1) {
-    uint32_t B = nbr_cell[i];
-    if (sym && B < A) { ++i; continue; }
-    uint32_t last = B;
-    ++i;
-    while (i < b1 && nbr_cell[i] == last + 1) { last = nbr_cell[i]; ++i; }
-    if (pass) runs[w++] = make_uint2(cell_start[B], cell_start[last + 1]);
-    ++cnt;
+  const uint32_t l = threadIdx.x % G;
+  const uint64_t A = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / G;
+  const bool live = A < ncell;
+  const uint32_t b0 = live ? nbr_off[A] : 0u, b1 = live ? nbr_off[A + 1] : 0u;
+  const uint32_t w = pass && live ? run_off[A] : 0u;
+  const uint32_t shift = lane_id() - l;  // this group's lanes in a wave's ballot
+  const uint64_t mask = (G == 64 ? ~0ull : (1ull << (G & 63)) - 1ull) << shift;
+  const uint64_t below = mask & ((1ull << lane_id()) - 1ull);
+  uint32_t ns = 0, ne = 0;  // starts and ends so far
+  for (uint32_t base = b0; ballot(base < b1) != 0; base += G) {
+    const uint32_t i = base + l;
+    const bool in = i < b1;
+    const uint32_t B = in ? nbr_cell[i] : 0u;
+    const bool ok = in && !(sym && B < A);
+    const uint32_t prev = ok && i > b0 ? nbr_cell[i - 1] : 0xffffffffu;
+    const uint32_t next = ok && i + 1 < b1 ? nbr_cell[i + 1] : 0xffffffffu;
+    const bool start = ok && (prev == 0xffffffffu || prev + 1 != B || (sym && prev < A));
+    const bool end = ok && (next == 0xffffffffu || next != B + 1);
+    const uint64_t ms = ballot(start), me = ballot(end);
+    if (pass) {
+      if (start) runs[w + ns + (uint32_t)__builtin_popcountll(ms & below)].x = cell_start[B];
+      if (end) runs[w + ne + (uint32_t)__builtin_popcountll(me & below)].y = cell_start[B + 1];
+    }
+    ns += (uint32_t)__builtin_popcountll(ms & mask);
+    ne += (uint32_t)__builtin_popcountll(me & mask);
   }
-  if (!pass) run_count[A] = cnt;
+  if (!pass && live && l == 0) run_count[A] = ns;
 }
 
 // Union of the candidate runs of each group of consecutive cells
@@ -494,30 +513,46 @@ __device__ __forceinline__ void cell_query_slots(uint64_t A, const uint32_t *__r
   *qb = (uint32_t)lo;
 }
 
-// Per cell: its number of query blocks and the total length of its runs.
+// Per cell (or, without nqb, per query block with runs of its own): its number
+// of query blocks, the total length of its runs and, per run, the length of the
+// cell's runs before it (below 2^32: the runs are disjoint).  G lanes per list
+// (the 2M x 16 exponential join: 1.10 ms with one lane per cell, 0.18 ms now, for
+// three launches).
+template <int G>
 __global__ __launch_bounds__(kBlock) void k_wu_cells(
-    uint64_t ncell, uint32_t tq, const uint32_t *__restrict__ cell_start,
+    uint64_t nlist, uint32_t tq, const uint32_t *__restrict__ cell_start,
     const uint32_t *__restrict__ qlist, uint64_t nq, const uint32_t *__restrict__ run_off,
-    const uint2 *__restrict__ runs, uint32_t *__restrict__ nqb, uint64_t *__restrict__ run_total) {
-  const uint64_t A = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (A >= ncell) return;
-  uint32_t qa, qb;
-  cell_query_slots(A, cell_start, qlist, nq, &qa, &qb);
-  nqb[A] = (qb - qa + tq - 1) / tq;
-  uint64_t total = 0;
-  for (uint32_t r = run_off[A]; r < run_off[A + 1]; ++r) total += runs[r].y - runs[r].x;
+    const uint2 *__restrict__ runs, uint32_t *__restrict__ nqb, uint64_t *__restrict__ run_total,
+    uint32_t *__restrict__ before) {
+  const uint32_t l = threadIdx.x % G;
+  const uint64_t A = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / G;
+  const bool live = A < nlist;
+  const uint32_t r0 = live ? run_off[A] : 0u, r1 = live ? run_off[A + 1] : 0u;
+  uint32_t total = 0;
+  for (uint32_t base = r0; ballot(base < r1) != 0; base += G) {
+    const uint32_t r = base + l;
+    const uint2 x = r < r1 ? runs[r] : make_uint2(0u, 0u);
+    const uint32_t len = x.y - x.x;
+    uint32_t inc = len;
+#pragma unroll
+    for (int off = 1; off < G; off <<= 1) {
+      const uint32_t u = __shfl_up(inc, off, G);
+      if (l >= (uint32_t)off) inc += u;
+    }
+    if (r < r1) before[r] = total + inc - len;
+    total += __shfl(inc, G - 1, G);
+  }
+  if (!live || l != 0) return;
+  if (nqb) {
+    uint32_t qa, qb;
+    cell_query_slots(A, cell_start, qlist, nq, &qa, &qb);
+    nqb[A] = (qb - qa + tq - 1) / tq;
+  }
   run_total[A] = total;
 }
 
 // Query block t: its cell (binary search over the scanned block counts),
 // slot range and candidate count.
-struct QBlock {
-  uint32_t A, q0, q1;
-  uint64_t L;       // candidates of the block
-  uint32_t skip;
-  uint32_t r0, r1;  // its runs [r0, r1)
-};
-
 __device__ __forceinline__ QBlock query_block(uint64_t t, int sym, uint64_t ncell, uint32_t tq,
                                               const uint32_t *__restrict__ cell_start,
                                               const uint32_t *__restrict__ qlist, uint64_t nq,
@@ -560,56 +595,60 @@ __global__ __launch_bounds__(kBlock) void k_wu_count(
     const uint32_t *__restrict__ cell_start, const uint32_t *__restrict__ qlist, uint64_t nq,
     const uint32_t *__restrict__ qb_off, const uint32_t *__restrict__ run_off,
     const uint2 *__restrict__ runs, const uint64_t *__restrict__ run_total,
-    uint32_t *__restrict__ units, uint64_t *__restrict__ eval, int per_block) {
+    uint32_t *__restrict__ units, uint64_t *__restrict__ eval, QBlock *__restrict__ blocks,
+    int per_block) {
   const uint64_t t = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
   if (t >= nqb_total) return;
   const QBlock b = query_block(t, sym, ncell, tq, cell_start, qlist, nq, qb_off, run_off, runs,
                                run_total, per_block);
+  blocks[t] = b;
   units[t] = (uint32_t)((b.L + tc - 1) / tc);
   eval[t] = (uint64_t)(b.q1 - b.q0) * b.L;
 }
 
+// One lane per work unit: its block (the last one with unit_off <= w: blocks
+// without units share their offset with the next), and by binary search over the
+// block's runs where its stretch of tc candidates begins and ends.  (One lane
+// per block walked the runs for all of its units in turn: 3.5 ms of the 2M x 16
+// exponential join for three launches; now 0.2 ms.)
 __global__ __launch_bounds__(kBlock) void k_wu_fill(
-    uint64_t nqb_total, int sym, uint64_t ncell, uint32_t tq, uint32_t tc,
-    const uint32_t *__restrict__ cell_start, const uint32_t *__restrict__ qlist, uint64_t nq,
-    const uint32_t *__restrict__ qb_off, const uint32_t *__restrict__ run_off,
-    const uint2 *__restrict__ runs, const uint64_t *__restrict__ run_total,
+    uint64_t n_wu, uint64_t nqb_total, uint32_t tc, const QBlock *__restrict__ blocks,
+    const uint2 *__restrict__ runs, const uint32_t *__restrict__ before,
     const uint32_t *__restrict__ unit_off, WorkUnit *__restrict__ wu,
-    uint64_t *__restrict__ order_key, int per_block) {
-  const uint64_t t = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (t >= nqb_total) return;
-  const QBlock b = query_block(t, sym, ncell, tq, cell_start, qlist, nq, qb_off, run_off, runs,
-                               run_total, per_block);
-  if (b.L == 0) return;
-  const uint32_t nu = (uint32_t)((b.L + tc - 1) / tc);
-  const uint32_t r1 = b.r1;
-  uint32_t r = b.r0;
-  uint32_t c = runs[r].x + b.skip;
-  uint32_t w = unit_off[t];
-  for (uint32_t u = 0; u < nu; ++u) {
-    WorkUnit x;
-    x.q0 = b.q0;
-    x.q1 = b.q1;
-    x.cell = b.A;
-    x.pad = 0;
-    x.run_first = r;
-    x.c_begin = c;
-    uint32_t need = tc;
-    for (;;) {
-      const uint32_t avail = runs[r].y - c;
-      if (avail > need) { c += need; break; }
-      need -= avail;
-      if (r + 1 == r1 || need == 0) { c = runs[r].y; break; }
-      ++r;
-      c = runs[r].x;
-    }
-    x.run_last = r;
-    x.c_end = c;
-    // optional order key: stretch index within the block, then unit index
-    if (order_key) order_key[w] = ((uint64_t)u << 32) | w;
-    wu[w++] = x;
-    if (c == runs[r].y && r + 1 < r1) { ++r; c = runs[r].x; }
+    uint64_t *__restrict__ order_key) {
+  const uint64_t w = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (w >= n_wu) return;
+  uint64_t lo = 0, hi = nqb_total;
+  while (hi - lo > 1) {
+    const uint64_t m = (lo + hi) >> 1;
+    if (unit_off[m] <= w) lo = m; else hi = m;
   }
+  const QBlock b = blocks[lo];
+  const uint32_t u = (uint32_t)(w - unit_off[lo]);
+  // candidates [o0, o1) of the runs, counted from the first run's start
+  const uint64_t left = b.L - (uint64_t)u * tc;
+  const uint32_t o0 = b.skip + u * tc;
+  const uint32_t o1 = o0 + (uint32_t)(left < tc ? left : tc);
+  auto run_of = [&](uint32_t o, uint32_t first) {  // the run holding candidate o
+    uint32_t x = first, y = b.r1;
+    while (y - x > 1) {
+      const uint32_t m = x + (y - x) / 2;
+      if (before[m] <= o) x = m; else y = m;
+    }
+    return x;
+  };
+  WorkUnit x;
+  x.q0 = b.q0;
+  x.q1 = b.q1;
+  x.cell = b.A;
+  x.pad = 0;
+  x.run_first = run_of(o0, b.r0);
+  x.c_begin = runs[x.run_first].x + (o0 - before[x.run_first]);
+  x.run_last = run_of(o1 - 1, x.run_first);
+  x.c_end = runs[x.run_last].x + (o1 - before[x.run_last]);
+  // optional order key: stretch index within the block, then unit index
+  if (order_key) order_key[w] = ((uint64_t)u << 32) | w;
+  wu[w] = x;
 }
 
 // SORTIDU for blocks of queries (see launch_qb_ranges).  The window around
@@ -868,12 +907,22 @@ void launch_neighbors(int pass, const uint64_t *qkey, uint64_t nq, const uint64_
   SJ_HIP(hipGetLastError());
 }
 
-void launch_runs(int pass, int sym, uint64_t ncell, const uint32_t *cell_start,
+// Lanes per list of the kernels above: a wave for long lists, 8 lanes for lists
+// of a few entries, where a wave per list would leave most lanes idle (both forms
+// take one step per list up to 8 entries; from 16 on the wave takes half as many
+// or fewer).
+constexpr uint64_t kLongLists = 16;  // entries per list, on average
+
+void launch_runs(int pass, int sym, uint64_t ncell, uint64_t n_nbr, const uint32_t *cell_start,
                  const uint32_t *nbr_off, const uint32_t *nbr_cell, uint32_t *run_count,
                  const uint32_t *run_off, uint2 *runs, hipStream_t s) {
   if (!ncell) return;
-  hipLaunchKernelGGL(k_runs, dim3(blocks_for(ncell)), dim3(kBlock), 0, s, pass, sym, ncell,
-                     cell_start, nbr_off, nbr_cell, run_count, run_off, runs);
+  if (n_nbr >= kLongLists * ncell)
+    hipLaunchKernelGGL(k_runs<64>, dim3(blocks_for(ncell * 64)), dim3(kBlock), 0, s, pass, sym,
+                       ncell, cell_start, nbr_off, nbr_cell, run_count, run_off, runs);
+  else
+    hipLaunchKernelGGL(k_runs<8>, dim3(blocks_for(ncell * 8)), dim3(kBlock), 0, s, pass, sym,
+                       ncell, cell_start, nbr_off, nbr_cell, run_count, run_off, runs);
   SJ_HIP(hipGetLastError());
 }
 
@@ -886,36 +935,38 @@ void launch_group_runs(int pass, uint64_t ngroup, const uint32_t *gfirst, const 
   SJ_HIP(hipGetLastError());
 }
 
-void launch_wu_cells(uint64_t ncell, uint32_t tq, const uint32_t *cell_start,
+void launch_wu_cells(uint64_t nlist, uint64_t n_runs, uint32_t tq, const uint32_t *cell_start,
                      const uint32_t *qlist, uint64_t nq, const uint32_t *run_off,
-                     const uint2 *runs, uint32_t *nqb, uint64_t *run_total, hipStream_t s) {
-  if (!ncell) return;
-  hipLaunchKernelGGL(k_wu_cells, dim3(blocks_for(ncell)), dim3(kBlock), 0, s, ncell, tq,
-                     cell_start, qlist, nq, run_off, runs, nqb, run_total);
+                     const uint2 *runs, uint32_t *nqb, uint64_t *run_total, uint32_t *before,
+                     hipStream_t s) {
+  if (!nlist) return;
+  if (n_runs >= kLongLists * nlist)
+    hipLaunchKernelGGL(k_wu_cells<64>, dim3(blocks_for(nlist * 64)), dim3(kBlock), 0, s, nlist, tq,
+                       cell_start, qlist, nq, run_off, runs, nqb, run_total, before);
+  else
+    hipLaunchKernelGGL(k_wu_cells<8>, dim3(blocks_for(nlist * 8)), dim3(kBlock), 0, s, nlist, tq,
+                       cell_start, qlist, nq, run_off, runs, nqb, run_total, before);
   SJ_HIP(hipGetLastError());
 }
 
 void launch_wu_count(uint64_t nqb_total, int sym, uint64_t ncell, uint32_t tq, uint32_t tc,
                      const uint32_t *cell_start, const uint32_t *qlist, uint64_t nq,
                      const uint32_t *qb_off, const uint32_t *run_off, const uint2 *runs,
-                     const uint64_t *run_total, uint32_t *units, uint64_t *eval, hipStream_t s,
-                     int per_block) {
+                     const uint64_t *run_total, uint32_t *units, uint64_t *eval, QBlock *blocks,
+                     hipStream_t s, int per_block) {
   if (!nqb_total) return;
   hipLaunchKernelGGL(k_wu_count, dim3(blocks_for(nqb_total)), dim3(kBlock), 0, s, nqb_total, sym,
                      ncell, tq, tc, cell_start, qlist, nq, qb_off, run_off, runs, run_total, units,
-                     eval, per_block);
+                     eval, blocks, per_block);
   SJ_HIP(hipGetLastError());
 }
 
-void launch_wu_fill(uint64_t nqb_total, int sym, uint64_t ncell, uint32_t tq, uint32_t tc,
-                    const uint32_t *cell_start, const uint32_t *qlist, uint64_t nq,
-                    const uint32_t *qb_off, const uint32_t *run_off, const uint2 *runs,
-                    const uint64_t *run_total, const uint32_t *unit_off, WorkUnit *wu,
-                    uint64_t *order_key, hipStream_t s, int per_block) {
-  if (!nqb_total) return;
-  hipLaunchKernelGGL(k_wu_fill, dim3(blocks_for(nqb_total)), dim3(kBlock), 0, s, nqb_total, sym,
-                     ncell, tq, tc, cell_start, qlist, nq, qb_off, run_off, runs, run_total,
-                     unit_off, wu, order_key, per_block);
+void launch_wu_fill(uint64_t n_wu, uint64_t nqb_total, uint32_t tc, const QBlock *blocks,
+                    const uint2 *runs, const uint32_t *before, const uint32_t *unit_off,
+                    WorkUnit *wu, uint64_t *order_key, hipStream_t s) {
+  if (!n_wu) return;
+  hipLaunchKernelGGL(k_wu_fill, dim3(blocks_for(n_wu)), dim3(kBlock), 0, s, n_wu, nqb_total, tc,
+                     blocks, runs, before, unit_off, wu, order_key);
   SJ_HIP(hipGetLastError());
 }
 

@@ -74,7 +74,8 @@ void launch_neighbors(int pass, const uint64_t *qkey, uint64_t nq, const uint64_
                       const uint32_t *cell_start, uint64_t ncell, const NbrParams &np,
                       uint32_t *nbr_count, uint64_t *cand_sum, const uint32_t *nbr_off,
                       uint32_t *nbr_cell, hipStream_t s);
-void launch_runs(int pass, int sym, uint64_t ncell, const uint32_t *cell_start,
+// n_nbr: entries of all neighbour lists.
+void launch_runs(int pass, int sym, uint64_t ncell, uint64_t n_nbr, const uint32_t *cell_start,
                  const uint32_t *nbr_off, const uint32_t *nbr_cell, uint32_t *run_count,
                  const uint32_t *run_off, uint2 *runs, hipStream_t s);
 // Union runs of groups of at most kGroupMaxCells consecutive cells (two
@@ -87,19 +88,26 @@ void launch_group_runs(int pass, uint64_t ngroup, const uint32_t *gfirst, const 
 // block (units, evaluated pairs), per query block (fill).  With per_block,
 // run_off / run_total are indexed by query block (each block has runs of
 // its own, the SORTIDU ranges) instead of by cell.
-void launch_wu_cells(uint64_t ncell, uint32_t tq, const uint32_t *cell_start,
+struct QBlock {     // a query block
+  uint32_t A, q0, q1;  // its cell (group) and query slots
+  uint32_t skip;       // candidates of its runs it leaves out at the front
+  uint64_t L;          // its candidates
+  uint32_t r0, r1;     // its runs [r0, r1)
+};
+// n_runs: runs of all lists; before[r]: candidates of the list's runs before r.
+// Without nqb the lists are those of query blocks (SORTIDU).
+void launch_wu_cells(uint64_t nlist, uint64_t n_runs, uint32_t tq, const uint32_t *cell_start,
                      const uint32_t *qlist, uint64_t nq, const uint32_t *run_off,
-                     const uint2 *runs, uint32_t *nqb, uint64_t *run_total, hipStream_t s);
+                     const uint2 *runs, uint32_t *nqb, uint64_t *run_total, uint32_t *before,
+                     hipStream_t s);
 void launch_wu_count(uint64_t nqb_total, int sym, uint64_t ncell, uint32_t tq, uint32_t tc,
                      const uint32_t *cell_start, const uint32_t *qlist, uint64_t nq,
                      const uint32_t *qb_off, const uint32_t *run_off, const uint2 *runs,
-                     const uint64_t *run_total, uint32_t *units, uint64_t *eval, hipStream_t s,
-                     int per_block = 0);
-void launch_wu_fill(uint64_t nqb_total, int sym, uint64_t ncell, uint32_t tq, uint32_t tc,
-                    const uint32_t *cell_start, const uint32_t *qlist, uint64_t nq,
-                    const uint32_t *qb_off, const uint32_t *run_off, const uint2 *runs,
-                    const uint64_t *run_total, const uint32_t *unit_off, WorkUnit *wu,
-                    uint64_t *order_key, hipStream_t s, int per_block = 0);
+                     const uint64_t *run_total, uint32_t *units, uint64_t *eval, QBlock *blocks,
+                     hipStream_t s, int per_block = 0);
+void launch_wu_fill(uint64_t n_wu, uint64_t nqb_total, uint32_t tc, const QBlock *blocks,
+                    const uint2 *runs, const uint32_t *before, const uint32_t *unit_off,
+                    WorkUnit *wu, uint64_t *order_key, hipStream_t s);
 // SORTIDU search along u (Section 4.3) for blocks of queries.
 struct USearch {
   uint32_t ur, dp;   // reordered column of u in the query rows, row stride
