@@ -25,16 +25,16 @@ __device__ __forceinline__ T wave_inclusive_scan(T v) {
 
 // Exclusive scan of one value per thread over the workgroup; *total gets
 // the workgroup sum.
-template <typename T>
+template <typename T, int W = kWavesPerBlock>
 __device__ __forceinline__ T block_exclusive_scan(T v, T *total) {
-  __shared__ T wsum[kWavesPerBlock];
+  __shared__ T wsum[W];
   const int w = threadIdx.x / kWave;
   T inc = wave_inclusive_scan(v);
   if (lane_id() == kWave - 1) wsum[w] = inc;
   __syncthreads();
   T before = 0, all = 0;
 #pragma unroll
-  for (int i = 0; i < kWavesPerBlock; ++i) {
+  for (int i = 0; i < W; ++i) {
     if (i < w) before += wsum[i];
     all += wsum[i];
   }
@@ -96,6 +96,56 @@ __global__ __launch_bounds__(kBlock) void k_scan_tile(const T *in, T *out, uint6
   if (total && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = off + btotal;
 }
 
+// The same over up to kScanOneMax values by one workgroup, tile after tile, the
+// next tile's values in flight: one launch of 4 to 9 us where reduce, scan of
+// the sums and tile scan took three of 2 to 3 us and the gaps between them.
+constexpr int kScanOneBlock = 1024;
+constexpr uint64_t kScanOneTile = (uint64_t)kScanOneBlock * kScanItems;  // 8192
+constexpr uint64_t kScanOneMax = 4 * kScanOneTile;
+
+template <typename T>
+__global__ __launch_bounds__(kScanOneBlock) void k_scan_one(const T *in, T *out, uint32_t n,
+                                                            T *total) {
+  __shared__ T tile[kScanOneTile];
+  T x[kScanItems];
+  auto load = [&](uint32_t base) {
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) {
+      const uint32_t idx = base + (uint32_t)i * kScanOneBlock + threadIdx.x;
+      x[i] = idx < n ? in[idx] : T(0);
+    }
+  };
+  T carry = 0;
+  load(0);
+  for (uint32_t base = 0; base < n; base += (uint32_t)kScanOneTile) {
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) tile[i * kScanOneBlock + threadIdx.x] = x[i];
+    __syncthreads();
+    load(base + (uint32_t)kScanOneTile);  // (past n: nothing)
+    T v[kScanItems];
+    T s = 0;
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) {
+      const T t = tile[threadIdx.x * kScanItems + i];
+      v[i] = s;
+      s += t;
+    }
+    T sum;
+    const T excl = carry + block_exclusive_scan<T, kScanOneBlock / kWave>(s, &sum);
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) tile[threadIdx.x * kScanItems + i] = v[i] + excl;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kScanItems; ++i) {
+      const uint32_t idx = base + (uint32_t)i * kScanOneBlock + threadIdx.x;
+      if (idx < n) out[idx] = tile[i * kScanOneBlock + threadIdx.x];
+    }
+    __syncthreads();
+    carry += sum;
+  }
+  if (total && threadIdx.x == 0) *total = carry;
+}
+
 template <typename T>
 size_t scan_levels_bytes(uint64_t n) {
   size_t bytes = 0;
@@ -109,13 +159,16 @@ size_t scan_levels_bytes(uint64_t n) {
 
 template <typename T>
 void scan_impl(const T *in, T *out, uint64_t n, T *d_total, char *tmp, hipStream_t s) {
-  if (n == 0) {
-    if (d_total) SJ_HIP(hipMemsetAsync(d_total, 0, sizeof(T), s));
-    return;
-  }
-  if (n <= (uint64_t)kScanTile) {
+  if (n == 0 && !d_total) return;
+  if (n <= (uint64_t)kScanTile) {  // (of nothing: a total of 0)
     hipLaunchKernelGGL(k_scan_tile<T>, dim3(1), dim3(kBlock), 0, s, in, out, n,
                        (const T *)nullptr, d_total);
+    SJ_HIP(hipGetLastError());
+    return;
+  }
+  if (n <= kScanOneMax) {
+    hipLaunchKernelGGL(k_scan_one<T>, dim3(1), dim3(kScanOneBlock), 0, s, in, out, (uint32_t)n,
+                       d_total);
     SJ_HIP(hipGetLastError());
     return;
   }
@@ -289,6 +342,112 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(
     const uint64_t pos = gbase[dg] + i;
     kout[pos] = k;
     if (kVals) vout[pos] = tval[i];
+  }
+}
+
+// All passes over at most kSmallSort keys in one launch of one workgroup, the
+// keys in LDS between passes (a pass of the general form is three launches,
+// 13 us with the gaps between them at these sizes; this takes 10 us for four).
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallWaves = kSmallBlock / kWave;
+constexpr int kSmallRounds = 4;
+constexpr uint32_t kSmallSort = kSmallBlock * kSmallRounds;
+struct SmallPasses {
+  int n;
+  uint8_t shift[16], width[16];
+};
+
+template <bool kVals>
+__global__ __launch_bounds__(kSmallBlock) void k_rs_small(uint64_t *keys, uint32_t *vals,
+                                                          uint32_t n_cap, SmallPasses ps,
+                                                          const unsigned long long *__restrict__
+                                                              d_count) {
+  __shared__ uint32_t cnt[kSmallWaves][kRadixBins];
+  __shared__ uint64_t tkey[kSmallSort];
+  __shared__ uint32_t tval[kVals ? kSmallSort : 1];
+  const uint32_t n = (uint32_t)live_count(n_cap, d_count);
+  const int w = threadIdx.x / kWave;
+  const uint32_t base = (uint32_t)w * (kSmallRounds * kWave) + lane_id();
+  uint64_t key[kSmallRounds];
+  uint32_t val[kSmallRounds];
+#pragma unroll
+  for (int r = 0; r < kSmallRounds; ++r) {
+    const uint32_t idx = base + (uint32_t)r * kWave;
+    key[r] = idx < n ? keys[idx] : 0ull;
+    if (kVals) val[r] = idx < n ? vals[idx] : 0u;
+  }
+  for (int p = 0; p < ps.n; ++p) {
+    const int shift = ps.shift[p], width = ps.width[p];
+    const uint32_t mask = (1u << width) - 1u;
+    for (int i = threadIdx.x; i < kSmallWaves * kRadixBins; i += kSmallBlock) (&cnt[0][0])[i] = 0;
+    __syncthreads();
+    // the ranks, offsets and placement of k_rs_scatter
+    uint32_t rank[kSmallRounds];
+#pragma unroll
+    for (int r = 0; r < kSmallRounds; ++r) {
+      const bool valid = base + (uint32_t)r * kWave < n;
+      const uint32_t dg = (uint32_t)(key[r] >> shift) & mask;
+      uint64_t peers = ballot(valid);
+      for (int b = 0; b < width; ++b) {
+        const bool bit = (dg >> b) & 1u;
+        const uint64_t m = ballot(bit);
+        peers &= bit ? m : ~m;
+      }
+      const uint32_t below = lanes_below(peers);
+      uint32_t before = 0;
+      if (valid) before = cnt[w][dg];
+      rank[r] = before + below;
+      __builtin_amdgcn_wave_barrier();
+      if (valid && below == 0) cnt[w][dg] = before + (uint32_t)__builtin_popcountll(peers);
+      __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    {
+      const uint32_t dg = threadIdx.x;
+      const bool own = dg < (uint32_t)kRadixBins;
+      uint32_t c[kSmallWaves], sum = 0;
+#pragma unroll
+      for (int i = 0; i < kSmallWaves; ++i) {
+        c[i] = own ? cnt[i][dg] : 0u;
+        sum += c[i];
+      }
+      uint32_t total;
+      uint32_t at = block_exclusive_scan<uint32_t, kSmallWaves>(sum, &total);
+      if (own) {
+#pragma unroll
+        for (int i = 0; i < kSmallWaves; ++i) {
+          cnt[i][dg] = at;
+          at += c[i];
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSmallRounds; ++r) {
+      if (base + (uint32_t)r * kWave < n) {
+        const uint32_t lp = cnt[w][(uint32_t)(key[r] >> shift) & mask] + rank[r];
+        tkey[lp] = key[r];
+        if (kVals) tval[lp] = val[r];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSmallRounds; ++r) {
+      const uint32_t idx = base + (uint32_t)r * kWave;
+      if (idx < n) {
+        key[r] = tkey[idx];
+        if (kVals) val[r] = tval[idx];
+      }
+    }
+    // (the next pass writes tkey after two more barriers)
+  }
+#pragma unroll
+  for (int r = 0; r < kSmallRounds; ++r) {
+    const uint32_t idx = base + (uint32_t)r * kWave;
+    if (idx < n) {
+      keys[idx] = key[r];
+      if (kVals) vals[idx] = val[r];
+    }
   }
 }
 
@@ -522,6 +681,25 @@ void radix_sort_u64(uint64_t *keys[2], uint32_t *vals[2], uint64_t n, const int 
                     const int *widths) {
   if (n == 0 || (n == 1 && !d_count) || n_passes == 0) return;
   if ((n + kRsTile - 1) / kRsTile > 0x7fffffffull) fail(SJ_ERR_INVALID_ARG, "radix sort too large");
+  if (n <= kSmallSort && n_passes <= 16) {
+    SmallPasses ps{};
+    ps.n = n_passes;
+    for (int p = 0; p < n_passes; ++p) {
+      const int w = widths ? widths[p] : kRadixBits;
+      if (w < 1 || w > kRadixBits || shifts[p] < 0 || shifts[p] > 63)
+        fail(SJ_ERR_INVALID_ARG, "radix digit width must be 1..8");
+      ps.shift[p] = (uint8_t)shifts[p];
+      ps.width[p] = (uint8_t)w;
+    }
+    if (vals)
+      hipLaunchKernelGGL(k_rs_small<true>, dim3(1), dim3(kSmallBlock), 0, s, keys[0], vals[0],
+                         (uint32_t)n, ps, d_count);
+    else
+      hipLaunchKernelGGL(k_rs_small<false>, dim3(1), dim3(kSmallBlock), 0, s, keys[0],
+                         (uint32_t *)nullptr, (uint32_t)n, ps, d_count);
+    SJ_HIP(hipGetLastError());
+    return;
+  }
   const uint32_t nb = (uint32_t)((n + kRsTile - 1) / kRsTile);
   const uint64_t nhist = (uint64_t)kRadixBins * nb;
   uint64_t *hist = static_cast<uint64_t *>(tmp);
