@@ -476,13 +476,10 @@ uint64_t build_grid(sj_index &ix, const float *P, const Geometry &g, BuildTmp &t
       SJ_HIP(hipMemcpyAsync(ix.skey.p, kb[0], n * 8, hipMemcpyDeviceToDevice, s));
     }
   }
-  uint32_t *d_ncell = t.small.as<uint32_t>();
-  launch_compact(kb[0], n, g.fine_bits, t.flag.as<uint32_t>(), d_ncell,
+  launch_compact(kb[0], n, g.fine_bits, t.flag.as<uint32_t>(), ix.word_as<uint32_t>(kWordCells),
                  ix.cell_key.as<uint64_t>(), ix.cell_start.as<uint32_t>(), t.scan.p, s);
-  uint32_t h_ncell = 0;
-  SJ_HIP(hipMemcpyAsync(&h_ncell, d_ncell, 4, hipMemcpyDeviceToHost, s));
   SJ_HIP(hipStreamSynchronize(s));
-  ix.ncell = h_ncell;
+  ix.ncell = *ix.word_as<uint32_t>(kWordCells);
   return build_neighbors(ix, ix, g.np, t, s, keep);
 }
 
@@ -499,45 +496,42 @@ uint64_t build_neighbors(sj_index &ix, const sj_index &E, NbrParams np, BuildTmp
   while ((ne + fs - 1) / fs > kFence) fs <<= 1;
   np.fstride = (uint32_t)fs;
   np.nfence = (uint32_t)((ne + fs - 1) / fs);
-  SJ_HIP(hipMemsetAsync(t.nbr_count.p, 0, (nc + 1) * 4, s));
-  SJ_HIP(hipMemsetAsync(t.cand_sum.p, 0, (nc + 1) * 8, s));
   launch_neighbors(0, ix.cell_key.as<uint64_t>(), nc, E.cell_key.as<uint64_t>(),
                    E.cell_start.as<uint32_t>(), ne, np, t.nbr_count.as<uint32_t>(),
                    t.cand_sum.as<uint64_t>(), nullptr, nullptr, s);
   launch_cell_products(nc, ix.cell_start.as<uint32_t>(), t.cand_sum.as<uint64_t>(),
                        t.prod.as<uint64_t>(), s);
-  uint64_t *d_c = reinterpret_cast<uint64_t *>(t.small.as<char>() + 8);
-  exclusive_scan_u64(t.prod.as<uint64_t>(), t.prod.as<uint64_t>(), nc, d_c, t.scan.p, s);
-  uint64_t h_c = 0;
-  SJ_HIP(hipMemcpyAsync(&h_c, d_c, 8, hipMemcpyDeviceToHost, s));
-  if (keep) {
-    // the adjacency lists use 32-bit offsets: their total, summed in 64 bits
-    // (the C scan above no longer needs t.prod), must stay below 2^32
-    launch_widen(t.nbr_count.as<uint32_t>(), t.prod.as<uint64_t>(), nc + 1, s);
-    uint64_t *d_nn64 = reinterpret_cast<uint64_t *>(t.small.as<char>() + 24);
-    exclusive_scan_u64(t.prod.as<uint64_t>(), t.prod.as<uint64_t>(), nc + 1, d_nn64, t.scan.p, s);
-    uint64_t h_nn64 = 0;
-    SJ_HIP(hipMemcpyAsync(&h_nn64, d_nn64, 8, hipMemcpyDeviceToHost, s));
+  exclusive_scan_u64(t.prod.as<uint64_t>(), t.prod.as<uint64_t>(), nc, ix.word(kWordCand),
+                     t.scan.p, s);
+  if (!keep) {
     SJ_HIP(hipStreamSynchronize(s));
-    if (h_nn64 > 0xffffffffull)
-      fail(SJ_ERR_KEY_OVERFLOW, "the adjacency lists over k=" + std::to_string(ix.geom.k) +
-                                    " dimensions hold " + std::to_string(h_nn64) +
-                                    " cells, more than 2^32 - 1; use a smaller k");
-    ix.nbr_off.alloc((nc + 1) * 4);
-    uint32_t *d_nn = reinterpret_cast<uint32_t *>(t.small.as<char>() + 16);
-    exclusive_scan_u32(t.nbr_count.as<uint32_t>(), ix.nbr_off.as<uint32_t>(), nc + 1, d_nn,
-                       t.scan.p, s);
-    uint32_t h_nn = 0;
-    SJ_HIP(hipMemcpyAsync(&h_nn, d_nn, 4, hipMemcpyDeviceToHost, s));
-    SJ_HIP(hipStreamSynchronize(s));
-    ix.n_nbr = h_nn;
-    ix.nbr_cell.alloc((uint64_t)h_nn * 4);
-    launch_neighbors(1, ix.cell_key.as<uint64_t>(), nc, E.cell_key.as<uint64_t>(),
-                     E.cell_start.as<uint32_t>(), ne, np, nullptr, nullptr,
-                     ix.nbr_off.as<uint32_t>(), ix.nbr_cell.as<uint32_t>(), s);
+    return *ix.word(kWordCand);
   }
+  // the adjacency lists use 32-bit offsets: where the cells times the most a
+  // list can hold could pass 2^32 - 1, their total is summed in 64 bits first
+  // (the C scan above no longer needs t.prod)
+  if ((double)nc * std::min<double>((double)np.n_off, (double)ne) > 4294967295.0) {
+    launch_widen(t.nbr_count.as<uint32_t>(), t.prod.as<uint64_t>(), nc, s);
+    exclusive_scan_u64(t.prod.as<uint64_t>(), t.prod.as<uint64_t>(), nc, ix.word(kWordNbr),
+                       t.scan.p, s);
+    SJ_HIP(hipStreamSynchronize(s));
+    const uint64_t nn = *ix.word(kWordNbr);
+    if (nn > 0xffffffffull)
+      fail(SJ_ERR_KEY_OVERFLOW, "the adjacency lists over k=" + std::to_string(ix.geom.k) +
+                                    " dimensions hold " + std::to_string(nn) +
+                                    " cells, more than 2^32 - 1; use a smaller k");
+  }
+  ix.nbr_off.alloc((nc + 1) * 4);
+  exclusive_scan_u32(t.nbr_count.as<uint32_t>(), ix.nbr_off.as<uint32_t>(), nc,
+                     ix.nbr_off.as<uint32_t>() + nc, t.scan.p, s,
+                     ix.word_as<uint32_t>(kWordNbr));
   SJ_HIP(hipStreamSynchronize(s));
-  return h_c;
+  ix.n_nbr = *ix.word_as<uint32_t>(kWordNbr);
+  ix.nbr_cell.alloc(ix.n_nbr * 4);
+  launch_neighbors(1, ix.cell_key.as<uint64_t>(), nc, E.cell_key.as<uint64_t>(),
+                   E.cell_start.as<uint32_t>(), ne, np, nullptr, nullptr,
+                   ix.nbr_off.as<uint32_t>(), ix.nbr_cell.as<uint32_t>(), s);
+  return *ix.word(kWordCand);
 }
 
 // Share of the lane work of the FP32 units of tq queries that falls on
@@ -549,15 +543,13 @@ double live_slot_share(const sj_index &ix, const uint64_t *cand_sum, uint32_t tq
   const uint64_t nc = ix.ncell;
   if (!nc || !ix.candidates) return 1.0;
   ScratchScope scope;  // the read-back below synchronises the stream
-  TmpBuf w, tot, scan;
+  TmpBuf w, scan;
   w.alloc(nc * 8);
-  tot.alloc(64);
   scan.alloc(scan_tmp_bytes(nc) + 64);
   launch_cell_slot_work(nc, ix.cell_start.as<uint32_t>(), cand_sum, tq, w.as<uint64_t>(), s);
-  exclusive_scan_u64(w.as<uint64_t>(), w.as<uint64_t>(), nc, tot.as<uint64_t>(), scan.p, s);
-  uint64_t h = 0;
-  SJ_HIP(hipMemcpyAsync(&h, tot.p, 8, hipMemcpyDeviceToHost, s));
+  exclusive_scan_u64(w.as<uint64_t>(), w.as<uint64_t>(), nc, ix.word(kWordSlots), scan.p, s);
   SJ_HIP(hipStreamSynchronize(s));
+  const uint64_t h = *ix.word(kWordSlots);
   return h ? (double)ix.candidates / (double)h : 1.0;
 }
 constexpr double kLiveSlotShareMin = 0.75;  // below it, units of one query per lane
@@ -567,17 +559,15 @@ uint64_t build_runs(sj_index &ix, int sym, DevBuf &off, DevBuf &runs, BuildTmp &
   const uint64_t nc = ix.ncell;
   ScratchScope scope;
   TmpBuf cnt;
-  cnt.alloc((nc + 1) * 4);
-  SJ_HIP(hipMemsetAsync(cnt.p, 0, (nc + 1) * 4, s));
+  cnt.alloc(nc * 4);
   const uint32_t *ecs = entries_of(ix).cell_start.as<uint32_t>();  // candidate cells
   launch_runs(0, sym, nc, ix.n_nbr, ecs, ix.nbr_off.as<uint32_t>(), ix.nbr_cell.as<uint32_t>(),
               cnt.as<uint32_t>(), nullptr, nullptr, s);
   off.alloc((nc + 1) * 4);
-  uint32_t *d_tot = t.small.as<uint32_t>() + 8;
-  exclusive_scan_u32(cnt.as<uint32_t>(), off.as<uint32_t>(), nc + 1, d_tot, t.scan.p, s);
-  uint32_t h_tot = 0;
-  SJ_HIP(hipMemcpyAsync(&h_tot, d_tot, 4, hipMemcpyDeviceToHost, s));
+  exclusive_scan_u32(cnt.as<uint32_t>(), off.as<uint32_t>(), nc, off.as<uint32_t>() + nc,
+                     t.scan.p, s, ix.word_as<uint32_t>(kWordRuns));
   SJ_HIP(hipStreamSynchronize(s));
+  const uint32_t h_tot = *ix.word_as<uint32_t>(kWordRuns);
   runs.alloc((uint64_t)h_tot * sizeof(uint2));
   launch_runs(1, sym, nc, ix.n_nbr, ecs, ix.nbr_off.as<uint32_t>(),
               ix.nbr_cell.as<uint32_t>(), nullptr, off.as<uint32_t>(), runs.as<uint2>(), s);
@@ -610,24 +600,21 @@ void build_cell_groups(sj_index &ix, uint32_t max_q, CellGroups &g, hipStream_t 
   gstart.push_back(start[nc]);
   const uint64_t ng = first.size() - 1;
   ScratchScope scope;  // the read-back below synchronises the stream
-  TmpBuf gfirst, cnt, tot, scan;
+  TmpBuf gfirst, cnt, scan;
   gfirst.alloc((ng + 1) * 4);
   SJ_HIP(hipMemcpyAsync(gfirst.p, first.data(), (ng + 1) * 4, hipMemcpyHostToDevice, s));
   g.n = ng;
   g.start.alloc((ng + 1) * 4);
   SJ_HIP(hipMemcpyAsync(g.start.p, gstart.data(), (ng + 1) * 4, hipMemcpyHostToDevice, s));
-  cnt.alloc((ng + 1) * 4);
-  SJ_HIP(hipMemsetAsync(cnt.p, 0, (ng + 1) * 4, s));
+  cnt.alloc(ng * 4);
   launch_group_runs(0, ng, gfirst.as<uint32_t>(), ix.run_off_sym.as<uint32_t>(),
                     ix.runs_sym.as<uint2>(), cnt.as<uint32_t>(), nullptr, nullptr, s);
   g.run_off.alloc((ng + 1) * 4);
-  tot.alloc(64);
   scan.alloc(scan_tmp_bytes(ng + 1) + 64);
-  exclusive_scan_u32(cnt.as<uint32_t>(), g.run_off.as<uint32_t>(), ng + 1, tot.as<uint32_t>(),
-                     scan.p, s);
-  uint32_t h_tot = 0;
-  SJ_HIP(hipMemcpyAsync(&h_tot, tot.p, 4, hipMemcpyDeviceToHost, s));
+  exclusive_scan_u32(cnt.as<uint32_t>(), g.run_off.as<uint32_t>(), ng,
+                     g.run_off.as<uint32_t>() + ng, scan.p, s, ix.word_as<uint32_t>(kWordGroups));
   SJ_HIP(hipStreamSynchronize(s));
+  const uint32_t h_tot = *ix.word_as<uint32_t>(kWordGroups);
   g.runs.alloc(std::max<uint64_t>(h_tot, 1) * sizeof(uint2));
   launch_group_runs(1, ng, gfirst.as<uint32_t>(), ix.run_off_sym.as<uint32_t>(),
                     ix.runs_sym.as<uint2>(), nullptr, g.run_off.as<uint32_t>(),
@@ -655,6 +642,7 @@ USearch usearch_of(const sj_index &ix) {
   return us;
 }
 
+// With tc = 0 only *eval is found (it does not depend on the stretches).
 // With u_ranges (SORTIDU; contiguous queries only), every query block gets
 // its own candidate ranges (launch_qb_ranges, into *u_ranges) and the units
 // are cut from those instead of from the cells' runs.
@@ -666,22 +654,18 @@ uint64_t build_workunits(sj_index &ix, int sym, const uint32_t *qlist, uint64_t 
   const uint64_t nc = groups ? groups->n : ix.ncell;
   const uint32_t *cstart = groups ? groups->start.as<uint32_t>() : ix.cell_start.as<uint32_t>();
   ScratchScope scope;  // every temporary below is dead at the final synchronisation
-  TmpBuf qb_off, run_total, before, scan, tot;
+  TmpBuf qb_off, run_total, before, scan;
   qb_off.alloc((nc + 1) * 4);
   run_total.alloc(nc * 8);
   uint64_t n_runs = runs.bytes / sizeof(uint2);
   before.alloc(n_runs * 4);
-  tot.alloc(64);
-  SJ_HIP(hipMemsetAsync(qb_off.p, 0, (nc + 1) * 4, s));
   launch_wu_cells(nc, n_runs, tq, cstart, qlist, nq, run_off.as<uint32_t>(), runs.as<uint2>(),
                   qb_off.as<uint32_t>(), run_total.as<uint64_t>(), before.as<uint32_t>(), s);
   scan.alloc(scan_tmp_bytes(std::max<uint64_t>(nc + 1, 1)) + 64);
-  exclusive_scan_u32(qb_off.as<uint32_t>(), qb_off.as<uint32_t>(), nc + 1, tot.as<uint32_t>(),
-                     scan.p, s);
-  uint32_t h_nqb = 0;
-  SJ_HIP(hipMemcpyAsync(&h_nqb, tot.p, 4, hipMemcpyDeviceToHost, s));
+  exclusive_scan_u32(qb_off.as<uint32_t>(), qb_off.as<uint32_t>(), nc,
+                     ix.word_as<uint32_t>(kWordBlocks), scan.p, s);
   SJ_HIP(hipStreamSynchronize(s));
-  const uint64_t nqb = h_nqb;
+  const uint64_t nqb = *ix.word_as<uint32_t>(kWordBlocks);
   // the runs the units are cut from: the cells' (indexed by cell), or with
   // SORTIDU each block's own ranges (indexed by block)
   const uint32_t *r_off = run_off.as<uint32_t>();
@@ -694,17 +678,16 @@ uint64_t build_workunits(sj_index &ix, int sym, const uint32_t *qlist, uint64_t 
     const USearch us = usearch_of(E);
     rcount.alloc((nqb + 1) * 4);
     rlen.alloc(nqb * 8);
-    SJ_HIP(hipMemsetAsync(rcount.p, 0, (nqb + 1) * 4, s));
     launch_qb_ranges(0, sym, nqb, nc, tq, ix.cell_start.as<uint32_t>(), qb_off.as<uint32_t>(),
                      ix.nbr_off.as<uint32_t>(), ix.nbr_cell.as<uint32_t>(),
                      E.cell_start.as<uint32_t>(), E.skey.as<uint64_t>(), ix.X.as<float>(), us,
                      rcount.as<uint32_t>(), rlen.as<uint64_t>(), nullptr, nullptr, s);
     scan.alloc(scan_tmp_bytes(nqb + 1) + 64);
-    exclusive_scan_u32(rcount.as<uint32_t>(), rcount.as<uint32_t>(), nqb + 1, tot.as<uint32_t>(),
-                       scan.p, s);
-    uint32_t h_nr = 0;
-    SJ_HIP(hipMemcpyAsync(&h_nr, tot.p, 4, hipMemcpyDeviceToHost, s));
+    exclusive_scan_u32(rcount.as<uint32_t>(), rcount.as<uint32_t>(), nqb,
+                       rcount.as<uint32_t>() + nqb, scan.p, s,
+                       ix.word_as<uint32_t>(kWordRanges));
     SJ_HIP(hipStreamSynchronize(s));
+    const uint32_t h_nr = *ix.word_as<uint32_t>(kWordRanges);
     u_ranges->alloc(std::max<uint64_t>(h_nr, 1) * sizeof(uint2));
     launch_qb_ranges(1, sym, nqb, nc, tq, ix.cell_start.as<uint32_t>(), qb_off.as<uint32_t>(),
                      ix.nbr_off.as<uint32_t>(), ix.nbr_cell.as<uint32_t>(),
@@ -723,21 +706,18 @@ uint64_t build_workunits(sj_index &ix, int sym, const uint32_t *qlist, uint64_t 
   blocks.alloc(nqb * sizeof(QBlock));
   units.alloc((nqb + 1) * 4);
   ev.alloc((nqb + 1) * 8);
-  SJ_HIP(hipMemsetAsync(units.p, 0, (nqb + 1) * 4, s));
-  SJ_HIP(hipMemsetAsync(ev.p, 0, (nqb + 1) * 8, s));
-  launch_wu_count(nqb, sym, nc, tq, tc, cstart, qlist, nq,
+  launch_wu_count(nqb, sym, nc, tq, std::max(tc, 1u), cstart, qlist, nq,
                   qb_off.as<uint32_t>(), r_off, r_runs, r_total, units.as<uint32_t>(),
                   ev.as<uint64_t>(), blocks.as<QBlock>(), s, per_block);
   scan.alloc(scan_tmp_bytes(nqb + 1) + 64);
-  exclusive_scan_u32(units.as<uint32_t>(), units.as<uint32_t>(), nqb + 1, tot.as<uint32_t>(),
-                     scan.p, s);
-  exclusive_scan_u64(ev.as<uint64_t>(), ev.as<uint64_t>(), nqb + 1, tot.as<uint64_t>() + 1,
-                     scan.p, s);
-  uint64_t h[2] = {0, 0};
-  SJ_HIP(hipMemcpyAsync(h, tot.p, 16, hipMemcpyDeviceToHost, s));
+  if (tc)
+    exclusive_scan_u32(units.as<uint32_t>(), units.as<uint32_t>(), nqb,
+                       ix.word_as<uint32_t>(kWordUnits), scan.p, s);
+  exclusive_scan_u64(ev.as<uint64_t>(), ev.as<uint64_t>(), nqb, ix.word(kWordEval), scan.p, s);
   SJ_HIP(hipStreamSynchronize(s));
-  const uint64_t n_wu = (uint32_t)h[0];
-  *eval = h[1];
+  *eval = *ix.word(kWordEval);
+  if (!tc) return 0;
+  const uint64_t n_wu = *ix.word_as<uint32_t>(kWordUnits);
   out.ensure(n_wu * sizeof(WorkUnit));  // kept when it fits: no wait for the device
   if (by_stretch && n_wu > 1) {
     TmpBuf unordered, keys[2], rtmp;
@@ -757,7 +737,8 @@ uint64_t build_workunits(sj_index &ix, int sym, const uint32_t *qlist, uint64_t 
     launch_wu_fill(n_wu, nqb, tc, blocks.as<QBlock>(), r_runs, before.as<uint32_t>(),
                    units.as<uint32_t>(), out.as<WorkUnit>(), nullptr, s);
   }
-  SJ_HIP(hipStreamSynchronize(s));
+  // an outer scope keeps the temporaries until its own synchronisation
+  if (thread_scratch().depth == 1) SJ_HIP(hipStreamSynchronize(s));
   return n_wu;
 }
 
@@ -950,9 +931,9 @@ void choose_fp32_form(sj_index &ix, hipStream_t s) {
   SJ_HIP(hipMemsetAsync(nsum.p, 0, 8, s));
   launch_norm_tables(ix.X.as<float>(), ix.n, ix.dp, s_hi, s_lo, kappa, ix.norm_qa.as<float>(),
                      ix.norm_cr.as<float>(), nsum.as<double>(), s);
-  double h = 0.0;
-  SJ_HIP(hipMemcpyAsync(&h, nsum.p, 8, hipMemcpyDeviceToHost, s));
+  launch_words_out(nsum.as<uint64_t>(), 1, ix.word(kWordNorm), s);
   SJ_HIP(hipStreamSynchronize(s));
+  const double h = *ix.word_as<double>(kWordNorm);
   const bool narrow = norm_band_narrow(ix, np, h / (double)ix.n);
   if (ix.opt.fp32_form == SJ_FP32_NORM || narrow) {
     ix.norm_form = true;
@@ -975,6 +956,13 @@ void fill_defaults(sj_options *o) {
   o->precision = SJ_PREC_FP32;
 }
 
+// An index of a small set is a chain of short launches, and the host's answers
+// between them: each read-back costs the host a wait of 10 to 15 us, an ordinary
+// copy twice that.  So sizes come back in pinned words that the scans write
+// themselves, lists end with the scan's total instead of being cleared first, and
+// what only the sample's or the other filter's launches would read is not built
+// (1000 x 8: 133 launches and 1.18 ms a pass, now 72 and 0.80 ms; 256 jobs 206 to
+// 186 ms).
 void build(sj_index &ix, const float *points, hipStream_t s) {
   ScratchScope scope;  // temporaries live until the final event synchronisation
   Event ev0, ev1;
@@ -987,6 +975,7 @@ void build(sj_index &ix, const float *points, hipStream_t s) {
   ix.dmin.assign(d, 0.0);
   ix.dmax.assign(d, 0.0);
   ix.counters.alloc(64);
+  ix.words.alloc(kWordStats * 8 + d * 32 + 256);
   compute_thresholds(ix);
   if (n == 0) {
     std::iota(ix.perm.begin(), ix.perm.end(), 0u);
@@ -1016,15 +1005,14 @@ void build(sj_index &ix, const float *points, hipStream_t s) {
   const uint64_t stride = n <= 10000 ? 1 : 100;
   const uint64_t m = (n + stride - 1) / stride;
   launch_variance(P, d, stride, m, var, s);
-  std::vector<uint32_t> hmin(d), hmax(d);
-  uint32_t hbad = 0;
-  std::vector<double> hvar(2 * (size_t)d);  // variances, then means
-  SJ_HIP(hipMemcpyAsync(hmin.data(), gmin, d * 4, hipMemcpyDeviceToHost, s));
-  SJ_HIP(hipMemcpyAsync(hmax.data(), gmax, d * 4, hipMemcpyDeviceToHost, s));
-  SJ_HIP(hipMemcpyAsync(&hbad, bad, 4, hipMemcpyDeviceToHost, s));
-  SJ_HIP(hipMemcpyAsync(hvar.data(), var, d * 16, hipMemcpyDeviceToHost, s));
+  const char *hs = reinterpret_cast<const char *>(ix.word(kWordStats));
+  SJ_HIP(hipMemcpyAsync(ix.word(kWordStats), stats.p, d * 32 + 256, hipMemcpyDeviceToHost, s));
   SJ_HIP(hipStreamSynchronize(s));
-  if (hbad) fail(SJ_ERR_INVALID_ARG, "points contain NaN or Inf coordinates");
+  const uint32_t *hmin = reinterpret_cast<const uint32_t *>(hs), *hmax = hmin + d;
+  const double *var_at = reinterpret_cast<const double *>(
+      hs + (reinterpret_cast<const char *>(var) - stats.as<char>()));
+  const std::vector<double> hvar(var_at, var_at + 2 * (size_t)d);  // variances, then means
+  if (hmax[d]) fail(SJ_ERR_INVALID_ARG, "points contain NaN or Inf coordinates");
   ix.dmean.assign(hvar.begin() + d, hvar.end());
   for (uint32_t t = 0; t < d; ++t) ix.mean_norm2 += hvar[t] + hvar[d + t] * hvar[d + t];
   for (uint32_t t = 0; t < d; ++t) {
@@ -1145,12 +1133,14 @@ void build(sj_index &ix, const float *points, hipStream_t s) {
     // symmetric pair count is (C + n) / 2 up to the tiles' rounding
     ev = (ix.candidates + n) / 2;
   } else {
-    build_workunits(ix, 1, nullptr, 0, ix.run_off_sym, ix.runs_sym, ix.tq, 16384, probe, &ev, s,
+    build_workunits(ix, 1, nullptr, 0, ix.run_off_sym, ix.runs_sym, ix.tq, 0, probe, &ev, s,
                     false, su ? &probe_r : nullptr);
+    ix.evaluated_sym = ev;
     ix.tc = mx32_tc(ix, ev);
+  }
+  if (!ix.batch_job && ix.opt.precision == SJ_PREC_FP32) {
     // FP32 units of small cells from groups of neighbouring cells
-    ix.wu_grouped = kFp32CellGroups && ix.small_cells && !su &&
-                    ix.opt.precision == SJ_PREC_FP32;
+    ix.wu_grouped = kFp32CellGroups && ix.small_cells && !su;
     if (ix.wu_grouped) build_cell_groups(ix, ix.tq, ix.groups, s);
     const CellGroups *grp = ix.wu_grouped ? &ix.groups : nullptr;
     ix.n_wu = build_workunits(ix, 1, nullptr, 0, grp ? grp->run_off : ix.run_off_sym,
@@ -1217,6 +1207,7 @@ void build_query(sj_index &q, const sj_index &E, const float *queries, hipStream
   q.info.fp32_form = E.mx32 ? SJ_FP32_DIFFERENCE : E.info.fp32_form;
   q.tq = E.tq;
   q.counters.alloc(64);
+  q.words.alloc(kWordStats * 8);
   q.perm_d.alloc(d * 4);
   q.inv_perm_d.alloc(d * 2);
   SJ_HIP(hipMemcpyAsync(q.perm_d.p, q.perm.data(), d * 4, hipMemcpyHostToDevice, s));
@@ -1304,20 +1295,17 @@ void build_query(sj_index &q, const sj_index &E, const float *queries, hipStream
   q.pos_of.alloc(m * 4);
   launch_gather(P, m, d, q.dp, q.perm_d.as<uint32_t>(), vb[0], q.X.as<float>(),
                 q.orig_id.as<uint32_t>(), q.pos_of.as<uint32_t>(), s);
-  unsigned long long h_far = 0;
-  SJ_HIP(hipMemcpyAsync(&h_far, d_far, 8, hipMemcpyDeviceToHost, s));
+  launch_words_out(reinterpret_cast<uint64_t *>(d_far), 1, q.word(kWordFar), s);
   SJ_HIP(hipStreamSynchronize(s));
-  q.n_near = m - h_far;  // far queries sort last: positions [n_near, m)
+  q.n_near = m - *q.word(kWordFar);  // far queries sort last: positions [n_near, m)
   q.cell_key.alloc((q.n_near + 1) * 8);
   q.cell_start.alloc((q.n_near + 1) * 4);
   if (q.n_near) {
-    uint32_t *d_ncell = t.small.as<uint32_t>();
-    launch_compact(kb[0], q.n_near, g.fine_bits, t.flag.as<uint32_t>(), d_ncell,
-                   q.cell_key.as<uint64_t>(), q.cell_start.as<uint32_t>(), t.scan.p, s);
-    uint32_t h_ncell = 0;
-    SJ_HIP(hipMemcpyAsync(&h_ncell, d_ncell, 4, hipMemcpyDeviceToHost, s));
+    launch_compact(kb[0], q.n_near, g.fine_bits, t.flag.as<uint32_t>(),
+                   q.word_as<uint32_t>(kWordCells), q.cell_key.as<uint64_t>(),
+                   q.cell_start.as<uint32_t>(), t.scan.p, s);
     SJ_HIP(hipStreamSynchronize(s));
-    q.ncell = h_ncell;
+    q.ncell = *q.word_as<uint32_t>(kWordCells);
   }
   if (q.ncell == 0) return finish();
   q.candidates = build_neighbors(q, E, g.np, t, s, true);
@@ -1350,8 +1338,8 @@ void build_query(sj_index &q, const sj_index &E, const float *queries, hipStream
   uint64_t ev = 0;
   DevBuf probe, probe_r;
   const bool su = q.opt.sortidu != 0;  // units from per-block SORTIDU ranges
-  build_workunits(q, 0, nullptr, 0, q.run_off_full, q.runs_full, q.tq, 16384, probe, &ev, s,
-                  false, su ? &probe_r : nullptr);
+  build_workunits(q, 0, nullptr, 0, q.run_off_full, q.runs_full, q.tq, 0, probe, &ev, s, false,
+                  su ? &probe_r : nullptr);
   q.tc = mx32_tc(q, ev);
   if (q.prec == SJ_PREC_FP32) {
     q.n_wu = build_workunits(q, 0, nullptr, 0, q.run_off_full, q.runs_full, q.tq, q.tc, q.wu,
@@ -1423,7 +1411,6 @@ MfmaView mfma_view(const sj_index &ix, const uint2 *runs, const uint32_t *qlist,
 bool debug_undersize();
 int debug_hits_mode();
 int debug_box_mode();
-uint64_t read_counter(sj_index &ix, int which, hipStream_t s);
 constexpr uint64_t kBandStart = 1u << 20;       // least band-list slots of a join
 constexpr uint64_t kCountBandStart = 1u << 16;  // and of a sampled count
 // result + band pairs per 32 x 32 tile above which the matrix-core kernels
@@ -1434,6 +1421,15 @@ constexpr double kFrequentHits = 1.5;
 constexpr uint32_t kBoxMaxDims = 24;  // dimensions up to which workgroup units use the box
 constexpr double kBoxMaxHitsPerTile = 0.1;  // and hits per 32 x 32 tile below which
 
+// The four counters into the handle's words, and one of them.
+void read_counters(sj_index &ix, hipStream_t s) {
+  launch_words_out(ix.counters.as<uint64_t>(), 4, ix.word(kWordCounters), s);
+  SJ_HIP(hipStreamSynchronize(s));
+}
+uint64_t counter(const sj_index &ix, int which) { return *ix.word(kWordCounters + which); }
+
+// One launch of the join or of its count-only form; the counters start at zero
+// and are in the handle's words (counter) when it returns.
 void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &runs,
                  const uint32_t *qlist, int sym, int count_only, uint64_t *out, uint64_t cap,
                  hipStream_t s, float *ms, uint32_t skip_below = 0) {
@@ -1535,14 +1531,8 @@ void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &ru
         ix.band_cap = want;
         ix.band.alloc(ix.band_cap * 8);
       }
-      // result, recheck and skip counts before this launch (a rerun starts
-      // from them)
-      uint64_t base[4] = {0, 0, 0, 0};
-      SJ_HIP(hipMemcpyAsync(base, ix.counters.p, 32, hipMemcpyDeviceToHost, s));
-      SJ_HIP(hipStreamSynchronize(s));
-      base[2] = 0;  // the band cursor
       for (int attempt = 0;; ++attempt) {
-        SJ_HIP(hipMemsetAsync(band_cursor, 0, 8, s));
+        launch_fill_u64(a.cursor, 4, 0ull, s);
         view.band = ix.band.as<uint64_t>();
         view.band_cap = ix.band_cap;
         view.band_cursor = band_cursor;
@@ -1550,30 +1540,23 @@ void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &ru
         else launch_join_mx32(x, s);
         if (!count_only) ix.info.join_launches++;
         launch_band_recheck(view, keys, slots, a.cursor, a.rechecks, s);
-        const uint64_t nb = read_counter(ix, 2, s);
+        SJ_HIP(hipEventRecord(e1.e, s));
+        read_counters(ix, s);
+        const uint64_t nb = counter(ix, 2);
         if (nb <= ix.band_cap) break;
         if (attempt == 2) fail(SJ_ERR_DEVICE, "band list size did not settle");
         ix.band_cap = nb + nb / 8;
-        ix.band.alloc(ix.band_cap * 8);
-        // the launch starts over
-        SJ_HIP(hipMemcpyAsync(ix.counters.p, base, 32, hipMemcpyHostToDevice, s));
-        SJ_HIP(hipStreamSynchronize(s));
+        ix.band.alloc(ix.band_cap * 8);  // the launch starts over
       }
     }
   } else {
+    launch_fill_u64(a.cursor, 4, 0ull, s);
     launch_join_fp32(a, s);
     if (!count_only) ix.info.join_launches++;
+    SJ_HIP(hipEventRecord(e1.e, s));
+    read_counters(ix, s);
   }
-  SJ_HIP(hipEventRecord(e1.e, s));
-  SJ_HIP(hipEventSynchronize(e1.e));
   *ms += elapsed_ms(e0, e1);
-}
-
-uint64_t read_counter(sj_index &ix, int which, hipStream_t s) {
-  uint64_t v = 0;
-  SJ_HIP(hipMemcpyAsync(&v, ix.counters.as<uint64_t>() + which, 8, hipMemcpyDeviceToHost, s));
-  SJ_HIP(hipStreamSynchronize(s));
-  return v;
 }
 
 // Estimate |R| from a strided sample of query positions (Section 3.2.2:
@@ -1614,18 +1597,17 @@ uint64_t estimate_pairs(sj_index &ix, hipStream_t s, float *ms) {
                                        : mx ? std::min<uint32_t>(ix.tc, 4096)
                                             : 4096,
                                        wu, &ev, s);
-  SJ_HIP(hipMemsetAsync(ix.counters.p, 0, 16, s));
   // the sample's band list: at most one pair in 512 is expected in the band
   // of the 16-bit filters, and fewer in the FP32 filter's, whose list holds
   // every pair it cannot reject where it accepts none (a larger band reruns
   // the count with the list at its exact size)
   if (mf || mx) ix.band_hint = ev / (mf ? 512 : 1024);
   join_launch(ix, wu, nwu, ix.runs_full, ql.as<uint32_t>(), 0, 1, nullptr, 0, s, ms);
-  const uint64_t cnt = read_counter(ix, 0, s);
+  const uint64_t cnt = counter(ix, 0);
   const double scale = (double)n / (double)nq;
   if (mf || mx) {
     // band pairs of the sample size the deferred recheck list of the join
-    const double nband = (double)read_counter(ix, 1, s);
+    const double nband = (double)counter(ix, 1);
     ix.band_hint = (uint64_t)std::ceil(nband * scale * 1.25) + (1u << 16);
     ix.hit_density = ev ? ((double)cnt + nband) / (double)ev : 0.0;
   }
@@ -1665,7 +1647,6 @@ void run_single(sj_index &ix, uint64_t est, hipStream_t s) {
   DevBuf other;
   for (int attempt = 0; attempt < 3; ++attempt) {
     ix.pairs.alloc(cap * 8);
-    SJ_HIP(hipMemsetAsync(ix.counters.p, 0, 16, s));
     const bool m = ix.prec != SJ_PREC_FP32;
     const bool self = !ix.entries;  // a self-join's units are symmetric
     const bool grouped = !m && ix.wu_grouped;
@@ -1674,7 +1655,7 @@ void run_single(sj_index &ix, uint64_t est, hipStream_t s) {
                                         : (self ? ix.runs_sym : ix.runs_full);
     join_launch(ix, m ? ix.wu_m : ix.wu, m ? ix.n_wu_m : ix.n_wu, runs, nullptr, self ? 1 : 0, 0,
                 ix.pairs.as<uint64_t>(), cap, s, &ms_join);
-    const uint64_t got = read_counter(ix, 0, s);
+    const uint64_t got = counter(ix, 0);
     if (got <= cap) {
       ix.total = got;
       break;
@@ -1682,7 +1663,7 @@ void run_single(sj_index &ix, uint64_t est, hipStream_t s) {
     cap = got;  // exact now
     if (attempt == 2) fail(SJ_ERR_DEVICE, "result count did not settle");
   }
-  ix.info.rechecks = read_counter(ix, 1, s);
+  ix.info.rechecks = counter(ix, 1);
   ix.info.ms_join += ms_join;
   Event e0, e1;
   SJ_HIP(hipEventRecord(e0.e, s));
@@ -1810,16 +1791,12 @@ void run_batched(sj_index &ix, uint64_t est, uint64_t per_batch, bool sym, hipSt
     uint64_t got = 0;
     for (int attempt = 0; attempt < 3; ++attempt) {
       sl.keys.ensure(cap * 8);
-      SJ_HIP(hipMemsetAsync(ix.counters.p, 0, 32, s));
       join_launch(ix, wu, nwu, ix.runs_full, p32.as<uint32_t>(), 0, 0, sl.keys.as<uint64_t>(),
                   cap, s, &ms_join, sym ? (uint32_t)i0 : 0u);
-      uint64_t c4[4];
-      SJ_HIP(hipMemcpyAsync(c4, ix.counters.p, 32, hipMemcpyDeviceToHost, s));
-      SJ_HIP(hipStreamSynchronize(s));
-      got = c4[0];
+      got = counter(ix, 0);
       if (got <= cap) {
-        ix.info.rechecks += c4[1];
-        skipped += c4[3];
+        ix.info.rechecks += counter(ix, 1);
+        skipped += counter(ix, 3);
         break;
       }
       if (attempt == 2) fail(SJ_ERR_DEVICE, "batch result count did not settle");

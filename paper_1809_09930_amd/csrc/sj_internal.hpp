@@ -123,13 +123,19 @@ static_assert(sizeof(WorkUnit) == 32, "WorkUnit layout");
 // ---------------------------------------------------------------------------
 // Primitives (sj_prims.hip)
 // ---------------------------------------------------------------------------
-// Exclusive prefix sum of n values in place-or-out; returns the total through
-// *d_total (device) when non-null.  `tmp` is scratch from scan_tmp_bytes().
+// Exclusive prefix sum of n values in place-or-out; writes the total to
+// *d_total and *total2 where non-null (device memory, or pinned host memory,
+// which is read after the stream is synchronised).  `tmp` is scratch from
+// scan_tmp_bytes().
 size_t scan_tmp_bytes(uint64_t n);
 void exclusive_scan_u32(const uint32_t *in, uint32_t *out, uint64_t n,
-                        uint32_t *d_total, void *tmp, hipStream_t s);
+                        uint32_t *d_total, void *tmp, hipStream_t s,
+                        uint32_t *total2 = nullptr);
 void exclusive_scan_u64(const uint64_t *in, uint64_t *out, uint64_t n,
-                        uint64_t *d_total, void *tmp, hipStream_t s);
+                        uint64_t *d_total, void *tmp, hipStream_t s,
+                        uint64_t *total2 = nullptr);
+// n <= 64 device words into pinned host memory (read after synchronising).
+void launch_words_out(const uint64_t *in, uint32_t n, uint64_t *out, hipStream_t s);
 
 // Stable LSD radix sort of 64-bit keys (optionally with 32-bit values) over
 // the bit ranges listed in `shifts`: digits of widths[p] bits (1..8; 8 when

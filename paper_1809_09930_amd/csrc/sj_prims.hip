@@ -61,11 +61,11 @@ __global__ __launch_bounds__(kBlock) void k_scan_reduce(const T *__restrict__ in
 
 // Exclusive scan of a 2048-value tile per workgroup, plus the workgroup's
 // offset (offsets[blockIdx.x], or 0).  The last workgroup writes the grand
-// total when `total` is non-null.  in == out is allowed.
+// total to `total` and `total2` where they are non-null.  in == out is allowed.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_scan_tile(const T *in, T *out, uint64_t n,
                                                       const T *__restrict__ offsets,
-                                                      T *__restrict__ total) {
+                                                      T *total, T *total2) {
   __shared__ T tile[kScanTile];
   const uint64_t base = (uint64_t)blockIdx.x * kScanTile;
 #pragma unroll
@@ -93,7 +93,10 @@ __global__ __launch_bounds__(kBlock) void k_scan_tile(const T *in, T *out, uint6
     uint64_t idx = base + (uint64_t)i * kBlock + threadIdx.x;
     if (idx < n) out[idx] = tile[i * kBlock + threadIdx.x];
   }
-  if (total && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = off + btotal;
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+    if (total) *total = off + btotal;
+    if (total2) *total2 = off + btotal;
+  }
 }
 
 // The same over up to kScanOneMax values by one workgroup, tile after tile, the
@@ -105,7 +108,7 @@ constexpr uint64_t kScanOneMax = 4 * kScanOneTile;
 
 template <typename T>
 __global__ __launch_bounds__(kScanOneBlock) void k_scan_one(const T *in, T *out, uint32_t n,
-                                                            T *total) {
+                                                            T *total, T *total2) {
   __shared__ T tile[kScanOneTile];
   T x[kScanItems];
   auto load = [&](uint32_t base) {
@@ -143,7 +146,10 @@ __global__ __launch_bounds__(kScanOneBlock) void k_scan_one(const T *in, T *out,
     __syncthreads();
     carry += sum;
   }
-  if (total && threadIdx.x == 0) *total = carry;
+  if (threadIdx.x == 0) {
+    if (total) *total = carry;
+    if (total2) *total2 = carry;
+  }
 }
 
 template <typename T>
@@ -158,17 +164,17 @@ size_t scan_levels_bytes(uint64_t n) {
 }
 
 template <typename T>
-void scan_impl(const T *in, T *out, uint64_t n, T *d_total, char *tmp, hipStream_t s) {
-  if (n == 0 && !d_total) return;
+void scan_impl(const T *in, T *out, uint64_t n, T *d_total, T *total2, char *tmp, hipStream_t s) {
+  if (n == 0 && !d_total && !total2) return;
   if (n <= (uint64_t)kScanTile) {  // (of nothing: a total of 0)
     hipLaunchKernelGGL(k_scan_tile<T>, dim3(1), dim3(kBlock), 0, s, in, out, n,
-                       (const T *)nullptr, d_total);
+                       (const T *)nullptr, d_total, total2);
     SJ_HIP(hipGetLastError());
     return;
   }
   if (n <= kScanOneMax) {
     hipLaunchKernelGGL(k_scan_one<T>, dim3(1), dim3(kScanOneBlock), 0, s, in, out, (uint32_t)n,
-                       d_total);
+                       d_total, total2);
     SJ_HIP(hipGetLastError());
     return;
   }
@@ -177,9 +183,9 @@ void scan_impl(const T *in, T *out, uint64_t n, T *d_total, char *tmp, hipStream
   char *rest = tmp + ((nb * sizeof(T) + 255) / 256) * 256;
   hipLaunchKernelGGL(k_scan_reduce<T>, dim3((uint32_t)nb), dim3(kBlock), 0, s, in, n, sums);
   SJ_HIP(hipGetLastError());
-  scan_impl<T>(sums, sums, nb, (T *)nullptr, rest, s);
+  scan_impl<T>(sums, sums, nb, (T *)nullptr, (T *)nullptr, rest, s);
   hipLaunchKernelGGL(k_scan_tile<T>, dim3((uint32_t)nb), dim3(kBlock), 0, s, in, out, n,
-                     (const T *)sums, d_total);
+                     (const T *)sums, d_total, total2);
   SJ_HIP(hipGetLastError());
 }
 
@@ -346,8 +352,9 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(
 }
 
 // All passes over at most kSmallSort keys in one launch of one workgroup, the
-// keys in LDS between passes (a pass of the general form is three launches,
-// 13 us with the gaps between them at these sizes; this takes 10 us for four).
+// keys in LDS between passes: 17 us for four passes over 1000 keys with ids, 5 us
+// for one over keys alone, where the general form's three launches a pass took 55
+// and 14 us of kernels, and the gaps between them.
 constexpr int kSmallBlock = 1024;
 constexpr int kSmallWaves = kSmallBlock / kWave;
 constexpr int kSmallRounds = 4;
@@ -474,6 +481,11 @@ __global__ void k_widen(const uint32_t *__restrict__ in, uint64_t *__restrict__ 
 __global__ void k_narrow(const uint64_t *__restrict__ in, uint32_t *__restrict__ out, uint64_t count) {
   const uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i < count) out[i] = (uint32_t)in[i];
+}
+
+// Device words into (device-visible) host memory.
+__global__ void k_words_out(const uint64_t *__restrict__ in, uint32_t n, uint64_t *out) {
+  if (threadIdx.x < n) out[threadIdx.x] = in[threadIdx.x];
 }
 
 // Stream split of result keys: every entry gives up to two keys for `out`
@@ -603,6 +615,12 @@ void launch_spill_take(const uint64_t *spill_in, uint64_t n, uint32_t i1, uint64
   SJ_HIP(hipGetLastError());
 }
 
+void launch_words_out(const uint64_t *in, uint32_t n, uint64_t *out, hipStream_t s) {
+  if (n > (uint32_t)kWave) fail(SJ_ERR_INVALID_ARG, "too many words");
+  hipLaunchKernelGGL(k_words_out, dim3(1), dim3(kWave), 0, s, in, n, out);
+  SJ_HIP(hipGetLastError());
+}
+
 void launch_iota_strided(uint32_t *out, uint64_t count, uint64_t stride, uint32_t run,
                          hipStream_t s) {
   if (!count) return;
@@ -627,13 +645,13 @@ void launch_narrow(const uint64_t *in, uint32_t *out, uint64_t count, hipStream_
 size_t scan_tmp_bytes(uint64_t n) { return scan_levels_bytes<uint64_t>(n); }
 
 void exclusive_scan_u32(const uint32_t *in, uint32_t *out, uint64_t n, uint32_t *d_total,
-                        void *tmp, hipStream_t s) {
-  scan_impl<uint32_t>(in, out, n, d_total, static_cast<char *>(tmp), s);
+                        void *tmp, hipStream_t s, uint32_t *total2) {
+  scan_impl<uint32_t>(in, out, n, d_total, total2, static_cast<char *>(tmp), s);
 }
 
 void exclusive_scan_u64(const uint64_t *in, uint64_t *out, uint64_t n, uint64_t *d_total,
-                        void *tmp, hipStream_t s) {
-  scan_impl<uint64_t>(in, out, n, d_total, static_cast<char *>(tmp), s);
+                        void *tmp, hipStream_t s, uint64_t *total2) {
+  scan_impl<uint64_t>(in, out, n, d_total, total2, static_cast<char *>(tmp), s);
 }
 
 size_t radix_tmp_bytes(uint64_t n) {

@@ -243,11 +243,30 @@ struct CellGroups {
 };
 }  // namespace sj
 
+namespace sj {
+// Words of a handle (sj_index::word).
+enum Word {
+  kWordCells, kWordCand, kWordNbr, kWordRuns, kWordBlocks, kWordRanges, kWordUnits, kWordEval,
+  kWordSlots, kWordGroups, kWordFar, kWordNorm,
+  kWordCounters = 16,  // the counters after a launch
+  kWordStats = 32      // minima, maxima, flag, variances and means of an index build
+};
+}  // namespace sj
+
 // The opaque handle of the C ABI.
 struct sj_index {
   typedef sj::DevBuf DevBuf;
   typedef sj::PinnedBuf PinnedBuf;
   int device = 0;
+  // Pinned words that kernels write for the host, so that a read-back is a
+  // synchronisation and no copy.  Declared ahead of the device buffers: they are
+  // freed first, and wait for the device, before the words are given back.
+  PinnedBuf words;
+  uint64_t *word(int i) const { return static_cast<uint64_t *>(words.p) + i; }
+  template <typename T>
+  T *word_as(int i) const {
+    return reinterpret_cast<T *>(word(i));
+  }
   uint64_t n = 0;
   uint32_t d = 0, dp = 0, k = 0;
   double eps = 0.0, eps2 = 0.0;
@@ -286,7 +305,7 @@ struct sj_index {
   DevBuf uruns, uruns_m;  // SORTIDU: per-query-block candidate ranges of wu / wu_m
   uint32_t tq = 256, tc = 16384;
   uint64_t candidates = 0, evaluated_sym = 0;
-  DevBuf counters;  // [0] cursor, [1] rechecks
+  DevBuf counters;  // [0] cursor, [1] rechecks, [2] band cursor, [3] skipped
 
   // matrix-core path
   uint32_t prec = SJ_PREC_FP32;  // precision actually used
