@@ -742,12 +742,17 @@ uint64_t build_workunits(sj_index &ix, int sym, const uint32_t *qlist, uint64_t 
   return n_wu;
 }
 
-// Candidate block length so a launch has enough work units to fill the chip.
-uint32_t choose_tc(uint64_t eval_pairs, uint32_t tq) {
+// Candidate block length so a launch has enough work units to fill the chip, at
+// least `least`: a vector unit needs little before its first candidate (64; the
+// 1000 x 8 join 78 us with units of 256 and its sampled count 147 with units of
+// 4096, together 45 us now), a matrix-core one loads its queries' operands and the
+// first rows (256 per wave).
+constexpr uint32_t kLeastVector = 64, kLeastTiles = 256;
+uint32_t choose_tc(uint64_t eval_pairs, uint32_t tq, uint32_t least = kLeastTiles) {
   const double target_units = 256.0 * 32.0;  // CUs x waves in flight, roughly
   double tc = (double)eval_pairs / ((double)tq * target_units);
-  tc = std::max(256.0, std::min(16384.0, tc));
-  uint32_t t = 256;
+  tc = std::max((double)least, std::min(16384.0, tc));
+  uint32_t t = least;
   while (t < tc) t <<= 1;
   return t;
 }
@@ -755,7 +760,7 @@ uint32_t choose_tc(uint64_t eval_pairs, uint32_t tq) {
 // The same for an FP32 handle: a matrix-core unit that is a whole workgroup has
 // stretches four times as long for the same number of waves.
 uint32_t mx32_tc(const sj_index &ix, uint64_t eval_pairs) {
-  const uint32_t tc = choose_tc(eval_pairs, ix.tq);
+  const uint32_t tc = choose_tc(eval_pairs, ix.tq, ix.mx32 ? kLeastTiles : kLeastVector);
   return ix.mx32 && !mx32_per_wave(ix.dp) ? std::max<uint32_t>(1024, 4 * tc) : tc;
 }
 
@@ -1589,14 +1594,16 @@ uint64_t estimate_pairs(sj_index &ix, hipStream_t s, float *ms) {
   // the matrix-core path counts with its own filter and its band list (no
   // keys are stored at capacity 0); the FP32 path has a count-only kernel
   const bool mf = ix.prec != SJ_PREC_FP32, mx = ix.mx32;
-  // candidate chunks of at most 4096: the sample's few units are split
-  // finely enough to spread over the chip
+  // candidate chunks of at most 4096, and short enough for the sample's units to
+  // fill the chip (by the sample's share of the candidates)
+  const uint64_t share = (uint64_t)((double)ix.candidates * ((double)nq / (double)n));
+  const uint32_t tq = mf ? ix.tq_single : ix.tq;
+  const bool wg = mf ? !ix.mfma_per_wave : mx && !mx32_per_wave(ix.dp);  // workgroup units
+  uint32_t tc = wg ? std::max<uint32_t>(1024, 4 * choose_tc(share, tq))
+                   : choose_tc(share, tq, mf || mx ? kLeastTiles : kLeastVector);
+  tc = std::min<uint32_t>(tc, 4096);
   const uint64_t nwu = build_workunits(ix, 0, ql.as<uint32_t>(), nq, ix.run_off_full,
-                                       ix.runs_full, mf ? ix.tq_single : ix.tq,
-                                       mf   ? std::min<uint32_t>(ix.tc_single, 4096)
-                                       : mx ? std::min<uint32_t>(ix.tc, 4096)
-                                            : 4096,
-                                       wu, &ev, s);
+                                       ix.runs_full, tq, tc, wu, &ev, s);
   // the sample's band list: at most one pair in 512 is expected in the band
   // of the 16-bit filters, and fewer in the FP32 filter's, whose list holds
   // every pair it cannot reject where it accepts none (a larger band reruns

@@ -832,7 +832,11 @@ void launch_minmax(const float *P, uint64_t n, uint32_t d, uint32_t *gmin, uint3
   SJ_HIP(hipGetLastError());
   const uint64_t total = n * d;
   if (total == 0) return;
-  uint32_t grid = (uint32_t)std::min<uint64_t>((total + kBlock - 1) / kBlock, 2048);
+  uint32_t grid = (uint32_t)std::min<uint64_t>((total + kBlock - 1) / kBlock, 1024);
+  // a stride of whole rows keeps a thread in one dimension (step == 0), its
+  // extremes in registers instead of two LDS atomics per coordinate
+  const uint32_t rows = d / std::gcd(d, (uint32_t)kBlock);
+  if (grid > rows) grid -= grid % rows;
   hipLaunchKernelGGL(k_minmax, dim3(grid), dim3(kBlock), 0, s, P, total, d, gmin, gmax, bad);
   SJ_HIP(hipGetLastError());
 }
