@@ -471,6 +471,11 @@ uint64_t build_grid(sj_index &ix, const float *P, const Geometry &g, BuildTmp &t
   if (keep) {
     launch_gather(P, n, ix.d, ix.dp, ix.perm_d.as<uint32_t>(), vb[0], ix.X.as<float>(),
                   ix.orig_id.as<uint32_t>(), ix.pos_of.as<uint32_t>(), s);
+    if (g.kp.pb) {
+      ix.pos_pivot.alloc(n);
+      launch_pivot_order(pid.as<uint8_t>(), n, ix.orig_id.as<uint32_t>(),
+                         ix.pos_pivot.as<uint8_t>(), s);
+    }
     if (ix.opt.sortidu) {  // the sorted keys: SORTIDU searches their u part
       ix.skey.alloc(n * 8);
       SJ_HIP(hipMemcpyAsync(ix.skey.p, kb[0], n * 8, hipMemcpyDeviceToDevice, s));
@@ -1300,6 +1305,11 @@ void build_query(sj_index &q, const sj_index &E, const float *queries, hipStream
   q.pos_of.alloc(m * 4);
   launch_gather(P, m, d, q.dp, q.perm_d.as<uint32_t>(), vb[0], q.X.as<float>(),
                 q.orig_id.as<uint32_t>(), q.pos_of.as<uint32_t>(), s);
+  if (g.kp.pb) {
+    q.pos_pivot.alloc(m);
+    launch_pivot_order(pid.as<uint8_t>(), m, q.orig_id.as<uint32_t>(), q.pos_pivot.as<uint8_t>(),
+                       s);
+  }
   launch_words_out(reinterpret_cast<uint64_t *>(d_far), 1, q.word(kWordFar), s);
   SJ_HIP(hipStreamSynchronize(s));
   q.n_near = m - *q.word(kWordFar);  // far queries sort last: positions [n_near, m)
@@ -1515,6 +1525,7 @@ void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &ru
       x.view.XS = E.mx_xs.p;
       x.view.nn = E.mx_nn.as<float>();
       x.view.pn = E.mx_pn.as<float>();
+      x.view.pid = ix.pos_pivot.as<uint8_t>();
       x.view.ctr = E.mx_ctr.as<float>();
       x.view.skip_below = skip_below;
       x.view.orig_id = a.orig_id;

@@ -195,6 +195,13 @@ __global__ __launch_bounds__(kBlock) void k_nearest_pivot(const float *__restric
   pid[i] = (uint8_t)best;
 }
 
+__global__ __launch_bounds__(kBlock) void k_pivot_order(const uint8_t *__restrict__ pid, uint64_t n,
+                                                        const uint32_t *__restrict__ orig_id,
+                                                        uint8_t *__restrict__ out) {
+  const uint64_t p = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (p < n) out[p] = pid[orig_id[p]];
+}
+
 // Keys of query points in the grid of an indexed set E (the general join
 // Q join_eps E of Section 3.1).  A query with some coordinate more than
 // two cell widths outside E's range [lo_t, hi_t] (lo = lo_t - 2w and
@@ -865,6 +872,13 @@ void launch_nearest_pivot(const float *P, uint64_t n, uint32_t d, const float *t
                           hipStream_t s) {
   if (!n) return;
   hipLaunchKernelGGL(k_nearest_pivot, dim3(blocks_for(n)), dim3(kBlock), 0, s, P, n, d, table, pid);
+  SJ_HIP(hipGetLastError());
+}
+
+void launch_pivot_order(const uint8_t *pid, uint64_t n, const uint32_t *orig_id, uint8_t *out,
+                        hipStream_t s) {
+  if (!n) return;
+  hipLaunchKernelGGL(k_pivot_order, dim3(blocks_for(n)), dim3(kBlock), 0, s, pid, n, orig_id, out);
   SJ_HIP(hipGetLastError());
 }
 

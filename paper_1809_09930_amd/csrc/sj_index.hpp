@@ -53,6 +53,9 @@ void launch_cellkey(const float *P, uint64_t n, uint32_t d, const KeyParams &kp,
 // the row nearest to each of n points among them.
 constexpr uint32_t kPivotBits = 6, kPivots = 1u << kPivotBits;
 void launch_pivot_table(const float *P, uint64_t stride, uint32_t d, float *table, hipStream_t s);
+// out[p] = pid[orig_id[p]]
+void launch_pivot_order(const uint8_t *pid, uint64_t n, const uint32_t *orig_id, uint8_t *out,
+                        hipStream_t s);
 void launch_nearest_pivot(const float *P, uint64_t n, uint32_t d, const float *table, uint8_t *pid,
                           hipStream_t s);
 // Sort keys of query points Q [m][d] in an indexed set's grid kp; queries

@@ -543,8 +543,10 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
 // ---------------------------------------------------------------------------
 // Above 24 padded dimensions: one workgroup per work unit of 256 queries.
 //
-// Group test.  The queries form 32 groups of eight consecutive ones; c_g is
-// the mean of a group's q~ rounded to FP16 and r_g the largest |q~ - c_g|.  A
+// Group test.  The queries form 32 groups of eight to some twenty consecutive
+// ones with the same nearest pivot (a group across two clusters would pass most
+// candidates for the whole unit: with eight each, 43 % of the tests of the 515k x
+// 90 mixture passed); c_g is the mean of a group's q~ rounded to FP16 and r_g the largest |q~ - c_g|.  A
 // pair within eps has |q~ - a~| <= R = sqrt(s_hi) (1 + 2^-18) + u (...), hence
 // |a1 - c_g| <= R + r_g + 2^-11 |a~|, and with 2xy <= x^2 + y^2
 //     |a1|^2 + |c_g|^2 - 2 c_g . a1 <= (R + r_g)^2 (1 + 2^-11)
@@ -569,6 +571,10 @@ struct Shape {
   static constexpr int CH = K <= 48 ? 64 : 32;
 };
 
+// group lengths tried (the last takes all queries of a pivot)
+constexpr int kGroupLens = 6;
+__device__ constexpr uint32_t kGroupLen[kGroupLens] = {8, 9, 11, 14, 20, 256};
+
 template <int K>
 __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
     Mx32View v, const WorkUnit *__restrict__ wus) {
@@ -592,6 +598,9 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
   __shared__ __align__(16) float ginit[32];  // -T_g
   __shared__ __align__(16) _Float16 gctr[32][K];
   __shared__ uint32_t wcnt[NW];
+  __shared__ uint64_t seg_mask[TQ / kWave];
+  __shared__ uint32_t len_cnt[kGroupLens][TQ / kWave];
+  __shared__ uint32_t gfirst[33];  // the groups' first queries, then nq
   const MfmaView &m = v.m;
   const WorkUnit wu = wus[blockIdx.x];
   const uint32_t tid = threadIdx.x;
@@ -623,40 +632,87 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
     }
   }
   __syncthreads();
-  // group g = 8 rows; NT / 32 threads per group, each over every NT/32-th dimension
+  // groups: runs of up to L queries of one pivot, L the least of kGroupLen for
+  // which 32 groups suffice (or eight each, where even 32 pivots do not)
+  {
+    const uint32_t idx = tid < (uint32_t)TQ ? tid : TQ - 1u;
+    const bool live = tid < nq;  // nq <= TQ <= NT
+    auto pivot = [&](uint32_t i) { return v.pid ? v.pid[qpos_s[i]] : (uint8_t)0; };
+    const bool cut = live && (idx == 0 || pivot(idx) != pivot(idx - 1));
+    const uint64_t cuts = ballot(cut);
+    if (l == 0 && w < TQ / kWave) seg_mask[w] = cuts;
+    __syncthreads();
+    uint32_t seg = 0;  // first query of this one's pivot
+    if (live) {
+      uint32_t i = idx / kWave;
+      uint64_t mask = seg_mask[i] & (~0ull >> (63 - idx % kWave));
+      while (!mask) mask = seg_mask[--i];  // (query 0 is a cut)
+      seg = i * kWave + 63u - (uint32_t)__builtin_clzll(mask);
+    }
+    uint32_t starts = 0;  // bit j: a group of length kGroupLen[j] starts here
+#pragma unroll
+    for (int j = 0; j < kGroupLens; ++j) {
+      const bool at = live && (idx - seg) % kGroupLen[j] == 0;
+      starts |= at ? 1u << j : 0u;
+      const uint64_t m64 = ballot(at);
+      if (l == 0 && w < TQ / kWave) len_cnt[j][w] = (uint32_t)__builtin_popcountll(m64);
+    }
+    __syncthreads();
+    int pick = -1;
+#pragma unroll
+    for (int j = kGroupLens - 1; j >= 0; --j) {
+      uint32_t total = 0;
+#pragma unroll
+      for (uint32_t i = 0; i < TQ / kWave; ++i) total += len_cnt[j][i];
+      if (total <= 32) pick = j;
+    }
+    const bool first = live && (pick < 0 ? idx % 8 == 0 : (starts >> pick & 1u) != 0);
+    const uint64_t fm = ballot(first);
+    if (l == 0 && w < TQ / kWave) wcnt[w] = (uint32_t)__builtin_popcountll(fm);
+    if (tid < 33) gfirst[tid] = nq;
+    __syncthreads();
+    if (first) {
+      uint32_t g = lanes_below(fm);
+      for (uint32_t i = 0; i < w; ++i) g += wcnt[i];
+      gfirst[g] = idx;
+    }
+    __syncthreads();
+  }
+  // NT / 32 threads per group: its centre, each over every NT/32-th dimension,
+  // then its radius, each over every NT/32-th query
   {
     constexpr uint32_t TG = NT / 32;
     const uint32_t g = tid / TG, i0 = tid % TG;
-    const uint32_t gn = g * 8 < nq ? (nq - g * 8 < 8u ? nq - g * 8 : 8u) : 0u;
-    double nc = 0.0, d2[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    const uint32_t a = gfirst[g], gn = gfirst[g + 1] - a;
+    double nc = 0.0;
     for (uint32_t t = i0; t < (uint32_t)K; t += TG) {
-      float y[8], s = 0.0f;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const bool on = (uint32_t)i < gn && t < dp;
-        const uint32_t p = on ? qpos_s[g * 8 + i] : 0u;
-        y[i] = on ? v.sc * (m.Xq[(uint64_t)p * dp + t] - v.ctr[t]) : 0.0f;
-        s += y[i];
-      }
-      const float cf = (float)(_Float16)(gn ? s / (float)gn : 0.0f);
+      float sum = 0.0f;
+      if (t < dp)
+        for (uint32_t i = 0; i < gn; ++i)
+          sum += v.sc * (m.Xq[(uint64_t)qpos_s[a + i] * dp + t] - v.ctr[t]);
+      const float cf = (float)(_Float16)(gn ? sum / (float)gn : 0.0f);
       gctr[g][t] = (_Float16)(-2.0f * cf);  // exact
       nc += (double)cf * (double)cf;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const double e = (double)y[i] - (double)cf;
-        if ((uint32_t)i < gn) d2[i] += e * e;
+    }
+    __syncthreads();
+    double r2 = 0.0;
+    for (uint32_t i = i0; i < gn; i += TG) {
+      const float *row = m.Xq + (uint64_t)qpos_s[a + i] * dp;
+      double d2 = 0.0;
+      for (uint32_t t = 0; t < dp; ++t) {
+        const float y = v.sc * (row[t] - v.ctr[t]);
+        const double e = (double)y + 0.5 * (double)(float)gctr[g][t];
+        d2 += e * e;
       }
+      r2 = d2 > r2 ? d2 : r2;
     }
 #pragma unroll
     for (uint32_t off = TG / 2; off > 0; off >>= 1) {
       nc += __shfl_xor(nc, off);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) d2[i] += __shfl_xor(d2[i], off);
+      const double o = __shfl_xor(r2, off);
+      r2 = o > r2 ? o : r2;
     }
     if (i0 == 0) {
-      double r2 = 0.0;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) r2 = d2[i] > r2 ? d2[i] : r2;
       // (1 + 2^-18): the rounded centring, at most u (|q~| + |a~|) against a
       // margin of 2^-13 |a|^2
       const double R = (__builtin_sqrt(v.s_hi) + __builtin_sqrt(r2)) * (1.0 + 0x1p-18);
@@ -774,6 +830,7 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
     fill();
     const uint32_t nn = tail - head < (uint32_t)CH ? tail - head : (uint32_t)CH;
     if (nn) gather(nn);  // in flight during the tiles below
+    if (w * QB * 32 < nq)  // (a wave without queries has no tiles)
 #pragma nounroll
     for (int blk = 0; blk < CH / 32; ++blk) {
       if (ncur <= 32u * (uint32_t)blk) break;

@@ -19,6 +19,7 @@ struct Mx32View {
   const float *nn;    // [n_pad] reject values of the tiles
   const float *pn;    // [n_pad] reject values of the group test
   float sc;           // scale of the centred coordinates (a power of two)
+  const uint8_t *pid; // nearest pivot of each query position (null: none), see k_join_fp32_mxg
   const float *ctr;   // [K] centre, reordered dimensions, zero padded
   uint32_t skip_below;           // candidates with caller index below this are skipped (0: none)
   const uint32_t *orig_id;       // candidate position -> caller index

@@ -321,6 +321,7 @@ struct sj_index {
   DevBuf box_rows;              // two planes of the points' first 8 dimensions (launch_box_rows)
   double mean_norm2 = 0.0;      // mean squared norm of the points (variance sample)
   DevBuf pivots;                // [d][kPivots] pivot points of the sort key (pb > 0)
+  DevBuf pos_pivot;             // nearest pivot of each position
   DevBuf band;                  // deferred recheck list of the matrix-core joins
   uint64_t band_cap = 0;
   uint64_t band_hint = 0;       // its expected size from the sampled count
