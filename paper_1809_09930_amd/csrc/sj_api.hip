@@ -373,6 +373,9 @@ bool mx32_in_range(const sj_index &ix) {
 // Pivots in the sort key: where the group test of k_join_fp32_mxg can use
 // cluster-wise query blocks.
 constexpr uint64_t kPivotMinPoints = 4096;
+// picked pivots take 0.1 to 0.2 ms more than rows at equal distances, and save a
+// third of a large clustered join: from joins of about a millisecond on
+constexpr uint64_t kPivotPickMin = 16384;
 bool use_pivots(const sj_index &ix) {
   return padded_dim(ix.d) > 24 && !ix.opt.sortidu && ix.n >= kPivotMinPoints && mx32_in_range(ix);
 }
@@ -457,8 +460,20 @@ uint64_t build_grid(sj_index &ix, const float *P, const Geometry &g, BuildTmp &t
   if (keep && g.kp.pb) {
     ix.pivots.alloc(kPivots * ix.d * 4);
     pid.alloc(n);
-    launch_pivot_table(P, n / kPivots, ix.d, ix.pivots.as<float>(), s);
+    if (n >= kPivotPickMin) {
+      TmpBuf sample;
+      sample.alloc((uint64_t)kPickSample * ix.d * 4);
+      launch_pivot_pick(P, n, ix.d, sample.as<float>(), ix.pivots.as<float>(), s);
+    } else {
+      launch_pivot_table(P, n / kPivots, ix.d, ix.pivots.as<float>(), s);
+    }
     launch_nearest_pivot(P, n, ix.d, ix.pivots.as<float>(), pid.as<uint8_t>(), s);
+    TmpBuf means;
+    means.alloc(kPivots * (ix.d + 1) * 4);
+    launch_pivot_means(P, n, ix.d, pid.as<uint8_t>(), means.as<float>(), s);
+    ix.pivot_means.resize(kPivots * (ix.d + 1));
+    SJ_HIP(hipMemcpyAsync(ix.pivot_means.data(), means.p, ix.pivot_means.size() * 4,
+                          hipMemcpyDeviceToHost, s));  // waited for below
   }
   launch_cellkey(P, n, ix.d, g.kp, pid.as<uint8_t>(), t.keys[0].as<uint64_t>(), t.ids[0].as<uint32_t>(), s);
   uint64_t *kb[2] = {t.keys[0].as<uint64_t>(), t.keys[1].as<uint64_t>()};
@@ -886,7 +901,7 @@ uint64_t mx32_rows(const sj_index &ix) { return ix.n + 64; }
 bool mx32_fits(const sj_index &ix) {
   // the split rows take up to twice the bytes of the FP32 rows: large sets
   // keep the vector form when they would not fit easily
-  const uint64_t bytes = mx32_rows(ix) * (mx32_k(ix.dp) * 4ull + 8ull);
+  const uint64_t bytes = mx32_rows(ix) * (mx32_k(ix.dp) * 4ull + kMx32Dirs * 2ull + 12ull);
   return bytes < (1ull << 30) || bytes < default_budget() / 3;
 }
 // Rows of the query-box test of an indexed set.
@@ -895,6 +910,69 @@ void box_prepare(sj_index &ix, hipStream_t s) {
   launch_box_rows(ix.X.as<float>(), ix.n, ix.dp, ix.box_rows.p, ix.box_rows.as<char>() + ix.n * 16,
                   s);
 }
+// Directions of the group test of k_join_fp32_mxg, [dp][kMx32Dirs]: an
+// orthonormal basis of the span of the pivots' means (the farthest residual
+// first), where clusters differ most, then of the coordinate axes in variance
+// order.  Any orthonormal set is valid.
+std::vector<float> mx32_directions(const sj_index &ix, const std::vector<float> &centre) {
+  const uint32_t d = ix.d;
+  std::vector<std::vector<double>> rest, basis;
+  for (uint32_t b = 0; b < ix.pivot_means.size() / (d + 1); ++b) {
+    const float *mean = &ix.pivot_means[b * (d + 1)];
+    if (mean[d] < 1.0f) continue;
+    std::vector<double> x(d);
+    for (uint32_t r = 0; r < d; ++r) x[r] = (double)mean[ix.perm[r]] - (double)centre[r];
+    rest.push_back(std::move(x));
+  }
+  auto dot = [&](const std::vector<double> &a, const std::vector<double> &b) {
+    return std::inner_product(a.begin(), a.end(), b.begin(), 0.0);
+  };
+  auto project_out = [&](std::vector<double> &x, const std::vector<double> &b) {
+    const double c = dot(x, b);
+    for (uint32_t r = 0; r < d; ++r) x[r] -= c * b[r];
+  };
+  auto accept = [&](std::vector<double> x) {
+    for (const auto &b : basis) project_out(x, b);  // once more, against rounding
+    const double n = std::sqrt(dot(x, x));
+    for (double &c : x) c /= n;
+    for (auto &y : rest) project_out(y, x);
+    basis.push_back(std::move(x));
+  };
+  double first = 0.0;
+  while (basis.size() < std::min(kMx32Dirs, d)) {
+    double best = 0.0;
+    size_t at = 0;
+    for (size_t i = 0; i < rest.size(); ++i)
+      if (const double n2 = dot(rest[i], rest[i]); n2 > best) {
+        best = n2;
+        at = i;
+      }
+    first = std::max(first, best);
+    if (!(best > 1e-4 * first)) break;
+    accept(rest[at]);
+  }
+  for (uint32_t r = 0; r < d && basis.size() < std::min(kMx32Dirs, d); ++r) {
+    std::vector<double> x(d, 0.0);
+    x[r] = 1.0;
+    for (const auto &b : basis) project_out(x, b);
+    if (dot(x, x) > 1e-3) accept(std::move(x));
+  }
+  std::vector<float> dirs((size_t)ix.dp * kMx32Dirs, 0.0f);
+  for (size_t j = 0; j < basis.size(); ++j)
+    for (uint32_t r = 0; r < d; ++r) dirs[(size_t)r * kMx32Dirs + j] = (float)basis[j][r];
+  return dirs;
+}
+
+// Projected rows of a handle's points on the indexed set's directions.
+void mx32_project(sj_index &ix, const sj_index &E, uint64_t n, hipStream_t s) {
+  const uint64_t np = n + 64;
+  ix.mx_ys.alloc(np * kMx32Dirs * 2);
+  ix.mx_pn.alloc(np * 4);
+  ix.mx_ye.alloc(np * 4);
+  launch_mx32_project(ix.X.as<float>(), n, np, E.dp, E.mx_dirs.as<float>(), E.mx_ctr.as<float>(),
+                      E.mx_scale, ix.mx_ys.p, ix.mx_pn.as<float>(), ix.mx_ye.as<float>(), s);
+}
+
 void mx32_prepare(sj_index &ix, hipStream_t s) {
   const uint32_t K = mx32_k(ix.dp);
   const uint64_t np = mx32_rows(ix);
@@ -917,11 +995,17 @@ void mx32_prepare(sj_index &ix, hipStream_t s) {
   ix.mx_ctr.alloc(K * 4);
   ix.mx_xs.alloc(np * K * 4);
   ix.mx_nn.alloc(np * 4);
-  ix.mx_pn.alloc(np * 4);
   SJ_HIP(hipMemcpyAsync(ix.mx_ctr.p, centre.data(), K * 4, hipMemcpyHostToDevice, s));
   launch_mx32_prep(ix.X.as<float>(), ix.n, np, ix.dp, ix.mx_ctr.as<float>(), ix.mx_scale,
-                   mx32_kappa(ix.d), ix.mx_xs.p, ix.mx_nn.as<float>(), ix.mx_pn.as<float>(), s);
-  SJ_HIP(hipStreamSynchronize(s));  // the centre's host copy ends here
+                   mx32_kappa(ix.d), ix.mx_xs.p, ix.mx_nn.as<float>(), s);
+  std::vector<float> dirs;
+  if (!mx32_per_wave(ix.dp)) {
+    dirs = mx32_directions(ix, centre);
+    ix.mx_dirs.alloc(dirs.size() * 4);
+    SJ_HIP(hipMemcpyAsync(ix.mx_dirs.p, dirs.data(), dirs.size() * 4, hipMemcpyHostToDevice, s));
+    mx32_project(ix, ix, ix.n, s);
+  }
+  SJ_HIP(hipStreamSynchronize(s));  // the host copies of centre and directions end here
 }
 
 void choose_fp32_form(sj_index &ix, hipStream_t s) {
@@ -1330,6 +1414,7 @@ void build_query(sj_index &q, const sj_index &E, const float *queries, hipStream
            live_slot_share(q, t.cand_sum.as<uint64_t>(), mx32_queries(q.dp), s) >=
                kMx32LiveSlotShareMin;
   if (q.mx32) q.info.fp32_form = SJ_FP32_NORM;
+  if (q.mx32 && !mx32_per_wave(q.dp)) mx32_project(q, E, q.n_near, s);
   q.small_cells =
       !q.mx32 &&
       live_slot_share(q, t.cand_sum.as<uint64_t>(),
@@ -1524,7 +1609,10 @@ void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &ru
                         : FLT_MAX;
       x.view.XS = E.mx_xs.p;
       x.view.nn = E.mx_nn.as<float>();
+      x.view.ys = E.mx_ys.p;
       x.view.pn = E.mx_pn.as<float>();
+      x.view.yq = ix.mx_ys.p;
+      x.view.ye = ix.mx_ye.as<float>();
       x.view.pid = ix.pos_pivot.as<uint8_t>();
       x.view.ctr = E.mx_ctr.as<float>();
       x.view.skip_below = skip_below;

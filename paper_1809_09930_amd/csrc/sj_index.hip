@@ -166,6 +166,78 @@ __global__ __launch_bounds__(kBlock) void k_pivot_table(const float *__restrict_
   if (e < kPivots * d) table[e] = P[(uint64_t)(e % kPivots) * stride * d + e / kPivots];
 }
 
+// Half of the pivots at equal distances in the sample, then the other half one by
+// one, each the sample's farthest row from those before: rows at equal distances
+// alone miss one of 20 clusters in half of all sets, and its points then share
+// other clusters' query blocks (a quarter to a third of all blocks, which pass
+// every candidate's group test).  One workgroup, a thread per sampled row; bound by
+// reading the sample ([d][kPickSample]) 33 times from L2, 0.1 to 0.2 ms.
+__global__ __launch_bounds__(kBlock) void k_pick_sample(const float *__restrict__ P,
+                                                        uint64_t stride, uint32_t d,
+                                                        float *__restrict__ sample) {
+  const uint32_t e = blockIdx.x * kBlock + threadIdx.x;
+  if (e >= kPickSample * d) return;
+  const uint32_t i = e / d, t = e - i * d;
+  sample[t * kPickSample + i] = P[(uint64_t)i * stride * d + t];
+}
+
+__global__ __launch_bounds__(kPickSample) void k_pivot_pick(const float *__restrict__ sample,
+                                                            uint32_t d,
+                                                            float *__restrict__ table) {
+  constexpr uint32_t kFirst = kPivots / 2, kW = kPickSample / kWave;
+  __shared__ float row[SJ_MAX_DIM][kFirst];
+  __shared__ uint64_t best[kW];
+  const uint32_t i = threadIdx.x;
+  for (uint32_t e = i; e < d * kFirst; e += kPickSample) {
+    const uint32_t t = e / kFirst, j = e % kFirst;
+    const float x = sample[t * kPickSample + j * (kPickSample / kFirst)];
+    row[t][j] = x;
+    table[t * kPivots + j] = x;
+  }
+  __syncthreads();
+  float near[kFirst];
+#pragma unroll
+  for (uint32_t j = 0; j < kFirst; ++j) near[j] = 0.0f;
+  for (uint32_t t = 0; t < d; ++t) {
+    const float x = sample[t * kPickSample + i];
+#pragma unroll
+    for (uint32_t j = 0; j < kFirst; ++j) {
+      const float e = x - row[t][j];
+      near[j] = __builtin_fmaf(e, e, near[j]);
+    }
+  }
+  float dist = near[0];
+#pragma unroll
+  for (uint32_t j = 1; j < kFirst; ++j) dist = __builtin_fminf(dist, near[j]);
+  for (uint32_t j = kFirst; j < kPivots; ++j) {
+    // (non-negative floats compare like their bits)
+    uint64_t b = ((uint64_t)__builtin_bit_cast(uint32_t, dist) << 32) | i;
+    for (int off = 32; off > 0; off >>= 1) {
+      const uint64_t o = __shfl_xor(b, off);
+      b = o > b ? o : b;
+    }
+    if (lane_id() == 0) best[i / kWave] = b;
+    __syncthreads();
+    b = best[0];
+    for (uint32_t w = 1; w < kW; ++w) b = best[w] > b ? best[w] : b;
+    const uint32_t pick = (uint32_t)b;
+    if (i < d) {
+      const float x = sample[i * kPickSample + pick];
+      row[i][0] = x;
+      table[i * kPivots + j] = x;
+    }
+    __syncthreads();
+    float e2 = 0.0f;
+#pragma unroll 8
+    for (uint32_t t = 0; t < d; ++t) {
+      const float e = sample[t * kPickSample + i] - row[t][0];
+      e2 = __builtin_fmaf(e, e, e2);
+    }
+    dist = __builtin_fminf(dist, e2);
+    // (row is written again after the next barrier)
+  }
+}
+
 __global__ __launch_bounds__(kBlock) void k_nearest_pivot(const float *__restrict__ P, uint64_t n,
                                                           uint32_t d,
                                                           const float *__restrict__ table,
@@ -193,6 +265,34 @@ __global__ __launch_bounds__(kBlock) void k_nearest_pivot(const float *__restric
       best = j;
     }
   pid[i] = (uint8_t)best;
+}
+
+// One workgroup per pivot: 256 sampled rows at a time, thread t sums dimension t
+// of those that are the pivot's.
+static_assert(SJ_MAX_DIM <= kBlock, "a thread per dimension");
+__global__ __launch_bounds__(kBlock) void k_pivot_means(const float *__restrict__ P, uint64_t m,
+                                                        uint64_t stride, uint32_t d,
+                                                        const uint8_t *__restrict__ pid,
+                                                        float *__restrict__ out) {
+  __shared__ uint64_t mine[kWavesPerBlock];
+  const uint32_t b = blockIdx.x, t = threadIdx.x;
+  float sum = 0.0f;
+  uint32_t cnt = 0;
+  for (uint64_t base = 0; base < m; base += kBlock) {
+    const uint64_t i = base + t;
+    const uint64_t hit = ballot(i < m && pid[i * stride] == b);
+    if (lane_id() == 0) mine[t / kWave] = hit;
+    __syncthreads();
+    for (uint32_t w = 0; w < (uint32_t)kWavesPerBlock; ++w)
+      for (uint64_t x = mine[w]; x; x &= x - 1) {
+        const uint64_t row = (base + w * kWave + (uint32_t)__builtin_ctzll(x)) * stride;
+        if (t < d) sum += P[row * d + t];
+        ++cnt;
+      }
+    __syncthreads();
+  }
+  if (t < d) out[(uint64_t)b * (d + 1) + t] = cnt ? sum / (float)cnt : 0.0f;
+  if (t == 0) out[(uint64_t)b * (d + 1) + d] = (float)cnt;
 }
 
 __global__ __launch_bounds__(kBlock) void k_pivot_order(const uint8_t *__restrict__ pid, uint64_t n,
@@ -868,10 +968,28 @@ void launch_pivot_table(const float *P, uint64_t stride, uint32_t d, float *tabl
   SJ_HIP(hipGetLastError());
 }
 
+void launch_pivot_pick(const float *P, uint64_t n, uint32_t d, float *sample, float *table,
+                       hipStream_t s) {
+  if (n < kPickSample || d > SJ_MAX_DIM) fail(SJ_ERR_INVALID_ARG, "too few rows to pick pivots");
+  hipLaunchKernelGGL(k_pick_sample, dim3(blocks_for(kPickSample * d)), dim3(kBlock), 0, s, P,
+                     n / kPickSample, d, sample);
+  SJ_HIP(hipGetLastError());
+  hipLaunchKernelGGL(k_pivot_pick, dim3(1), dim3(kPickSample), 0, s, sample, d, table);
+  SJ_HIP(hipGetLastError());
+}
+
 void launch_nearest_pivot(const float *P, uint64_t n, uint32_t d, const float *table, uint8_t *pid,
                           hipStream_t s) {
   if (!n) return;
   hipLaunchKernelGGL(k_nearest_pivot, dim3(blocks_for(n)), dim3(kBlock), 0, s, P, n, d, table, pid);
+  SJ_HIP(hipGetLastError());
+}
+
+void launch_pivot_means(const float *P, uint64_t n, uint32_t d, const uint8_t *pid, float *out,
+                        hipStream_t s) {
+  if (!n) return;
+  const uint64_t stride = std::max<uint64_t>(1, n / kPivotSample), m = n / stride;
+  hipLaunchKernelGGL(k_pivot_means, dim3(kPivots), dim3(kBlock), 0, s, P, m, stride, d, pid, out);
   SJ_HIP(hipGetLastError());
 }
 

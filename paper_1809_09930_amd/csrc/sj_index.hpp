@@ -49,10 +49,20 @@ void launch_variance(const float *P, uint32_t d, uint64_t stride, uint64_t m, do
 // pid: nearest pivots (launch_nearest_pivot), or null (number 0).
 void launch_cellkey(const float *P, uint64_t n, uint32_t d, const KeyParams &kp,
                     const uint8_t *pid, uint64_t *keys, uint32_t *ids, hipStream_t s);
+// Pivots among kPickSample rows at equal distances in P (n >= kPickSample), into
+// a table like launch_pivot_table's; sample is scratch of kPickSample d floats.
+constexpr uint32_t kPickSample = 1024;
+void launch_pivot_pick(const float *P, uint64_t n, uint32_t d, float *sample, float *table,
+                       hipStream_t s);
 // Table [d][kPivots] of the rows 0, stride, 2 stride, ... of P, and the number of
 // the row nearest to each of n points among them.
 constexpr uint32_t kPivotBits = 6, kPivots = 1u << kPivotBits;
 void launch_pivot_table(const float *P, uint64_t stride, uint32_t d, float *table, hipStream_t s);
+// Mean of each pivot's points over a sample of up to kPivotSample rows, and
+// their number: [kPivots][d + 1].
+constexpr uint64_t kPivotSample = 16384;
+void launch_pivot_means(const float *P, uint64_t n, uint32_t d, const uint8_t *pid, float *out,
+                        hipStream_t s);
 // out[p] = pid[orig_id[p]]
 void launch_pivot_order(const uint8_t *pid, uint64_t n, const uint32_t *orig_id, uint8_t *out,
                         hipStream_t s);

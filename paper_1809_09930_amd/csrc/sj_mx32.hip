@@ -37,7 +37,7 @@
 // used to accept is now decided in FP64.
 // Measured joins, vector forms before and this: uniform 2M x 16 at S_D 64 505
 // and 131 ms, exponential 2M x 16 at eps 0.03 151 and 42 ms, mixture 515k x 90
-// 253 and 54 ms, mixture 301k x 37 in 5 result batches 177 and 50 ms.  The
+// 253 and 14.5 ms, mixture 301k x 37 in result batches 177 and 28 ms.  The
 // matrix cores hold about 1.4 PFLOP/s on random FP16 operands here (power), so
 // the products of the 2M x 16 join (0.43 of 2e12 pairs after the box test, 83
 // TFLOP) cannot take less than 60 ms.
@@ -46,8 +46,8 @@
 // at once (a bound on the distance, so no pair is lost):
 //   up to 24 padded dimensions, the distance from the bounding box of the
 //   queries over the first 8 dimensions (k_join_box);
-//   above, the distance from the centres of groups of eight queries, itself a
-//   matrix product of the leading parts (k_join_fp32_mxg).
+//   above, the distance from the centres of groups of queries in a projection,
+//   itself a matrix product (k_join_fp32_mxg).
 #include "sj_mx32.hpp"
 
 #include <algorithm>
@@ -119,37 +119,70 @@ __global__ __launch_bounds__(kBlock) void k_mx32_split(const float *__restrict__
   }
 }
 
-// Per candidate: nn, what a tile element must stay below to be a hit (the float
-// above -|a~|^2 (1 - kappa) rounded up), and rounded up
-// pn = -(|a1|^2 (1 - 2^-13) - |a~|^2 (2^-11 + 2^-15)), that of the group
-// test (see k_join_fp32_mxg).  Rows n .. n_pad - 1 get -inf (never a hit).
+// Per candidate nn, what a tile element must stay below to be a hit: the float
+// above -|a~|^2 (1 - kappa) rounded up.  Rows n .. n_pad - 1 get -inf (never a hit).
 __global__ __launch_bounds__(kBlock) void k_mx32_norms(const float *__restrict__ X, uint64_t n,
                                                        uint64_t n_pad, uint32_t dp,
                                                        const float *__restrict__ ctr, float sc,
                                                        double kappa,
-                                                       float *__restrict__ nn,
-                                                       float *__restrict__ pn) {
+                                                       float *__restrict__ nn) {
   const uint64_t p = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
   if (p >= n_pad) return;
   if (p >= n) {
     nn[p] = -__builtin_inff();
-    pn[p] = -__builtin_inff();
     return;
   }
   const f32x4 *x4 = reinterpret_cast<const f32x4 *>(X + p * dp);
-  double s = 0.0, s1 = 0.0;
+  double s = 0.0;
   for (uint32_t t4 = 0; t4 < dp / 4; ++t4) {
     const f32x4 x = x4[t4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float y = sc * (x[i] - ctr[4 * t4 + i]);
-      const float y1 = (float)(_Float16)y;
       s += (double)y * (double)y;
-      s1 += (double)y1 * (double)y1;
     }
   }
   nn[p] = strict(round_up_f32(-s * (1.0 - kappa)));
-  pn[p] = round_up_f32(-(s1 * (1.0 - 0x1p-13) - s * (0x1p-11 + 0x1p-15)));
+}
+
+// Projected rows y = 2^-4 V x~ in FP16 (|V x~| <= |x~| < 2^18), the reject value
+// pn of the group test and the error radius ye of a query (see k_join_fp32_mxg).
+// The directions are wave-uniform scalar loads; a lane holds one point's 32 sums.
+constexpr double kEta = 0x1p-11 + 0x1p-13;
+__global__ __launch_bounds__(kBlock) void k_mx32_project(
+    const float *__restrict__ X, uint64_t n, uint64_t n_pad, uint32_t dp,
+    const float *__restrict__ dirs, const float *__restrict__ ctr, float sc,
+    half8 *__restrict__ ys, float *__restrict__ pn, float *__restrict__ ye) {
+  const uint64_t p = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (p >= n_pad) return;
+  float y[kMx32Dirs];
+#pragma unroll
+  for (uint32_t j = 0; j < kMx32Dirs; ++j) y[j] = 0.0f;
+  double s = 0.0;
+  if (p < n) {
+    for (uint32_t t = 0; t < dp; ++t) {
+      const float x = sc * (X[p * dp + t] - ctr[t]);
+      s += (double)x * (double)x;
+#pragma unroll
+      for (uint32_t j = 0; j < kMx32Dirs; ++j)
+        y[j] = __builtin_fmaf(x, dirs[t * kMx32Dirs + j], y[j]);
+    }
+  }
+  double s1 = 0.0;
+#pragma unroll
+  for (uint32_t g = 0; g < kMx32Dirs / 8; ++g) {
+    half8 h;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      h[i] = (_Float16)(0x1p-4f * y[8 * g + i]);
+      s1 += (double)(float)h[i] * (double)(float)h[i];
+    }
+    ys[p * (kMx32Dirs / 8) + g] = h;
+  }
+  s *= 0x1p-8;
+  pn[p] = p < n ? round_up_f32(-(s1 * (1.0 - 0x1p-13) - s * (kEta + kEta * kEta)))
+                : -__builtin_inff();
+  ye[p] = round_up_f32(__builtin_sqrt(s) * kEta * (1.0 + 0x1p-20));
 }
 
 // The first 8 dimensions of the cell-ordered rows as two planes of 16-byte
@@ -543,31 +576,43 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
 // ---------------------------------------------------------------------------
 // Above 24 padded dimensions: one workgroup per work unit of 256 queries.
 //
-// Group test.  The queries form 32 groups of eight to some twenty consecutive
-// ones with the same nearest pivot (a group across two clusters would pass most
-// candidates for the whole unit: with eight each, 43 % of the tests of the 515k x
-// 90 mixture passed); c_g is the mean of a group's q~ rounded to FP16 and r_g the largest |q~ - c_g|.  A
-// pair within eps has |q~ - a~| <= R = sqrt(s_hi) (1 + 2^-18) + u (...), hence
-// |a1 - c_g| <= R + r_g + 2^-11 |a~|, and with 2xy <= x^2 + y^2
-//     |a1|^2 + |c_g|^2 - 2 c_g . a1 <= (R + r_g)^2 (1 + 2^-11)
-//                                      + |a~|^2 (2^-11 + 2^-22).
-// One 32x32 tile of leading products tests 32 candidates against all groups
-// (1/24 of the work it can save): the rows start from -T_g, and candidates
-// above pn in every row are dropped.  The margins of 2^-13 on both sides cover
-// the FP32 accumulation (gamma_129(2^-23) < 2^-15), the rounding of T_g and
-// that of the centring.
+// Group test.  Points are projected on 32 orthonormal directions that span the
+// pivots' means (y1 = 2^-4 V x~ in FP16): clusters stay as far apart as they are
+// while the scatter inside them falls to its share of 32 dimensions, and the test
+// reads 64 bytes per candidate.  The queries form up to 32 groups of consecutive
+// ones with the same nearest pivot; c_g is the mean of a group's y1 rounded to
+// FP16.  With eta = 2^-11 + 2^-13 (the FP16 rounding, the FP32 sums of up to 128
+// terms, sqrt(32) 130 2^-24, the directions' and the centring's rounding), A =
+// 2^-4 |a~| and tiny = 2^-20 (FP16 subnormals), |y1(a) - 2^-4 V a~| <= eta A +
+// tiny / 2, likewise for a query, and a pair within eps has |V (q~ - a~)| <=
+// |q~ - a~| <= R = sqrt(s_hi) (1 + 2^-16).  Hence with r_g the largest
+// |y1(q) - c_g| + eta 2^-4 |q~| of a group and x = 2^-4 R + r_g + tiny
+//     |y1(a)|^2 + |c_g|^2 - 2 c_g . y1(a) <= (x + eta A)^2
+//                                         <= x^2 (1 + eta) + A^2 (eta + eta^2).
+// One 32x32 tile tests 32 candidates against all groups: the rows start from
+// -T_g, and candidates above pn in every row are dropped.  Margins of 2^-13 on
+// both sides cover the FP32 accumulation (gamma_34(2^-23) < 2^-17) and the
+// rounding of T_g.
+// Against the leading parts of the whole rows, as before, groups of one cluster
+// still passed a quarter of the other clusters' points of the 515k x 90 mixture
+// (|a - c|^2 about 18 against (R + r)^2 = 16), and the test was bound by reading
+// rows of 192 bytes that the caches hold only in part.  The join of that set took
+// 50.1 ms then, 37.7 with the projected test and 14.5 with picked pivots (36, 36
+// and 7 % of the tests passed); now the tests alone take 7.9 ms, bound by
+// instruction issue (two products, 8 minima and 4 LDS reads per 32 candidates).
 //
 // Survivors' positions enter a ring in LDS; chunks of CH of them are staged,
 // split rows and all, into a double-buffered LDS tile that every wave reads.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kRing = 512;  // >= 63 pending + one window of 256
+constexpr uint32_t kRing = 2048;  // >= 63 pending + one window of 1024
+constexpr int kTestBlocks = 4;    // blocks of 32 candidates that a wave tests at a time
 
 // Tile shapes by K (dimensions padded to 16): waves per workgroup, query row
 // blocks per wave and candidate columns per staged chunk.
 template <int K>
 struct Shape {
-  static constexpr int NW = K <= 64 ? 4 : 8;
-  static constexpr int QB = K <= 64 ? 2 : 1;
+  static constexpr int NW = 8;
+  static constexpr int QB = 1;
   static constexpr int CH = K <= 48 ? 64 : 32;
 };
 
@@ -585,7 +630,8 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
   constexpr int RV = 2 * (K / 8);     // 16-byte vectors per split row
   constexpr int RS = RV + 1;          // and per staged row (odd: no bank conflicts)
   constexpr int PER_THREAD = (CH * RV + NT - 1) / NT;
-  constexpr uint32_t WIN = NW * 32;   // candidates tested at a time
+  constexpr uint32_t WIN = NW * 32 * kTestBlocks;  // candidates tested at a time
+  constexpr int KT = kMx32Dirs / 16;
   static_assert(TQ == 256, "units hold 256 queries in 32 groups");
   static_assert(RV % 2 == 0, "the padded stride is odd");
   __shared__ uint64_t band_mem[NW][kBandStage];
@@ -596,7 +642,7 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
   __shared__ __align__(16) float cinit[TQ];  // -Thi of each query row
   __shared__ uint32_t qpos_s[TQ];
   __shared__ __align__(16) float ginit[32];  // -T_g
-  __shared__ __align__(16) _Float16 gctr[32][K];
+  __shared__ __align__(16) _Float16 gctr[32][kMx32Dirs];
   __shared__ uint32_t wcnt[NW];
   __shared__ uint64_t seg_mask[TQ / kWave];
   __shared__ uint32_t len_cnt[kGroupLens][TQ / kWave];
@@ -678,52 +724,50 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
     }
     __syncthreads();
   }
-  // NT / 32 threads per group: its centre, each over every NT/32-th dimension,
+  // NT / 32 threads per group: its centre, each over every NT/32-th direction,
   // then its radius, each over every NT/32-th query
   {
     constexpr uint32_t TG = NT / 32;
     const uint32_t g = tid / TG, i0 = tid % TG;
     const uint32_t a = gfirst[g], gn = gfirst[g + 1] - a;
+    const _Float16 *__restrict__ yq = static_cast<const _Float16 *>(v.yq);
     double nc = 0.0;
-    for (uint32_t t = i0; t < (uint32_t)K; t += TG) {
+    for (uint32_t t = i0; t < kMx32Dirs; t += TG) {
       float sum = 0.0f;
-      if (t < dp)
-        for (uint32_t i = 0; i < gn; ++i)
-          sum += v.sc * (m.Xq[(uint64_t)qpos_s[a + i] * dp + t] - v.ctr[t]);
+      for (uint32_t i = 0; i < gn; ++i) sum += (float)yq[(uint64_t)qpos_s[a + i] * kMx32Dirs + t];
       const float cf = (float)(_Float16)(gn ? sum / (float)gn : 0.0f);
       gctr[g][t] = (_Float16)(-2.0f * cf);  // exact
       nc += (double)cf * (double)cf;
     }
     __syncthreads();
-    double r2 = 0.0;
+    double r = 0.0;
     for (uint32_t i = i0; i < gn; i += TG) {
-      const float *row = m.Xq + (uint64_t)qpos_s[a + i] * dp;
+      const uint32_t p = qpos_s[a + i];
       double d2 = 0.0;
-      for (uint32_t t = 0; t < dp; ++t) {
-        const float y = v.sc * (row[t] - v.ctr[t]);
-        const double e = (double)y + 0.5 * (double)(float)gctr[g][t];
+      for (uint32_t t = 0; t < kMx32Dirs; ++t) {
+        const double e = (double)(float)yq[(uint64_t)p * kMx32Dirs + t] +
+                         0.5 * (double)(float)gctr[g][t];
         d2 += e * e;
       }
-      r2 = d2 > r2 ? d2 : r2;
+      const double x = __builtin_sqrt(d2) * (1.0 + 0x1p-40) + (double)v.ye[p];
+      r = x > r ? x : r;
     }
 #pragma unroll
     for (uint32_t off = TG / 2; off > 0; off >>= 1) {
       nc += __shfl_xor(nc, off);
-      const double o = __shfl_xor(r2, off);
-      r2 = o > r2 ? o : r2;
+      const double o = __shfl_xor(r, off);
+      r = o > r ? o : r;
     }
     if (i0 == 0) {
-      // (1 + 2^-18): the rounded centring, at most u (|q~| + |a~|) against a
-      // margin of 2^-13 |a|^2
-      const double R = (__builtin_sqrt(v.s_hi) + __builtin_sqrt(r2)) * (1.0 + 0x1p-18);
-      const double T = R * R * (1.0 + 0x1p-11) + 0x1p-13 * (R * R + 2.0 * nc) + v.tiny - nc;
+      const double x = __builtin_sqrt(v.s_hi) * (0x1p-4 * (1.0 + 0x1p-16)) + r + 0x1p-20;
+      const double T = x * x * (1.0 + kEta) + 0x1p-13 * (x * x + 2.0 * nc) - nc;
       ginit[g] = gn ? -round_up_f32(T) : __builtin_inff();
     }
   }
   __syncthreads();
-  half8 G[KS];
+  half8 G[KT];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks)
+  for (int ks = 0; ks < KT; ++ks)
     G[ks] = *reinterpret_cast<const half8 *>(&gctr[col][ks * 16 + half * 8]);
   float16v c0[QB];
 #pragma unroll
@@ -734,6 +778,7 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
   uint64_t n_skip = 0;
   const KeyForm kf{m.key_hi, m.pshift, m.symmetric != 0};
   const half8 *__restrict__ XS = static_cast<const half8 *>(v.XS);
+  const half8 *__restrict__ YS = static_cast<const half8 *>(v.ys);
 
   // candidate stream (uniform over the workgroup) and the ring of survivors
   uint32_t r = wu.run_first, c = wu.c_begin;
@@ -751,24 +796,33 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
   auto fill = [&]() __attribute__((always_inline)) {
     while (tail - head < (uint32_t)CH && c < ce) {
       const uint32_t wl = ce - c < WIN ? ce - c : WIN;
-      const uint32_t ci = w * 32 + col;  // this column's candidate (both halves)
-      const bool valid = ci < wl;
-      const uint32_t p = c + (valid ? ci : 0u);
-      const half8 *row = XS + (uint64_t)p * RV + half;
-      half8 b[KS];
+      const uint32_t first = w * (32u * kTestBlocks) + col;  // (both halves)
+      half8 b[kTestBlocks][KT];
+      float pnv[kTestBlocks];
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) b[ks] = row[2 * ks];
-      const float pnv = v.pn[p];
-      const bool early = v.skip_below && valid && v.orig_id[p] < v.skip_below;
-      float16v a = rows_init(ginit, half);
+      for (int i = 0; i < kTestBlocks; ++i) {
+        const uint32_t ci = first + 32u * (uint32_t)i, p = c + (ci < wl ? ci : 0u);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) a = mfma(G[ks], b[ks], a);
-      // a column passes when some row of either half does
-      const uint64_t pm = ballot(min16(a, __builtin_inff()) <= pnv && valid && !early);
-      const uint32_t keep = (uint32_t)pm | (uint32_t)(pm >> 32);
-      if (v.skip_below)  // earlier result batches took these pairs (halves agree)
-        n_skip += (uint64_t)__builtin_popcount((uint32_t)ballot(early)) * nq;
-      if (l == 0) wcnt[w] = (uint32_t)__builtin_popcount(keep);
+        for (int ks = 0; ks < KT; ++ks) b[i][ks] = YS[(uint64_t)p * (2 * KT) + 2 * ks + half];
+        pnv[i] = v.pn[p];
+      }
+      uint32_t keep[kTestBlocks], mine = 0;
+#pragma unroll
+      for (int i = 0; i < kTestBlocks; ++i) {
+        const uint32_t ci = first + 32u * (uint32_t)i;
+        const bool valid = ci < wl;
+        const bool early = v.skip_below && valid && v.orig_id[c + ci] < v.skip_below;
+        float16v a = rows_init(ginit, half);
+#pragma unroll
+        for (int ks = 0; ks < KT; ++ks) a = mfma(G[ks], b[i][ks], a);
+        // a column passes when some row of either half does
+        const uint64_t pm = ballot(min16(a, __builtin_inff()) <= pnv[i] && valid && !early);
+        keep[i] = (uint32_t)pm | (uint32_t)(pm >> 32);
+        mine += (uint32_t)__builtin_popcount(keep[i]);
+        if (v.skip_below)  // earlier result batches took these pairs (halves agree)
+          n_skip += (uint64_t)__builtin_popcount((uint32_t)ballot(early)) * nq;
+      }
+      if (l == 0) wcnt[w] = mine;
       __syncthreads();
       uint32_t before = 0, total = 0;
 #pragma unroll
@@ -777,9 +831,13 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
         before += (uint32_t)i < w ? k : 0u;
         total += k;
       }
-      if (half == 0 && ((keep >> col) & 1u))
-        ring[(tail + before + (uint32_t)__builtin_popcount(keep & ((1u << col) - 1u))) % kRing] =
-            p;
+#pragma unroll
+      for (int i = 0; i < kTestBlocks; ++i) {
+        if (half == 0 && ((keep[i] >> col) & 1u))
+          ring[(tail + before + (uint32_t)__builtin_popcount(keep[i] & ((1u << col) - 1u))) %
+               kRing] = c + first + 32u * (uint32_t)i;
+        before += (uint32_t)__builtin_popcount(keep[i]);
+      }
       __syncthreads();  // the ring is read and wcnt rewritten after this
       tail += total;
       c += wl;
@@ -934,7 +992,7 @@ uint32_t mx32_queries(uint32_t dp) {
 bool mx32_per_wave(uint32_t dp) { return dp <= 24; }
 
 void launch_mx32_prep(const float *X, uint64_t n, uint64_t n_pad, uint32_t dp, const float *ctr,
-                      float sc, double kappa, void *XS, float *nn, float *pn, hipStream_t s) {
+                      float sc, double kappa, void *XS, float *nn, hipStream_t s) {
   if (!n_pad) return;
   const uint32_t K = mx32_k(dp);
   const uint64_t vecs = n_pad * (K / 8);
@@ -944,7 +1002,16 @@ void launch_mx32_prep(const float *X, uint64_t n, uint64_t n_pad, uint32_t dp, c
                      static_cast<half8 *>(XS));
   SJ_HIP(hipGetLastError());
   hipLaunchKernelGGL(k_mx32_norms, dim3((uint32_t)((n_pad + kBlock - 1) / kBlock)), dim3(kBlock),
-                     0, s, X, n, n_pad, dp, ctr, sc, kappa, nn, pn);
+                     0, s, X, n, n_pad, dp, ctr, sc, kappa, nn);
+  SJ_HIP(hipGetLastError());
+}
+
+void launch_mx32_project(const float *X, uint64_t n, uint64_t n_pad, uint32_t dp,
+                         const float *dirs, const float *ctr, float sc, void *ys, float *pn,
+                         float *ye, hipStream_t s) {
+  if (!n_pad) return;
+  hipLaunchKernelGGL(k_mx32_project, dim3((uint32_t)((n_pad + kBlock - 1) / kBlock)), dim3(kBlock),
+                     0, s, X, n, n_pad, dp, dirs, ctr, sc, static_cast<half8 *>(ys), pn, ye);
   SJ_HIP(hipGetLastError());
 }
 

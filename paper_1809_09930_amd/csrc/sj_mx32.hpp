@@ -17,7 +17,10 @@ struct Mx32View {
   float kacc;     // 1 + 4 kappa, rounded up; FLT_MAX: no pair is accepted without FP64
   const void *XS;     // [n_pad][2][K] split candidate rows
   const float *nn;    // [n_pad] reject values of the tiles
-  const float *pn;    // [n_pad] reject values of the group test
+  // group test above 24 dimensions (see k_join_fp32_mxg): projected candidates
+  // and queries, the candidates' reject values and the queries' error radii
+  const void *ys, *yq;  // [n_pad][kMx32Dirs] FP16
+  const float *pn, *ye;
   float sc;           // scale of the centred coordinates (a power of two)
   const uint8_t *pid; // nearest pivot of each query position (null: none), see k_join_fp32_mxg
   const float *ctr;   // [K] centre, reordered dimensions, zero padded
@@ -43,7 +46,13 @@ bool mx32_per_wave(uint32_t dp);
 // Split rows and reject values of the cell-ordered rows X ([n][dp]); rows
 // n .. n_pad - 1 become padding.
 void launch_mx32_prep(const float *X, uint64_t n, uint64_t n_pad, uint32_t dp, const float *ctr,
-                      float sc, double kappa, void *XS, float *nn, float *pn, hipStream_t s);
+                      float sc, double kappa, void *XS, float *nn, hipStream_t s);
+// Directions of the group test and the rows projected on them: dirs is
+// [dp][kMx32Dirs], orthonormal columns (zero rows past d).
+constexpr uint32_t kMx32Dirs = 32;
+void launch_mx32_project(const float *X, uint64_t n, uint64_t n_pad, uint32_t dp,
+                         const float *dirs, const float *ctr, float sc, void *ys, float *pn,
+                         float *ye, hipStream_t s);
 // Planes of the rows' dimensions 0 .. 3 and 4 .. 7 (16 bytes per point each).
 void launch_box_rows(const float *X, uint64_t n, uint32_t dp, void *box0, void *box1,
                      hipStream_t s);

@@ -316,7 +316,10 @@ struct sj_index {
   bool mfma_per_wave = false;   // matrix-core single join with per-wave units
   uint32_t tq_single = 0, tc_single = 0;  // its unit shape (queries, candidates)
   // FP32 on the matrix cores: split rows, reject values, centre (see Mx32View)
-  DevBuf mx_xs, mx_nn, mx_pn, mx_ctr;
+  DevBuf mx_xs, mx_nn, mx_ctr;
+  // and above 24 dimensions the group test's directions and projected rows
+  DevBuf mx_dirs, mx_ys, mx_pn, mx_ye;
+  std::vector<float> pivot_means;  // [kPivots][d + 1] means and sizes of the pivots' points
   float mx_scale = 1.0f;
   DevBuf box_rows;              // two planes of the points' first 8 dimensions (launch_box_rows)
   double mean_norm2 = 0.0;      // mean squared norm of the points (variance sample)
