@@ -343,6 +343,18 @@ uint64_t default_budget();
 constexpr bool kFp32CellGroups = SJ_FP32_CELL_GROUPS != 0;
 constexpr double kLookupsPerSec = 2.0e10;
 constexpr double kPairsPerSec = 1.5e12;
+// The matrix-core joins take ten times the pairs (2M x 16 exponential FP32
+// 1.5e13/s, 515k x 90 mixture 0.9e13), but a cell's queries in whole units: their
+// pairs are those of all query slots.  At that rate most sets of up to a few 100k
+// points finish before another grid is counted, so a larger k is probed only while
+// the last step saved more than a probe takes (kProbeSec and a radix sort of n keys).
+// Passes with the model of the vector join, with this one, and the best k by hand:
+// mixture 301k x 37 FP32 13.6, 7.3, 6.6 (k 3) ms, 200k x 32 tables FP16 5.2, 3.6,
+// 3.6, mixture 1M x 40 FP32 56, 15, 15, mixture 300k x 18 FP16 3.4, 2.3, 2.3;
+// 2M x 16 exponential k 8 either way.  The lookups: 2.9e8 in two passes, 3.4 ms.
+constexpr double kMatrixLookupsPerSec = 8.0e10;
+constexpr double kMatrixPairsPerSec = 1.5e13;
+constexpr double kProbeSec = 1.5e-4, kProbeSecPerPoint = 2e-10;
 
 constexpr uint32_t kBoxMaxKp = 32;  // K padding up to which the 16-bit filters have the box form
 
@@ -449,12 +461,12 @@ struct BuildTmp {  // temporaries of the grid builds (thread scratch)
 };
 
 uint64_t build_neighbors(sj_index &ix, const sj_index &E, NbrParams np, BuildTmp &t,
-                         hipStream_t s, bool keep);
+                         hipStream_t s, bool keep, uint32_t slot_tq = 0);
 
 // Keys, sort, gather, compaction and neighbour counts for geometry g.
 // Returns the candidate count C and fills ncell.
 uint64_t build_grid(sj_index &ix, const float *P, const Geometry &g, BuildTmp &t, hipStream_t s,
-                    bool keep) {
+                    bool keep, uint32_t slot_tq = 0) {
   const uint64_t n = ix.n;
   TmpBuf pid;
   if (keep && g.kp.pb) {
@@ -500,15 +512,16 @@ uint64_t build_grid(sj_index &ix, const float *P, const Geometry &g, BuildTmp &t
                  ix.cell_key.as<uint64_t>(), ix.cell_start.as<uint32_t>(), t.scan.p, s);
   SJ_HIP(hipStreamSynchronize(s));
   ix.ncell = *ix.word_as<uint32_t>(kWordCells);
-  return build_neighbors(ix, ix, g.np, t, s, keep);
+  return build_neighbors(ix, ix, g.np, t, s, keep, slot_tq);
 }
 
 // Adjacent non-empty cells of ix's cells in E's cell table (E = ix in a
 // self-join; np of E's grid).  Returns the candidate count C, the sum over
 // ix's points of the sizes of their adjacent cells of E; with keep, fills
-// ix.nbr_off / ix.nbr_cell.
+// ix.nbr_off / ix.nbr_cell.  A probe with slot_tq also leaves the candidates of
+// all query slots in kWordSlots, each cell's queries rounded up to slot_tq.
 uint64_t build_neighbors(sj_index &ix, const sj_index &E, NbrParams np, BuildTmp &t,
-                         hipStream_t s, bool keep) {
+                         hipStream_t s, bool keep, uint32_t slot_tq) {
   const uint64_t nc = ix.ncell;
   const uint64_t ne = E.ncell;
   const uint64_t kFence = 8192;
@@ -524,6 +537,12 @@ uint64_t build_neighbors(sj_index &ix, const sj_index &E, NbrParams np, BuildTmp
   exclusive_scan_u64(t.prod.as<uint64_t>(), t.prod.as<uint64_t>(), nc, ix.word(kWordCand),
                      t.scan.p, s);
   if (!keep) {
+    if (slot_tq) {
+      launch_cell_slot_work(nc, ix.cell_start.as<uint32_t>(), t.cand_sum.as<uint64_t>(), slot_tq,
+                            t.prod.as<uint64_t>(), s);
+      exclusive_scan_u64(t.prod.as<uint64_t>(), t.prod.as<uint64_t>(), nc, ix.word(kWordSlots),
+                         t.scan.p, s);
+    }
     SJ_HIP(hipStreamSynchronize(s));
     return *ix.word(kWordCand);
   }
@@ -1165,16 +1184,55 @@ void build(sj_index &ix, const float *points, hipStream_t s) {
       all_adjacent = std::floor((ix.dmax[t] - ix.dmin[t]) / (ix.eps * kWidthSlack)) <= 1.0;
     }
     if (all_adjacent && make_geometry(ix, k0, g)) have = true;
+    const bool matrix = ix.opt.precision != SJ_PREC_FP32 || mx32_in_range(ix);
+    // (the builds of batched jobs run side by side: only their kernels count)
+    const double probe_sec =
+        (ix.batch_job ? 0.3 : 1.0) * (kProbeSec + kProbeSecPerPoint * (double)n);
+    // even every pair of points takes less than counting another grid
+    if (matrix && !have && 0.5 * (double)n * (double)n / kMatrixPairsPerSec < 2.0 * probe_sec &&
+        make_geometry(ix, k0, g))
+      have = all_adjacent = true;
+    const uint32_t unit = ix.opt.precision == SJ_PREC_FP32
+                              ? mx32_queries(ix.dp)
+                              : ix.batch_job ? 32u * (uint32_t)mfma_qb(mfma_kp(d))
+                                             : mfma_wg_queries(mfma_kp(d));
+    // a result batch holds a share of each cell's queries (Section 3.2.2 uses at
+    // least three batches)
+    const uint32_t shares = std::max(ix.opt.min_batches, ix.opt.batch_pairs ? 3u : 1u);
+    const uint32_t slot_tq = matrix ? unit * std::min(shares, 64u) : 0u;
+    double last = 0.0;
     for (uint32_t k = k0; k <= k1 && !all_adjacent; ++k) {
       Geometry gk;
       if (!make_geometry(ix, k, gk)) break;  // longer keys would overflow: stop
-      const uint64_t C = build_grid(ix, P, gk, t, s, false);
+      const uint64_t C = build_grid(ix, P, gk, t, s, false, slot_tq);
       // adjacency lists that could pass 2^32 - 1 entries (at most 3^k, and
       // at most #G, per cell) rule out this k and every larger one
       const double nc_k = (double)ix.ncell;
       if (nc_k * std::min<double>((double)gk.np.n_off, nc_k) > 4294967295.0) break;
-      const double cost = (double)C * 0.5 / kPairsPerSec +
-                          (double)ix.ncell * (double)gk.np.n_off / kLookupsPerSec;
+      const double lookups = nc_k * (double)gk.np.n_off;
+      double cost = (double)C * 0.5 / kPairsPerSec + lookups / kLookupsPerSec;
+      if (matrix) {
+        const double slots = (double)*ix.word(kWordSlots);
+        const double vec = cost;
+        // mostly idle slots: FP32 goes to the vector join, the 16-bit filters to
+        // units of 32 queries
+        double pairs = slots;
+        if (ix.opt.precision != SJ_PREC_FP32) pairs = std::min(slots, 1.5 * (double)C);
+        cost = 0.5 * pairs / kMatrixPairsPerSec + lookups / kMatrixLookupsPerSec;
+        if (ix.opt.precision == SJ_PREC_FP32 &&
+            ((double)C < kMx32MinCandidates ||
+             (double)C < kMx32LiveSlotShareMin * slots))
+          cost = vec;
+        const bool less = !have || cost < 0.98 * best;
+        if (less) {
+          best = cost;
+          g = gk;
+          have = true;
+        }
+        if (k == k0 ? 0.5 * cost < probe_sec : last - cost < probe_sec) break;
+        last = cost;
+        continue;
+      }
       if (!have || cost < best * (1.0 - 1e-9)) {
         best = cost;
         g = gk;
