@@ -365,6 +365,12 @@ constexpr uint32_t kBoxMaxKp = 32;  // K padding up to which the 16-bit filters 
 // 2^-25 per coordinate, 4 sqrt(128) 2^-25 (|q~| + |a~|) <= 2^-23 (|q~|^2 + |a~|^2)
 // + 2^-17 (the first part is in mx32_kappa's).
 constexpr double kMx32Tiny = 0x1p-16;
+// The leading product alone rejects with a radius wider by 2^-10 of the norms: its
+// tiles come first while that is a small part of eps^2.  Behind the query box its
+// waves hold twice the queries, so joins of few units keep all three products
+// (20k x 16: 0.12 ms, 0.14 with the leading one first; 400k x 20: 22.6 and 14.5).
+constexpr double kMx32LeadMax = 0.1;
+constexpr double kMx32LeadMin = 1073741824.0;
 constexpr double kMx32MinCandidates = 16777216.0;
 constexpr double kMx32LiveSlotShareMin = 0.4;
 bool mx32_in_range(const sj_index &ix) {
@@ -1127,7 +1133,10 @@ void build(sj_index &ix, const float *points, hipStream_t s) {
   const std::vector<double> hvar(var_at, var_at + 2 * (size_t)d);  // variances, then means
   if (hmax[d]) fail(SJ_ERR_INVALID_ARG, "points contain NaN or Inf coordinates");
   ix.dmean.assign(hvar.begin() + d, hvar.end());
-  for (uint32_t t = 0; t < d; ++t) ix.mean_norm2 += hvar[t] + hvar[d + t] * hvar[d + t];
+  for (uint32_t t = 0; t < d; ++t) {
+    ix.mean_norm2 += hvar[t] + hvar[d + t] * hvar[d + t];
+    ix.var_sum += hvar[t];
+  }
   for (uint32_t t = 0; t < d; ++t) {
     ix.dmin[t] = (double)ordered_to_float(hmin[t]);
     ix.dmax[t] = (double)ordered_to_float(hmax[t]);
@@ -1193,7 +1202,7 @@ void build(sj_index &ix, const float *points, hipStream_t s) {
         make_geometry(ix, k0, g))
       have = all_adjacent = true;
     const uint32_t unit = ix.opt.precision == SJ_PREC_FP32
-                              ? mx32_queries(ix.dp)
+                              ? mx32_live_queries(ix.dp)
                               : ix.batch_job ? 32u * (uint32_t)mfma_qb(mfma_kp(d))
                                              : mfma_wg_queries(mfma_kp(d));
     // a result batch holds a share of each cell's queries (Section 3.2.2 uses at
@@ -1258,7 +1267,7 @@ void build(sj_index &ix, const float *points, hipStream_t s) {
   ix.n_runs_full = build_runs(ix, 0, ix.run_off_full, ix.runs_full, t, s);
   // FP32 on the matrix cores for joins of some size with most tile rows live
   ix.mx32 = mx32_in_range(ix) && (double)ix.candidates >= kMx32MinCandidates && mx32_fits(ix) &&
-            live_slot_share(ix, t.cand_sum.as<uint64_t>(), mx32_queries(ix.dp), s) >=
+            live_slot_share(ix, t.cand_sum.as<uint64_t>(), mx32_live_queries(ix.dp), s) >=
                 kMx32LiveSlotShareMin;
   if (ix.mx32) {
     ix.info.fp32_form = SJ_FP32_NORM;
@@ -1469,7 +1478,7 @@ void build_query(sj_index &q, const sj_index &E, const float *queries, hipStream
   // as for an index, over the query cells; an index joined on the matrix cores
   // has no norm tables, so its small query sets take the difference form
   q.mx32 = E.mx32 && (double)q.candidates >= kMx32MinCandidates &&
-           live_slot_share(q, t.cand_sum.as<uint64_t>(), mx32_queries(q.dp), s) >=
+           live_slot_share(q, t.cand_sum.as<uint64_t>(), mx32_live_queries(q.dp), s) >=
                kMx32LiveSlotShareMin;
   if (q.mx32) q.info.fp32_form = SJ_FP32_NORM;
   if (q.mx32 && !mx32_per_wave(q.dp)) mx32_project(q, E, q.n_near, s);
@@ -1569,6 +1578,7 @@ MfmaView mfma_view(const sj_index &ix, const uint2 *runs, const uint32_t *qlist,
 bool debug_undersize();
 int debug_hits_mode();
 int debug_box_mode();
+int debug_lead_mode();
 constexpr uint64_t kBandStart = 1u << 20;       // least band-list slots of a join
 constexpr uint64_t kCountBandStart = 1u << 16;  // and of a sampled count
 // result + band pairs per 32 x 32 tile above which the matrix-core kernels
@@ -1658,6 +1668,15 @@ void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &ru
       x.view.s_lo = np.s_lo * sc * sc;
       x.view.kappa = mx32_kappa(ix.d);
       x.view.tiny = kMx32Tiny;
+      x.view.lead_kappa = mx32_lead_kappa(ix.d);
+      x.view.widen = std::nextafter(
+          (float)(1.0 - 1.01 * (x.view.lead_kappa - x.view.kappa) - 0x1p-21), 0.0f);
+      x.view.lead = 2.1 * x.view.lead_kappa * (2.0 * E.var_sum + np.s_hi) <=
+                                kMx32LeadMax * ix.eps2 &&
+                            (!mx32_per_wave(ix.dp) || (double)ix.candidates >= kMx32LeadMin)
+                        ? 1
+                        : 0;
+      if (const int forced = debug_lead_mode(); forced >= 0) x.view.lead = forced;
       // Pairs are accepted on the split sums only where the vector norm form
       // would be chosen, whose error is larger than theirs on every kind of
       // data; everywhere else FP64 decides every pair that is not rejected
@@ -2215,6 +2234,10 @@ int debug_box_mode() {
   return v && (v[0] == '0' || v[0] == '1') ? v[0] - '0' : -1;
 }
 
+int debug_lead_mode() {
+  const char *v = std::getenv("SJ_DEBUG_LEAD");
+  return v && (v[0] == '0' || v[0] == '1') ? v[0] - '0' : -1;
+}
 int debug_hits_mode() {
   const char *v = std::getenv("SJ_DEBUG_HITS");
   return v && (v[0] == '0' || v[0] == '1') ? v[0] - '0' : -1;

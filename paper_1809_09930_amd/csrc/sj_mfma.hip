@@ -429,8 +429,8 @@ __global__ __launch_bounds__(kBlock) void k_join_mfma_wave(MfmaView v,
   const uint64_t u = (uint64_t)blockIdx.x * kWavesPerBlock + w;
   if (u >= n_wu) return;  // whole wave leaves; no workgroup barrier follows
   const WorkUnit wu = wus[u];
-  Stage st{&stage_mem[w][0], 0u};
-  BandSink bs{v.band, v.band_cap, v.band_cursor, Stage{&band_mem[w][0], 0u}};
+  Stage st{&stage_mem[w][0], 0u, kStage};
+  BandSink bs{v.band, v.band_cap, v.band_cursor, Stage{&band_mem[w][0], 0u, kBandStage}};
   mfma_unit<KP, FMT, SJ_WAVE_QB, HM>(v, wu, st, bs, cinit[w], delta[w], qpos[w], out, capacity,
                                      cursor);
   flush(st, out, capacity, cursor);
@@ -525,8 +525,8 @@ __global__ __launch_bounds__(wg_threads<QB>) void k_join_mfma_wg(
   Queries<KP, FMT, QB> q;
   load_queries<KP, FMT, QB>(v, wu.q0 + w * QB * 32, wu.q1, cinit[w], delta[w], qpos[w], q);
   const KeyForm kf = key_form(v);
-  Stage st{&stage_mem[w][0], 0u};
-  BandSink bs{v.band, v.band_cap, v.band_cursor, Stage{&band_mem[w][0], 0u}};
+  Stage st{&stage_mem[w][0], 0u, kStage};
+  BandSink bs{v.band, v.band_cap, v.band_cursor, Stage{&band_mem[w][0], 0u, kBandStage}};
   wait_loads();
   store(0);
   __syncthreads();
@@ -610,7 +610,7 @@ __global__ __launch_bounds__(kWave) void k_band_recheck_staged(
   __shared__ uint16_t perm[SJ_MAX_DIM];
   const uint32_t l = threadIdx.x;
   for (uint32_t t = l; t < v.d; t += kWave) perm[t] = v.inv_perm[t];
-  Stage st{stage_mem, 0u};
+  Stage st{stage_mem, 0u, kStage};
   const uint64_t total = *band_count;
   const uint64_t count = total < v.band_cap ? total : v.band_cap;
   const uint32_t dv = v.dp / 4;  // 16-byte vectors per row (dp <= DPM, a multiple of 8)
@@ -687,8 +687,8 @@ __global__ __launch_bounds__(kBlock) void k_join_batched(
   const uint32_t w = uniform_u32(threadIdx.x / kWave);
   __shared__ __align__(16) float tables[kWavesPerBlock][96 * SJ_BATCH_QB];
   float *tab = &tables[w][0];
-  Stage st{&stage_mem[w][0], 0u};
-  BandSink bs{band, band_cap, band_cursor, Stage{&band_mem[w][0], 0u}};
+  Stage st{&stage_mem[w][0], 0u, kStage};
+  BandSink bs{band, band_cap, band_cursor, Stage{&band_mem[w][0], 0u, kBandStage}};
   const uint64_t capacity = *capacity_p;
   for (;;) {
     unsigned int u0 = 0;
@@ -729,7 +729,7 @@ __global__ __launch_bounds__(kBlock) void k_band_recheck_batched(
     unsigned long long *__restrict__ cursor, unsigned long long *__restrict__ rechecks) {
   __shared__ uint64_t stage_mem[kWavesPerBlock][kStage];
   const uint32_t w = uniform_u32(threadIdx.x / kWave);
-  Stage st{&stage_mem[w][0], 0u};
+  Stage st{&stage_mem[w][0], 0u, kStage};
   const uint64_t capacity = *capacity_p;
   const uint64_t total = *band_count;
   const uint64_t count = total < band_cap ? total : band_cap;

@@ -36,7 +36,7 @@
 // 4.3e-7, here 7.4e-7) no pair is accepted on this estimate: what the FP32 sum
 // used to accept is now decided in FP64.
 // Measured joins, vector forms before and this: uniform 2M x 16 at S_D 64 505
-// and 131 ms, exponential 2M x 16 at eps 0.03 151 and 42 ms, mixture 515k x 90
+// and 105 ms, exponential 2M x 16 at eps 0.03 151 and 31 ms, mixture 515k x 90
 // 253 and 14.5 ms, mixture 301k x 37 in result batches 177 and 28 ms.  The
 // matrix cores hold about 1.4 PFLOP/s on random FP16 operands here (power), so
 // the products of the 2M x 16 join (0.43 of 2e12 pairs after the box test, 83
@@ -227,7 +227,10 @@ __device__ __forceinline__ void query_slice(const float *__restrict__ row, const
   }
 }
 
-// -Thi and Thi - Tlo of a query with |q~|^2 = n
+// -Thi of the leading product; -Thi and Thi - Tlo of a query with |q~|^2 = n
+__device__ __forceinline__ float lead_bound(const Mx32View &v, double lead_kappa, double n) {
+  return -round_up_f32(v.s_hi - n + 2.1 * lead_kappa * (n + v.s_hi) + v.tiny);
+}
 __device__ __forceinline__ void query_bounds(const Mx32View &v, double n, float &cinit,
                                              float &delta) {
   const double k2 = 2.1 * v.kappa;
@@ -257,14 +260,21 @@ __device__ __forceinline__ void query_bounds(const Mx32View &v, double n, float 
 // whole pass of the 2M x 16 uniform join at 64 neighbours: FP16 105 ms with
 // workgroups of four waves, candidates as rows and a product's minima right
 // behind it, 77 ms with one wave per workgroup and queries as rows, 69 ms with
-// products issued ahead; FP32 141 to 130 ms.
+// products issued ahead; FP32 141 to 130 ms.  With kLead an FP32 tile is the leading
+// product alone, and the second parts (queries' in LDS, candidates' in the gathered
+// rows) come in for the tiles that pass: the registers then hold 8 query blocks (4 at
+// K 32), and half as many candidates are tested and gathered: the join kernels of
+// 2M x 16 uniform 124 to 105 ms, 2M x 16 exponential at eps 0.03 41 to 31 ms, 400k x
+// 20 uniform 22.6 to 14.5 ms.  (With 4 query blocks the leading product alone gave
+// nothing: 122 to 121 ms; nor did rows further ahead: 3, 4 and 6 blocks 123, 128
+// and 133 ms.)
 // ---------------------------------------------------------------------------
 constexpr int kBoxDims = 8;
 constexpr uint32_t kBatch = 512;
 constexpr int kWindows = 4;
 constexpr uint32_t kRingW = 1024;  // >= kBatch - 1 pending + 2 kWindows windows of 64
 
-template <int FMT, int PARTS, int K, int QB>
+template <int FMT, int PARTS, int K, int QB, bool kLead>
 __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *__restrict__ wus,
                                                      uint32_t parts_per_unit,
                                                      uint64_t *__restrict__ out, uint64_t capacity,
@@ -274,10 +284,16 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
   constexpr int RV = PARTS * (K / 8);  // 16-byte vectors per candidate row
   constexpr bool kTwo = PARTS == 2 && K > 16;  // a second accumulator for the small products
   constexpr bool kAccept = PARTS == 1 || K <= 16;
-  __shared__ uint64_t stage_mem[kAccept ? kStage : 1];
-  __shared__ uint64_t band_mem[kBandStage];
-  __shared__ uint32_t ring_mem[kRingW];
-  __shared__ float ring_n_mem[kRingW];
+  static_assert(PARTS == 2 || !kLead, "a second part to leave out");
+  // kLead: 20 KB in all, so that a CU holds eight waves
+  constexpr int kStageN = kLead ? 256 : kStage, kBandN = kLead ? 96 : kBandStage;
+  __shared__ uint64_t stage_mem[kAccept ? kStageN : 1];
+  __shared__ uint64_t band_mem[kBandN];
+  __shared__ __align__(16) uint32_t ring_mem[kRingW];
+  __shared__ float ring_n_mem[kLead ? 1 : kRingW];
+  __shared__ V8 a2_mem[kLead ? QB * KS * kWave : 1];
+  __shared__ float box_mem[kLead ? 2 * kBoxDims : 1];
+  static_assert(!kLead || kRingW >= QB * 32, "the ring holds the leading thresholds at first");
   __shared__ V8 rows_mem[32 * RV];
   __shared__ __align__(16) float cinit_mem[QB * 32];
   __shared__ __align__(16) float delta_mem[QB * 32];
@@ -294,7 +310,8 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
   uint32_t *ring = ring_mem;
   float *ring_n = ring_n_mem;
 
-  V8 A1[QB][KS], A2[PARTS == 2 ? QB : 1][KS];
+  V8 A1[QB][KS], A2[PARTS == 2 && !kLead ? QB : 1][KS];
+  float *const lead_mem = reinterpret_cast<float *>(ring_mem);
   float blo[kBoxDims], bhi[kBoxDims];
 #pragma unroll
   for (int t = 0; t < kBoxDims; ++t) {
@@ -308,14 +325,19 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
     const uint32_t slot = wu.q0 + idx;
     const uint32_t p = live ? (m.qlist ? m.qlist[slot] : slot) : 0u;
     const float *row = m.Xq + (uint64_t)p * dp;
-    float ci, de;
+    float ci, de, li = 0.0f;
     if constexpr (PARTS == 2) {
       double n = 0.0;
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-        query_slice(row, v, (uint32_t)ks * 16 + half * 8, live, A1[j][ks], A2[j][ks], n);
+      for (int ks = 0; ks < KS; ++ks) {
+        V8 second;
+        query_slice(row, v, (uint32_t)ks * 16 + half * 8, live, A1[j][ks], second, n);
+        if constexpr (kLead) a2_mem[(j * KS + ks) * kWave + l] = second;
+        else A2[j][ks] = second;
+      }
       n += __shfl_xor(n, 32);
       query_bounds(v, n, ci, de);
+      if (kLead) li = lead_bound(v, v.lead_kappa, n);
     } else {
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
@@ -325,6 +347,7 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
     }
     if (half == 0) {
       cinit_mem[idx] = live ? ci : __builtin_inff();
+      if (kLead) lead_mem[idx] = live ? li : __builtin_inff();
       delta_mem[idx] = live ? de : 0.0f;
       qpos_mem[idx] = live ? p : 0xffffffffu;
     }
@@ -347,17 +370,23 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
       a = __builtin_fminf(a, __shfl_xor(a, off));
       b = __builtin_fmaxf(b, __shfl_xor(b, off));
     }
-    // (kept in vector registers: an instruction reads one scalar register)
+    // (kept in vector registers: an instruction reads one scalar register; with
+    // kLead they are read again from LDS ahead of each test phase)
     blo[t] = a;
     bhi[t] = b;
+    if (kLead && l == 0) {
+      box_mem[t] = a;
+      box_mem[kBoxDims + t] = b;
+    }
   }
   __builtin_amdgcn_wave_barrier();
   float16v c0[QB];
 #pragma unroll
-  for (int j = 0; j < QB; ++j) c0[j] = rows_init(&cinit_mem[j * 32], half);
+  for (int j = 0; j < QB; ++j) c0[j] = rows_init(&(kLead ? lead_mem : cinit_mem)[j * 32], half);
 
-  Stage st{&stage_mem[0], 0u};
-  BandSink bs{m.band, m.band_cap, m.band_cursor, Stage{&band_mem[0], 0u}};
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the ring follows in the same memory
+  Stage st{&stage_mem[0], 0u, kStageN};
+  BandSink bs{m.band, m.band_cap, m.band_cursor, Stage{&band_mem[0], 0u, kBandN}};
   uint64_t n_skip = 0;
   const KeyForm kf{m.key_hi, m.pshift, m.symmetric != 0};
 
@@ -375,7 +404,7 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
   struct Window {
     uint32_t c, n;  // first position, length (0: the stream is done)
     f32x4 x0, x1;   // this lane's candidate: its first 8 dimensions
-    float nn;       // and its reject value
+    float nn;       // and its reject value (kLead: read with the rows)
   };
   auto load_window = [&](Window &x) __attribute__((always_inline)) {
     x.n = c < ce ? (ce - c < (uint32_t)kWave ? ce - c : (uint32_t)kWave) : 0u;
@@ -383,7 +412,7 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
     const uint32_t p = x.c + (l < x.n ? l : 0u);
     x.x0 = reinterpret_cast<const f32x4 *>(m.box0)[p];
     x.x1 = reinterpret_cast<const f32x4 *>(m.box1)[p];
-    x.nn = v.nn[p];
+    if (!kLead) x.nn = v.nn[p];
     c += x.n;
     normalise();
   };
@@ -409,7 +438,7 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
     if ((km >> l) & 1ull) {
       const uint32_t at = (head + cnt + lanes_below(km)) % kRingW;
       ring[at] = x.c + l;
-      ring_n[at] = x.nn;
+      if (!kLead) ring_n[at] = x.nn;
     }
     cnt += (uint32_t)__builtin_popcountll(km);
   };
@@ -425,6 +454,7 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
   constexpr uint32_t kSwz = RV < 8 ? RV - 1 : 7;
   struct Rows {
     V8 x[RT];
+    float nn;     // kLead: reject value of this column's candidate
     uint32_t at;  // first ring entry
   };
   auto load_rows = [&](Rows &q) __attribute__((always_inline)) {
@@ -435,11 +465,12 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
       const uint32_t pos = ring[(head + row) % kRingW];
       q.x[i] = XS[(uint64_t)pos * RV + ((e % RV) ^ (row & kSwz))];
     }
+    if (kLead) q.nn = v.nn[ring[(head + col) % kRingW]];
     head += 32;
     __builtin_amdgcn_sched_barrier(0);  // issued here, ahead of the tiles
   };
   struct Block {
-    V8 b[PARTS][KS];
+    V8 b[kLead ? 1 : PARTS][KS];
     float an;
     uint32_t cp;
   };
@@ -449,18 +480,35 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
     for (int i = 0; i < RT; ++i) t[(uint32_t)i * kWave + l] = q.x[i];
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int i = 0; i < PARTS; ++i)
+    for (int i = 0; i < (kLead ? 1 : PARTS); ++i)
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
         b.b[i][ks] = t[col * RV + (((uint32_t)(i * (K / 8) + 2 * ks) + half) ^ (col & kSwz))];
     const uint32_t at = (q.at + col) % kRingW;
-    b.an = ring_n[at];
+    b.an = kLead ? q.nn : ring_n[at];
     b.cp = ring[at];
     __builtin_amdgcn_wave_barrier();
   };
-  // tile j of a block
-  auto product = [&](int j, const Block &cur) __attribute__((always_inline)) {
+  // tile j of a block from the leading parts alone
+  auto lead = [&](int j, const Block &cur) __attribute__((always_inline)) {
     float16v acc = c0[j];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) acc = Mat<FMT>::mfma(A1[j][ks], cur.b[0][ks], acc);
+    return acc;
+  };
+  // and from all products
+  auto product = [&](int j, const Block &cur) __attribute__((always_inline)) {
+    float16v acc = kLead ? rows_init(&cinit_mem[j * 32], half) : c0[j];
+    // (kLead: the second parts wait in LDS, the block's rows until the next block's)
+    auto a2 = [&](int ks) {
+      if constexpr (kLead) return a2_mem[(j * KS + ks) * kWave + l];
+      else return A2[j][ks];
+    };
+    auto b2 = [&](int ks) {
+      if constexpr (kLead)
+        return rows_mem[col * RV + (((uint32_t)(K / 8 + 2 * ks) + half) ^ (col & kSwz))];
+      else return cur.b[PARTS - 1][ks];
+    };
     if constexpr (PARTS == 1) {
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) acc = Mat<FMT>::mfma(A1[j][ks], cur.b[0][ks], acc);
@@ -470,35 +518,42 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
       for (int e = 0; e < 16; ++e) lo[e] = 0.0f;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        lo = Mat<FMT>::mfma(A1[j][ks], cur.b[PARTS - 1][ks], lo);
+        lo = Mat<FMT>::mfma(A1[j][ks], b2(ks), lo);
         acc = Mat<FMT>::mfma(A1[j][ks], cur.b[0][ks], acc);
-        lo = Mat<FMT>::mfma(A2[j][ks], cur.b[0][ks], lo);
+        lo = Mat<FMT>::mfma(a2(ks), cur.b[0][ks], lo);
       }
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[e] += lo[e];
     } else {
-      acc = Mat<FMT>::mfma(A1[j][0], cur.b[PARTS - 1][0], acc);
-      acc = Mat<FMT>::mfma(A2[j][0], cur.b[0][0], acc);
+      acc = Mat<FMT>::mfma(A1[j][0], b2(0), acc);
+      acc = Mat<FMT>::mfma(a2(0), cur.b[0][0], acc);
       acc = Mat<FMT>::mfma(A1[j][0], cur.b[0][0], acc);
     }
     return acc;
   };
   // The tiles of a block: products and minima without a branch, so that they
-  // overlap; a tile with a hit is computed again for its masks.
+  // overlap; a tile with a hit is computed again for its masks.  With kLead the
+  // first look is at the leading product, whose bound is wider by 2^-10 of the
+  // norms, and only tiles that pass take the other two.
+  auto first_look = [&](int j, const Block &cur) __attribute__((always_inline)) {
+    if constexpr (kLead) return lead(j, cur);
+    else return product(j, cur);
+  };
   auto tiles = [&](const Block &cur) __attribute__((always_inline)) {
     Min16 mn[QB];
     float least = __builtin_inff();
-    float16v acc = product(0, cur);
+    const float an1 = kLead ? __builtin_fmaxf(cur.an * v.widen, cur.an) : cur.an;
+    float16v acc = first_look(0, cur);
 #pragma unroll
     for (int j = 0; j < QB; ++j) {
       float16v next = acc;
-      if (j + 1 < QB) next = product(j + 1, cur);
+      if (j + 1 < QB) next = first_look(j + 1, cur);
       __builtin_amdgcn_sched_barrier(0);  // the next product runs under these minima
       mn[j] = min16(acc);
       least = __builtin_fminf(__builtin_fminf(least, mn[j].a), mn[j].b);
       acc = next;
     }
-    if (ballot(least < cur.an) == 0) return;
+    if (ballot(least < an1) == 0) return;
     const float nacc =
         PARTS == 1 ? cur.an : (cur.an < 0.0f ? cur.an * v.kacc : -__builtin_inff());
 #pragma unroll
@@ -506,7 +561,7 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
       uint64_t hits = 0, within = 0;
 #pragma unroll
       for (int j = j0; j < QB && j < j0 + 4; ++j) {
-        if (ballot(__builtin_fminf(mn[j].a, mn[j].b) < cur.an) == 0) continue;
+        if (ballot(__builtin_fminf(mn[j].a, mn[j].b) < an1) == 0) continue;
         uint32_t h, a;
         tile_masks<kAccept>(product(j, cur), cur.an, nacc, &delta_mem[j * 32], half, h, a);
         hits |= (uint64_t)h << (16 * (j - j0));
@@ -522,6 +577,13 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
   while (cnt || c < ce) {
     {
       // test phase: kWindows windows in flight, all tested before it ends
+      if (kLead) {
+#pragma unroll
+        for (int t = 0; t < kBoxDims; ++t) {
+          blo[t] = box_mem[t];
+          bhi[t] = box_mem[kBoxDims + t];
+        }
+      }
       Window x[kWindows];
 #pragma unroll
       for (int i = 0; i < kWindows; ++i) load_window(x[i]);
@@ -540,7 +602,7 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
       if (l < pad) {
         const uint32_t at = (head + cnt + l) % kRingW;
         ring[at] = m.pad_row;
-        ring_n[at] = -__builtin_inff();
+        if (!kLead) ring_n[at] = -__builtin_inff();  // (as the padding row's)
       }
       cnt += pad;
     }
@@ -640,6 +702,7 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
   __shared__ uint32_t tile_pos[2][CH];
   __shared__ uint32_t ring[kRing];
   __shared__ __align__(16) float cinit[TQ];  // -Thi of each query row
+  __shared__ __align__(16) float linit[TQ];  // and that of the leading product
   __shared__ uint32_t qpos_s[TQ];
   __shared__ __align__(16) float ginit[32];  // -T_g
   __shared__ __align__(16) _Float16 gctr[32][kMx32Dirs];
@@ -674,6 +737,7 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
       float ci, de;
       query_bounds(v, n, ci, de);
       cinit[idx] = live ? ci : __builtin_inff();
+      linit[idx] = live ? lead_bound(v, v.lead_kappa, n) : __builtin_inff();
       qpos_s[idx] = live ? p : 0xffffffffu;
     }
   }
@@ -771,10 +835,11 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
     G[ks] = *reinterpret_cast<const half8 *>(&gctr[col][ks * 16 + half * 8]);
   float16v c0[QB];
 #pragma unroll
-  for (int j = 0; j < QB; ++j) c0[j] = rows_init(&cinit[(w * QB + (uint32_t)j) * 32], half);
+  for (int j = 0; j < QB; ++j)
+    c0[j] = rows_init(&(v.lead ? linit : cinit)[(w * QB + (uint32_t)j) * 32], half);
 
-  Stage none{nullptr, 0u};
-  BandSink bs{m.band, m.band_cap, m.band_cursor, Stage{&band_mem[w][0], 0u}};
+  Stage none{nullptr, 0u, 0u};
+  BandSink bs{m.band, m.band_cap, m.band_cursor, Stage{&band_mem[w][0], 0u, kBandStage}};
   uint64_t n_skip = 0;
   const KeyForm kf{m.key_hi, m.pshift, m.symmetric != 0};
   const half8 *__restrict__ XS = static_cast<const half8 *>(v.XS);
@@ -893,10 +958,24 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
     for (int blk = 0; blk < CH / 32; ++blk) {
       if (ncur <= 32u * (uint32_t)blk) break;
       const half8 *brow = &tile[cur][(blk * 32 + col) * RS + half];
+      const float an = tile_n[cur][blk * 32 + col];
       float16v acc[QB], lo[QB];
+      if (v.lead) {  // the leading product first (see k_join_box)
+        const float an1 = __builtin_fmaxf(an * v.widen, an);
+        bool pass = false;
+#pragma unroll
+        for (int j = 0; j < QB; ++j) acc[j] = c0[j];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+          for (int j = 0; j < QB; ++j) acc[j] = mfma(A1[j][ks], brow[ks * 2], acc[j]);
+#pragma unroll
+        for (int j = 0; j < QB; ++j) pass |= min16(acc[j], __builtin_inff()) < an1;
+        if (ballot(pass) == 0) continue;
+      }
 #pragma unroll
       for (int j = 0; j < QB; ++j) {
-        acc[j] = c0[j];
+        acc[j] = v.lead ? rows_init(&cinit[(w * QB + (uint32_t)j) * 32], half) : c0[j];
 #pragma unroll
         for (int e = 0; e < 16; ++e) lo[j][e] = 0.0f;
       }
@@ -914,7 +993,6 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
       for (int j = 0; j < QB; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[j][e] += lo[j][e];
-      const float an = tile_n[cur][blk * 32 + col];
       bool any = false;
 #pragma unroll
       for (int j = 0; j < QB; ++j) any |= min16(acc[j], __builtin_inff()) < an;
@@ -944,11 +1022,12 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
 
 // query blocks per wave of k_join_box: FP32 at K = 16 and 32, 16 bits likewise
 constexpr int kQbBox16 = 4, kQbBox32 = 2, kQbHalf16 = 8, kQbHalf32 = 4;
+constexpr int kQbLead16 = 8, kQbLead32 = 4;  // FP32 with the leading product first: a unit
 
-template <int FMT, int PARTS, int K, int QB>
+template <int FMT, int PARTS, int K, int QB, bool kLead = false>
 void launch_box(const Mx32View &v, const WorkUnit *wu, uint64_t n_wu, uint32_t parts,
                 uint64_t *out, uint64_t capacity, unsigned long long *cursor, hipStream_t s) {
-  hipLaunchKernelGGL((k_join_box<FMT, PARTS, K, QB>), dim3((uint32_t)(n_wu * parts)), dim3(kWave),
+  hipLaunchKernelGGL((k_join_box<FMT, PARTS, K, QB, kLead>), dim3((uint32_t)(n_wu * parts)), dim3(kWave),
                      0, s, v, wu, parts, out, capacity, cursor);
   SJ_HIP(hipGetLastError());
 }
@@ -983,9 +1062,17 @@ double mx32_kappa(uint32_t d) {
   return 1.02 * (acc + 4.2 * std::ldexp(1.0, -24) + 2.0 * std::ldexp(1.0, -21));
 }
 
+// + what the leading product leaves out: 2 (|q||a| - q1 a1) <= (2^-10 + 2^-21)
+// (|q|^2 + |a|^2)
+double mx32_lead_kappa(uint32_t d) { return mx32_kappa(d) + 0x1p-10 * (1.0 + 0x1p-10); }
+
 uint32_t mx32_k(uint32_t dp) { return (dp + 15) / 16 * 16; }
 
 uint32_t mx32_queries(uint32_t dp) {
+  return dp <= 16 ? 32u * kQbLead16 : dp <= 24 ? 32u * kQbLead32 : 256u;
+}
+
+uint32_t mx32_live_queries(uint32_t dp) {
   return dp <= 16 ? 32u * kQbBox16 : dp <= 24 ? 32u * kQbBox32 : 256u;
 }
 
@@ -1027,14 +1114,18 @@ void launch_box_rows(const float *X, uint64_t n, uint32_t dp, void *box0, void *
 
 void launch_join_mx32(const Mx32Launch &a, hipStream_t s) {
   if (!a.n_wu) return;
-  if (a.n_wu > 0x7fffffffull) fail(SJ_ERR_INVALID_ARG, "too many work units");
+  if (a.n_wu > 0x3fffffffull) fail(SJ_ERR_INVALID_ARG, "too many work units");  // two parts each
   const uint32_t dp = a.view.m.dp;
+  auto box = [&](auto launch, int qb) {
+    launch(a.view, a.wu, a.n_wu, mx32_queries(dp) / (32u * (uint32_t)qb), a.out, a.capacity,
+           a.cursor, s);
+  };
   if (dp <= 16)
-    return launch_box<kFmtF16, 2, 16, kQbBox16>(a.view, a.wu, a.n_wu, 1, a.out, a.capacity,
-                                                a.cursor, s);
+    return a.view.lead ? box(launch_box<kFmtF16, 2, 16, kQbLead16, true>, kQbLead16)
+                       : box(launch_box<kFmtF16, 2, 16, kQbBox16>, kQbBox16);
   if (dp <= 24)
-    return launch_box<kFmtF16, 2, 32, kQbBox32>(a.view, a.wu, a.n_wu, 1, a.out, a.capacity,
-                                                a.cursor, s);
+    return a.view.lead ? box(launch_box<kFmtF16, 2, 32, kQbLead32, true>, kQbLead32)
+                       : box(launch_box<kFmtF16, 2, 32, kQbBox32>, kQbBox32);
   switch (mx32_k(dp)) {
     case 32: launch_g<32>(a, s); break;
     case 48: launch_g<48>(a, s); break;

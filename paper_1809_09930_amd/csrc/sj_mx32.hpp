@@ -14,6 +14,9 @@ struct Mx32View {
   double s_hi, s_lo;
   double kappa;   // mx32_kappa(d)
   double tiny;    // absolute error of FP16 parts below the normal range
+  double lead_kappa;  // mx32_lead_kappa(d)
+  int lead;       // 1: tiles start with the leading product alone (mx32_lead_kappa)
+  float widen;    // factor from a candidate's reject value to that of the leading product
   float kacc;     // 1 + 4 kappa, rounded up; FLT_MAX: no pair is accepted without FP64
   const void *XS;     // [n_pad][2][K] split candidate rows
   const float *nn;    // [n_pad] reject values of the tiles
@@ -42,6 +45,9 @@ struct Mx32Launch {
 // (else a workgroup's), for padded dimension dp.
 uint32_t mx32_k(uint32_t dp);
 uint32_t mx32_queries(uint32_t dp);
+// Query slots over which the share of live ones decides for this form (the least
+// that its waves take at a time).
+uint32_t mx32_live_queries(uint32_t dp);
 bool mx32_per_wave(uint32_t dp);
 // Split rows and reject values of the cell-ordered rows X ([n][dp]); rows
 // n .. n_pad - 1 become padding.
@@ -56,6 +62,8 @@ void launch_mx32_project(const float *X, uint64_t n, uint64_t n_pad, uint32_t dp
 // Planes of the rows' dimensions 0 .. 3 and 4 .. 7 (16 bytes per point each).
 void launch_box_rows(const float *X, uint64_t n, uint32_t dp, void *box0, void *box1,
                      hipStream_t s);
+// Relative error factor of the leading product alone.
+double mx32_lead_kappa(uint32_t d);
 // Relative error factor of the filter for d dimensions.
 double mx32_kappa(uint32_t d);
 void launch_join_mx32(const Mx32Launch &a, hipStream_t s);

@@ -323,6 +323,7 @@ struct sj_index {
   float mx_scale = 1.0f;
   DevBuf box_rows;              // two planes of the points' first 8 dimensions (launch_box_rows)
   double mean_norm2 = 0.0;      // mean squared norm of the points (variance sample)
+  double var_sum = 0.0;         // and around their mean
   DevBuf pivots;                // [d][kPivots] pivot points of the sort key (pb > 0)
   DevBuf pos_pivot;             // nearest pivot of each position
   DevBuf band;                  // deferred recheck list of the matrix-core joins
@@ -392,6 +393,9 @@ int debug_hits_mode();
 // Test hook: SJ_DEBUG_BOX=0 or 1 switches the query-box prefilter of the
 // matrix-core workgroup kernel off or on (default: on up to 32 dimensions).
 int debug_box_mode();
+// Test hook: SJ_DEBUG_LEAD=0 or 1 forces the FP32 matrix-core joins' tiles to start
+// with all products or with the leading one.
+int debug_lead_mode();
 
 template <typename F>
 int guarded(F &&f) {

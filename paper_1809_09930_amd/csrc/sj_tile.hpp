@@ -42,6 +42,7 @@ __device__ __forceinline__ float round_down_f32(double v) {
 struct Stage {
   uint64_t *buf;
   uint32_t cnt;
+  uint32_t size;  // entries of buf, at least 128 (band lists: 64)
 };
 
 __device__ __forceinline__ void flush(Stage &st, uint64_t *__restrict__ out, uint64_t capacity,
@@ -172,7 +173,7 @@ __device__ __forceinline__ void emit_hits(M hits, M within, const uint32_t *qpos
     const uint64_t bm = ballot(band);
     if (bm) {
       const uint32_t nb = (uint32_t)__builtin_popcountll(bm);
-      if (bs.st.cnt + nb > (uint32_t)kBandStage) flush(bs.st, bs.buf, bs.cap, bs.cursor);
+      if (bs.st.cnt + nb > bs.st.size) flush(bs.st, bs.buf, bs.cap, bs.cursor);
       if (band) bs.st.buf[bs.st.cnt + lanes_below(bm)] = key;
       bs.st.cnt += nb;
     }
@@ -182,7 +183,7 @@ __device__ __forceinline__ void emit_hits(M hits, M within, const uint32_t *qpos
         const bool two = acc_ok && kf.sym && qp != cp;
         const uint64_t m2 = ballot(two);
         const uint32_t total = (uint32_t)(__builtin_popcountll(am) + __builtin_popcountll(m2));
-        if (st.cnt + total > (uint32_t)kStage) flush(st, out, capacity, cursor);
+        if (st.cnt + total > st.size) flush(st, out, capacity, cursor);
         const uint32_t off = st.cnt + lanes_below(am) + lanes_below(m2);
         if (acc_ok) {
           st.buf[off] = key;
