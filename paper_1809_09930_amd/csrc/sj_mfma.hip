@@ -659,8 +659,11 @@ __global__ __launch_bounds__(kWave) void k_band_recheck_staged(
 }
 
 // query column blocks per wave of the persistent batched kernel
+// Query blocks per wave: the candidate stream from L2 bounds this kernel, and a
+// block of candidates serves QB tiles (graph of the 256 jobs with 1, 2 and 4:
+// 114, 83 and 76 ms; 150 clustered jobs of up to 100k x 64: 37, 32 and 29 ms).
 #ifndef SJ_BATCH_QB
-#define SJ_BATCH_QB 1
+#define SJ_BATCH_QB 4
 #endif
 
 // Many independent joins in one persistent launch.  Every wave takes
