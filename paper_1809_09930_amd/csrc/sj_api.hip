@@ -371,6 +371,8 @@ constexpr double kMx32Tiny = 0x1p-16;
 // (20k x 16: 0.12 ms, 0.14 with the leading one first; 400k x 20: 22.6 and 14.5).
 constexpr double kMx32LeadMax = 0.1;
 constexpr double kMx32LeadMin = 1073741824.0;
+// hits per tile: 2M x 16 uniform at 0.04 105 ms (124 without), at 0.26 184 (176)
+constexpr double kMx32LeadMaxHits = 0.15;
 constexpr double kMx32MinCandidates = 16777216.0;
 constexpr double kMx32LiveSlotShareMin = 0.4;
 bool mx32_in_range(const sj_index &ix) {
@@ -1673,7 +1675,9 @@ void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &ru
           (float)(1.0 - 1.01 * (x.view.lead_kappa - x.view.kappa) - 0x1p-21), 0.0f);
       x.view.lead = 2.1 * x.view.lead_kappa * (2.0 * E.var_sum + np.s_hi) <=
                                 kMx32LeadMax * ix.eps2 &&
-                            (!mx32_per_wave(ix.dp) || (double)ix.candidates >= kMx32LeadMin)
+                            (!mx32_per_wave(ix.dp) ||
+                             ((double)ix.candidates >= kMx32LeadMin &&
+                              ix.hit_density * 1024.0 < kMx32LeadMaxHits))
                         ? 1
                         : 0;
       if (const int forced = debug_lead_mode(); forced >= 0) x.view.lead = forced;

@@ -666,15 +666,18 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
 // Survivors' positions enter a ring in LDS; chunks of CH of them are staged,
 // split rows and all, into a double-buffered LDS tile that every wave reads.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kRing = 2048;  // >= 63 pending + one window of 1024
+constexpr uint32_t kRing = 2048;  // >= 63 pending + one window of up to 1024
 constexpr int kTestBlocks = 4;    // blocks of 32 candidates that a wave tests at a time
 
 // Tile shapes by K (dimensions padded to 16): waves per workgroup, query row
-// blocks per wave and candidate columns per staged chunk.
+// blocks per wave and candidate columns per staged chunk.  Two blocks per wave
+// halve the LDS reads per product (uniform 400k x 64 27.5 to 22.9 ms, exponential
+// 500k x 45 32.5 to 24.9); above K 64 their registers leave too few waves (515k x
+// 90 14.7 to 19.3).
 template <int K>
 struct Shape {
-  static constexpr int NW = 8;
-  static constexpr int QB = 1;
+  static constexpr int NW = K <= 64 ? 4 : 8;
+  static constexpr int QB = K <= 64 ? 2 : 1;
   static constexpr int CH = K <= 48 ? 64 : 32;
 };
 
