@@ -243,19 +243,18 @@ __global__ __launch_bounds__(kBlock) void k_nearest_pivot(const float *__restric
                                                           const float *__restrict__ table,
                                                           uint8_t *__restrict__ pid) {
   const uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= n) return;
   float s[kPivots];
 #pragma unroll
   for (uint32_t j = 0; j < kPivots; ++j) s[j] = 0.0f;
-  for (uint32_t t = 0; t < d; ++t) {
-    const float x = P[i * d + t];
+  for_row(P, n, d, [&](uint32_t t, float x) {
     const float *q = table + t * kPivots;
 #pragma unroll
     for (uint32_t j = 0; j < kPivots; ++j) {
       const float e = x - q[j];
       s[j] = __builtin_fmaf(e, e, s[j]);
     }
-  }
+  });
+  if (i >= n) return;
   uint32_t best = 0;
   float b = s[0];
 #pragma unroll

@@ -120,6 +120,31 @@ struct WorkUnit {
 };
 static_assert(sizeof(WorkUnit) == 32, "WorkUnit layout");
 
+// f(t, x) for every coordinate t of the thread's row blockIdx.x kBlock + threadIdx.x
+// of P ([n][d]; x is arbitrary past row n).  Rows pass through LDS in slices of 16
+// coordinates: a lane that reads its own row touches a cache line per load, and at
+// 515k x 90 the caches dropped the lines between a line's loads (nearest pivots 0.69
+// to 0.26 ms, projections 0.70 to 0.15).  Every thread of the workgroup must come here.
+template <class F>
+__device__ __forceinline__ void for_row(const float *__restrict__ P, uint64_t n, uint32_t d,
+                                        F &&f) {
+  constexpr uint32_t C = 16;
+  __shared__ float slice[kBlock * (C + 1)];
+  const uint64_t row0 = (uint64_t)blockIdx.x * kBlock;
+  const uint32_t rows = row0 >= n ? 0u : (uint32_t)(n - row0 < kBlock ? n - row0 : kBlock);
+  for (uint32_t t0 = 0; t0 < d; t0 += C) {
+    const uint32_t nc = d - t0 < C ? d - t0 : C;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t i = 0; i < C; ++i) {
+      const uint32_t e = i * kBlock + threadIdx.x, r = e / C, c = e % C;
+      if (r < rows && c < nc) slice[r * (C + 1) + c] = P[(row0 + r) * d + t0 + c];
+    }
+    __syncthreads();
+    for (uint32_t c = 0; c < nc; ++c) f(t0 + c, slice[threadIdx.x * (C + 1) + c]);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Primitives (sj_prims.hip)
 // ---------------------------------------------------------------------------

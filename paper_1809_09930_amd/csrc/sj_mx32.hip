@@ -154,20 +154,18 @@ __global__ __launch_bounds__(kBlock) void k_mx32_project(
     const float *__restrict__ dirs, const float *__restrict__ ctr, float sc,
     half8 *__restrict__ ys, float *__restrict__ pn, float *__restrict__ ye) {
   const uint64_t p = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (p >= n_pad) return;
   float y[kMx32Dirs];
 #pragma unroll
   for (uint32_t j = 0; j < kMx32Dirs; ++j) y[j] = 0.0f;
   double s = 0.0;
-  if (p < n) {
-    for (uint32_t t = 0; t < dp; ++t) {
-      const float x = sc * (X[p * dp + t] - ctr[t]);
-      s += (double)x * (double)x;
+  for_row(X, n, dp, [&](uint32_t t, float xt) {
+    const float x = p < n ? sc * (xt - ctr[t]) : 0.0f;
+    s += (double)x * (double)x;
 #pragma unroll
-      for (uint32_t j = 0; j < kMx32Dirs; ++j)
-        y[j] = __builtin_fmaf(x, dirs[t * kMx32Dirs + j], y[j]);
-    }
-  }
+    for (uint32_t j = 0; j < kMx32Dirs; ++j)
+      y[j] = __builtin_fmaf(x, dirs[t * kMx32Dirs + j], y[j]);
+  });
+  if (p >= n_pad) return;
   double s1 = 0.0;
 #pragma unroll
   for (uint32_t g = 0; g < kMx32Dirs / 8; ++g) {
