@@ -340,7 +340,11 @@ constexpr bool kWuByStretch = SJ_WU_BY_STRETCH != 0;  // join work units in stre
 #endif
 
 uint64_t default_budget();
+bool debug_groups();
 constexpr bool kFp32CellGroups = SJ_FP32_CELL_GROUPS != 0;
+// Groups save some 3 % of a join (5M x 18 mixture 52.7 to 51.0 ms) and cost four
+// copies and two waits (0.08 ms): from joins of a few milliseconds on.
+constexpr double kGroupMinCandidates = 8589934592.0;
 constexpr double kLookupsPerSec = 2.0e10;
 constexpr double kPairsPerSec = 1.5e12;
 // The matrix-core joins take ten times the pairs (2M x 16 exponential FP32
@@ -1303,7 +1307,8 @@ void build(sj_index &ix, const float *points, hipStream_t s) {
   }
   if (!ix.batch_job && ix.opt.precision == SJ_PREC_FP32) {
     // FP32 units of small cells from groups of neighbouring cells
-    ix.wu_grouped = kFp32CellGroups && ix.small_cells && !su;
+    ix.wu_grouped = kFp32CellGroups && ix.small_cells && !su &&
+                    ((double)ix.candidates >= kGroupMinCandidates || debug_groups());
     if (ix.wu_grouped) build_cell_groups(ix, ix.tq, ix.groups, s);
     const CellGroups *grp = ix.wu_grouped ? &ix.groups : nullptr;
     ix.n_wu = build_workunits(ix, 1, nullptr, 0, grp ? grp->run_off : ix.run_off_sym,
@@ -1827,8 +1832,9 @@ void sort_pairs(sj_index &ix, DevBuf &a, DevBuf &b, uint64_t cnt, hipStream_t s,
 }
 
 // Single batch: symmetric join of all work units into device memory.
+constexpr uint64_t kPairSlack = 1u << 20;  // result slots beyond the estimate
 void run_single(sj_index &ix, uint64_t est, hipStream_t s) {
-  uint64_t cap = est + est / 8 + (1u << 20);
+  uint64_t cap = est + est / 8 + kPairSlack;
   if (debug_undersize()) cap = std::max<uint64_t>(1, est / 16);
   float ms_join = 0.0f;
   DevBuf other;
@@ -2059,8 +2065,16 @@ void run(sj_index &ix, hipStream_t s) {
     ix.info.batches = 0;
   } else {
     float ms_est = 0.0f;
-    const uint64_t est = estimate_pairs(ix, s, &ms_est);
     const uint64_t budget = ix.opt.mem_budget ? ix.opt.mem_budget : default_budget();
+    // where all candidate pairs fit the least result buffer (and the least band
+    // list) there is nothing to size by a sampled count (1000 x 8: 0.1 ms of 0.6)
+    const bool fits = !ix.opt.batch_pairs && ix.opt.min_batches <= 1 && !debug_undersize() &&
+                      ix.candidates <= std::min(kPairSlack, budget / 40);
+    if (fits) {
+      ix.band_hint = 0;
+      ix.hit_density = 0.0;
+    }
+    const uint64_t est = fits ? 0 : estimate_pairs(ix, s, &ms_est);
     // a single batch holds the keys twice (sort ping-pong) plus sort scratch
     const uint64_t fit = budget / 20;
     uint64_t per_batch = ix.opt.batch_pairs ? ix.opt.batch_pairs : fit;
@@ -2238,6 +2252,10 @@ int debug_box_mode() {
   return v && (v[0] == '0' || v[0] == '1') ? v[0] - '0' : -1;
 }
 
+bool debug_groups() {
+  const char *v = std::getenv("SJ_DEBUG_GROUPS");
+  return v && v[0] == '1';
+}
 int debug_lead_mode() {
   const char *v = std::getenv("SJ_DEBUG_LEAD");
   return v && (v[0] == '0' || v[0] == '1') ? v[0] - '0' : -1;

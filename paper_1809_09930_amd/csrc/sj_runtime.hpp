@@ -393,6 +393,9 @@ int debug_hits_mode();
 // Test hook: SJ_DEBUG_BOX=0 or 1 switches the query-box prefilter of the
 // matrix-core workgroup kernel off or on (default: on up to 32 dimensions).
 int debug_box_mode();
+// Test hook: SJ_DEBUG_GROUPS=1 makes small FP32 joins of small cells take their units
+// from groups of cells too.
+bool debug_groups();
 // Test hook: SJ_DEBUG_LEAD=0 or 1 forces the FP32 matrix-core joins' tiles to start
 // with all products or with the leading one.
 int debug_lead_mode();

@@ -33,3 +33,17 @@ def test_a_cell_per_point(n):
     x = np.random.default_rng(n).permutation(1 << 16)[:n].astype(np.float32) / np.float32(1 << 16)
     print("case cells", n, flush=True)
     assert_same_as_oracle(np.ascontiguousarray(x[:, None]), 0.5 / (1 << 16), k=1)
+
+
+@pytest.mark.parametrize("groups", ["0", "1"])
+@pytest.mark.parametrize("n", [300, 1023, 1024, 1025, 5000])
+def test_without_sampled_count(n, groups, monkeypatch):
+    """All pairs of up to 1024 points fit the least result buffer (every pair is a
+    result here), more go through the sampled count; units of single cells and of
+    groups of them."""
+    monkeypatch.setenv("SJ_DEBUG_GROUPS", groups)
+    P = datagen.offgrid("uniform64", n, 4, seed=850 + n)
+    print("case count", n, groups, flush=True)
+    assert_same_as_oracle(P, 10.0 * float(np.ptp(P)) if n <= 1025 else calibrated(P, 9, stride=3))
+    assert_same_as_oracle(P, calibrated(P, 5, stride=3), precision="bf16")
+    assert_same_as_oracle(P, calibrated(P, 5, stride=3), mem_budget=1000)
