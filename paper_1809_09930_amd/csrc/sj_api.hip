@@ -1203,8 +1203,11 @@ void build(sj_index &ix, const float *points, hipStream_t s) {
     // (the builds of batched jobs run side by side: only their kernels count)
     const double probe_sec =
         (ix.batch_job ? 0.3 : 1.0) * (kProbeSec + kProbeSecPerPoint * (double)n);
-    // even every pair of points takes less than counting another grid
-    if (matrix && !have && 0.5 * (double)n * (double)n / kMatrixPairsPerSec < 2.0 * probe_sec &&
+    // even every pair of points takes less than counting another grid (an FP32 join
+    // may still turn out to be the vector join's)
+    const double least_rate =
+        ix.opt.precision == SJ_PREC_FP32 ? kPairsPerSec : kMatrixPairsPerSec;
+    if (matrix && !have && 0.5 * (double)n * (double)n / least_rate < 2.0 * probe_sec &&
         make_geometry(ix, k0, g))
       have = all_adjacent = true;
     const uint32_t unit = ix.opt.precision == SJ_PREC_FP32
