@@ -675,10 +675,9 @@ void build_cell_groups(sj_index &ix, uint32_t max_q, CellGroups &g, hipStream_t 
 
 // Work units over the given runs; qlist == nullptr: contiguous queries.
 // Returns the number of units; *eval receives the evaluated pair count.
-// With by_stretch, the units are ordered by their stretch index within
-// their query block, then by block: units that run at the same time then
-// read overlapping candidate rows (shared in the caches) instead of every
-// stretch of one block.
+// With by_stretch, the units are ordered by their stretch, then by block: units
+// that run at the same time then read the same candidate rows (shared in the
+// caches) instead of every stretch of one block.
 // SORTIDU search parameters of a handle (its sort keys' u part).
 USearch usearch_of(const sj_index &ix) {
   const Geometry &g = ix.geom;
@@ -777,9 +776,10 @@ uint64_t build_workunits(sj_index &ix, int sym, const uint32_t *qlist, uint64_t 
     keys[1].alloc(n_wu * 8);
     launch_wu_fill(n_wu, nqb, tc, blocks.as<QBlock>(), r_runs, before.as<uint32_t>(),
                    units.as<uint32_t>(), unordered.as<WorkUnit>(), keys[0].as<uint64_t>(), s);
-    // stable LSD sort on the stretch index (high word) keeps block order
+    // stable LSD sort on the stretch (high word) keeps block order
     std::vector<int> sh;
-    for (uint32_t b = 0; b < bits_for(n_wu - 1); b += 8) sh.push_back(32 + (int)b);
+    const uint64_t last = 2 * entries_of(ix).n / tc + 1;  // stretches end below this one
+    for (uint32_t b = 0; b < bits_for(last); b += 8) sh.push_back(32 + (int)b);
     rtmp.alloc(radix_tmp_bytes(n_wu));
     uint64_t *kb[2] = {keys[0].as<uint64_t>(), keys[1].as<uint64_t>()};
     radix_sort_u64(kb, nullptr, n_wu, sh.data(), (int)sh.size(), rtmp.p, s);
