@@ -210,6 +210,8 @@ __global__ __launch_bounds__(kBlock) void k_mfma_maxima(uint64_t n, const double
 //     E' = gamma_{K+4}(2^-23) (1.01 (hi_root^2 + n_b) + N + F + 2 |b~| Rq) + F + 2^-120
 //   (N, Rq, F = maxima of n_a, |a~| and |n_a - fl32(n_a)|; |Thi| <= hi_root^2 +
 //   n_b up to the last percent), and S_q = n_a - 2 a~.b~ + n_b.
+//   (Thi is at most FLT_MAX, so that a tile starts from finite values: every pair
+//   has n_a - 2 b~.a~ <= 3 N, and N is below 2e30.)
 // Then
 //   Thi(b) = (sqrt(s_hi) + Delta_b)^2 - n_b + E'   (canonical accept => a hit)
 //   Tlo(b) = (max(0, sqrt(s_lo) - Delta_b))^2 - n_b - E'   (at or below: accept)
@@ -245,7 +247,7 @@ __global__ __launch_bounds__(kBlock) void k_mfma_thresholds(
   } else {
     tlo_v = (lo_root * lo_root - nb - E) - m * (lo_root * lo_root + nb + E);
   }
-  thi[p] = round_up_f32(thi_v);
+  thi[p] = __builtin_fminf(round_up_f32(thi_v), FLT_MAX);
   tlo[p] = round_down_f32(tlo_v);
 }
 
