@@ -6,6 +6,7 @@
 //   non-empty cells -> adjacent cells by binary search in an LDS-staged key
 //   table -> candidate runs -> work units for the distance kernels.
 #include "sj_index.hpp"
+#include "sj_launch.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -519,32 +520,36 @@ __global__ __launch_bounds__(kBlock) void k_runs(int pass, int sym, uint64_t nce
                                                  const uint32_t *__restrict__ run_off,
                                                  uint2 *__restrict__ runs) {
   const uint32_t l = threadIdx.x % G;
-  const uint64_t A = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / G;
-  const bool live = A < ncell;
-  const uint32_t b0 = live ? nbr_off[A] : 0u, b1 = live ? nbr_off[A + 1] : 0u;
-  const uint32_t w = pass && live ? run_off[A] : 0u;
   const uint32_t shift = lane_id() - l;  // this group's lanes in a wave's ballot
   const uint64_t mask = (G == 64 ? ~0ull : (1ull << (G & 63)) - 1ull) << shift;
   const uint64_t below = mask & ((1ull << lane_id()) - 1ull);
-  uint32_t ns = 0, ne = 0;  // starts and ends so far
-  for (uint32_t base = b0; ballot(base < b1) != 0; base += G) {
-    const uint32_t i = base + l;
-    const bool in = i < b1;
-    const uint32_t B = in ? nbr_cell[i] : 0u;
-    const bool ok = in && !(sym && B < A);
-    const uint32_t prev = ok && i > b0 ? nbr_cell[i - 1] : 0xffffffffu;
-    const uint32_t next = ok && i + 1 < b1 ? nbr_cell[i + 1] : 0xffffffffu;
-    const bool start = ok && (prev == 0xffffffffu || prev + 1 != B || (sym && prev < A));
-    const bool end = ok && (next == 0xffffffffu || next != B + 1);
-    const uint64_t ms = ballot(start), me = ballot(end);
-    if (pass) {
-      if (start) runs[w + ns + (uint32_t)__builtin_popcountll(ms & below)].x = cell_start[B];
-      if (end) runs[w + ne + (uint32_t)__builtin_popcountll(me & below)].y = cell_start[B + 1];
+  // (A0: the wave's first list)
+  for (uint64_t A0 = ((uint64_t)blockIdx.x * kBlock + (threadIdx.x & ~63u)) / G; A0 < ncell;
+       A0 += (uint64_t)gridDim.x * (kBlock / G)) {
+    const uint64_t A = A0 + lane_id() / G;
+    const bool live = A < ncell;
+    const uint32_t b0 = live ? nbr_off[A] : 0u, b1 = live ? nbr_off[A + 1] : 0u;
+    const uint32_t w = pass && live ? run_off[A] : 0u;
+    uint32_t ns = 0, ne = 0;  // starts and ends so far
+    for (uint32_t base = b0; ballot(base < b1) != 0; base += G) {
+      const uint32_t i = base + l;
+      const bool in = i < b1;
+      const uint32_t B = in ? nbr_cell[i] : 0u;
+      const bool ok = in && !(sym && B < A);
+      const uint32_t prev = ok && i > b0 ? nbr_cell[i - 1] : 0xffffffffu;
+      const uint32_t next = ok && i + 1 < b1 ? nbr_cell[i + 1] : 0xffffffffu;
+      const bool start = ok && (prev == 0xffffffffu || prev + 1 != B || (sym && prev < A));
+      const bool end = ok && (next == 0xffffffffu || next != B + 1);
+      const uint64_t ms = ballot(start), me = ballot(end);
+      if (pass) {
+        if (start) runs[w + ns + (uint32_t)__builtin_popcountll(ms & below)].x = cell_start[B];
+        if (end) runs[w + ne + (uint32_t)__builtin_popcountll(me & below)].y = cell_start[B + 1];
+      }
+      ns += (uint32_t)__builtin_popcountll(ms & mask);
+      ne += (uint32_t)__builtin_popcountll(me & mask);
     }
-    ns += (uint32_t)__builtin_popcountll(ms & mask);
-    ne += (uint32_t)__builtin_popcountll(me & mask);
+    if (!pass && live && l == 0) run_count[A] = ns;
   }
-  if (!pass && live && l == 0) run_count[A] = ns;
 }
 
 // Union of the candidate runs of each group of consecutive cells
@@ -631,30 +636,33 @@ __global__ __launch_bounds__(kBlock) void k_wu_cells(
     const uint2 *__restrict__ runs, uint32_t *__restrict__ nqb, uint64_t *__restrict__ run_total,
     uint32_t *__restrict__ before) {
   const uint32_t l = threadIdx.x % G;
-  const uint64_t A = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) / G;
-  const bool live = A < nlist;
-  const uint32_t r0 = live ? run_off[A] : 0u, r1 = live ? run_off[A + 1] : 0u;
-  uint32_t total = 0;
-  for (uint32_t base = r0; ballot(base < r1) != 0; base += G) {
-    const uint32_t r = base + l;
-    const uint2 x = r < r1 ? runs[r] : make_uint2(0u, 0u);
-    const uint32_t len = x.y - x.x;
-    uint32_t inc = len;
+  for (uint64_t A0 = ((uint64_t)blockIdx.x * kBlock + (threadIdx.x & ~63u)) / G; A0 < nlist;
+       A0 += (uint64_t)gridDim.x * (kBlock / G)) {
+    const uint64_t A = A0 + lane_id() / G;
+    const bool live = A < nlist;
+    const uint32_t r0 = live ? run_off[A] : 0u, r1 = live ? run_off[A + 1] : 0u;
+    uint32_t total = 0;
+    for (uint32_t base = r0; ballot(base < r1) != 0; base += G) {
+      const uint32_t r = base + l;
+      const uint2 x = r < r1 ? runs[r] : make_uint2(0u, 0u);
+      const uint32_t len = x.y - x.x;
+      uint32_t inc = len;
 #pragma unroll
-    for (int off = 1; off < G; off <<= 1) {
-      const uint32_t u = __shfl_up(inc, off, G);
-      if (l >= (uint32_t)off) inc += u;
+      for (int off = 1; off < G; off <<= 1) {
+        const uint32_t u = __shfl_up(inc, off, G);
+        if (l >= (uint32_t)off) inc += u;
+      }
+      if (r < r1) before[r] = total + inc - len;
+      total += __shfl(inc, G - 1, G);
     }
-    if (r < r1) before[r] = total + inc - len;
-    total += __shfl(inc, G - 1, G);
+    if (!live || l != 0) continue;
+    if (nqb) {
+      uint32_t qa, qb;
+      cell_query_slots(A, cell_start, qlist, nq, &qa, &qb);
+      nqb[A] = (qb - qa + tq - 1) / tq;
+    }
+    run_total[A] = total;
   }
-  if (!live || l != 0) return;
-  if (nqb) {
-    uint32_t qa, qb;
-    cell_query_slots(A, cell_start, qlist, nq, &qa, &qb);
-    nqb[A] = (qb - qa + tq - 1) / tq;
-  }
-  run_total[A] = total;
 }
 
 // Query block t: its cell (binary search over the scanned block counts),
@@ -921,12 +929,6 @@ __global__ void k_cell_products(uint64_t ncell, const uint32_t *__restrict__ cel
 }
 
 inline uint32_t blocks_for(uint64_t n) { return (uint32_t)((n + kBlock - 1) / kBlock); }
-// Workgroups of a grid-stride launch over n elements: one element per
-// thread up to 2^20 workgroups (a dispatch holds at most 2^32 work-items).
-inline uint32_t stride_blocks(uint64_t n) {
-  return (uint32_t)std::min<uint64_t>((n + kBlock - 1) / kBlock, 1u << 20);
-}
-
 // Pairs per row of sorted keys (row = key >> 32): counts[i] += the number
 // of keys of row i.  Each wave adds one count per row it holds: the lane
 // that starts a run of equal rows inside the wave adds the run's length.
@@ -1073,7 +1075,8 @@ void launch_neighbors(int pass, const uint64_t *qkey, uint64_t nq, const uint64_
 // Lanes per list of the kernels above: a wave for long lists, 8 lanes for lists
 // of a few entries, where a wave per list would leave most lanes idle (both forms
 // take one step per list up to 8 entries; from 16 on the wave takes half as many
-// or fewer).
+// or fewer).  Strided launches: 64 lanes for each of 2^26 lists pass what a dispatch
+// holds.
 constexpr uint64_t kLongLists = 16;  // entries per list, on average
 
 void launch_runs(int pass, int sym, uint64_t ncell, uint64_t n_nbr, const uint32_t *cell_start,
@@ -1081,10 +1084,10 @@ void launch_runs(int pass, int sym, uint64_t ncell, uint64_t n_nbr, const uint32
                  const uint32_t *run_off, uint2 *runs, hipStream_t s) {
   if (!ncell) return;
   if (n_nbr >= kLongLists * ncell)
-    hipLaunchKernelGGL(k_runs<64>, dim3(blocks_for(ncell * 64)), dim3(kBlock), 0, s, pass, sym,
+    hipLaunchKernelGGL(k_runs<64>, dim3(stride_blocks(ncell * 64)), dim3(kBlock), 0, s, pass, sym,
                        ncell, cell_start, nbr_off, nbr_cell, run_count, run_off, runs);
   else
-    hipLaunchKernelGGL(k_runs<8>, dim3(blocks_for(ncell * 8)), dim3(kBlock), 0, s, pass, sym,
+    hipLaunchKernelGGL(k_runs<8>, dim3(stride_blocks(ncell * 8)), dim3(kBlock), 0, s, pass, sym,
                        ncell, cell_start, nbr_off, nbr_cell, run_count, run_off, runs);
   SJ_HIP(hipGetLastError());
 }
@@ -1104,10 +1107,10 @@ void launch_wu_cells(uint64_t nlist, uint64_t n_runs, uint32_t tq, const uint32_
                      hipStream_t s) {
   if (!nlist) return;
   if (n_runs >= kLongLists * nlist)
-    hipLaunchKernelGGL(k_wu_cells<64>, dim3(blocks_for(nlist * 64)), dim3(kBlock), 0, s, nlist, tq,
+    hipLaunchKernelGGL(k_wu_cells<64>, dim3(stride_blocks(nlist * 64)), dim3(kBlock), 0, s, nlist, tq,
                        cell_start, qlist, nq, run_off, runs, nqb, run_total, before);
   else
-    hipLaunchKernelGGL(k_wu_cells<8>, dim3(blocks_for(nlist * 8)), dim3(kBlock), 0, s, nlist, tq,
+    hipLaunchKernelGGL(k_wu_cells<8>, dim3(stride_blocks(nlist * 8)), dim3(kBlock), 0, s, nlist, tq,
                        cell_start, qlist, nq, run_off, runs, nqb, run_total, before);
   SJ_HIP(hipGetLastError());
 }

@@ -29,6 +29,7 @@
 #include <type_traits>
 
 #include "sj_internal.hpp"
+#include "sj_launch.hpp"
 
 namespace sj {
 
@@ -673,7 +674,8 @@ __global__ __launch_bounds__(kBlock) void k_unpack(const uint64_t *__restrict__ 
 }
 
 template <int DP, int kRq, bool kNorm, bool kSC>
-void launch_rq(const JoinLaunch &a, uint32_t grid, hipStream_t s) {
+void launch_rq(const JoinLaunch &a, hipStream_t s) {
+  const uint32_t grid = (uint32_t)((a.n_wu + kWavesPerBlock - 1) / kWavesPerBlock);
   if (a.count_only)
     hipLaunchKernelGGL((k_count_fp32<DP, kRq, kNorm, kSC>), dim3(grid), dim3(kBlock), 0, s, a.X,
                        a.orig_id, a.Xq, a.qid, a.inv_perm, a.wu, a.n_wu, a.runs, a.qlist, a.d,
@@ -690,15 +692,18 @@ void launch_rq(const JoinLaunch &a, uint32_t grid, hipStream_t s) {
 // Queries per lane: the class default, or one when the cells are small
 // (a.rq == 1: a cell's queries would leave most lanes of a wider unit idle).
 template <int DP, bool kNorm, bool kSC>
-void launch_form(const JoinLaunch &a, hipStream_t s) {
-  const uint32_t grid = (uint32_t)((a.n_wu + kWavesPerBlock - 1) / kWavesPerBlock);
-  if (grid == 0) return;
+void launch_form(const JoinLaunch &all, hipStream_t s) {
   constexpr int kRq = kNorm ? (DP <= 24 ? SJ_NORM_RQ_SMALL : (DP <= 64 ? SJ_NORM_RQ_MID : 1))
                             : (DP <= 24 ? SJ_FP32_RQ_SMALL : (DP <= 64 ? SJ_FP32_RQ_MID : 1));
-  if (kRq != 1 && a.rq == 1)
-    launch_rq<DP, 1, kNorm, kSC>(a, grid, s);
-  else
-    launch_rq<DP, kRq, kNorm, kSC>(a, grid, s);
+  for_unit_launches(all.n_wu, kWave, [&](uint64_t u, uint64_t n) {
+    JoinLaunch a = all;
+    a.wu += u;
+    a.n_wu = n;
+    if (kRq != 1 && a.rq == 1)
+      launch_rq<DP, 1, kNorm, kSC>(a, s);
+    else
+      launch_rq<DP, kRq, kNorm, kSC>(a, s);
+  });
 }
 
 template <int DP>

@@ -25,6 +25,7 @@
 // over 16 values (v_min3) and one compare; only tiles with a hit enter the
 // per-element path (tile_masks, emit_hits in sj_tile.hpp).
 #include "sj_internal.hpp"
+#include "sj_launch.hpp"
 #include "sj_mfma.hpp"
 #include "sj_mx32.hpp"
 #include "sj_tile.hpp"
@@ -817,26 +818,26 @@ __global__ __launch_bounds__(kBlock) void k_pos_to_id(uint64_t *__restrict__ key
 
 template <int KP, int FMT>
 void launch_kp(const MfmaLaunch &a, hipStream_t s) {
-  const uint32_t grid = (uint32_t)((a.n_wu + kWavesPerBlock - 1) / kWavesPerBlock);
-  if (!grid) return;
+  constexpr int QB = wg_qb<KP>;
   const MfmaView v = a.view;
-  if (a.per_wave) {  // one wave per work unit
-    if (a.hits_frequent)
+  // one wave per work unit, or one workgroup
+  for_unit_launches(a.n_wu, a.per_wave ? kWave : wg_threads<QB>, [&](uint64_t u, uint64_t n) {
+    const WorkUnit *wu = a.wu + u;
+    const uint32_t grid = (uint32_t)((n + kWavesPerBlock - 1) / kWavesPerBlock);
+    if (a.per_wave && a.hits_frequent)
       hipLaunchKernelGGL((k_join_mfma_wave<KP, FMT, kHitsFrequent>), dim3(grid), dim3(kBlock), 0,
-                         s, v, a.wu, a.n_wu, a.out, a.capacity, a.cursor);
-    else
+                         s, v, wu, n, a.out, a.capacity, a.cursor);
+    else if (a.per_wave)
       hipLaunchKernelGGL((k_join_mfma_wave<KP, FMT, kHitsRare>), dim3(grid), dim3(kBlock), 0, s,
-                         v, a.wu, a.n_wu, a.out, a.capacity, a.cursor);
-  } else {  // one workgroup per work unit
-    constexpr int QB = wg_qb<KP>;
-    if (a.hits_frequent)
-      hipLaunchKernelGGL((k_join_mfma_wg<KP, FMT, QB, kHitsFrequent>), dim3((uint32_t)a.n_wu),
-                         dim3(wg_threads<QB>), 0, s, v, a.wu, a.n_wu, a.out, a.capacity, a.cursor);
+                         v, wu, n, a.out, a.capacity, a.cursor);
+    else if (a.hits_frequent)
+      hipLaunchKernelGGL((k_join_mfma_wg<KP, FMT, QB, kHitsFrequent>), dim3((uint32_t)n),
+                         dim3(wg_threads<QB>), 0, s, v, wu, n, a.out, a.capacity, a.cursor);
     else
-      hipLaunchKernelGGL((k_join_mfma_wg<KP, FMT, QB, kHitsRare>), dim3((uint32_t)a.n_wu),
-                         dim3(wg_threads<QB>), 0, s, v, a.wu, a.n_wu, a.out, a.capacity, a.cursor);
-  }
-  SJ_HIP(hipGetLastError());
+      hipLaunchKernelGGL((k_join_mfma_wg<KP, FMT, QB, kHitsRare>), dim3((uint32_t)n),
+                         dim3(wg_threads<QB>), 0, s, v, wu, n, a.out, a.capacity, a.cursor);
+    SJ_HIP(hipGetLastError());
+  });
 }
 
 template <int FMT>

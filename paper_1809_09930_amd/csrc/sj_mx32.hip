@@ -53,6 +53,7 @@
 #include <algorithm>
 #include <cmath>
 
+#include "sj_launch.hpp"
 #include "sj_tile.hpp"
 
 namespace sj {
@@ -1028,9 +1029,11 @@ constexpr int kQbLead16 = 8, kQbLead32 = 4;  // FP32 with the leading product fi
 template <int FMT, int PARTS, int K, int QB, bool kLead = false>
 void launch_box(const Mx32View &v, const WorkUnit *wu, uint64_t n_wu, uint32_t parts,
                 uint64_t *out, uint64_t capacity, unsigned long long *cursor, hipStream_t s) {
-  hipLaunchKernelGGL((k_join_box<FMT, PARTS, K, QB, kLead>), dim3((uint32_t)(n_wu * parts)), dim3(kWave),
-                     0, s, v, wu, parts, out, capacity, cursor);
-  SJ_HIP(hipGetLastError());
+  for_unit_launches(n_wu, parts * kWave, [&](uint64_t u, uint64_t m) {
+    hipLaunchKernelGGL((k_join_box<FMT, PARTS, K, QB, kLead>), dim3((uint32_t)(m * parts)),
+                       dim3(kWave), 0, s, v, wu + u, parts, out, capacity, cursor);
+    SJ_HIP(hipGetLastError());
+  });
 }
 
 template <int FMT>
@@ -1045,9 +1048,11 @@ void launch_half(const MfmaLaunch &a, const Mx32View &v, uint32_t tq, hipStream_
 
 template <int K>
 void launch_g(const Mx32Launch &a, hipStream_t s) {
-  hipLaunchKernelGGL((k_join_fp32_mxg<K>), dim3((uint32_t)a.n_wu), dim3(Shape<K>::NW * kWave), 0,
-                     s, a.view, a.wu);
-  SJ_HIP(hipGetLastError());
+  for_unit_launches(a.n_wu, Shape<K>::NW * kWave, [&](uint64_t u, uint64_t m) {
+    hipLaunchKernelGGL((k_join_fp32_mxg<K>), dim3((uint32_t)m), dim3(Shape<K>::NW * kWave), 0, s,
+                       a.view, a.wu + u);
+    SJ_HIP(hipGetLastError());
+  });
 }
 
 }  // namespace
@@ -1115,7 +1120,6 @@ void launch_box_rows(const float *X, uint64_t n, uint32_t dp, void *box0, void *
 
 void launch_join_mx32(const Mx32Launch &a, hipStream_t s) {
   if (!a.n_wu) return;
-  if (a.n_wu > 0x3fffffffull) fail(SJ_ERR_INVALID_ARG, "too many work units");  // two parts each
   const uint32_t dp = a.view.m.dp;
   auto box = [&](auto launch, int qb) {
     launch(a.view, a.wu, a.n_wu, mx32_queries(dp) / (32u * (uint32_t)qb), a.out, a.capacity,
@@ -1143,7 +1147,7 @@ void launch_join_box16(const MfmaLaunch &a, hipStream_t s) {
   if (!a.n_wu) return;
   const uint32_t tq = mfma_wg_queries(a.kp);
   static_assert(256 % (32 * kQbHalf16) == 0 && 256 % (32 * kQbHalf32) == 0, "whole parts");
-  if (tq != 256 || a.n_wu > 0x1fffffffull || a.kp > 32)
+  if (tq != 256 || a.kp > 32)
     fail(SJ_ERR_INVALID_ARG, "unsupported box launch");
   Mx32View v{};
   v.m = a.view;
