@@ -531,13 +531,14 @@ __global__ __launch_bounds__(kBlock) void k_runs(int pass, int sym, uint64_t nce
     const uint32_t b0 = live ? nbr_off[A] : 0u, b1 = live ? nbr_off[A + 1] : 0u;
     const uint32_t w = pass && live ? run_off[A] : 0u;
     uint32_t ns = 0, ne = 0;  // starts and ends so far
-    for (uint32_t base = b0; ballot(base < b1) != 0; base += G) {
-      const uint32_t i = base + l;
-      const bool in = i < b1;
+    const uint32_t steps = list_steps(b0, b1, G);
+    for (uint32_t t = 0; ballot(t < steps) != 0; ++t) {
+      uint32_t i;
+      const bool in = list_entry(b0, b1, t, G, l, &i);
       const uint32_t B = in ? nbr_cell[i] : 0u;
       const bool ok = in && !(sym && B < A);
       const uint32_t prev = ok && i > b0 ? nbr_cell[i - 1] : 0xffffffffu;
-      const uint32_t next = ok && i + 1 < b1 ? nbr_cell[i + 1] : 0xffffffffu;
+      const uint32_t next = ok && b1 - i > 1 ? nbr_cell[i + 1] : 0xffffffffu;
       const bool start = ok && (prev == 0xffffffffu || prev + 1 != B || (sym && prev < A));
       const bool end = ok && (next == 0xffffffffu || next != B + 1);
       const uint64_t ms = ballot(start), me = ballot(end);
@@ -642,9 +643,11 @@ __global__ __launch_bounds__(kBlock) void k_wu_cells(
     const bool live = A < nlist;
     const uint32_t r0 = live ? run_off[A] : 0u, r1 = live ? run_off[A + 1] : 0u;
     uint32_t total = 0;
-    for (uint32_t base = r0; ballot(base < r1) != 0; base += G) {
-      const uint32_t r = base + l;
-      const uint2 x = r < r1 ? runs[r] : make_uint2(0u, 0u);
+    const uint32_t steps = list_steps(r0, r1, G);
+    for (uint32_t t = 0; ballot(t < steps) != 0; ++t) {
+      uint32_t r;
+      const bool in = list_entry(r0, r1, t, G, l, &r);
+      const uint2 x = in ? runs[r] : make_uint2(0u, 0u);
       const uint32_t len = x.y - x.x;
       uint32_t inc = len;
 #pragma unroll
@@ -652,7 +655,7 @@ __global__ __launch_bounds__(kBlock) void k_wu_cells(
         const uint32_t u = __shfl_up(inc, off, G);
         if (l >= (uint32_t)off) inc += u;
       }
-      if (r < r1) before[r] = total + inc - len;
+      if (in) before[r] = total + inc - len;
       total += __shfl(inc, G - 1, G);
     }
     if (!live || l != 0) continue;

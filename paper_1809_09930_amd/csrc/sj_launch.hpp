@@ -26,4 +26,18 @@ void for_unit_launches(uint64_t n, uint32_t threads, F &&f) {
   for (uint64_t u = 0; u < n; u += most) f(u, std::min(most, n - u));
 }
 
+// Steps of `lanes` lanes over the entries [b0, b1) of a list, and a lane's entry at a
+// step: false past the list.  (Totals of lists may come up to 2^32 - 1 entries, and
+// lanes that share a wave step on to its longest list: positions in 32 bits would
+// wrap to other lists' entries.)
+constexpr uint32_t list_steps(uint32_t b0, uint32_t b1, uint32_t lanes) {
+  return (uint32_t)(((uint64_t)(b1 - b0) + lanes - 1) / lanes);
+}
+constexpr bool list_entry(uint32_t b0, uint32_t b1, uint32_t step, uint32_t lanes, uint32_t lane,
+                          uint32_t *i) {
+  const uint64_t at = (uint64_t)b0 + (uint64_t)step * lanes + lane;
+  *i = (uint32_t)at;
+  return at < b1;
+}
+
 }  // namespace sj
