@@ -1607,10 +1607,12 @@ void read_counters(sj_index &ix, hipStream_t s) {
 uint64_t counter(const sj_index &ix, int which) { return *ix.word(kWordCounters + which); }
 
 // One launch of the join or of its count-only form; the counters start at zero
-// and are in the handle's words (counter) when it returns.
+// and are in the handle's words (counter) when it returns.  list_slots: expected
+// pairs of the matrix-core filters' recheck list.
 void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &runs,
                  const uint32_t *qlist, int sym, int count_only, uint64_t *out, uint64_t cap,
-                 hipStream_t s, float *ms, uint32_t skip_below = 0) {
+                 hipStream_t s, float *ms, uint64_t list_slots, uint32_t skip_below = 0,
+                 uint64_t list_most = UINT64_MAX) {
   const sj_index &E = entries_of(ix);  // candidates; ix holds the queries
   JoinLaunch a{};
   a.X = E.X.as<float>();
@@ -1716,10 +1718,12 @@ void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &ru
     {
       // band pairs are collected during the join and rechecked afterwards,
       // one per lane; a band list that overflowed is grown and the join rerun
-      // (a count-only pass counts the accepted band pairs the same way)
+      // (a count-only pass counts the accepted band pairs the same way, unless its
+      // list would pass list_most: it then keeps what fits)
       unsigned long long *band_cursor = ix.counters.as<unsigned long long>() + 2;
       const uint64_t least = count_only ? kCountBandStart : kBandStart;
-      const uint64_t want = debug_undersize() ? 16 : std::max(least, ix.band_hint);
+      const uint64_t want =
+          debug_undersize() ? 16 : std::max(least, std::min(list_slots, list_most));
       if (ix.band_cap < want) {
         ix.band_cap = want;
         ix.band.alloc(ix.band_cap * 8);
@@ -1736,7 +1740,7 @@ void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &ru
         SJ_HIP(hipEventRecord(e1.e, s));
         read_counters(ix, s);
         const uint64_t nb = counter(ix, 2);
-        if (nb <= ix.band_cap) break;
+        if (nb <= ix.band_cap || nb + nb / 8 > list_most) break;
         if (attempt == 2) fail(SJ_ERR_DEVICE, "band list size did not settle");
         ix.band_cap = nb + nb / 8;
         ix.band.alloc(ix.band_cap * 8);  // the launch starts over
@@ -1752,9 +1756,15 @@ void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &ru
   *ms += elapsed_ms(e0, e1);
 }
 
+uint64_t band_slots(const sj_index &ix, double share) {
+  return (uint64_t)std::ceil(ix.band_pairs * share * 1.25) + (1u << 16);
+}
+
 // Estimate |R| from a strided sample of query positions (Section 3.2.2:
-// a count-only pass over a fraction of the points).  Counts pairs the FP32
-// filter cannot reject, so it is an upper-bound estimate.  The sample is
+// a count-only pass over a fraction of the points).  The vector FP32 filter
+// counts the pairs that it cannot reject, the matrix-core filters those that are
+// decided, but for what a list of list_most slots does not hold: an estimate from
+// above either way.  The sample is
 // 1/64 of the queries, at least 1024 and at most 8192 of them, so it stays
 // a small part of the join's work for small and mid-sized inputs too.  It
 // takes runs of 8 consecutive positions (mostly of one cell): a wave then
@@ -1762,7 +1772,7 @@ void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &ru
 // positions would leave it one, which matters when cells are small.
 constexpr uint32_t kSampleRun = 8;
 
-uint64_t estimate_pairs(sj_index &ix, hipStream_t s, float *ms) {
+uint64_t estimate_pairs(sj_index &ix, hipStream_t s, float *ms, uint64_t list_most) {
   const uint64_t n = ix.n_near;  // query positions in cells
   const uint64_t target = std::min<uint64_t>(8192, std::max<uint64_t>(1024, n / 64));
   uint64_t stride = 1, nq = n;
@@ -1796,15 +1806,17 @@ uint64_t estimate_pairs(sj_index &ix, hipStream_t s, float *ms) {
   // of the 16-bit filters, and fewer in the FP32 filter's, whose list holds
   // every pair it cannot reject where it accepts none (a larger band reruns
   // the count with the list at its exact size)
-  if (mf || mx) ix.band_hint = ev / (mf ? 512 : 1024);
-  join_launch(ix, wu, nwu, ix.runs_full, ql.as<uint32_t>(), 0, 1, nullptr, 0, s, ms);
-  const uint64_t cnt = counter(ix, 0);
+  join_launch(ix, wu, nwu, ix.runs_full, ql.as<uint32_t>(), 0, 1, nullptr, 0, s, ms,
+              ev / (mf ? 512 : 1024), 0, std::max(list_most, kCountBandStart));
+  uint64_t cnt = counter(ix, 0);
   const double scale = (double)n / (double)nq;
   if (mf || mx) {
+    const uint64_t listed = counter(ix, 2);
+    // (pairs past the list's end: counted, as they are not rejected)
+    if (listed > ix.band_cap) cnt += listed - ix.band_cap;
     // band pairs of the sample size the deferred recheck list of the join
-    const double nband = (double)counter(ix, 1);
-    ix.band_hint = (uint64_t)std::ceil(nband * scale * 1.25) + (1u << 16);
-    ix.hit_density = ev ? ((double)cnt + nband) / (double)ev : 0.0;
+    ix.band_pairs = (double)listed * scale;
+    ix.hit_density = ev ? ((double)cnt + (double)listed) / (double)ev : 0.0;
   }
   return (uint64_t)std::ceil((double)cnt * scale);
 }
@@ -1834,6 +1846,13 @@ void sort_pairs(sj_index &ix, DevBuf &a, DevBuf &b, uint64_t cnt, hipStream_t s,
   radix_sort_u64(kb, nullptr, cnt, sh.data(), (int)sh.size(), tmp.p, s, nullptr, wd.data());
 }
 
+// The recheck list goes back once the joins are done (a second run of the handle
+// returns the first one's result).
+void release_band(sj_index &ix) {
+  ix.band.reset();
+  ix.band_cap = 0;
+}
+
 // Single batch: symmetric join of all work units into device memory.
 constexpr uint64_t kPairSlack = 1u << 20;  // result slots beyond the estimate
 void run_single(sj_index &ix, uint64_t est, hipStream_t s) {
@@ -1849,8 +1868,10 @@ void run_single(sj_index &ix, uint64_t est, hipStream_t s) {
     const DevBuf &runs = ix.opt.sortidu ? (m ? ix.uruns_m : ix.uruns)
                          : grouped      ? ix.groups.runs
                                         : (self ? ix.runs_sym : ix.runs_full);
+    // (a symmetric launch lists each unordered pair once, and each point with itself)
+    const uint64_t slots = self ? band_slots(ix, 0.5) + ix.n / 2 : band_slots(ix, 1.0);
     join_launch(ix, m ? ix.wu_m : ix.wu, m ? ix.n_wu_m : ix.n_wu, runs, nullptr, self ? 1 : 0, 0,
-                ix.pairs.as<uint64_t>(), cap, s, &ms_join);
+                ix.pairs.as<uint64_t>(), cap, s, &ms_join, slots);
     const uint64_t got = counter(ix, 0);
     if (got <= cap) {
       ix.total = got;
@@ -1861,6 +1882,7 @@ void run_single(sj_index &ix, uint64_t est, hipStream_t s) {
   }
   ix.info.rechecks = counter(ix, 1);
   ix.info.ms_join += ms_join;
+  release_band(ix);  // before the sort's second buffer
   Event e0, e1;
   SJ_HIP(hipEventRecord(e0.e, s));
   if (ix.prec != SJ_PREC_FP32 || ix.mx32)
@@ -1988,7 +2010,7 @@ void run_batched(sj_index &ix, uint64_t est, uint64_t per_batch, bool sym, hipSt
     for (int attempt = 0; attempt < 3; ++attempt) {
       sl.keys.ensure(cap * 8);
       join_launch(ix, wu, nwu, ix.runs_full, p32.as<uint32_t>(), 0, 0, sl.keys.as<uint64_t>(),
-                  cap, s, &ms_join, sym ? (uint32_t)i0 : 0u);
+                  cap, s, &ms_join, band_slots(ix, 1.0 / (double)nb), sym ? (uint32_t)i0 : 0u);
       got = counter(ix, 0);
       if (got <= cap) {
         ix.info.rechecks += counter(ix, 1);
@@ -2049,6 +2071,7 @@ void run_batched(sj_index &ix, uint64_t est, uint64_t per_batch, bool sym, hipSt
   for (size_t e = 0; e + 1 < sort_ev.size(); e += 2)
     ix.info.ms_sort += elapsed_ms(*sort_ev[e], *sort_ev[e + 1]);
   ix.info.ms_join += ms_join;
+  release_band(ix);
   ix.info.batches = (uint32_t)ix.host_res.size();
   ix.info.evaluated = evaluated - std::min(evaluated, skipped);
   ix.on_host = true;
@@ -2074,23 +2097,32 @@ void run(sj_index &ix, hipStream_t s) {
     const bool fits = !ix.opt.batch_pairs && ix.opt.min_batches <= 1 && !debug_undersize() &&
                       ix.candidates <= std::min(kPairSlack, budget / 40);
     if (fits) {
-      ix.band_hint = 0;
+      ix.band_pairs = 0.0;
       ix.hit_density = 0.0;
     }
-    const uint64_t est = fits ? 0 : estimate_pairs(ix, s, &ms_est);
-    // a single batch holds the keys twice (sort ping-pong) plus sort scratch
+    // a single batch holds the keys twice (sort ping-pong) plus sort scratch, or
+    // during the join the keys once and the recheck list
     const uint64_t fit = budget / 20;
+    const uint64_t est = fits ? 0 : estimate_pairs(ix, s, &ms_est, fit);
+    const uint64_t joining = est * 9 + band_slots(ix, ix.entries ? 1.0 : 0.5) * 8;
+    const bool list_fits = !ix.mx32 || joining <= std::max<uint64_t>(budget, 1u << 25);
+    // a batch's list stays beside its keys: up to 10 bytes per pair where the FP32
+    // filter accepts none itself (the 16-bit filters list few pairs)
+    uint64_t fit_batch = fit;
+    if (ix.mx32 && est)
+      fit_batch = (uint64_t)((double)budget / (20.0 + 10.0 * ix.band_pairs / (double)est));
     uint64_t per_batch = ix.opt.batch_pairs ? ix.opt.batch_pairs : fit;
     per_batch = std::min(per_batch, fit);
     per_batch = std::min<uint64_t>(per_batch, 1ull << 36);  // 512 GiB of keys: beyond HBM
     const uint32_t min_b = ix.opt.min_batches;
-    if (est + est / 8 <= per_batch && min_b <= 1) {
+    if (est + est / 8 <= per_batch && list_fits && min_b <= 1) {
       run_single(ix, est, s);
     } else {
       // FP32 self-joins take each unordered pair once across batches when
       // the spill fits the budget next to the batches
       const bool sym = ix.prec == SJ_PREC_FP32 && !ix.entries &&
                        (est / 4 + est / 8) * 16 <= budget / 2;
+      per_batch = std::min(per_batch, fit_batch);
       try {
         run_batched(ix, est, std::max<uint64_t>(per_batch, 1), sym, s);
       } catch (const OneWayRetry &) {

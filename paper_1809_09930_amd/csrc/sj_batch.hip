@@ -455,7 +455,7 @@ void run_batch(sj_batch &b, const sj_job *jobs, uint32_t njobs, const sj_options
   // the band list from the jobs' sampled band counts
   uint64_t band_cap = 1u << 16;
   for (uint32_t j = 0; j < njobs; ++j)
-    if (b.jobs[j]->n) band_cap += b.jobs[j]->band_hint;
+    if (b.jobs[j]->n) band_cap += band_slots(*b.jobs[j], 1.0);
   if (debug_undersize()) band_cap = 16;
   b.band_cap = band_cap;
   b.band.alloc(band_cap * 8);

@@ -328,7 +328,7 @@ struct sj_index {
   DevBuf pos_pivot;             // nearest pivot of each position
   DevBuf band;                  // deferred recheck list of the matrix-core joins
   uint64_t band_cap = 0;
-  uint64_t band_hint = 0;       // its expected size from the sampled count
+  double band_pairs = 0.0;      // ordered pairs the join lists, from the sampled count
   double hit_density = 0.0;     // result + band pairs per evaluated pair of the sampled count
   bool mx32 = false;            // FP32 filter on the matrix cores (sj_mx32.hip)
   bool norm_form = false;       // FP32 filter in norm form on the vector ALUs
@@ -378,7 +378,10 @@ void build_cell_groups(sj_index &ix, uint32_t max_q, CellGroups &g, hipStream_t 
 void build_query(sj_index &q, const sj_index &E, const float *queries, hipStream_t s);
 // The indexed (candidate) side of a handle: its entries, or itself.
 inline const sj_index &entries_of(const sj_index &ix) { return ix.entries ? *ix.entries : ix; }
-uint64_t estimate_pairs(sj_index &ix, hipStream_t s, float *ms);
+// list_most: slots that the recheck list of the count may take (see estimate_pairs).
+uint64_t estimate_pairs(sj_index &ix, hipStream_t s, float *ms, uint64_t list_most = UINT64_MAX);
+// Recheck list slots for a share of the ordered pairs.
+uint64_t band_slots(const sj_index &ix, double share);
 uint64_t default_budget();
 MfmaView mfma_view(const sj_index &ix, const uint2 *runs, const uint32_t *qlist, int sym);
 // Fault injection from the host: SJ_DEBUG_UNDERSIZE=1 makes the first
