@@ -341,6 +341,7 @@ constexpr bool kWuByStretch = SJ_WU_BY_STRETCH != 0;  // join work units in stre
 
 uint64_t default_budget();
 bool debug_groups();
+int debug_box_mode();
 constexpr bool kFp32CellGroups = SJ_FP32_CELL_GROUPS != 0;
 // Groups save some 3 % of a join (5M x 18 mixture 52.7 to 51.0 ms) and cost four
 // copies and two waits (0.08 ms): from joins of a few milliseconds on.
@@ -361,6 +362,7 @@ constexpr double kMatrixPairsPerSec = 1.5e13;
 constexpr double kProbeSec = 1.5e-4, kProbeSecPerPoint = 2e-10;
 
 constexpr uint32_t kBoxMaxKp = 32;  // K padding up to which the 16-bit filters have the box form
+constexpr uint32_t kBoxMaxDims = 24;  // dimensions up to which workgroup units use the box
 
 // Whether a handle's FP32 join may run on the matrix cores (sj_mx32.hip): it
 // does for joins of at least kMx32MinCandidates ordered candidate pairs with
@@ -1330,7 +1332,8 @@ void build(sj_index &ix, const float *points, hipStream_t s) {
     ix.mfma_per_wave =
         live_slot_share(ix, t.cand_sum.as<uint64_t>(), tq_wg, s) < kLiveSlotShareMin;
     // (a query set may have workgroup units where the index has not)
-    if (ix.kp <= kBoxMaxKp && !ix.batch_job) box_prepare(ix, s);
+    if (!ix.batch_job && (d <= kBoxMaxDims || (ix.kp <= kBoxMaxKp && debug_box_mode() == 1)))
+      box_prepare(ix, s);
     ix.info.units = ix.mfma_per_wave ? SJ_UNITS_SMALL_CELLS : SJ_UNITS_CELL;
     ix.tq_single = ix.mfma_per_wave ? mfma_wave_queries() : tq_wg;
     ix.tc_single = ix.mfma_per_wave ? choose_tc(ev, ix.tq_single)
@@ -1596,7 +1599,6 @@ constexpr uint64_t kCountBandStart = 1u << 16;  // and of a sampled count
 // (measured: 1.5 against the former 0.2 / 0.05 with a mask-building hit path
 // took the 2M x 16 FP16 join at S_D 512 from 168 to 135 ms)
 constexpr double kFrequentHits = 1.5;
-constexpr uint32_t kBoxMaxDims = 24;  // dimensions up to which workgroup units use the box
 constexpr double kBoxMaxHitsPerTile = 0.1;  // and hits per 32 x 32 tile below which
 
 // The four counters into the handle's words, and one of them.
