@@ -264,7 +264,8 @@ template <int KP, int FMT, int QB>
 struct Queries {
   typedef typename Fmt<FMT>::V8 V8;
   V8 A[QB][KP / 16];
-  float16v c0[QB];
+  float16v c0[QB];       // (where they stay in registers)
+  const float *cinit;    // and the values that they come from
   const float *delta;    // Thi - Tlo, rounded up
   const uint32_t *qpos;  // positions (0xffffffff: no query)
 };
@@ -297,6 +298,7 @@ __device__ __forceinline__ void load_queries(const MfmaView &v, uint32_t q0, uin
   __builtin_amdgcn_wave_barrier();  // the tables belong to this wave
 #pragma unroll
   for (int j = 0; j < QB; ++j) q.c0[j] = rows_init(cinit + j * 32, half);
+  q.cinit = cinit;
   q.delta = delta;
   q.qpos = qpos;
 }
@@ -333,6 +335,38 @@ __device__ __forceinline__ void tiles(const Queries<KP, FMT, QB> &q,
       within |= (uint64_t)a << (16 * j);
     }
     acc = next;
+  }
+  if (QB > 1 && HM != kHitsFrequent && ballot(hits != 0) == 0) return;
+  emit_hits<true>(hits, within, q.qpos, half, cp, kf, st, bs, out, capacity, cursor);
+}
+
+// The same with the initial accumulators read from LDS: q.c0 holds those of the
+// block, and each tile's are loaded again once its elements are done with, so that
+// they are there for the next block.
+template <int KP, int FMT, int QB, int HM>
+__device__ __forceinline__ void tiles_reload(Queries<KP, FMT, QB> &q,
+                                             const typename Fmt<FMT>::V8 (&b)[KP / 16], float nn,
+                                             uint32_t cp, uint32_t half, const KeyForm &kf,
+                                             Stage &st, BandSink &bs, uint64_t *__restrict__ out,
+                                             uint64_t capacity,
+                                             unsigned long long *__restrict__ cursor) {
+  static_assert(QB <= 4, "64 hit bits per lane");
+  uint64_t hits = 0, within = 0;
+#pragma unroll
+  for (int j = 0; j < QB; ++j)
+#pragma unroll
+    for (int ks = 0; ks < KP / 16; ++ks) q.c0[j] = Fmt<FMT>::mfma(q.A[j][ks], b[ks], q.c0[j]);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int j = 0; j < QB; ++j) {
+    if (HM == kHitsFrequent || ballot(min16(q.c0[j], __builtin_inff()) < nn) != 0) {
+      uint32_t h, a;
+      tile_masks<true>(q.c0[j], nn, nn, q.delta + j * 32, half, h, a);
+      hits |= (uint64_t)h << (16 * j);
+      within |= (uint64_t)a << (16 * j);
+    }
+    q.c0[j] = rows_init(q.cinit + j * 32, half);
+    __builtin_amdgcn_sched_barrier(0);
   }
   if (QB > 1 && HM != kHitsFrequent && ballot(hits != 0) == 0) return;
   emit_hits<true>(hits, within, q.qpos, half, cp, kf, st, bs, out, capacity, cursor);
@@ -459,6 +493,14 @@ constexpr uint32_t kUnitQueries = 256;
 template <int KP>
 constexpr int wg_qb = KP <= 64 ? 4 : 2;
 
+// Where three waves per SIMD fit once the initial accumulators leave the registers
+// (K 80: 184 to 152, K 96: 200 to 164 of them; at K 112 and 128 LDS holds two either
+// way).  Joins with the accumulators kept and reloaded: 515k x 90 mixture FP16 27.0
+// and 25.0 ms, BF16 28.1 and 25.9, 400k x 70 uniform BF16 18.1 and 16.3, 400k x 96
+// FP16 17.3 and 16.0 (400k x 110: 19.3 and 19.5).
+template <int KP>
+constexpr bool kReloadRows = KP > 64 && KP <= 96;
+
 template <int QB>
 constexpr int wg_threads = (int)kUnitQueries / (32 * QB) * kWave;
 
@@ -550,8 +592,12 @@ __global__ __launch_bounds__(wg_threads<QB>) void k_join_mfma_wg(
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) b2[ks] = tile[cur][(32 + col) * RS + ks * 2 + half];
       const float nn2 = tile_n[cur][32 + col];
-      tiles<KP, FMT, QB, HM>(q, b, nn, cc + blk * 32 + col, half, kf, st, bs, out, capacity,
-                             cursor);
+      if constexpr (kReloadRows<KP>)
+        tiles_reload<KP, FMT, QB, HM>(q, b, nn, cc + blk * 32 + col, half, kf, st, bs, out,
+                                      capacity, cursor);
+      else
+        tiles<KP, FMT, QB, HM>(q, b, nn, cc + blk * 32 + col, half, kf, st, bs, out, capacity,
+                               cursor);
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) b[ks] = b2[ks];
       nn = nn2;
