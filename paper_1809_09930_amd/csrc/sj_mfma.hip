@@ -337,7 +337,7 @@ __device__ __forceinline__ void tiles(const Queries<KP, FMT, QB> &q,
     acc = next;
   }
   if (QB > 1 && HM != kHitsFrequent && ballot(hits != 0) == 0) return;
-  emit_hits<true>(hits, within, q.qpos, half, cp, kf, st, bs, out, capacity, cursor);
+  emit_hits<true>(hits, within, q.qpos, half, cp, nn, kf, st, bs, out, capacity, cursor);
 }
 
 // The same with the initial accumulators read from LDS: q.c0 holds those of the
@@ -369,7 +369,7 @@ __device__ __forceinline__ void tiles_reload(Queries<KP, FMT, QB> &q,
     __builtin_amdgcn_sched_barrier(0);
   }
   if (QB > 1 && HM != kHitsFrequent && ballot(hits != 0) == 0) return;
-  emit_hits<true>(hits, within, q.qpos, half, cp, kf, st, bs, out, capacity, cursor);
+  emit_hits<true>(hits, within, q.qpos, half, cp, nn, kf, st, bs, out, capacity, cursor);
 }
 
 __device__ __forceinline__ KeyForm key_form(const MfmaView &v) {

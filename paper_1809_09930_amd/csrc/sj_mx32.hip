@@ -566,8 +566,8 @@ __global__ __launch_bounds__(kWave) void k_join_box(Mx32View v, const WorkUnit *
         hits |= (uint64_t)h << (16 * (j - j0));
         within |= (uint64_t)a << (16 * (j - j0));
       }
-      emit_hits<kAccept>(hits, within, &qpos_mem[j0 * 32], half, cur.cp, kf, st, bs, out,
-                         capacity, cursor);
+      emit_hits<kAccept>(hits, within, &qpos_mem[j0 * 32], half, cur.cp, PARTS == 1 ? cur.an : 0.0f, kf,
+                         st, bs, out, capacity, cursor);
     }
   };
 
@@ -1007,7 +1007,7 @@ __global__ __launch_bounds__(Shape<K>::NW * kWave) void k_join_fp32_mxg(
           tile_masks<false>(acc[j], an, 0.0f, nullptr, half, h, a);
           hits |= h << (16 * j);
         }
-        emit_hits<false>(hits, 0u, &qpos_s[w * QB * 32], half, cp, kf, none, bs, nullptr, 0,
+        emit_hits<false>(hits, 0u, &qpos_s[w * QB * 32], half, cp, 0.0f, kf, none, bs, nullptr, 0,
                          nullptr);
       }
     }

@@ -122,8 +122,8 @@ __device__ __forceinline__ float16v rows_init(const float *rows32, uint32_t half
 // One tile's hits (element < nn) as a 16-bit mask per lane, and with kAccept
 // the mask of the pairs proven within eps (element + its row's delta < nacc).
 // Element e is bit 15 - e: the sign bits of the differences are shifted in one
-// by one (v_alignbit).  A candidate with nn = -inf (padding) has no hits whatever
-// its elements are: the sign of -inf - -inf is not defined.
+// by one (v_alignbit).  A candidate with nn = -inf (padding) has none of finite
+// elements; the sign of -inf - -inf is open, and emit_hits drops what it leaves.
 template <bool kAccept>
 __device__ __forceinline__ void tile_masks(const float16v &acc, float nn, float nacc,
                                            const float *delta32, uint32_t half, uint32_t &hit,
@@ -142,7 +142,6 @@ __device__ __forceinline__ void tile_masks(const float16v &acc, float nn, float 
             __builtin_amdgcn_alignbit(within, __builtin_bit_cast(uint32_t, x + d[i] - nacc), 31);
     }
   }
-  hit = nn == -__builtin_inff() ? 0u : hit;
 }
 
 // How emitted keys are formed: key_hi | pos_q << pshift | pos_c.
@@ -155,22 +154,24 @@ struct KeyForm {
 // Emits the hits of up to 64 / 16 tiles of one 32-candidate block: every lane
 // with hits left takes its lowest one per round, so the rounds are few (a lane
 // rarely has two) and there is one copy of the emission code.  hits / within:
-// tile j's masks at bits 16 j; cp: the lane's candidate; qpos: the tiles' query
-// positions, 32 per tile.  Pairs proven within eps go to the result stage, the
-// others to the recheck list.
+// tile j's masks at bits 16 j; cp: the lane's candidate and nn its reject value
+// (-inf: padding, nothing is emitted; 0 where all thresholds are finite, and padding
+// has no hits); qpos: the tiles' query positions, 32 per tile.  Pairs proven within
+// eps go to the result stage, the others to the recheck list.
 template <bool kAccept, class M>
 __device__ __forceinline__ void emit_hits(M hits, M within, const uint32_t *qpos, uint32_t half,
-                                          uint32_t cp, const KeyForm &kf, Stage &st, BandSink &bs,
-                                          uint64_t *__restrict__ out, uint64_t capacity,
+                                          uint32_t cp, float nn, const KeyForm &kf, Stage &st,
+                                          BandSink &bs, uint64_t *__restrict__ out,
+                                          uint64_t capacity,
                                           unsigned long long *__restrict__ cursor) {
-  // (0xffffffff: a row without a query)
-  const uint32_t last_q = kf.sym ? cp : 0xfffffffeu;
+  // queries below this take part (0xffffffff: a row without a query)
+  const uint32_t end_q = nn == -__builtin_inff() ? 0u : kf.sym ? cp + 1u : 0xffffffffu;
   while (ballot(hits != 0)) {
     const bool live = hits != 0;
     const uint32_t b = live ? (uint32_t)__builtin_ctzll((uint64_t)hits) : 0u;
     const uint32_t e = 15u - (b & 15u);
     const uint32_t qp = qpos[(b & ~15u) * 2 + 8 * (e / 4) + 4 * half + (e & 3u)];
-    const bool ok = live && qp <= last_q;
+    const bool ok = live && qp < end_q;
     const bool acc_ok = kAccept && ok && ((within >> b) & 1) != 0;
     const bool band = ok && !acc_ok;
     const uint64_t key = kf.key_hi | ((uint64_t)qp << kf.pshift) | cp;
