@@ -193,6 +193,7 @@ typedef struct sj_info {
     uint32_t join_launches;   /* launches of the distance kernel in the last run (reruns after an undersized buffer included) */
     uint32_t fp32_form;       /* form of the FP32 filter (enum sj_fp32_form; 0 on the matrix-core path) */
     uint32_t units;           /* work units of the distance kernel (enum sj_units; set by the build, 0 for an empty input) */
+    uint32_t fp32_matrix;     /* 1: the FP32 filter runs on the matrix cores (its form is then reported as NORM) */
 } sj_info;
 
 /*

@@ -1280,6 +1280,7 @@ void build(sj_index &ix, const float *points, hipStream_t s) {
   ix.mx32 = mx32_in_range(ix) && (double)ix.candidates >= kMx32MinCandidates && mx32_fits(ix) &&
             live_slot_share(ix, t.cand_sum.as<uint64_t>(), mx32_live_queries(ix.dp), s) >=
                 kMx32LiveSlotShareMin;
+  ix.info.fp32_matrix = ix.mx32 ? 1u : 0u;
   if (ix.mx32) {
     ix.info.fp32_form = SJ_FP32_NORM;
     mx32_prepare(ix, s);
@@ -1493,6 +1494,7 @@ void build_query(sj_index &q, const sj_index &E, const float *queries, hipStream
   q.mx32 = E.mx32 && (double)q.candidates >= kMx32MinCandidates &&
            live_slot_share(q, t.cand_sum.as<uint64_t>(), mx32_live_queries(q.dp), s) >=
                kMx32LiveSlotShareMin;
+  q.info.fp32_matrix = q.mx32 ? 1u : 0u;
   if (q.mx32) q.info.fp32_form = SJ_FP32_NORM;
   if (q.mx32 && !mx32_per_wave(q.dp)) mx32_project(q, E, q.n_near, s);
   q.small_cells =

@@ -79,7 +79,8 @@ class SjInfo(ctypes.Structure):
                 ("ms_run", ctypes.c_float),
                 ("join_launches", ctypes.c_uint32),
                 ("fp32_form", ctypes.c_uint32),
-                ("units", ctypes.c_uint32)]
+                ("units", ctypes.c_uint32),
+                ("fp32_matrix", ctypes.c_uint32)]
 
 
 class SjJob(ctypes.Structure):
