@@ -1597,10 +1597,15 @@ int debug_lead_mode();
 constexpr uint64_t kBandStart = 1u << 20;       // least band-list slots of a join
 constexpr uint64_t kCountBandStart = 1u << 16;  // and of a sampled count
 // result + band pairs per 32 x 32 tile above which the matrix-core kernels
-// scan every tile's elements instead of testing each tile's minimum first
-// (measured: 1.5 against the former 0.2 / 0.05 with a mask-building hit path
-// took the 2M x 16 FP16 join at S_D 512 from 168 to 135 ms)
-constexpr double kFrequentHits = 1.5;
+// scan every tile's elements instead of testing each tile's minimum first, and K
+// padding from which on they do so at all: there a tile's masks cost little beside
+// its products.  Minimum first and scan, FP16 joins at hits per tile: 150k x 90 2.5
+// 4.17 and 4.20 ms, 4.0 4.74 and 4.63, 7.2 5.87 and 5.74, 21 14.5 either way; 100k x
+// 120 3.1 2.83 and 2.75; but 300k x 16 2.8 8.2 and 9.1, 9.5 24.2 and 24.3, 52 124
+// either way; 200k x 64 1.4 6.6 and 7.4, 2.8 7.9 and 8.0, 5.1 9.4 and 9.2; mixture 300k
+// x 40 9.2 12.8 and 13.8; 2M x 64 exponential at eps 0.18 (1.6) 450 and 500.
+constexpr double kFrequentHits = 3.0;
+constexpr uint32_t kFrequentMinKp = 80;
 constexpr double kBoxMaxHitsPerTile = 0.1;  // and hits per 32 x 32 tile below which
 
 // The four counters into the handle's words, and one of them.
@@ -1667,7 +1672,7 @@ void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &ru
       m.per_wave = ix.mfma_per_wave ? 1 : 0;
       // hits common enough: scan the elements of every tile directly
       const double per_tile = ix.hit_density * 1024.0;
-      m.hits_frequent = per_tile > kFrequentHits ? 1 : 0;
+      m.hits_frequent = ix.kp >= kFrequentMinKp && per_tile > kFrequentHits ? 1 : 0;
       if (const int forced = debug_hits_mode(); forced >= 0) m.hits_frequent = forced;
       // the query-box prefilter pays where 8 dimensions are a good part of
       // the distance (the bound uses the first 8 of the variance order) and
