@@ -1855,8 +1855,9 @@ void sort_pairs(sj_index &ix, DevBuf &a, DevBuf &b, uint64_t cnt, hipStream_t s,
   radix_sort_u64(kb, nullptr, cnt, sh.data(), (int)sh.size(), tmp.p, s, nullptr, wd.data());
 }
 
-// The recheck list goes back once the joins are done (a second run of the handle
-// returns the first one's result).
+// The recheck list goes back once the run is done (a second run of the handle
+// returns the first one's result), and ahead of the sort's second buffer where the
+// budget does not hold both.
 void release_band(sj_index &ix) {
   ix.band.reset();
   ix.band_cap = 0;
@@ -1864,7 +1865,7 @@ void release_band(sj_index &ix) {
 
 // Single batch: symmetric join of all work units into device memory.
 constexpr uint64_t kPairSlack = 1u << 20;  // result slots beyond the estimate
-void run_single(sj_index &ix, uint64_t est, hipStream_t s) {
+void run_single(sj_index &ix, uint64_t est, uint64_t budget, hipStream_t s) {
   uint64_t cap = est + est / 8 + kPairSlack;
   if (debug_undersize()) cap = std::max<uint64_t>(1, est / 16);
   float ms_join = 0.0f;
@@ -1891,7 +1892,7 @@ void run_single(sj_index &ix, uint64_t est, hipStream_t s) {
   }
   ix.info.rechecks = counter(ix, 1);
   ix.info.ms_join += ms_join;
-  release_band(ix);  // before the sort's second buffer
+  if (ix.pairs.bytes + ix.band.bytes + ix.total * 8 > budget) release_band(ix);
   Event e0, e1;
   SJ_HIP(hipEventRecord(e0.e, s));
   if (ix.prec != SJ_PREC_FP32 || ix.mx32)
@@ -2080,7 +2081,6 @@ void run_batched(sj_index &ix, uint64_t est, uint64_t per_batch, bool sym, hipSt
   for (size_t e = 0; e + 1 < sort_ev.size(); e += 2)
     ix.info.ms_sort += elapsed_ms(*sort_ev[e], *sort_ev[e + 1]);
   ix.info.ms_join += ms_join;
-  release_band(ix);
   ix.info.batches = (uint32_t)ix.host_res.size();
   ix.info.evaluated = evaluated - std::min(evaluated, skipped);
   ix.on_host = true;
@@ -2125,7 +2125,7 @@ void run(sj_index &ix, hipStream_t s) {
     per_batch = std::min<uint64_t>(per_batch, 1ull << 36);  // 512 GiB of keys: beyond HBM
     const uint32_t min_b = ix.opt.min_batches;
     if (est + est / 8 <= per_batch && list_fits && min_b <= 1) {
-      run_single(ix, est, s);
+      run_single(ix, est, budget, s);
     } else {
       // FP32 self-joins take each unordered pair once across batches when
       // the spill fits the budget next to the batches
@@ -2142,6 +2142,7 @@ void run(sj_index &ix, hipStream_t s) {
   }
   SJ_HIP(hipEventRecord(e1.e, s));
   SJ_HIP(hipEventSynchronize(e1.e));
+  release_band(ix);
   ix.info.ms_run = elapsed_ms(e0, e1);
   ix.info.pairs = ix.total;
   ix.info.result_on_host = ix.on_host ? 1u : 0u;
