@@ -1088,8 +1088,9 @@ void fill_defaults(sj_options *o) {
 // copy twice that.  So sizes come back in pinned words that the scans write
 // themselves, lists end with the scan's total instead of being cleared first, and
 // what only the sample's or the other filter's launches would read is not built
-// (1000 x 8: 133 launches and 1.18 ms a pass, now 72 and 0.80 ms; 256 jobs 206 to
-// 186 ms).
+// (1000 x 8: 133 launches and 1.18 ms a pass, then 72 and 0.80 ms; 57 and 0.46 with
+// the one-launch sorts and scans and without a sampled count.  256 jobs: 206 to 186
+// ms by this alone).
 void build(sj_index &ix, const float *points, hipStream_t s) {
   ScratchScope scope;  // temporaries live until the final event synchronisation
   Event ev0, ev1;
@@ -1490,7 +1491,9 @@ void build_query(sj_index &q, const sj_index &E, const float *queries, hipStream
   if (q.ncell == 0) return finish();
   q.candidates = build_neighbors(q, E, g.np, t, s, true);
   // as for an index, over the query cells; an index joined on the matrix cores
-  // has no norm tables, so its small query sets take the difference form
+  // has no norm tables, so its small query sets take the difference form (with one
+  // query per lane it is the faster one: 20,000 queries against 2M x 16 exponential
+  // points 15.3 ms, 18.8 in norm form; 40,000 against 2M x 8 uniform 8.0 and 10.3)
   q.mx32 = E.mx32 && (double)q.candidates >= kMx32MinCandidates &&
            live_slot_share(q, t.cand_sum.as<uint64_t>(), mx32_live_queries(q.dp), s) >=
                kMx32LiveSlotShareMin;
@@ -1585,7 +1588,7 @@ MfmaView mfma_view(const sj_index &ix, const uint2 *runs, const uint32_t *qlist,
   v.hi = ix.hi32;
   v.box0 = E.box_rows.p;
   v.box1 = E.box_rows.p ? E.box_rows.as<char>() + E.n * 16 : nullptr;
-  v.pad_row = (uint32_t)E.n;  // rows n .. n_pad-1: zero operands, norm +inf
+  v.pad_row = (uint32_t)E.n;  // rows n .. n_pad-1: zero operands, reject value -inf
   return v;
 }
 

@@ -46,7 +46,6 @@ template <>
 struct Fmt<kFmtF16> {
   typedef _Float16 T;
   typedef half8 V8;
-  __device__ static T inf() { return (T)__builtin_inff(); }
   __device__ static float16v mfma(V8 a, V8 b, float16v c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
   }
@@ -55,7 +54,6 @@ template <>
 struct Fmt<kFmtBF16> {
   typedef __bf16 T;
   typedef bf16x8 V8;
-  __device__ static T inf() { return (T)__builtin_inff(); }
   __device__ static float16v mfma(V8 a, V8 b, float16v c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   }
@@ -83,8 +81,9 @@ __device__ __forceinline__ typename Fmt<FMT>::T prep_coord(float x, float c) {
 }
 
 // The operand rows: 8 consecutive K slots per thread, so that the 16-byte
-// stores of XA and XB are contiguous across the lanes.  A rows [x~ | 0],
-// B columns [-2 x~ | 0] (scaling by -2 is exact); padding rows are zero.
+// stores of XA and XB are contiguous across the lanes.  Candidates XA [x~ | 0],
+// the tiles' columns; queries XB [-2 x~ | 0], their rows (scaling by -2 is exact);
+// padding is zero.
 template <int FMT>
 __global__ __launch_bounds__(kBlock) void k_mfma_prep(
     const float *__restrict__ X, uint64_t n, uint64_t n_pad, uint32_t d, uint32_t dp,

@@ -18,7 +18,7 @@ struct MfmaBand {
 
 // Everything a work unit of the matrix-core filter reads.
 struct MfmaView {
-  const void *XA, *XB;      // [n_pad][kp] 16-bit operands (candidate rows / query columns)
+  const void *XA, *XB;      // [n_pad][kp] 16-bit operands: candidates (tile columns), queries (rows)
   const float *cn;          // [n_pad] what a tile element must stay below to be a hit (the
                             // float above minus the candidate's norm; -inf: never)
   const float *thi, *tlo;   // per-point thresholds

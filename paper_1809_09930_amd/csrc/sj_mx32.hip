@@ -36,11 +36,12 @@
 // 4.3e-7, here 7.4e-7) no pair is accepted on this estimate: what the FP32 sum
 // used to accept is now decided in FP64.
 // Measured joins, vector forms before and this: uniform 2M x 16 at S_D 64 505
-// and 105 ms, exponential 2M x 16 at eps 0.03 151 and 31 ms, mixture 515k x 90
-// 253 and 14.5 ms, mixture 301k x 37 in result batches 177 and 28 ms.  The
-// matrix cores hold about 1.4 PFLOP/s on random FP16 operands here (power), so
-// the products of the 2M x 16 join (0.43 of 2e12 pairs after the box test, 83
-// TFLOP) cannot take less than 60 ms.
+// and 101 ms, exponential 2M x 16 at eps 0.03 151 and 30 ms, mixture 515k x 90
+// 253 and 14.5 ms, mixture 301k x 37 in result batches 177 and 10 ms.  A large
+// product of FP16 operands reaches about 1.3 PFLOP/s on this card (power), so the
+// leading products of the 2M x 16 join (0.43 of 2e12 pairs after the box test, 28
+// TFLOP) would take 21 ms: it is bound by the issue of box tests, gathers and
+// minima, as the others are by their tests.
 //
 // Candidates reach a tile only after a test against all of the unit's queries
 // at once (a bound on the distance, so no pair is lost):
