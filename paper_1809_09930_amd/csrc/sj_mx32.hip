@@ -40,8 +40,8 @@
 // 253 and 14.5 ms, mixture 301k x 37 in result batches 177 and 10 ms.  A large
 // product of FP16 operands reaches about 1.3 PFLOP/s on this card (power), so the
 // leading products of the 2M x 16 join (0.43 of 2e12 pairs after the box test, 28
-// TFLOP) would take 21 ms: it is bound by the issue of box tests, gathers and
-// minima, as the others are by their tests.
+// TFLOP) would take 21 ms.  Vector issue is 0.38 there and the matrix units are busy
+// 0.14 of the time: two waves per SIMD wait for gathered rows and LDS.
 //
 // Candidates reach a tile only after a test against all of the unit's queries
 // at once (a bound on the distance, so no pair is lost):
@@ -255,8 +255,8 @@ __device__ __forceinline__ void query_bounds(const Mx32View &v, double n, float 
 // as the registers of two waves per SIMD hold: 8 with one product (4 at K 32),
 // 4 with three (2 at K 32).
 //
-// Bound by instruction issue: the vector ALU's (8 minima per tile, 27
-// instructions per 64 candidates tested) beside the matrix unit's.  Measured,
+// With one product bound by instruction issue (0.68 of the vector ALU's at 2M x 16
+// FP16): 8 minima per tile, 27 instructions per 64 candidates tested.  Measured,
 // whole pass of the 2M x 16 uniform join at 64 neighbours: FP16 105 ms with
 // workgroups of four waves, candidates as rows and a product's minima right
 // behind it, 77 ms with one wave per workgroup and queries as rows, 69 ms with
