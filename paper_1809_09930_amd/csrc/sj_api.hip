@@ -932,10 +932,10 @@ bool norm_band_narrow(const sj_index &ix, const NormParams &np, double mean_norm
 // grows with the distances from it).
 uint64_t mx32_rows(const sj_index &ix) { return ix.n + 64; }
 bool mx32_fits(const sj_index &ix) {
-  // the split rows take up to twice the bytes of the FP32 rows: large sets
-  // keep the vector form when they would not fit easily
+  // the split rows take up to twice the bytes of the FP32 rows: sets keep the
+  // vector form when they would not fit easily
   const uint64_t bytes = mx32_rows(ix) * (mx32_k(ix.dp) * 4ull + kMx32Dirs * 2ull + 12ull);
-  return bytes < (1ull << 30) || bytes < default_budget() / 3;
+  return bytes < default_budget() / 3;
 }
 // Rows of the query-box test of an indexed set.
 void box_prepare(sj_index &ix, hipStream_t s) {

@@ -81,3 +81,32 @@ def test_vector_forms_say_so(form, lead):
     P = datagen.offgrid("uniform64", 4700, 10, seed=1160)
     info = assert_same_as_oracle(P, calibrated(P, 15, stride=9), k=1, fp32_form=form)
     assert (info["fp32_matrix"], info["fp32_form"]) == (0, form)
+
+
+def test_little_memory_keeps_the_vector_form(lead):
+    """The split rows are taken only where they fit a share of the free memory."""
+    from paper_1809_09930_amd import selfjoin as sj
+    n, d = 600_000, 16
+    P = torch.rand((n, d), device="cuda", generator=torch.Generator("cuda").manual_seed(5))
+    routes, pairs = [], []
+    for leave in (None, 300 << 20):
+        torch.cuda.empty_cache()
+        sj.selfjoin_release_cache()
+        held = []
+        for part in (2 << 30, 64 << 20, 4 << 20):  # (one block of it all leaves more)
+            while leave and torch.cuda.mem_get_info()[0] - part >= leave:
+                held.append(torch.empty(part, dtype=torch.uint8, device="cuda"))
+        assert not leave or torch.cuda.mem_get_info()[0] < leave + (64 << 20)
+        print("case route memory", leave, lead, flush=True)
+        h = sj.selfjoin_build_index(P, 0.45, k=4)
+        try:
+            routes.append(sj.selfjoin_get_info(h)["fp32_matrix"])
+            total = sj.selfjoin_run(h)
+            i, j = (torch.empty(total, dtype=torch.int32) for _ in range(2))
+            sj.selfjoin_fetch_pairs(h, 0, i, j, max_pairs=total)
+            pairs.append((i, j))
+        finally:
+            sj.selfjoin_free(h)
+            del held
+    assert routes == [1, 0]
+    assert torch.equal(pairs[0][0], pairs[1][0]) and torch.equal(pairs[0][1], pairs[1][1])
