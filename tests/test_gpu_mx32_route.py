@@ -86,10 +86,10 @@ def test_vector_forms_say_so(form, lead):
 def test_little_memory_keeps_the_vector_form(lead):
     """The split rows are taken only where they fit a share of the free memory."""
     from paper_1809_09930_amd import selfjoin as sj
-    n, d = 600_000, 16
+    n, d = 3_500_000, 16  # 0.49 GB of split rows
     P = torch.rand((n, d), device="cuda", generator=torch.Generator("cuda").manual_seed(5))
     routes, pairs = [], []
-    for leave in (None, 300 << 20):
+    for leave in (None, 2 << 30):
         torch.cuda.empty_cache()
         sj.selfjoin_release_cache()
         held = []
@@ -98,7 +98,7 @@ def test_little_memory_keeps_the_vector_form(lead):
                 held.append(torch.empty(part, dtype=torch.uint8, device="cuda"))
         assert not leave or torch.cuda.mem_get_info()[0] < leave + (64 << 20)
         print("case route memory", leave, lead, flush=True)
-        h = sj.selfjoin_build_index(P, 0.45, k=4)
+        h = sj.selfjoin_build_index(P, 0.1, k=4)
         try:
             routes.append(sj.selfjoin_get_info(h)["fp32_matrix"])
             total = sj.selfjoin_run(h)
@@ -108,5 +108,6 @@ def test_little_memory_keeps_the_vector_form(lead):
         finally:
             sj.selfjoin_free(h)
             del held
+            torch.cuda.empty_cache()
     assert routes == [1, 0]
     assert torch.equal(pairs[0][0], pairs[1][0]) and torch.equal(pairs[0][1], pairs[1][1])
