@@ -1621,7 +1621,7 @@ uint64_t counter(const sj_index &ix, int which) { return *ix.word(kWordCounters 
 // One launch of the join or of its count-only form; the counters start at zero
 // and are in the handle's words (counter) when it returns.  list_slots: expected
 // pairs of the matrix-core filters' recheck list.
-void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &runs,
+void join_launch(sj_index &ix, const WorkUnit *wu, uint64_t n_wu, const DevBuf &runs,
                  const uint32_t *qlist, int sym, int count_only, uint64_t *out, uint64_t cap,
                  hipStream_t s, float *ms, uint64_t list_slots, uint32_t skip_below = 0,
                  uint64_t list_most = UINT64_MAX) {
@@ -1632,7 +1632,7 @@ void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &ru
   a.Xq = ix.X.as<float>();
   a.qid = ix.orig_id.as<uint32_t>();
   a.inv_perm = ix.inv_perm_d.as<uint16_t>();
-  a.wu = wu.as<WorkUnit>();
+  a.wu = wu;
   a.n_wu = n_wu;
   a.runs = runs.as<uint2>();
   a.qlist = qlist;
@@ -1752,9 +1752,9 @@ void join_launch(sj_index &ix, const DevBuf &wu, uint64_t n_wu, const DevBuf &ru
         SJ_HIP(hipEventRecord(e1.e, s));
         read_counters(ix, s);
         const uint64_t nb = counter(ix, 2);
-        if (nb <= ix.band_cap || nb + nb / 8 > list_most) break;
+        if (nb <= ix.band_cap || nb > list_most) break;
         if (attempt == 2) fail(SJ_ERR_DEVICE, "band list size did not settle");
-        ix.band_cap = nb + nb / 8;
+        ix.band_cap = std::min(nb + nb / 8, list_most);
         ix.band.alloc(ix.band_cap * 8);  // the launch starts over
       }
     }
@@ -1774,9 +1774,9 @@ uint64_t band_slots(const sj_index &ix, double share) {
 
 // Estimate |R| from a strided sample of query positions (Section 3.2.2:
 // a count-only pass over a fraction of the points).  The vector FP32 filter
-// counts the pairs that it cannot reject, the matrix-core filters those that are
-// decided, but for what a list of list_most slots does not hold: an estimate from
-// above either way.  The sample is
+// counts the pairs that it cannot reject (an estimate from above), the matrix-core
+// filters those that are results, in parts where a list of list_most slots does not
+// hold the sample's undecided pairs.  The sample is
 // 1/64 of the queries, at least 1024 and at most 8192 of them, so it stays
 // a small part of the join's work for small and mid-sized inputs too.  It
 // takes runs of 8 consecutive positions (mostly of one cell): a wave then
@@ -1818,14 +1818,36 @@ uint64_t estimate_pairs(sj_index &ix, hipStream_t s, float *ms, uint64_t list_mo
   // of the 16-bit filters, and fewer in the FP32 filter's, whose list holds
   // every pair it cannot reject where it accepts none (a larger band reruns
   // the count with the list at its exact size)
-  join_launch(ix, wu, nwu, ix.runs_full, ql.as<uint32_t>(), 0, 1, nullptr, 0, s, ms,
-              ev / (mf ? 512 : 1024), 0, std::max(list_most, kCountBandStart));
-  uint64_t cnt = counter(ix, 0);
+  list_most = std::max(list_most, kBandStart);
+  auto count = [&](uint64_t u0, uint64_t u1) {
+    join_launch(ix, wu.as<WorkUnit>() + u0, u1 - u0, ix.runs_full, ql.as<uint32_t>(), 0, 1,
+                nullptr, 0, s, ms, ev / (mf ? 512 : 1024), 0, list_most);
+    return counter(ix, 0);
+  };
+  uint64_t cnt = count(0, nwu);
   const double scale = (double)n / (double)nq;
   if (mf || mx) {
     const uint64_t listed = counter(ix, 2);
-    // (pairs past the list's end: counted, as they are not rejected)
-    if (listed > ix.band_cap) cnt += listed - ix.band_cap;
+    if (listed > ix.band_cap) {
+      // parts of the units, halved where the list does not hold one either (it
+      // holds every pair of a unit: at most 256 queries and 4096 candidates)
+      static_assert(kBandStart >= 256 * 4096, "a unit's pairs");
+      const uint64_t parts = std::min(nwu, listed / list_most + 1);
+      std::vector<std::pair<uint64_t, uint64_t>> todo;
+      for (uint64_t p = 0; p < parts; ++p) todo.push_back({nwu * p / parts, nwu * (p + 1) / parts});
+      cnt = 0;
+      while (!todo.empty()) {
+        const auto [u0, u1] = todo.back();
+        todo.pop_back();
+        const uint64_t found = count(u0, u1);
+        if (counter(ix, 2) > ix.band_cap && u1 - u0 > 1) {
+          todo.push_back({u0, (u0 + u1) / 2});
+          todo.push_back({(u0 + u1) / 2, u1});
+        } else {
+          cnt += found;
+        }
+      }
+    }
     // band pairs of the sample size the deferred recheck list of the join
     ix.band_pairs = (double)listed * scale;
     ix.hit_density = ev ? ((double)cnt + (double)listed) / (double)ev : 0.0;
@@ -1883,8 +1905,8 @@ void run_single(sj_index &ix, uint64_t est, uint64_t budget, hipStream_t s) {
                                         : (self ? ix.runs_sym : ix.runs_full);
     // (a symmetric launch lists each unordered pair once, and each point with itself)
     const uint64_t slots = self ? band_slots(ix, 0.5) + ix.n / 2 : band_slots(ix, 1.0);
-    join_launch(ix, m ? ix.wu_m : ix.wu, m ? ix.n_wu_m : ix.n_wu, runs, nullptr, self ? 1 : 0, 0,
-                ix.pairs.as<uint64_t>(), cap, s, &ms_join, slots);
+    join_launch(ix, (m ? ix.wu_m : ix.wu).as<WorkUnit>(), m ? ix.n_wu_m : ix.n_wu, runs, nullptr,
+                self ? 1 : 0, 0, ix.pairs.as<uint64_t>(), cap, s, &ms_join, slots);
     const uint64_t got = counter(ix, 0);
     if (got <= cap) {
       ix.total = got;
@@ -2022,8 +2044,8 @@ void run_batched(sj_index &ix, uint64_t est, uint64_t per_batch, bool sym, hipSt
     uint64_t got = 0;
     for (int attempt = 0; attempt < 3; ++attempt) {
       sl.keys.ensure(cap * 8);
-      join_launch(ix, wu, nwu, ix.runs_full, p32.as<uint32_t>(), 0, 0, sl.keys.as<uint64_t>(),
-                  cap, s, &ms_join, band_slots(ix, 1.0 / (double)nb), sym ? (uint32_t)i0 : 0u);
+      join_launch(ix, wu.as<WorkUnit>(), nwu, ix.runs_full, p32.as<uint32_t>(), 0, 0,
+                  sl.keys.as<uint64_t>(), cap, s, &ms_join, band_slots(ix, 1.0 / (double)nb), sym ? (uint32_t)i0 : 0u);
       got = counter(ix, 0);
       if (got <= cap) {
         ix.info.rechecks += counter(ix, 1);

@@ -52,10 +52,24 @@ def test_list_is_sized_by_a_batch():
 @pytest.mark.parametrize("mem_budget", [1 << 20, 40 << 20])
 @pytest.mark.parametrize("d", [24, 40])
 def test_small_budgets(d, mem_budget):
-    """Few slots for the sampled count's list (its estimate is then from above) and
-    several batches that hand mirrored pairs on."""
+    """Few slots for the sampled count's list (it counts in parts then) and several
+    batches that hand mirrored pairs on."""
     P = datagen.offgrid("uniform64", 4700, d, seed=870 + d)
     eps = calibrated(P, 700, stride=40)
     print("case list budget", d, mem_budget, flush=True)
     info = assert_same_as_oracle(P, eps, mem_budget=mem_budget)
     assert info["fp32_form"] == 2 and info["batches"] >= 2
+
+
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+def test_wide_band_under_a_small_budget(prec):
+    """Outliers widen the 16-bit band to most pairs: the sampled count's list does not
+    hold them, and the batches still follow the pairs that are results."""
+    P = datagen.offgrid("uniform64", 4500, 20, seed=880)
+    eps = calibrated(P, 30, stride=9)
+    P[:3] *= np.float32(2.0 ** 9)
+    budget = 1 << 20
+    print("case wide band", prec, flush=True)
+    info = assert_same_as_oracle(P, eps, precision=prec, mem_budget=budget)
+    assert info["rechecks"] > 10 * info["pairs"]
+    assert info["batches"] <= 2 * info["pairs"] // (budget // 20) + 2
