@@ -1882,9 +1882,9 @@ void sort_pairs(sj_index &ix, DevBuf &a, DevBuf &b, uint64_t cnt, hipStream_t s,
 
 // The recheck list goes back once the run is done (a second run of the handle
 // returns the first one's result), and ahead of the sort's second buffer where the
-// budget does not hold both.
+// budget does not hold both.  The run's stream has been waited for at either place.
 void release_band(sj_index &ix) {
-  ix.band.reset();
+  ix.band.reset(true);
   ix.band_cap = 0;
 }
 

@@ -48,8 +48,9 @@ struct DevBuf {
   DevBuf(const DevBuf &) = delete;
   DevBuf &operator=(const DevBuf &) = delete;
   ~DevBuf() { reset(); }
-  void reset() {
-    if (p) dev_free(p, got, dev);
+  // idle: no queued work uses the block (no wait needed)
+  void reset(bool idle = false) {
+    if (p) dev_free(p, got, dev, idle);
     p = nullptr;
     bytes = 0;
     got = 0;
